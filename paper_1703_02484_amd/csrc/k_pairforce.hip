@@ -3,32 +3,40 @@
 // for positions and species that live in device memory owned by the caller,
 // with no simulation handle.
 //
-// Layout.  The j range is cut into J equal splits; one workgroup takes 512
-// particles i (2 per lane) against one split, stages the split's positions and
-// species through LDS in blocks of 512 (the shared-memory broadcast of the
-// paper's n-body kernel, Sec. 6: every lane reads the same j from LDS), and
-// writes its K-weighted sums to part[split][i].  A second kernel adds the J
-// splits in FP64 in split order and writes F in caller order, so results do
-// not depend on the launch timing.  The only device memory beyond the
+// Two layouts, chosen from n, the precision and whether there is a cutoff
+// (pf_plan), bound by the VALU in both:
+//   rows   (few particles) one wavefront per particle i, its lanes over the
+//          j; the 64 partial sums are added across the wavefront in FP64.  One launch, no working memory: with few
+//          particles the time is the launch and the chain of one lane's j.
+//   tiles  the j range is cut into J equal splits; one workgroup takes
+//          256 * P particles i (P per lane) against one split, staged through
+//          LDS in blocks of kPfJ (the shared-memory broadcast of the paper's
+//          n-body kernel, Sec. 6: every lane reads the same j from LDS).  A
+//          staged block is ordered by species, so the strength matrix leaves
+//          the pair loop: it weights the sum over each species' part of the
+//          block.  part[split][i] holds the weighted sums; a second kernel
+//          adds the J splits in FP64 in split order.
+// Neither depends on the launch timing.  The only device memory beyond the
 // caller's inputs and outputs is `part` (J * n * 2 values of the working
 // precision).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 
 #include "../../include/bd.h"
 
 namespace {
 
 constexpr int kPfBlock = 256;
-constexpr int kPfPer = 2;                      // particles i per lane
-constexpr int kPfI = kPfBlock * kPfPer;        // particles i per workgroup
 constexpr int kPfJ = 512;                      // j staged in LDS per pass
 constexpr int kPfTargetGroups = 2048;          // workgroups aimed for (8 per CU)
 constexpr int kPfMaxSplits = 64;
+constexpr int kPfChunks = kPfJ / 64;           // wavefront-sized pieces of a staged block
 
 struct PfLaw {
     int kind, S;
@@ -47,85 +55,343 @@ struct Vec2<double> {
     using type = double2;
 };
 
-// g(d)/d for the law (the factor multiplying r_i - r_j); 0 beyond the cutoff.
+// The law's form, fixed at compile time: the inverse-square law r / r^3, any other power, the screened law.
+enum { PF_Q2 = 0, PF_POWER = 1, PF_SCREENED = 2 };
+
 template <typename T>
-__device__ __forceinline__ T law_factor(T d2, const PfLaw &law, T cut2, T expo, T invlam) {
-    if (cut2 > (T)0 && d2 > cut2) return (T)0;
-    if (law.kind == BD_FORCE_POWER) {
-        if (law.q == 2.0) {
-            const T r = (T)1 / sqrt(d2);
-            return r * r * r;
-        }
-        return pow(d2, expo);
+struct PfConst {
+    T cut2, expo, invlam, A;
+    __device__ explicit PfConst(const PfLaw &law)
+        : cut2(law.cutoff > 0.0 ? (T)(law.cutoff * law.cutoff) : (T)0), expo((T)(-0.5 * (law.q + 1.0))),
+          invlam((T)(1.0 / law.lam)), A((T)law.A) {}
+};
+
+// g(d)/d for the law (the factor multiplying r_i - r_j).  Inverse square: d^-3 from the hardware estimate of
+// d2^-1/2; in FP64 corrected by y^3 (1 + 3/2 e + 15/8 e^2), e = 1 - d2 y^2, which leaves an error of order
+// e^3 (below rounding).  d2 is capped where d^-3 is 0 anyway, so that an overflowed d2 gives 0 and not NaN.
+template <int LAW>
+__device__ __forceinline__ float law_factor(float d2, const PfConst<float> &c) {
+    if (LAW == PF_Q2) {
+        const float r = __builtin_amdgcn_rsqf(d2);
+        return r * r * r;
     }
-    const T d = sqrt(d2);
-    return (T)law.A * exp(-d * invlam) / d2;
+    if (LAW == PF_POWER) return powf(d2, c.expo);
+    const float d = sqrtf(d2);
+    return c.A * expf(-d * c.invlam) / d2;
+}
+template <int LAW>
+__device__ __forceinline__ double law_factor(double d2, const PfConst<double> &c) {
+    if (LAW == PF_Q2) {
+        d2 = fmin(d2, 1e300);
+        const double y = __builtin_amdgcn_rsq(d2);
+        const double y2 = y * y;
+        const double e = fma(-d2, y2, 1.0);
+        return (y2 * y) * fma(fma(1.875, e, 1.5), e, 1.0);
+    }
+    if (LAW == PF_POWER) return pow(d2, c.expo);
+    const double d = sqrt(d2);
+    return c.A * exp(-d * c.invlam) / d2;
 }
 
-// grid (ceil(n / 512), J); part[split * n + i] = sum over the split's j of K[s_i][s_j] g (r_i - r_j) / d.
+// ---------------------------------------------------------------- rows
+// Sum over the wavefront in a fixed order; every lane ends with it.
+__device__ __forceinline__ double wave_sum(double v) {
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    return v;
+}
+
+// One wavefront per particle i, lanes over j.  The piece of 64 j that holds i, and the ragged last one, test each
+// j; the others do not.  777 particles in FP64: 8 us (4 workgroups that each took 512 particles: 178 us).
+template <typename T, int LAW, bool CUT>
+__global__ __launch_bounds__(kPfBlock) void k_pf_rows(int n, const double *__restrict__ xy,
+                                                      const int32_t *__restrict__ species, PfLaw law,
+                                                      double *__restrict__ f) {
+    __shared__ T kw[BD_MAX_SPECIES * BD_MAX_SPECIES];
+    const int S = law.S;
+    for (int k = threadIdx.x; k < S * S; k += kPfBlock) kw[k] = (T)law.K[k];
+    __syncthreads();
+    const PfConst<T> c(law);
+    const int lane = threadIdx.x & 63;
+    const int i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kPfBlock / 64) + (threadIdx.x >> 6)));
+    if (i >= n) return;   // after the workgroup's only barrier
+    const T xi = (T)xy[2 * (size_t)i], yi = (T)xy[2 * (size_t)i + 1];
+    const int si = species[i] * S;
+    T ax = (T)0, ay = (T)0;
+    auto piece = [&](int b, auto check) {
+        constexpr bool CHECK = decltype(check)::value;
+        const int j = b * 64 + lane;
+        const int jc = CHECK ? min(j, n - 1) : j;
+        const T xj = (T)xy[2 * (size_t)jc], yj = (T)xy[2 * (size_t)jc + 1];
+        const int sj = S > 1 ? species[jc] : 0;
+        const T dx = xi - xj, dy = yi - yj;
+        const T d2 = dx * dx + dy * dy;
+        T g = law_factor<LAW>(d2, c);
+        if (S > 1) g *= kw[si + sj];
+        if (CUT) g = d2 > c.cut2 ? (T)0 : g;
+        if (CHECK) g = (j >= n || j == i) ? (T)0 : g;
+        ax += dx * g;
+        ay += dy * g;
+    };
+    using Yes = std::integral_constant<bool, true>;
+    using No = std::integral_constant<bool, false>;
+    const int own = i >> 6, nfull = n >> 6;
+    const int a = min(own, nfull);
+#pragma unroll 4
+    for (int b = 0; b < a; ++b) piece(b, No{});
+    if (own < nfull) piece(own, Yes{});
+#pragma unroll 4
+    for (int b = own + 1; b < nfull; ++b) piece(b, No{});
+    if (nfull * 64 < n) piece(nfull, Yes{});
+    double fx = wave_sum((double)ax), fy = wave_sum((double)ay);
+    if (S == 1) {
+        fx *= (double)kw[0];
+        fy *= (double)kw[0];
+    }
+    if (lane == 0) {
+        f[2 * (size_t)i] = fx;
+        f[2 * (size_t)i + 1] = fy;
+    }
+}
+
+// ---------------------------------------------------------------- tiles
+// A block of j staged in LDS, ordered by species (ascending j inside a species): seg[s] .. seg[s + 1) holds species s.
 template <typename T>
+struct PfStage {
+    typename Vec2<T>::type pos[kPfJ];
+    short idx[kPfJ];                                  // j - jb
+    int cnt[BD_MAX_SPECIES * kPfChunks];              // per species and wavefront-sized piece: count, then start
+    int seg[BD_MAX_SPECIES + 1];
+};
+
+template <typename T>
+__device__ __forceinline__ void pf_stage(PfStage<T> &st, int S, int jb, int m, const double *__restrict__ xy,
+                                         const int32_t *__restrict__ species) {
+    using T2 = typename Vec2<T>::type;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int kRounds = kPfJ / kPfBlock;
+    __syncthreads();   // the previous block has been read
+    if (S == 1) {
+        for (int k = tid; k < m; k += kPfBlock) {
+            T2 v;
+            v.x = (T)xy[2 * (size_t)(jb + k)];
+            v.y = (T)xy[2 * (size_t)(jb + k) + 1];
+            st.pos[k] = v;
+            st.idx[k] = (short)k;
+        }
+        if (tid == 0) {
+            st.seg[0] = 0;
+            st.seg[1] = m;
+        }
+        __syncthreads();
+        return;
+    }
+    T2 v[kRounds];
+    int sp[kRounds], rank[kRounds];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const int k = r * kPfBlock + tid;
+        sp[r] = k < m ? species[jb + k] : -1;
+        if (k < m) {
+            v[r].x = (T)xy[2 * (size_t)(jb + k)];
+            v[r].y = (T)xy[2 * (size_t)(jb + k) + 1];
+        }
+        for (int s = 0; s < S; ++s) {
+            const unsigned long long mm = __ballot(sp[r] == s);
+            if (sp[r] == s) rank[r] = __popcll(mm & ((1ull << lane) - 1ull));
+            if (lane == 0) st.cnt[s * kPfChunks + r * (kPfBlock / 64) + wave] = __popcll(mm);
+        }
+    }
+    __syncthreads();
+    if (tid < 64) {   // exclusive scan of the S * kPfChunks <= 64 counts, species by species
+        const int c = tid < S * kPfChunks ? st.cnt[tid] : 0;
+        int incl = c;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int u = __shfl_up(incl, off);
+            if (tid >= off) incl += u;
+        }
+        if (tid < S * kPfChunks) st.cnt[tid] = incl - c;
+        if (tid < S * kPfChunks && tid % kPfChunks == 0) st.seg[tid / kPfChunks] = incl - c;
+        if (tid == S * kPfChunks - 1) st.seg[S] = incl;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const int s = sp[r];
+        if ((unsigned)s >= (unsigned)S) continue;
+        const int at = st.cnt[s * kPfChunks + r * (kPfBlock / 64) + wave] + rank[r];
+        st.pos[at] = v[r];
+        st.idx[at] = (short)(r * kPfBlock + tid);
+    }
+    __syncthreads();
+}
+
+// Adds the staged j [k0, k1) to the sums of P particles i.  SELF: the block may hold i itself (at index own[p]).
+template <typename T, int LAW, int P, bool SELF>
+__device__ __forceinline__ void pf_block(const PfStage<T> &st, int k0, int k1, const PfConst<T> &c, const T (&xi)[P],
+                                         const T (&yi)[P], const int (&own)[P], T (&ax)[P], T (&ay)[P]) {
+#pragma unroll 4
+    for (int k = k0; k < k1; ++k) {
+        const auto q = st.pos[k];
+        const int jk = SELF ? (int)st.idx[k] : 0;
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const T dx = xi[p] - q.x, dy = yi[p] - q.y;
+            const T d2 = dx * dx + dy * dy;
+            T g = law_factor<LAW>(d2, c);
+            if (SELF) g = own[p] == jk ? (T)0 : g;
+            ax[p] += dx * g;
+            ay[p] += dy * g;
+        }
+    }
+}
+
+// The same with a cutoff.  Most pairs are beyond it and a law costs many times the test, so a lane only notes the
+// staged j inside its cutoff (kPfHits per particle at most) and the wavefront evaluates the noted pairs together,
+// when a lane's list is full and at the end of the part: each lane still adds its pairs in staged order.
+constexpr int kPfHits = 16;
+
+template <typename T, int LAW, int P, bool SELF>
+__device__ __forceinline__ void pf_block_cut(const PfStage<T> &st, short (&hit)[P][kPfHits][kPfBlock], int k0, int k1,
+                                             const PfConst<T> &c, const T (&xi)[P], const T (&yi)[P],
+                                             const int (&own)[P], T (&ax)[P], T (&ay)[P]) {
+    const int tid = threadIdx.x;
+    int cnt[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) cnt[p] = 0;
+    auto evaluate = [&](int p, T &sx, T &sy) {
+        for (int h = 0; __ballot(h < cnt[p]) != 0; ++h) {
+            if (h < cnt[p]) {
+                const auto q = st.pos[hit[p][h][tid]];
+                const T dx = xi[p] - q.x, dy = yi[p] - q.y;
+                const T g = law_factor<LAW>(dx * dx + dy * dy, c);
+                sx += dx * g;
+                sy += dy * g;
+            }
+        }
+        cnt[p] = 0;
+    };
+    auto test = [&](int k, const typename Vec2<T>::type &q, int jk) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const T dx = xi[p] - q.x, dy = yi[p] - q.y;
+            const T d2 = dx * dx + dy * dy;
+            bool in = !(d2 > c.cut2);   // a d2 that is not a number is evaluated
+            if (SELF) in = in && own[p] != jk;
+            if (__ballot(in) != 0) {
+                if (in) hit[p][cnt[p]++][tid] = (short)k;
+                if (__ballot(cnt[p] == kPfHits) != 0) evaluate(p, ax[p], ay[p]);
+            }
+        }
+    };
+    constexpr int kU = 4;   // staged j read ahead
+    int k = k0;
+    for (; k + kU <= k1; k += kU) {
+        typename Vec2<T>::type q[kU];
+        int jk[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            q[u] = st.pos[k + u];
+            jk[u] = SELF ? (int)st.idx[k + u] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) test(k + u, q[u], jk[u]);
+    }
+    for (; k < k1; ++k) test(k, st.pos[k], SELF ? (int)st.idx[k] : 0);
+#pragma unroll
+    for (int p = 0; p < P; ++p) evaluate(p, ax[p], ay[p]);
+}
+
+// VALU-bound.  65,536 particles, two species, FP32 inverse square: 0.99 ms, 9 instructions an ordered pair at 0.99
+// of the issue rate (4.1 ms with the strength and the self test in the pair loop and an IEEE square root and
+// division).  20,011 particles, screened law, cutoff 12, FP64: 0.11 ms (0.41 ms evaluating the law wherever one of
+// the wavefront's lanes was in range).
+// grid (ceil(n / (256 P)), J); part[split * n + i] = sum over the split's j of K[s_i][s_j] g (r_i - r_j) / d.
+template <typename T, int LAW, bool CUT, int P>
 __global__ __launch_bounds__(kPfBlock) void k_pf_tiles(int n, int J, const double *__restrict__ xy,
                                                        const int32_t *__restrict__ species, PfLaw law,
                                                        typename Vec2<T>::type *__restrict__ part) {
     using T2 = typename Vec2<T>::type;
-    __shared__ T2 pos[kPfJ];
-    __shared__ int spc[kPfJ];
+    __shared__ PfStage<T> st;
     __shared__ T kw[BD_MAX_SPECIES * BD_MAX_SPECIES];
+    __shared__ short hit[CUT ? P : 1][CUT ? kPfHits : 1][CUT ? kPfBlock : 1];
     const int S = law.S;
-    for (int k = threadIdx.x; k < S * S; k += kPfBlock) kw[k] = (T)law.K[k];
-    const T cut2 = law.cutoff > 0.0 ? (T)(law.cutoff * law.cutoff) : (T)0;
-    const T expo = (T)(-0.5 * (law.q + 1.0));
-    const T invlam = (T)(1.0 / law.lam);
-
-    const int ib = blockIdx.x * kPfI;
-    T xi[kPfPer], yi[kPfPer], ax[kPfPer], ay[kPfPer];
-    int ii[kPfPer], si[kPfPer];
+    for (int k = threadIdx.x; k < S * S; k += kPfBlock) kw[k] = (T)law.K[k];   // read after pf_stage's barriers
+    const PfConst<T> c(law);
+    const int ib = blockIdx.x * kPfBlock * P;
+    T xi[P], yi[P], fx[P], fy[P];
+    int ii[P], si[P];
 #pragma unroll
-    for (int p = 0; p < kPfPer; ++p) {
+    for (int p = 0; p < P; ++p) {
         const int i = ib + p * kPfBlock + threadIdx.x;
-        const int c = i < n ? i : n - 1;
+        const int ic = i < n ? i : n - 1;
         ii[p] = i;
-        xi[p] = (T)xy[2 * (size_t)c];
-        yi[p] = (T)xy[2 * (size_t)c + 1];
-        si[p] = species[c];
-        ax[p] = (T)0;
-        ay[p] = (T)0;
+        xi[p] = (T)xy[2 * (size_t)ic];
+        yi[p] = (T)xy[2 * (size_t)ic + 1];
+        si[p] = species[ic] * S;
+        fx[p] = (T)0;
+        fy[p] = (T)0;
     }
+    // with a cutoff the pairs beyond it are skipped: a coordinate at infinity, whose pairs all lie beyond it but give
+    // 0 * inf, is found here instead (0 * x is 0 for every finite x)
+    __shared__ int at_infinity;
+    T zx = (T)0, zy = (T)0;
+    if (CUT && threadIdx.x == 0) at_infinity = 0;   // read after pf_stage's barriers
     const long long per = ((long long)n + J - 1) / J;
     const int j0 = (int)min((long long)n, per * blockIdx.y);
     const int j1 = (int)min((long long)n, per * (blockIdx.y + 1));
     for (int jb = j0; jb < j1; jb += kPfJ) {
         const int m = min(kPfJ, j1 - jb);
-        __syncthreads();   // the previous block of j has been read (and kw written before the first)
-        for (int k = threadIdx.x; k < m; k += kPfBlock) {
-            T2 v;
-            v.x = (T)xy[2 * (size_t)(jb + k)];
-            v.y = (T)xy[2 * (size_t)(jb + k) + 1];
-            pos[k] = v;
-            spc[k] = species[jb + k];
-        }
-        __syncthreads();
-        for (int k = 0; k < m; ++k) {
-            const T2 q = pos[k];
-            const int sj = spc[k];
-            const int j = jb + k;
+        pf_stage<T>(st, S, jb, m, xy, species);
+        if (CUT)
+            for (int k = threadIdx.x; k < m; k += kPfBlock) {
+                zx += (T)0 * (T)xy[2 * (size_t)(jb + k)];
+                zy += (T)0 * (T)xy[2 * (size_t)(jb + k) + 1];
+            }
+        const bool self = jb < ib + kPfBlock * P && jb + m > ib;   // uniform in the workgroup
+        int own[P];
 #pragma unroll
-            for (int p = 0; p < kPfPer; ++p) {
-                const T dx = xi[p] - q.x;
-                const T dy = yi[p] - q.y;
-                const T d2 = dx * dx + dy * dy;
-                const T g = ii[p] == j ? (T)0 : kw[si[p] * S + sj] * law_factor<T>(d2, law, cut2, expo, invlam);
-                ax[p] += dx * g;
-                ay[p] += dy * g;
+        for (int p = 0; p < P; ++p) own[p] = ii[p] - jb;
+        for (int s = 0; s < S; ++s) {
+            const int k0 = __builtin_amdgcn_readfirstlane(st.seg[s]), k1 = __builtin_amdgcn_readfirstlane(st.seg[s + 1]);
+            T ax[P], ay[P];
+#pragma unroll
+            for (int p = 0; p < P; ++p) ax[p] = ay[p] = (T)0;
+            if constexpr (CUT) {
+                if (self)
+                    pf_block_cut<T, LAW, P, true>(st, hit, k0, k1, c, xi, yi, own, ax, ay);
+                else
+                    pf_block_cut<T, LAW, P, false>(st, hit, k0, k1, c, xi, yi, own, ax, ay);
+            } else {
+                if (self)
+                    pf_block<T, LAW, P, true>(st, k0, k1, c, xi, yi, own, ax, ay);
+                else
+                    pf_block<T, LAW, P, false>(st, k0, k1, c, xi, yi, own, ax, ay);
+            }
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                const T w = kw[si[p] + s];
+                fx[p] += w * ax[p];
+                fy[p] += w * ay[p];
             }
         }
     }
+    if (CUT) {
+        if (zx != (T)0) atomicOr(&at_infinity, 1);
+        if (zy != (T)0) atomicOr(&at_infinity, 2);
+        __syncthreads();
+        const T nan = (T)NAN;
 #pragma unroll
-    for (int p = 0; p < kPfPer; ++p) {
+        for (int p = 0; p < P; ++p) {
+            fx[p] += (at_infinity & 1) ? nan : (T)0 * xi[p];
+            fy[p] += (at_infinity & 2) ? nan : (T)0 * yi[p];
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
         if (ii[p] < n) {
             T2 v;
-            v.x = ax[p];
-            v.y = ay[p];
+            v.x = fx[p];
+            v.y = fy[p];
             part[(size_t)blockIdx.y * n + ii[p]] = v;
         }
     }
@@ -137,6 +403,7 @@ __global__ void k_pf_reduce(int n, int J, const typename Vec2<T>::type *__restri
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     double fx = 0.0, fy = 0.0;
+#pragma unroll 8
     for (int s = 0; s < J; ++s) {
         const auto v = part[(size_t)s * n + i];
         fx += (double)v.x;
@@ -144,17 +411,6 @@ __global__ void k_pf_reduce(int n, int J, const typename Vec2<T>::type *__restri
     }
     f[2 * (size_t)i] = fx;
     f[2 * (size_t)i + 1] = fy;
-}
-
-// Number of j splits for n particles: enough workgroups to fill the device,
-// at least one block of i per split.  Depends on n only.
-int pf_splits(int n) {
-    const long long nb = ((long long)n + kPfI - 1) / kPfI;
-    long long J = (kPfTargetGroups + nb - 1) / nb;
-    J = J < 1 ? 1 : J;
-    J = J > kPfMaxSplits ? kPfMaxSplits : J;
-    const long long jmax = ((long long)n + kPfI - 1) / kPfI;
-    return (int)(J > jmax ? jmax : J);
 }
 
 size_t pf_value_bytes(int precision) { return precision == BD_PREC_FP32 ? sizeof(float2) : sizeof(double2); }
@@ -183,20 +439,85 @@ int pf_check(int32_t n, const double *xy, const int32_t *species, const bd_force
     return BD_OK;
 }
 
-// Enqueues the two kernels on `stream` with `part` as the split sums.
-int pf_enqueue(int32_t n, const double *xy, const int32_t *species, const PfLaw &law, int32_t precision,
-               double *f_out, hipStream_t stream, void *part, int J) {
-    const dim3 grid((n + kPfI - 1) / kPfI, J);
-    const dim3 rgrid((n + 255) / 256);
-    if (precision == BD_PREC_FP32) {
-        hipLaunchKernelGGL(k_pf_tiles<float>, grid, dim3(kPfBlock), 0, stream, n, J, xy, species, law,
-                           (float2 *)part);
-        hipLaunchKernelGGL(k_pf_reduce<float>, rgrid, dim3(256), 0, stream, n, J, (const float2 *)part, f_out);
-    } else {
-        hipLaunchKernelGGL(k_pf_tiles<double>, grid, dim3(kPfBlock), 0, stream, n, J, xy, species, law,
-                           (double2 *)part);
-        hipLaunchKernelGGL(k_pf_reduce<double>, rgrid, dim3(256), 0, stream, n, J, (const double2 *)part, f_out);
+// How a call runs; depends on n, the precision and the law only.
+struct PfPlan {
+    bool rows;   // rows layout
+    int J;       // tiles layout: j splits
+    size_t bytes;
+};
+
+constexpr size_t kPfPartBytes = size_t(32) << 20;   // most working memory of a call that more than one split needs
+
+// Particles i per lane of the tiles: one LDS read of a j serves them all.  Four for the shortest pair loop
+// (FP32 inverse square: 9 instructions); two where a pair is longer or notes its hits.
+template <typename T, int LAW, bool CUT>
+constexpr int pf_per_lane() { return sizeof(T) == 4 && LAW == PF_Q2 && !CUT ? 4 : 2; }
+
+PfPlan pf_plan(int n, int precision, const PfLaw &law) {
+    PfPlan p{};
+    const bool cut = law.cutoff > 0.0;
+    // Rows up to these sizes.  Measured, rows against tiles, two species, us: no cutoff, inverse square, FP64
+    // 27 / 33 at 5,000, 36 / 47 at 6,000, 60 / 49 at 8,192, FP32 25 / 34 at 6,000, 49 / 35 at 8,192; screened FP64
+    // 72 / 80 at 5,000, 165 / 137 at 8,192.  With a cutoff (12, 0.4 of the area covered), where rows evaluates the
+    // law for the lanes out of range too: screened FP64 43 / 47 at 3,300, 52 / 44 at 4,096, FP32 32 / 43 at 4,096,
+    // inverse square 22 / 42 at 4,096.
+    p.rows = n <= (cut ? 4096 : 6144);
+    if (p.rows) return p;
+    const bool four = precision == BD_PREC_FP32 && law.kind == BD_FORCE_POWER && law.q == 2.0 && !cut;
+    const long long per_group = (long long)kPfBlock * (four ? 4 : 2), nb = (n + per_group - 1) / per_group;
+    // enough splits to fill the device, of at least kPfBlock j, as far as the working memory reaches
+    long long J = (kPfTargetGroups + nb - 1) / nb;
+    const size_t row = (size_t)n * pf_value_bytes(precision);
+    J = std::min({J, (long long)kPfMaxSplits, ((long long)n + kPfBlock - 1) / kPfBlock,
+                  (long long)(kPfPartBytes / row)});
+    p.J = (int)std::max(1ll, J);
+    p.bytes = p.J * row;
+    return p;
+}
+
+template <typename T, int LAW, bool CUT>
+void pf_launch(int n, const double *xy, const int32_t *species, const PfLaw &law, double *f_out, hipStream_t stream,
+               void *part, const PfPlan &p) {
+    using T2 = typename Vec2<T>::type;
+    const dim3 block(kPfBlock);
+    if (p.rows) {
+        constexpr int kWaves = kPfBlock / 64;
+        hipLaunchKernelGGL((k_pf_rows<T, LAW, CUT>), dim3((n + kWaves - 1) / kWaves), block, 0, stream, n, xy,
+                           species, law, f_out);
+        return;
     }
+    constexpr int P = pf_per_lane<T, LAW, CUT>();
+    const dim3 grid((n + kPfBlock * P - 1) / (kPfBlock * P), p.J);
+    hipLaunchKernelGGL((k_pf_tiles<T, LAW, CUT, P>), grid, block, 0, stream, n, p.J, xy, species, law, (T2 *)part);
+    hipLaunchKernelGGL(k_pf_reduce<T>, dim3((n + 255) / 256), dim3(256), 0, stream, n, p.J, (const T2 *)part, f_out);
+}
+
+template <typename T>
+void pf_launch_law(int n, const double *xy, const int32_t *species, const PfLaw &law, double *f_out,
+                   hipStream_t stream, void *part, const PfPlan &p) {
+    const bool cut = law.cutoff > 0.0;
+    auto go = [&](auto form) {
+        constexpr int LAW = decltype(form)::value;
+        if (cut)
+            pf_launch<T, LAW, true>(n, xy, species, law, f_out, stream, part, p);
+        else
+            pf_launch<T, LAW, false>(n, xy, species, law, f_out, stream, part, p);
+    };
+    if (law.kind == BD_FORCE_SCREENED)
+        go(std::integral_constant<int, PF_SCREENED>{});
+    else if (law.q == 2.0)
+        go(std::integral_constant<int, PF_Q2>{});
+    else
+        go(std::integral_constant<int, PF_POWER>{});
+}
+
+// Enqueues the call's kernels on `stream` with `part` as the split sums.
+int pf_enqueue(int32_t n, const double *xy, const int32_t *species, const PfLaw &law, int32_t precision,
+               double *f_out, hipStream_t stream, void *part, const PfPlan &p) {
+    if (precision == BD_PREC_FP32)
+        pf_launch_law<float>(n, xy, species, law, f_out, stream, part, p);
+    else
+        pf_launch_law<double>(n, xy, species, law, f_out, stream, part, p);
     return hipGetLastError() == hipSuccess ? BD_OK : BD_ERR_DEVICE;
 }
 
@@ -208,15 +529,15 @@ extern "C" int bd_pair_forces_dev(int32_t n, const double *xy, const int32_t *sp
     const int rc = pf_check(n, xy, species, fp, precision, f_out, law);
     if (rc != BD_OK) return rc;
     const hipStream_t st = (hipStream_t)stream;
-    const int J = pf_splits(n);
+    const PfPlan p = pf_plan(n, precision, law);
     void *part = nullptr;
-    if (hipMalloc(&part, (size_t)J * n * pf_value_bytes(precision)) != hipSuccess) {
+    if (p.bytes && hipMalloc(&part, p.bytes) != hipSuccess) {
         (void)hipGetLastError();
         return BD_ERR_OOM;
     }
-    int out = pf_enqueue(n, xy, species, law, precision, f_out, st, part, J);
+    int out = pf_enqueue(n, xy, species, law, precision, f_out, st, part, p);
     if (hipStreamSynchronize(st) != hipSuccess) out = BD_ERR_DEVICE;
-    if (hipFree(part) != hipSuccess) out = BD_ERR_DEVICE;
+    if (part && hipFree(part) != hipSuccess) out = BD_ERR_DEVICE;
     return out;
 }
 
@@ -229,7 +550,7 @@ extern "C" int bd_pair_forces_dev(int32_t n, const double *xy, const int32_t *sp
 // never the array's host-side name.
 namespace {
 
-constexpr size_t kScratchBytes = size_t(32) << 20;
+constexpr size_t kScratchBytes = kPfPartBytes;
 constexpr int kMaxDevices = 64;
 
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -263,15 +584,14 @@ extern "C" int bd_pair_forces_dev_noalloc(int32_t n, const double *xy, const int
     PfLaw law;
     const int rc = pf_check(n, xy, species, fp, precision, f_out, law);
     if (rc != BD_OK) return rc;
-    const int J = pf_splits(n);
-    const size_t need = (size_t)J * (size_t)n * pf_value_bytes(precision);
-    if (need > kScratchBytes) {
+    const PfPlan p = pf_plan(n, precision, law);
+    if (p.bytes > kScratchBytes) {
         std::fprintf(stderr, "bd_pair_forces_dev_noalloc: n = %d needs %zu bytes of scratch, more than its %zu\n",
-                     (int)n, need, kScratchBytes);
+                     (int)n, p.bytes, kScratchBytes);
         return BD_ERR_INVALID_ARG;
     }
     void *part = scratch_for_current_device();
     if (!part) return BD_ERR_DEVICE;
     // every split sum that the reduction reads is written first: nothing to clear
-    return pf_enqueue(n, xy, species, law, precision, f_out, (hipStream_t)stream, part, J);
+    return pf_enqueue(n, xy, species, law, precision, f_out, (hipStream_t)stream, part, p);
 }

@@ -75,3 +75,47 @@ def test_pair_forces_dev_rejects_bad_arguments():
         binding.pair_forces_dev(xy, sp, np.zeros((9, 9)))   # S above BD_MAX_SPECIES
     with pytest.raises(binding.BDError):
         binding.pair_forces_dev(xy, sp, w.K, kind="screened", lam=-1.0)
+
+
+@pytest.mark.parametrize("law", ["q2", "q6", "screened_cut"])
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("n", [63, 64, 4096, 4097, 6144, 6145])
+def test_pair_forces_dev_layout_edges(law, fp32, n):
+    """Sizes around the layouts' limits (one wavefront per particle; staged tiles), ragged blocks, three species of
+    uneven number, one of them absent from whole staged blocks."""
+    import torch
+
+    w = synth.make("C1", n=n)
+    species = np.where(np.arange(n) < n // 2, 0, np.where(np.arange(n) % 7 == 0, 2, 1)).astype(np.int32)
+    K = np.array([[1e-2, -5e-3, 4e-3], [2e-3, 1e-2, 0.0], [-1e-3, 3e-3, 7e-3]])
+    xy = torch.from_numpy(np.ascontiguousarray(w.xy)).cuda()
+    sp = torch.from_numpy(species).cuda()
+    f = binding.pair_forces_dev(xy, sp, K, fp32=fp32, **LAWS[law]).cpu().numpy()
+    idx = np.unique(np.concatenate([[0, n // 2, n - 1], np.random.default_rng(3).integers(0, n, 400)])).astype(np.int32)
+    fo = oracle.forces(w.xy, species, K, idx=idx, **LAWS[law])
+    tol = 1e-4 if fp32 else 1e-12
+    assert np.abs(f[idx] - fo).max() <= tol * np.abs(fo).max()
+
+
+@pytest.mark.parametrize("n", [200, 7000])
+@pytest.mark.parametrize("law", ["q2", "screened_cut"])
+@pytest.mark.parametrize("fp32", [False, True])
+def test_pair_forces_dev_singular_positions(n, law, fp32):
+    """Two particles at one place: both forces non-finite, the others as without the pair's mutual term.  A particle
+    at infinity: its pairs give 0 * inf along x in every force, with and without a cutoff, and nothing along y."""
+    import torch
+
+    w = synth.make("C1", n=n)
+    sp = torch.zeros(n, dtype=torch.int32, device="cuda")
+    K = np.array([[1.0]])
+    xy = w.xy.copy()
+    xy[n - 1] = xy[3]
+    f = binding.pair_forces_dev(torch.from_numpy(xy).cuda(), sp, K, fp32=fp32, **LAWS[law]).cpu().numpy()
+    bad = np.zeros(n, bool)
+    bad[[3, n - 1]] = True
+    assert not np.isfinite(f[bad]).any() and np.isfinite(f[~bad]).all()
+    xy = w.xy.copy()
+    xy[5, 0] = np.inf
+    f = binding.pair_forces_dev(torch.from_numpy(xy).cuda(), sp, K, fp32=fp32, **LAWS[law]).cpu().numpy()
+    rest = np.arange(n) != 5
+    assert np.isnan(f[:, 0]).all() and np.isfinite(f[rest, 1]).all()
