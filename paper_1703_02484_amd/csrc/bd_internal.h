@@ -291,6 +291,8 @@ struct Sim {
     int *vt = nullptr;               // [T + 64] triangles rewritten by flips since the last overlap detection
     double2 *newpos = nullptr;
     double2 *oldpos = nullptr;       // positions of touched disks before an overlap round
+    int *star = nullptr;             // [n][16] stars of the disks of the current overlap round, by queue position
+    int *star_deg = nullptr;         // [n]
     // repair fallback: topology snapshot and the move it must replay
     int *snap_v = nullptr, *snap_twin = nullptr, *snap_vh = nullptr;
     double *xa = nullptr, *ya = nullptr, *xb = nullptr, *yb = nullptr;
@@ -380,23 +382,21 @@ void launch_nl_tail(Sim &s, const NlTailPlan &p);
 // reversal: 0 no test; 1 count reversed edges (Sec. 4.3); 2 count them and flag the step (K_REV) for halving
 void launch_flip_eval_full(Sim &s, int round, int slot, int reversal);
 void launch_flip_eval_list(Sim &s, int round, int slot);
+// the first evaluation after overlap round k: the edges at the disks it moved (and the slot's worklist)
+void launch_flip_eval_star(Sim &s, int k, int round, int slot);
 void launch_flip_apply(Sim &s, int round, int slot);
 void launch_flip_fix(Sim &s, int round, int slot);
 void launch_validate(Sim &s, int rep, int last = -1);   // last >= 0: also the repair check
-// validation after the repair that follows overlap round k: triangles at the disks round k moved and
-// triangles rewritten by flips since round k's detection
-void launch_validate_local(Sim &s, int rep, int k, int last = -1);
 void launch_snapshot(Sim &s);
 // overlap correction (k: overlap-round slot)
 // check: 0 none, 1 the overlap check of round k, 2 that and the final check
 // vrep >= 0: the same pass validates every triangle for repair vrep (last round slot vlast) and checks it first
 void launch_ovl_detect(Sim &s, int vstamp, int k, int check = 0, int vrep = -1, int vlast = -1);
-// validation after overlap round k's repair fused with round knew's detection (stars walked once)
-void launch_validate_detect_local(Sim &s, int rep, int k, int last, int vstamp, int knew, int check);
-// detection after round kprev: only edges at disks moved by round kprev and edges flipped since
-void launch_ovl_detect_local(Sim &s, int vstamp, int k, int kprev, int check = 0);
+// validation after overlap round k's repair (first flip round rfirst) fused with round knew's detection: the
+// triangles and edges at the disks round k moved, the triangles and edges flips rewrote since its detection
+void launch_validate_detect_local(Sim &s, int rep, int k, int rfirst, int last, int vstamp, int knew, int check);
 void launch_ovl_gather(Sim &s, int k);
-void launch_ovl_apply(Sim &s, int k, int next_round, int slot);
+void launch_ovl_apply(Sim &s, int k);
 // kinetic fallback helpers
 void launch_scatter_oldpos(Sim &s, int k);            // xa[v] = old position for disks touched in round k
 void launch_interp(Sim &s, int i, int k);             // x = xa + (i/k)(xb - xa); exactly xb when i == k

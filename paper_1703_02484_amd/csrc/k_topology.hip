@@ -22,7 +22,7 @@
 //          triangles with the round.
 //   fix    each flipped quad repairs the twin links of its outer half-edges
 //          (through `moved` when the neighbour flipped in the same round) and
-//          pushes the edges whose status may have changed to the next
+//          queues the edges whose status may have changed to the next
 //          worklist; a candidate that lost without any neighbour flipping
 //          re-queues itself.
 // The globally lowest candidate always wins both claims, so every round with a
@@ -35,6 +35,8 @@
 // left for the host to finish) or the overlap loop is done.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "bd_internal.h"
 #include "geom.h"
 
@@ -44,6 +46,7 @@ namespace {
 constexpr int kMaxGrid = 512;      // full scans over triangles that take per-workgroup atomics
 constexpr int kScanGrid = 4096;    // full scans without them (many waves in flight hide the gathers' latency)
 constexpr int kScanBlock = 1024;   // full scans with per-workgroup atomics: few workgroups, many waves
+constexpr int kStarGridMax = 1024;  // launches with one group of lanes per star
 constexpr int kListGridMax = 256;  // worklist-driven launches (usually a few hundred items, often none)
 
 struct Topo {
@@ -63,6 +66,7 @@ struct Topo {
     int *touched;           // [2][n], by overlap-round parity
     int *det_stamp, *fl_stamp, *fl, *vt_stamp, *vt;
     double2 *newpos, *oldpos;
+    int *star, *star_deg;   // star of each queued disk as its round's gather found it (see star_walk)
     int *ctl;
     unsigned long long *acc;
     const StepBase *base;   // stamps passed to kernels are relative to base->rbase / base->vbase
@@ -110,6 +114,8 @@ Topo topo_of(Sim &s) {
     t.vt = s.vt;
     t.newpos = s.newpos;
     t.oldpos = s.oldpos;
+    t.star = s.star;
+    t.star_deg = s.star_deg;
     t.ctl = s.ctl;
     t.acc = s.acc;
     t.base = s.dbase;
@@ -151,19 +157,26 @@ __device__ __forceinline__ void topo_err(const Topo &t) { atomicAdd(&t.ctl[K_TOP
 // the one the triangle spans.
 __device__ __forceinline__ double sep_p(double v, double P) { return P > 0.0 ? bd_min_image(v, P) : v; }
 
-__device__ __forceinline__ int flip_rule_of(const Topo &t, int a, int b, int c, int d, bool *inverted) {
-    const double2 pa = t.xy[a], pb = t.xy[b], pc = t.xy[c], pd = t.xy[d];
+__device__ __forceinline__ int flip_rule_at(const Topo &t, int a, int b, int c, int d, double2 pa, double2 pb,
+                                            double2 pc, double2 pd, bool *inverted) {
     if (t.P <= 0.0) return bd_flip_rule_xy(a, b, c, d, t.inf, pa.x, pa.y, pb.x, pb.y, pc.x, pc.y, pd.x, pd.y, true, inverted);
     return bd_flip_rule_quad(0.0, 0.0, sep_p(pb.x - pa.x, t.P), sep_p(pb.y - pa.y, t.P), sep_p(pc.x - pa.x, t.P),
                              sep_p(pc.y - pa.y, t.P), sep_p(pd.x - pa.x, t.P), sep_p(pd.y - pa.y, t.P), true,
                              inverted);
 }
 
-__device__ __forceinline__ double orient_of(const Topo &t, int a, int b, int c) {
-    const double2 pa = t.xy[a], pb = t.xy[b], pc = t.xy[c];
+__device__ __forceinline__ int flip_rule_of(const Topo &t, int a, int b, int c, int d, bool *inverted) {
+    return flip_rule_at(t, a, b, c, d, t.xy[a], t.xy[b], t.xy[c], t.xy[d], inverted);
+}
+
+__device__ __forceinline__ double orient_at(const Topo &t, double2 pa, double2 pb, double2 pc) {
     if (t.P <= 0.0) return bd_orient(pa.x, pa.y, pb.x, pb.y, pc.x, pc.y);
     return bd_orient(0.0, 0.0, sep_p(pb.x - pa.x, t.P), sep_p(pb.y - pa.y, t.P), sep_p(pc.x - pa.x, t.P),
                      sep_p(pc.y - pa.y, t.P));
+}
+
+__device__ __forceinline__ double orient_of(const Topo &t, int a, int b, int c) {
+    return orient_at(t, t.xy[a], t.xy[b], t.xy[c]);
 }
 
 __device__ __forceinline__ unsigned long long claim_key(int round, int e) {
@@ -278,22 +291,160 @@ __device__ __forceinline__ void push_edge(const Topo &t, int e, int stamp, int s
         wl_of(t, slot)[atomicAdd(&t.ctl[K_WL + slot], 1)] = e;
 }
 
+// push_edge for N edges of each lane at once (-1: none): their exchanges are in flight together, and one atomic
+// takes the positions of all of them.
+template <int CAP, int N>
+__device__ __forceinline__ void push_edges(const Topo &t, const int (&e)[N], int stamp, int slot, Stage<CAP> *st) {
+    int old[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) old[k] = e[k] >= 0 ? atomicExch(&t.edge_stamp[e[k]], stamp) : stamp;
+    unsigned long long m[N];
+    int total = 0;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        m[k] = __ballot(old[k] != stamp);
+        total += __popcll(m[k]);
+    }
+    if (total == 0) return;   // the same in every active lane
+    const int lane = __lane_id();
+    const int leader = __ffsll((unsigned long long)__ballot(true)) - 1;
+    int base = 0;
+    if (lane == leader) base = atomicAdd(st ? &st->cnt : &t.ctl[K_WL + slot], total);
+    base = __shfl(base, leader);
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        if (old[k] != stamp) {
+            const int pos = base + __popcll(m[k] & ((1ull << lane) - 1ull));
+            if (!st)
+                wl_of(t, slot)[pos] = e[k];
+            else if (pos < CAP)
+                st->buf[pos] = e[k];
+            else
+                wl_of(t, slot)[atomicAdd(&t.ctl[K_WL + slot], 1)] = e[k];
+        }
+        base += __popcll(m[k]);
+    }
+}
+
 // Is d already a neighbour of the finite vertex c?  A flip of (a, b) into
 // (c, d) is only a flip if c-d is not an edge yet: on an embedded
 // triangulation that always holds, but on a folded one (several inverted
 // triangles around a disk that crossed more than one edge) the inverted-
 // triangle rule can ask for it, and performing it would glue a duplicate edge.
 // The star is read during evaluation, before any flip of the round.
+// The two directions around c are walked at once: the walk is a chain of dependent loads, and this halves it.
 __device__ __forceinline__ bool adjacent(const Topo &t, int c, int d) {
     const int h0 = t.vert_he[c];
     if (bad_he(t, h0)) return true;
-    int h = h0, guard = 0;
-    do {
-        if (t.he_v[bd_next(h)] == d) return true;
-        h = t.he_twin[bd_prev(h)];
-        if (bad_he(t, h) || ++guard > 4096) return true;
-    } while (h != h0);
-    return false;
+    if (t.he_v[bd_next(h0)] == d) return true;
+    int hf = h0, hb = h0, guard = 0;
+    for (;;) {
+        const int tf = t.he_twin[bd_prev(hf)], tb = t.he_twin[hb];
+        if (bad_he(t, tf)) return true;
+        if (tf == hb) return false;
+        if (bad_he(t, tb)) return true;
+        const int nb = bd_next(tb);
+        if (t.he_v[bd_next(tf)] == d || t.he_v[bd_next(nb)] == d) return true;
+        if (nb == tf) return false;
+        if (++guard > 2048) return true;
+        hf = tf;
+        hb = nb;
+    }
+}
+
+// Stars, one per kStarLanes lanes.  The star of a disk is its outgoing half-edges in counter-clockwise order from
+// vert_he; lane q of the group holds half-edges q and q + kStarLanes with their far vertices.  Finding it is a
+// chain of dependent loads (each half-edge from the one before), walked from both ends at once by the whole group
+// (same addresses); everything after it is one load per lane.  Stars above kStarMax are left to one lane.
+constexpr int kStarLanes = 8, kStarMax = 16;
+
+struct Star {
+    int deg;         // kStarLarge: more than kStarMax; 0: the walk met an index out of range
+    int h[2], w[2];
+};
+constexpr int kStarLarge = -1;
+
+__device__ __forceinline__ int star_base() { return (int)__lane_id() & ~(kStarLanes - 1); }
+__device__ __forceinline__ int star_lane() { return (int)__lane_id() & (kStarLanes - 1); }
+// Value held for half-edge i of the star (two: some star of the wavefront has more than kStarLanes).
+template <typename T>
+__device__ __forceinline__ T star_get(const T (&x)[2], int i, bool two) {
+    const int src = star_base() + (i & (kStarLanes - 1));
+    const T a = __shfl(x[0], src);
+    if (!two) return a;
+    const T b = __shfl(x[1], src);
+    return i < kStarLanes ? a : b;
+}
+__device__ __forceinline__ double2 star_get2(const double2 (&x)[2], int i, bool two) {
+    const double ax[2] = {x[0].x, x[1].x}, ay[2] = {x[0].y, x[1].y};
+    return make_double2(star_get(ax, i, two), star_get(ay, i, two));
+}
+
+__device__ __forceinline__ Star star_walk(const Topo &t, int v) {
+    Star s;
+    s.deg = 0;
+    s.h[0] = s.h[1] = s.w[0] = s.w[1] = -1;
+    const int q = star_lane();
+    const int h0 = t.vert_he[v];
+    if (bad_he(t, h0)) return s;
+    int bh = -1, bw = -1;   // lane r: the r-th half-edge clockwise from vert_he
+    int hf = h0, hb = h0, nf = 1, nb = 0;
+    if (q == 0) {
+        s.h[0] = h0;
+        s.w[0] = t.he_v[bd_next(h0)];
+    }
+    for (;;) {
+        const int tf = t.he_twin[bd_prev(hf)], tb = t.he_twin[hb];
+        if (bad_he(t, tf)) return s;
+        if (tf == hb) break;
+        if (bad_he(t, tb)) return s;
+        if (nf + nb >= kStarMax) {
+            s.deg = kStarLarge;
+            return s;
+        }
+        const int cw = bd_next(tb);
+        if (q == (nf & (kStarLanes - 1))) {
+            const int w = t.he_v[bd_next(tf)];
+            if (nf < kStarLanes) {
+                s.h[0] = tf;
+                s.w[0] = w;
+            } else {
+                s.h[1] = tf;
+                s.w[1] = w;
+            }
+        }
+        ++nf;
+        if (cw == tf) break;
+        if (nf + nb >= kStarMax) {
+            s.deg = kStarLarge;
+            return s;
+        }
+        if (q == nb) {
+            bh = cw;
+            bw = t.he_v[bd_next(cw)];
+        }
+        ++nb;
+        hf = tf;
+        hb = cw;
+    }
+    const int deg = nf + nb;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {   // half-edge i >= nf is the (deg - 1 - i)-th clockwise one
+        const int i = q + u * kStarLanes;
+        const int src = star_base() + ((deg - 1 - i) & (kStarLanes - 1));
+        const int h = __shfl(bh, src), w = __shfl(bw, src);
+        if (i >= nf && i < deg) {
+            s.h[u] = h;
+            s.w[u] = w;
+        }
+    }
+    bool ok = true;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+        if (q + u * kStarLanes < deg && bad_v(t, s.w[u])) ok = false;
+    const unsigned long long group = ((1ull << kStarLanes) - 1ull) << star_base();
+    s.deg = (__ballot(!ok) & group) != 0 ? 0 : deg;
+    return s;
 }
 
 // Workgroup staging of flip candidates (LDS), for the full evaluation: lanes
@@ -321,6 +472,16 @@ __device__ __forceinline__ void register_flip(const Topo &t, int h, int tw, int 
         return;
     }
     const int t1 = h / 3, t2 = tw / 3;
+    // an edge may be evaluated more than once in a round: the first evaluation is the one that does not find its
+    // own claim.  An edge that finds a stronger claim cannot win this round and is looked at again in the next.
+    const unsigned long long key = claim_key(round, h);
+    const unsigned long long held = atomicMax(&t.claim[t1], key);
+    if (held == key) return;
+    atomicMax(&t.claim[t2], key);
+    if (held > key) {
+        push_edge(t, h, round + 1, slot + 1 == MAXR ? 0 : slot + 1);
+        return;
+    }
     const int2 cand = make_int2(h, t2 | (rule == BD_FLIP_INVERSION ? (int)0x80000000 : 0));
     if (st) {
         const int p = wave_reserve(&st->cnt, true);
@@ -331,9 +492,6 @@ __device__ __forceinline__ void register_flip(const Topo &t, int h, int tw, int 
     } else {
         t.cand[wave_reserve(&t.ctl[K_CAND + slot], true)] = cand;
     }
-    const unsigned long long key = claim_key(round, h);
-    atomicMax(&t.claim[t1], key);
-    atomicMax(&t.claim[t2], key);
 }
 
 // Evaluates the canonical edge h (h < twin) and, if it must flip, registers
@@ -504,6 +662,127 @@ __global__ void k_flip_eval_list(Topo t, int round, int slot) {
     cand_flush(t, slot, st);
 }
 
+// First evaluation of the repair after overlap round k: every edge of the triangles at the disks the round moved,
+// from the stars its gather recorded (the topology has not changed since).  Lane i of a star takes the edge to
+// its far vertex w_i and the edge w_i - w_(i+1) across from the disk.  No worklist: an edge of two moved disks is
+// evaluated by both.  65,536 disks: 17 us for the walk that queued the edges and 8 us for their evaluation before.
+template <int CAP = 1>
+__device__ __forceinline__ void flip_eval_star_body(const Topo &t, int k, int round, int slot, int i0, int stride,
+                                                    CandStage<CAP> *st = nullptr) {
+    if (stopped(t.ctl)) return;
+    round += t.base->rbase;
+    const int ntouched = t.ctl[K_TOUCH + k];
+    const int *touched = touched_of(t, k);
+    const int q = star_lane();
+    for (int g = i0 / kStarLanes; g < ntouched; g += stride / kStarLanes) {
+        const int v = touched[g];
+        const int deg = t.star_deg[g];
+        if (deg == kStarLarge) {
+            if (q != 0) continue;
+            const int h0 = t.vert_he[v];
+            if (bad_he(t, h0)) {
+                topo_err(t);
+                continue;
+            }
+            int h = h0, guard = 0;
+            do {
+                const int l = bd_next(h), tw = t.he_twin[h], lt = t.he_twin[l];
+                if (bad_he(t, tw) || bad_he(t, lt)) {
+                    topo_err(t);
+                    break;
+                }
+                eval_edge<CAP>(t, h < tw ? h : tw, h < tw ? tw : h, round, slot, 0, st);
+                eval_edge<CAP>(t, l < lt ? l : lt, l < lt ? lt : l, round, slot, 0, st);
+                h = t.he_twin[bd_prev(h)];
+                if (bad_he(t, h)) {
+                    topo_err(t);
+                    break;
+                }
+            } while (h != h0 && ++guard < 4096);
+            continue;
+        }
+        const bool two = __ballot(deg > kStarLanes) != 0;
+        const double2 pv = t.xy[v];
+        int h[2], w[2], lt[2], far[2];
+        double2 pw[2], pf[2];
+        const bool in[2] = {q < deg, q + kStarLanes < deg};
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            h[u] = w[u] = lt[u] = far[u] = -1;
+            pw[u] = pf[u] = pv;
+            if (u == 1 && !two) continue;
+            if (in[u]) h[u] = t.star[(size_t)g * kStarMax + u * kStarLanes + q];
+        }
+        bool ok = true;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if ((u == 1 && !two) || !in[u]) continue;
+            w[u] = t.he_v[bd_next(h[u])];
+            lt[u] = t.he_twin[bd_next(h[u])];
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if ((u == 1 && !two) || !in[u]) continue;
+            if (bad_he(t, lt[u]) || bad_v(t, w[u])) {
+                ok = false;
+                continue;
+            }
+            far[u] = t.he_v[bd_prev(lt[u])];
+            pw[u] = t.xy[w[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if ((u == 1 && !two) || !in[u] || !ok) continue;
+            if (bad_v(t, far[u])) {
+                ok = false;
+                continue;
+            }
+            pf[u] = t.xy[far[u]];
+        }
+        if (!ok) topo_err(t);
+        const unsigned long long group = ((1ull << kStarLanes) - 1ull) << star_base();
+        if ((__ballot(!ok) & group) != 0) continue;   // the group's lanes are here together
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (u == 1 && !two) continue;
+            const int i = q + u * kStarLanes;
+            const int ip = i + 1 >= deg ? 0 : i + 1, im = i == 0 ? deg - 1 : i - 1;
+            const int wn = star_get(w, ip, two), wp = star_get(w, im, two), hp = star_get(h, im, two);
+            const double2 pn = star_get2(pw, ip, two), pp = star_get2(pw, im, two);
+            if (!in[u]) continue;
+            {   // the edge v - w_i: triangles (v, w_i, w_(i+1)) and (w_i, v, w_(i-1))
+                const int tw = bd_prev(hp);
+                const bool fwd = h[u] < tw;
+                bool inverted = false;
+                const int rule = fwd ? flip_rule_at(t, v, w[u], wn, wp, pv, pw[u], pn, pp, &inverted)
+                                     : flip_rule_at(t, w[u], v, wp, wn, pw[u], pv, pp, pn, &inverted);
+                register_flip<CAP>(t, fwd ? h[u] : tw, fwd ? tw : h[u], fwd ? wn : wp, fwd ? wp : wn, rule, inverted,
+                                   round, slot, st);
+            }
+            {   // the edge w_i - w_(i+1): triangles (w_i, w_(i+1), v) and (w_(i+1), w_i, far)
+                const int l = bd_next(h[u]);
+                const bool fwd = l < lt[u];
+                bool inverted = false;
+                const int rule = fwd ? flip_rule_at(t, w[u], wn, v, far[u], pw[u], pn, pv, pf[u], &inverted)
+                                     : flip_rule_at(t, wn, w[u], far[u], v, pn, pw[u], pf[u], pv, &inverted);
+                register_flip<CAP>(t, fwd ? l : lt[u], fwd ? lt[u] : l, fwd ? v : far[u], fwd ? far[u] : v, rule,
+                                   inverted, round, slot, st);
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void k_flip_eval_star(Topo t, int k, int round, int slot) {
+    __shared__ CandStage<kEvalStage> st;
+    if (stopped(t.ctl)) return;   // nothing in this launch writes the stop flags: uniform
+    if (threadIdx.x == 0) st.cnt = 0;
+    __syncthreads();
+    const int i0 = xcd_block() * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+    flip_eval_star_body<kEvalStage>(t, k, round, slot, i0, stride, &st);
+    flip_eval_list_body<kEvalStage>(t, round, slot, i0, stride, &st);   // edges the repair before left blocked
+    cand_flush(t, slot, st);
+}
+
 __device__ __forceinline__ void flip_apply_body(const Topo &t, int round, int slot, int i0, int stride) {
     round += t.base->rbase;
     if (stopped(t.ctl)) return;
@@ -560,16 +839,23 @@ __device__ __forceinline__ void flip_apply_body(const Topo &t, int round, int sl
         t.cand_won[idx] = 1;
         // the new diagonal joins two disks that may never have been tested for overlap
         const int e = s1 + 2 < s2 + 2 ? s1 + 2 : s2 + 2;
-        const bool new_e = atomicExch(&t.fl_stamp[e], epoch) != epoch;
-        const int pe = wave_reserve(&t.ctl[K_FL_N], new_e);
-        if (new_e) t.fl[pe] = e;
-        // both rewritten triangles, for the validation that ends the repair
-        const bool new_t1 = atomicExch(&t.vt_stamp[t1], epoch) != epoch;
-        const bool new_t2 = atomicExch(&t.vt_stamp[t2], epoch) != epoch;
-        const int p1 = wave_reserve(&t.ctl[K_VT_N], new_t1);
-        const int p2 = wave_reserve(&t.ctl[K_VT_N], new_t2);
-        if (new_t1) t.vt[p1] = t1;
-        if (new_t2) t.vt[p2] = t2;
+        // and both rewritten triangles go to the validation that ends the repair (the exchanges, then the two
+        // counters, are in flight together: each is a round trip to the L2)
+        const int old_e = atomicExch(&t.fl_stamp[e], epoch);
+        const int old_1 = atomicExch(&t.vt_stamp[t1], epoch), old_2 = atomicExch(&t.vt_stamp[t2], epoch);
+        const unsigned long long me = __ballot(old_e != epoch), m1 = __ballot(old_1 != epoch),
+                                 m2 = __ballot(old_2 != epoch), lt = (1ull << __lane_id()) - 1ull;
+        const int leader = __ffsll((unsigned long long)__ballot(true)) - 1;
+        int be = 0, bt = 0;
+        if (__lane_id() == leader) {
+            be = atomicAdd(&t.ctl[K_FL_N], __popcll(me));
+            bt = atomicAdd(&t.ctl[K_VT_N], __popcll(m1) + __popcll(m2));
+        }
+        be = __shfl(be, leader);
+        bt = __shfl(bt, leader);
+        if (old_e != epoch) t.fl[be + __popcll(me & lt)] = e;
+        if (old_1 != epoch) t.vt[bt + __popcll(m1 & lt)] = t1;
+        if (old_2 != epoch) t.vt[bt + __popcll(m1) + __popcll(m2 & lt)] = t2;
         wave_count64(&t.acc[A_FLIPS], true);
         wave_count64(&t.acc[A_INV_FLIPS], (cd.y & (int)0x80000000) != 0);
     }
@@ -590,35 +876,46 @@ __device__ __forceinline__ void flip_fix_body(const Topo &t, int round, int slot
     for (int idx = i0; idx < ncand; idx += stride) {
         const int2 cd = t.cand[idx];
         const int h = cd.x, t1 = h / 3, t2 = cd.y & 0x7FFFFFFF;
+        // the edges to queue: a flip's four outer edges and its diagonal, or the candidate itself when it lost
+        // and neither of its triangles flipped (loads, exchanges and list positions of the five taken together)
+        int e[5] = {-1, -1, -1, -1, -1};
         if (!t.cand_won[idx]) {
-            if (t.tri_stamp[t1] != round && t.tri_stamp[t2] != round) push_edge(t, h, next, nslot, st);
-            continue;
-        }
-        const int outer[4] = {3 * t1 + 0, 3 * t1 + 1, 3 * t2 + 0, 3 * t2 + 1};
+            if (t.tri_stamp[t1] != round && t.tri_stamp[t2] != round) e[4] = h;
+        } else {
+            const int outer[4] = {3 * t1 + 0, 3 * t1 + 1, 3 * t2 + 0, 3 * t2 + 1};
+            int o[4], mv[4], ts[4];
+            bool ok[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int nh = outer[k];
-            const int o = t.he_twin[nh];
-            if (bad_he(t, o)) {
-                topo_err(t);
-                continue;
+            for (int k = 0; k < 4; ++k) {
+                o[k] = t.he_twin[outer[k]];
+                ok[k] = !bad_he(t, o[k]);
+                if (!ok[k]) topo_err(t);
             }
-            int tw;
-            if (t.tri_stamp[o / 3] == round) {
-                tw = t.moved[o];
-                if (bad_he(t, tw)) {
-                    topo_err(t);
-                    continue;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                ts[k] = ok[k] ? t.tri_stamp[o[k] / 3] : 0;
+                mv[k] = ok[k] ? t.moved[o[k]] : 0;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (!ok[k]) continue;
+                int tw = o[k];
+                if (ts[k] == round) {
+                    tw = mv[k];
+                    if (bad_he(t, tw)) {
+                        topo_err(t);
+                        continue;
+                    }
+                    t.he_twin[outer[k]] = tw;
+                } else {
+                    t.he_twin[tw] = outer[k];
                 }
-                t.he_twin[nh] = tw;
-            } else {
-                tw = o;
-                t.he_twin[o] = nh;
+                e[k] = outer[k] < tw ? outer[k] : tw;
             }
-            push_edge(t, nh < tw ? nh : tw, next, nslot, st);
+            const int d1 = 3 * t1 + 2, d2 = 3 * t2 + 2;
+            e[4] = d1 < d2 ? d1 : d2;
         }
-        const int d1 = 3 * t1 + 2, d2 = 3 * t2 + 2;
-        push_edge(t, d1 < d2 ? d1 : d2, next, nslot, st);
+        push_edges<CAP, 5>(t, e, next, nslot, st);
     }
 }
 
@@ -644,44 +941,6 @@ __device__ __forceinline__ void validate_tri(const Topo &t, int tri, int *inv) {
     }
     if (a >= t.inf || b >= t.inf || c >= t.inf) return;
     if (orient_of(t, a, b, c) <= 0.0) atomicAdd(inv, 1);
-}
-
-// After the repair that follows overlap round k the triangulation was valid
-// before the round, so a triangle can only have lost its orientation if one
-// of its disks moved in round k or a flip rewrote it: only those are checked
-// (a triangle may be checked more than once; the count only has to be > 0).
-__device__ __forceinline__ void validate_local_body(const Topo &t, int *inv, int k, int i0, int stride) {
-    if (stopped(t.ctl)) return;
-    const int nmoved = t.ctl[K_TOUCH + k];
-    const int nvt = t.ctl[K_VT_N];
-    const int *moved = touched_of(t, k);
-    for (int idx = i0; idx < nmoved + nvt; idx += stride) {
-        if (idx >= nmoved) {
-            const int tri = t.vt[idx - nmoved];
-            if ((unsigned)tri >= (unsigned)t.T) {
-                topo_err(t);
-                continue;
-            }
-            validate_tri(t, tri, inv);
-            continue;
-        }
-        const int v = moved[idx];
-        const int h0 = t.vert_he[v];
-        if (bad_he(t, h0)) {
-            topo_err(t);
-            continue;
-        }
-        int h = h0, guard = 0;
-        do {
-            validate_tri(t, h / 3, inv);
-            h = t.he_twin[bd_prev(h)];
-            if (bad_he(t, h) || ++guard > 4096) {
-                atomicAdd(inv, 1);
-                topo_err(t);
-                break;
-            }
-        } while (h != h0);
-    }
 }
 
 // End of repair `rep` whose last round used slot `last`: halt the step when the
@@ -727,16 +986,6 @@ __global__ __launch_bounds__(kScanBlock) void k_validate(Topo t, int rep, int la
     if (last >= 0 && last_workgroup(t.ctl, added) && threadIdx.x == 0) repair_check_body(t.ctl, rep, last);
 }
 
-__global__ void k_validate_local(Topo t, int rep, int k, int last) {
-    __shared__ int inv;
-    if (stopped(t.ctl)) return;
-    if (threadIdx.x == 0) inv = 0;
-    __syncthreads();
-    validate_local_body(t, &inv, k, xcd_block() * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
-    const bool added = add_block_count(&t.ctl[K_INV + rep], &inv);
-    if (last >= 0 && last_workgroup(t.ctl, added) && threadIdx.x == 0) repair_check_body(t.ctl, rep, last);
-}
-
 // ---------------------------------------------------------------- overlaps
 // Detect: every Delaunay edge between two disks with d < (r_i + r_j)(1 - tol)
 // (Algorithm 2 test, Sec. 2.3 contact distance); both ends are queued once
@@ -761,14 +1010,6 @@ __device__ __forceinline__ void mark_touched(const Topo &t, int v, int stamp, in
 
 __device__ __forceinline__ void ovl_check_body(int *ctl, int k, int stamp, const StepBase *base);
 __device__ __forceinline__ void final_check_body(int *ctl, int k);
-
-// Check after detection k (check = 1), and the final check after the last
-// budgeted detection (check = 2), run by the detection's last workgroup.
-__device__ __forceinline__ void detect_checks(const Topo &t, int k, int stamp, int check, bool released) {
-    if (check == 0 || !last_workgroup(t.ctl, released) || threadIdx.x != 0) return;
-    ovl_check_body(t.ctl, k, stamp, t.base);
-    if (check == 2) final_check_body(t.ctl, k);
-}
 
 // Full detection.  A step's first detection finds tens of thousands of
 // overlapping pairs on a large system; the disks it marks are staged in the
@@ -884,63 +1125,30 @@ __global__ __launch_bounds__(kDetBlock) void k_ovl_detect(Topo t, int rstamp, do
 // edge that overlapped at round kprev's detection moved) or if a flip since
 // that detection created it; every other edge was tested then and neither of
 // its disks has moved.  So only the stars of the disks moved by round kprev
-// and the flipped list are tested, each edge once (det_stamp).
+// and the flipped list are tested; an overlapping edge counts once (det_stamp).
+// An overlapping edge (canonical id e), counted and its disks queued the first time it is found.
+template <int CAP = 1>
+__device__ __forceinline__ void found_edge(const Topo &t, int e, int a, int b, int stamp, int k, int &found,
+                                           Stage<CAP> *st = nullptr) {
+    if (atomicExch(&t.det_stamp[e], stamp) == stamp) return;
+    ++found;
+    mark_touched(t, a, stamp, k, st);
+    mark_touched(t, b, stamp, k, st);
+}
+
 template <int CAP = 1>
 __device__ __forceinline__ void detect_edge(const Topo &t, int h, int stamp, double keep, int k, int &found,
                                             Stage<CAP> *st = nullptr) {
     const int tw = t.he_twin[h];
     if (bad_he(t, tw)) return topo_err(t);
     const int e = h < tw ? h : tw;
-    if (atomicExch(&t.det_stamp[e], stamp) == stamp) return;
     const int a = t.he_v[e], b = t.he_v[bd_next(e)];
     if (bad_v(t, a) || bad_v(t, b)) return topo_err(t);
     if (a >= t.n || b >= t.n) return;
     const double2 pa = t.xy[a], pb = t.xy[b];
     const double dx = sep_p(pa.x - pb.x, t.P), dy = sep_p(pa.y - pb.y, t.P);
     const double d = sqrt(dx * dx + dy * dy);
-    if (d < (t.ru > 0.0 ? t.ru + t.ru : t.rad[a] + t.rad[b]) * keep) {
-        ++found;
-        mark_touched(t, a, stamp, k, st);
-        mark_touched(t, b, stamp, k, st);
-    }
-}
-
-// Returns the overlapping edges this thread found (the caller adds them to K_OVL + k).
-__device__ __forceinline__ int ovl_detect_local_body(const Topo &t, int stamp, double keep, int k, int kprev, int i0, int stride) {
-#pragma clang fp contract(off)
-    if (stopped(t.ctl)) return 0;
-    stamp += t.base->vbase;
-    const int nprev = t.ctl[K_TOUCH + kprev];
-    const int nfl = t.ctl[K_FL_N];
-    const int *prev = touched_of(t, kprev);
-    int found = 0;
-    for (int idx = i0; idx < nprev + nfl; idx += stride) {
-        if (idx >= nprev) {
-            const int e = t.fl[idx - nprev];
-            if (bad_he(t, e)) {
-                topo_err(t);
-                continue;
-            }
-            detect_edge(t, e, stamp, keep, k, found);
-            continue;
-        }
-        const int v = prev[idx];
-        const int h0 = t.vert_he[v];
-        if (bad_he(t, h0)) {
-            topo_err(t);
-            continue;
-        }
-        int h = h0, guard = 0;
-        do {
-            detect_edge(t, h, stamp, keep, k, found);
-            h = t.he_twin[bd_prev(h)];
-            if (bad_he(t, h) || ++guard > 4096) {
-                topo_err(t);
-                break;
-            }
-        } while (h != h0);
-    }
-    return found;
+    if (d < (t.ru > 0.0 ? t.ru + t.ru : t.rad[a] + t.rad[b]) * keep) found_edge(t, e, a, b, stamp, k, found, st);
 }
 
 // The validation of the repair after overlap round k fused with the next
@@ -954,59 +1162,124 @@ __device__ __forceinline__ int ovl_detect_local_body(const Topo &t, int stamp, d
 // Body: inv is the repair's invalid-triangle counter, or a workgroup's share
 // of it in LDS; the stamp st is absolute.  Returns the overlapping edges this thread found (the caller adds them
 // to K_OVL + knew).
+// The stars are those the round's gather recorded where no flip of the repair (rounds rfirst and later, relative)
+// rewrote one of their triangles, else walked again.  One lane per edge and triangle of a star: 65,536 disks,
+// 23 us as one thread per star, which exchanged a stamp per edge.
 template <int CAP = 1>
-__device__ __forceinline__ int validate_detect_local_body(const Topo &t, int *inv, int k, int st, double keep,
-                                                          int knew, int i0, int stride, Stage<CAP> *stage = nullptr) {
+__device__ __forceinline__ int validate_detect_local_body(const Topo &t, int *inv, int k, int rfirst, int st,
+                                                          double keep, int knew, int i0, int stride,
+                                                          Stage<CAP> *stage = nullptr) {
 #pragma clang fp contract(off)
     const int nmoved = t.ctl[K_TOUCH + k];
     const int nvt = t.ctl[K_VT_N];
     const int nfl = t.ctl[K_FL_N];
+    rfirst += t.base->rbase;
     const int *moved = touched_of(t, k);
+    const int q = star_lane();
     int found = 0;
-    for (int idx = i0; idx < nmoved + nvt + nfl; idx += stride) {
-        if (idx >= nmoved + nvt) {
-            const int e = t.fl[idx - nmoved - nvt];
-            if (bad_he(t, e)) {
-                topo_err(t);
-                continue;
-            }
-            detect_edge(t, e, st, keep, knew, found, stage);
-            continue;
+    for (int g = i0 / kStarLanes; g < nmoved; g += stride / kStarLanes) {
+        const int v = moved[g];
+        Star s;
+        s.deg = t.star_deg[g];
+        bool rewritten = s.deg <= 0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int i = q + u * kStarLanes;
+            s.h[u] = i < s.deg ? t.star[(size_t)g * kStarMax + i] : -1;
+            s.w[u] = i < s.deg ? t.he_v[bd_next(s.h[u])] : -1;
+            if (i < s.deg && t.tri_stamp[s.h[u] / 3] >= rfirst) rewritten = true;
         }
-        if (idx >= nmoved) {
-            const int tri = t.vt[idx - nmoved];
-            if ((unsigned)tri >= (unsigned)t.T) {
-                topo_err(t);
-                continue;
-            }
-            validate_tri(t, tri, inv);
-            continue;
-        }
-        const int v = moved[idx];
-        const int h0 = t.vert_he[v];
-        if (bad_he(t, h0)) {
-            topo_err(t);
-            continue;
-        }
-        int h = h0, guard = 0;
-        do {
-            validate_tri(t, h / 3, inv);
-            detect_edge(t, h, st, keep, knew, found, stage);
-            h = t.he_twin[bd_prev(h)];
-            if (bad_he(t, h) || ++guard > 4096) {
+        const unsigned long long group = ((1ull << kStarLanes) - 1ull) << star_base();
+        if ((__ballot(rewritten) & group) != 0) s = star_walk(t, v);
+        if (s.deg == 0) {
+            if (q == 0) {
                 atomicAdd(inv, 1);
                 topo_err(t);
-                break;
             }
-        } while (h != h0);
+            continue;
+        }
+        if (s.deg == kStarLarge) {
+            if (q != 0) continue;
+            const int h0 = t.vert_he[v];
+            int h = h0, guard = 0;
+            do {
+                validate_tri(t, h / 3, inv);
+                detect_edge(t, h, st, keep, knew, found, stage);
+                h = t.he_twin[bd_prev(h)];
+                if (bad_he(t, h) || ++guard > 4096) {
+                    atomicAdd(inv, 1);
+                    topo_err(t);
+                    break;
+                }
+            } while (h != h0);
+            continue;
+        }
+        const bool two = __ballot(s.deg > kStarLanes) != 0;
+        const double2 pv = t.xy[v];
+        const double rv = t.ru > 0.0 ? t.ru : t.rad[v];
+        double2 pw[2] = {pv, pv};
+        bool bad = false;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (q + u * kStarLanes < s.deg) {
+                bad = bad || bad_v(t, s.w[u]);
+                if (!bad) pw[u] = t.xy[s.w[u]];
+            }
+        if (bad) {
+            atomicAdd(inv, 1);
+            topo_err(t);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (u == 1 && !two) continue;
+            const int i = q + u * kStarLanes;
+            const int ip = i + 1 >= s.deg ? 0 : i + 1;
+            const int wn = star_get(s.w, ip, two);
+            const double2 pn = star_get2(pw, ip, two);
+            if (i >= s.deg || bad) continue;
+            const int w = s.w[u];
+            if (w < t.inf && wn < t.inf) {   // the triangle (v, w, wn), tested from its first half-edge on
+                const int r = s.h[u] % 3;
+                const double o = r == 0   ? orient_at(t, pv, pw[u], pn)
+                                 : r == 1 ? orient_at(t, pn, pv, pw[u])
+                                          : orient_at(t, pw[u], pn, pv);
+                if (o <= 0.0) atomicAdd(inv, 1);
+            }
+            if (w < t.n) {
+                const double dx = sep_p(pv.x - pw[u].x, t.P), dy = sep_p(pv.y - pw[u].y, t.P);
+                const double d = sqrt(dx * dx + dy * dy);
+                if (d < (rv + (t.ru > 0.0 ? t.ru : t.rad[w])) * keep) {
+                    const int tw = t.he_twin[s.h[u]];
+                    if (bad_he(t, tw))
+                        topo_err(t);
+                    else
+                        found_edge(t, s.h[u] < tw ? s.h[u] : tw, v, w, st, knew, found, stage);
+                }
+            }
+        }
+    }
+    for (int idx = i0; idx < nvt + nfl; idx += stride) {
+        if (idx >= nvt) {
+            const int e = t.fl[idx - nvt];
+            if (bad_he(t, e))
+                topo_err(t);
+            else
+                detect_edge(t, e, st, keep, knew, found, stage);
+            continue;
+        }
+        const int tri = t.vt[idx];
+        if ((unsigned)tri >= (unsigned)t.T)
+            topo_err(t);
+        else
+            validate_tri(t, tri, inv);
     }
     return found;
 }
 
 constexpr int kTouchStage = 2048;
 
-__global__ void k_validate_detect_local(Topo t, int rep, int k, int last, int stamp, double keep, int knew,
-                                        int check) {
+__global__ __launch_bounds__(256) void k_validate_detect_local(Topo t, int rep, int k, int rfirst, int last, int stamp,
+                                                               double keep, int knew, int check) {
     __shared__ int inv, nfound;
     __shared__ Stage<kTouchStage> st;
     if (stopped(t.ctl)) return;   // nothing in this launch writes the stop flags before its last workgroup
@@ -1015,7 +1288,7 @@ __global__ void k_validate_detect_local(Topo t, int rep, int k, int last, int st
         nfound = 0;
     }
     stage_init(st);
-    int found = validate_detect_local_body(t, &inv, k, stamp + t.base->vbase, keep, knew,
+    int found = validate_detect_local_body(t, &inv, k, rfirst, stamp + t.base->vbase, keep, knew,
                                            xcd_block() * blockDim.x + threadIdx.x, gridDim.x * blockDim.x, &st);
     stage_flush(st, &t.ctl[K_TOUCH + knew], touched_of(t, knew));
     for (int off = 32; off > 0; off >>= 1) found += __shfl_xor(found, off);
@@ -1027,19 +1300,6 @@ __global__ void k_validate_detect_local(Topo t, int rep, int k, int last, int st
         ovl_check_body(t.ctl, knew, stamp, t.base);
         if (check == 2) final_check_body(t.ctl, knew);
     }
-}
-
-__global__ void k_ovl_detect_local(Topo t, int stamp, double keep, int k, int kprev, int check) {
-    __shared__ int nfound;
-    if (stopped(t.ctl)) return;
-    if (threadIdx.x == 0) nfound = 0;
-    __syncthreads();
-    int found = ovl_detect_local_body(t, stamp, keep, k, kprev, xcd_block() * blockDim.x + threadIdx.x,
-                                      gridDim.x * blockDim.x);
-    for (int off = 32; off > 0; off >>= 1) found += __shfl_xor(found, off);
-    if (__lane_id() == 0 && found) atomicAdd(&nfound, found);
-    const bool added = add_block_count(&t.ctl[K_OVL + k], &nfound);
-    detect_checks(t, k, stamp, check, added);
 }
 
 // Overlap round k found nothing: the overlap loop of this step is done.  The
@@ -1073,132 +1333,142 @@ __device__ __forceinline__ void final_check_body(int *ctl, int k) {
 // (Sec. 2.3 displacement along the unit vector, factor f), starting at the
 // neighbour of smallest id so the summation order is independent of flip
 // history; truncate the sum to cap_frac * r (Sec. 4.4); reflect at the walls
-// (fold into the box when periodic).  The star is walked once: each
-// neighbour's contribution is kept in registers (stars of up to kStarCache
-// neighbours) and the sum is then folded in the canonical order with static
-// indices; a larger star is walked a second time in that order.
-constexpr int kStarCache = 10;
+// (fold into the box when periodic).  One group of lanes per star (star_walk),
+// which is recorded for the first evaluation of the repair and the detection
+// that follow; the lanes' contributions are added in the canonical order.  The
+// time is the chain of the walk: 65,536 disks, 16 us as one thread per star
+// walked from one end.
+
+// Displacement of disk v (at pv, radius rv) by its neighbour w; false when they do not overlap.
+__device__ __forceinline__ bool ovl_term(const Topo &t, double2 pv, double rv, int w, double2 pw, double f,
+                                         double keep, double &cx, double &cy) {
+#pragma clang fp contract(off)
+    const double dx = sep_p(pv.x - pw.x, t.P), dy = sep_p(pv.y - pw.y, t.P);
+    const double d = sqrt(dx * dx + dy * dy);
+    const double contact = rv + (t.ru > 0.0 ? t.ru : t.rad[w]);
+    if (!(d < contact * keep)) return false;
+    const double sc = f * (contact - d) / d;
+    cx = sc * dx;
+    cy = sc * dy;
+    return true;
+}
 
 __device__ __forceinline__ void ovl_gather_body(const Topo &t, int k, double f, double cap_frac, double keep, int i0, int stride) {
 #pragma clang fp contract(off)
     if (stopped(t.ctl)) return;
     const int ntouched = t.ctl[K_TOUCH + k];
     const int *touched = touched_of(t, k);
-    for (int idx = i0; idx < ntouched; idx += stride) {
+    const int q = star_lane();
+    const bool rec = t.tev != nullptr;   // adjoint tape: entry idx of this round for disk idx
+    for (int idx = i0 / kStarLanes; idx < ntouched; idx += stride / kStarLanes) {
         const int v = touched[idx];
         const double2 pv = t.xy[v];
-        const double xv = pv.x, yv = pv.y, rv = t.ru > 0.0 ? t.ru : t.rad[v];
+        const double rv = t.ru > 0.0 ? t.ru : t.rad[v];
         const double L = t.Lr[t.rep_of[v]];
-        t.newpos[idx] = make_double2(xv, yv);
-        const int h0 = t.vert_he[v];
-        if (bad_he(t, h0)) {
-            topo_err(t);
+        const Star s = star_walk(t, v);
+        if (q == 0) t.star_deg[idx] = s.deg;
+        if (s.deg == 0) {
+            if (q == 0) {
+                t.newpos[idx] = pv;
+                topo_err(t);
+                atomicAdd(&t.ctl[K_STAR], 1);
+            }
             continue;
         }
-        // walk: neighbour ids and contributions (0 for a non-overlapping or non-disk neighbour)
-        int nid[kStarCache];
-        double cxs[kStarCache], cys[kStarCache];
-        int best = h0, bestid = 0x7FFFFFFF, bestpos = 0, deg = 0;
-        int h = h0;
-        int guard = 0;
-        bool broken = false;
-#pragma unroll
-        for (int q = 0; q < kStarCache; ++q) {
-            nid[q] = -1;
-            cxs[q] = 0.0;
-            cys[q] = 0.0;
-        }
-        do {
-            const int w = t.he_v[bd_next(h)];
-            if (bad_v(t, w)) {
-                broken = true;
-                break;
-            }
-            if (w < t.inf && w < bestid) {
-                bestid = w;
-                best = h;
-                bestpos = deg;
-            }
-            if (deg < kStarCache && w < t.n) {
-                const double2 pw = t.xy[w];
-                const double dx = sep_p(xv - pw.x, t.P), dy = sep_p(yv - pw.y, t.P);
-                const double d = sqrt(dx * dx + dy * dy);
-                const double contact = rv + (t.ru > 0.0 ? t.ru : t.rad[w]);
-                double cx = 0.0, cy = 0.0;
-                int id = -1;
-                if (d < contact * keep) {
-                    const double sc = f * (contact - d) / d;
-                    cx = sc * dx;
-                    cy = sc * dy;
-                    id = w;
-                }
-#pragma unroll
-                for (int q = 0; q < kStarCache; ++q)
-                    if (q == deg) {
-                        nid[q] = id;
-                        cxs[q] = cx;
-                        cys[q] = cy;
-                    }
-            }
-            ++deg;
-            h = t.he_twin[bd_prev(h)];
-            if (bad_he(t, h) || ++guard > 4096) {
-                broken = true;
-                break;
-            }
-        } while (h != h0);
-        if (broken) {
-            topo_err(t);
-            atomicAdd(&t.ctl[K_STAR], 1);
-            continue;
-        }
-        // adjoint tape: entry of this disk in this round
-        const bool rec = t.tev != nullptr;
         const int e = rec ? t.tent_base + t.ctl[K_TAPE_ENT] + idx : 0;
         const bool room = rec && e < t.tcap_ent;
-        if (rec && !room) atomicOr(&t.ctl[K_TAPE_OVF], 1);
+        if (rec && !room && q == 0) atomicOr(&t.ctl[K_TAPE_OVF], 1);
         int na = 0;
         double sx = 0.0, sy = 0.0;
-        if (deg <= kStarCache) {
-            // canonical order: positions bestpos .. deg-1, then 0 .. bestpos-1
-#pragma unroll
-            for (int pass = 0; pass < 2; ++pass) {
-#pragma unroll
-                for (int q = 0; q < kStarCache; ++q) {
-                    const bool in = pass == 0 ? (q >= bestpos && q < deg) : (q < bestpos);
-                    if (in && nid[q] >= 0) {
-                        sx += cxs[q];
-                        sy += cys[q];
-                        if (room && na < MAXACT) t.tenb[(size_t)e * MAXACT + na] = nid[q];
-                        ++na;
-                    }
+        if (s.deg == kStarLarge) {
+            if (q != 0) continue;
+            // one lane: the neighbour of smallest id, then the sum around the star from there
+            const int h0 = t.vert_he[v];
+            int best = h0, bestid = 0x7FFFFFFF, h = h0, guard = 0;
+            bool broken = false;
+            do {
+                const int w = t.he_v[bd_next(h)];
+                if (bad_v(t, w)) {
+                    broken = true;
+                    break;
                 }
+                if (w < t.inf && w < bestid) {
+                    bestid = w;
+                    best = h;
+                }
+                h = t.he_twin[bd_prev(h)];
+                if (bad_he(t, h) || ++guard > 4096) {
+                    broken = true;
+                    break;
+                }
+            } while (h != h0);
+            if (broken) {
+                t.newpos[idx] = pv;
+                topo_err(t);
+                atomicAdd(&t.ctl[K_STAR], 1);
+                continue;
             }
-        } else {
             h = best;
             do {
-                int w = t.he_v[bd_next(h)];
-                if (w < t.n) {
-                    const double2 pw = t.xy[w];
-                    double dx = sep_p(xv - pw.x, t.P), dy = sep_p(yv - pw.y, t.P);
-                    double d = sqrt(dx * dx + dy * dy);
-                    double contact = rv + (t.ru > 0.0 ? t.ru : t.rad[w]);
-                    if (d < contact * keep) {
-                        double sc = f * (contact - d) / d;
-                        sx += sc * dx;
-                        sy += sc * dy;
-                        if (room && na < MAXACT) t.tenb[(size_t)e * MAXACT + na] = w;
-                        ++na;
-                    }
+                const int w = t.he_v[bd_next(h)];
+                double cx, cy;
+                if (w < t.n && ovl_term(t, pv, rv, w, t.xy[w], f, keep, cx, cy)) {
+                    sx += cx;
+                    sy += cy;
+                    if (room && na < MAXACT) t.tenb[(size_t)e * MAXACT + na] = w;
+                    ++na;
                 }
                 h = t.he_twin[bd_prev(h)];
             } while (h != best);
+        } else {
+            const bool two = __ballot(s.deg > kStarLanes) != 0;
+            double cx[2] = {0.0, 0.0}, cy[2] = {0.0, 0.0};
+            unsigned hits = 0;   // bit i: neighbour i overlaps
+            int bestid = 0x7FFFFFFF, best = 0;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (u == 1 && !two) continue;
+                const int i = q + u * kStarLanes;
+                bool hit = false;
+                if (i < s.deg) {
+                    t.star[(size_t)idx * kStarMax + i] = s.h[u];
+                    if (s.w[u] < t.n) hit = ovl_term(t, pv, rv, s.w[u], t.xy[s.w[u]], f, keep, cx[u], cy[u]);
+                    if (s.w[u] < t.inf && s.w[u] < bestid) {
+                        bestid = s.w[u];
+                        best = i;
+                    }
+                }
+                hits |= (unsigned)((__ballot(hit) >> star_base()) & ((1ull << kStarLanes) - 1ull)) << (u * kStarLanes);
+            }
+            for (int off = kStarLanes / 2; off > 0; off >>= 1) {
+                const int oid = __shfl_xor(bestid, off), ob = __shfl_xor(best, off);
+                if (oid < bestid) {
+                    bestid = oid;
+                    best = ob;
+                }
+            }
+            // canonical order: neighbours best .. deg - 1, then 0 .. best - 1
+            unsigned part = hits & ~((1u << best) - 1u), rest = hits & ((1u << best) - 1u);
+            while ((part | rest) != 0) {
+                if (part == 0) {
+                    part = rest;
+                    rest = 0;
+                }
+                const int i = __ffs(part) - 1;
+                part &= part - 1;
+                sx += star_get(cx, i, two);
+                sy += star_get(cy, i, two);
+                const int w = star_get(s.w, i, two);
+                if (room && q == 0 && na < MAXACT) t.tenb[(size_t)e * MAXACT + na] = w;
+                ++na;
+            }
+            if (q != 0) continue;
         }
         if (room) {
             if (na > MAXACT) atomicOr(&t.ctl[K_TAPE_OVF], 2);
             t.tev[e] = v;
             t.tecnt[e] = na < MAXACT ? na : MAXACT;
-            t.teold[e] = make_double2(xv, yv);
+            t.teold[e] = pv;
             t.tedisp[e] = make_double2(sx, sy);
         }
         const double len = sqrt(sx * sx + sy * sy);
@@ -1209,6 +1479,7 @@ __device__ __forceinline__ void ovl_gather_body(const Topo &t, int k, double f, 
             sy = sy * sc;
             wave_count64(&t.acc[A_CAP_HITS], true);
         }
+        const double xv = pv.x, yv = pv.y;
         if (room) {
             t.tewf[2 * (size_t)e] = bd_wall_slope(xv + sx, rv, L);
             t.tewf[2 * (size_t)e + 1] = bd_wall_slope(yv + sy, rv, L);
@@ -1220,18 +1491,13 @@ __device__ __forceinline__ void ovl_gather_body(const Topo &t, int k, double f, 
     }
 }
 
-__global__ void k_ovl_gather(Topo t, int k, double f, double cap_frac, double keep) {
+__global__ __launch_bounds__(256) void k_ovl_gather(Topo t, int k, double f, double cap_frac, double keep) {
     ovl_gather_body(t, k, f, cap_frac, keep, xcd_block() * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
-// Apply: write the new positions (keeping the old ones for a replay) and queue
-// every edge of the moved disk's triangles (incident and link edges) as the
-// worklist of round slot `slot`, the first round of the following repair.
-template <int CAP = 1>
-__device__ __forceinline__ void ovl_apply_body(const Topo &t, int k, int next_round, int slot, int i0, int stride,
-                                               Stage<CAP> *st = nullptr) {
+// Apply: write the new positions, keeping the old ones for a replay.
+__device__ __forceinline__ void ovl_apply_body(const Topo &t, int k, int i0, int stride) {
     if (stopped(t.ctl)) return;
-    next_round += t.base->rbase;
     const int ntouched = t.ctl[K_TOUCH + k];
     if (t.tev != nullptr && i0 == 0) {
         // adjoint tape: close the round's entries (written by the gather)
@@ -1251,39 +1517,12 @@ __device__ __forceinline__ void ovl_apply_body(const Topo &t, int k, int next_ro
         ((double *)t.x)[v] = np.x;
         ((double *)t.y)[v] = np.y;
         ((double2 *)t.xy)[v] = np;
-        const int h0 = t.vert_he[v];
-        if (bad_he(t, h0)) {
-            topo_err(t);
-            continue;
-        }
-        int h = h0, guard = 0;
-        do {
-            int tw = t.he_twin[h];
-            int l = bd_next(h);
-            int lt = t.he_twin[l];
-            if (bad_he(t, tw) || bad_he(t, lt)) {
-                topo_err(t);
-                break;
-            }
-            push_edge(t, h < tw ? h : tw, next_round, slot, st);
-            push_edge(t, l < lt ? l : lt, next_round, slot, st);
-            h = t.he_twin[bd_prev(h)];
-            if (bad_he(t, h)) {
-                topo_err(t);
-                break;
-            }
-        } while (h != h0 && ++guard < 4096);
     }
 }
 
-constexpr int kApplyStage = 4096;
-
-__global__ void k_ovl_apply(Topo t, int k, int next_round, int slot) {
-    __shared__ Stage<kApplyStage> st;
+__global__ void k_ovl_apply(Topo t, int k) {
     if (stopped(t.ctl)) return;
-    stage_init(st);
-    ovl_apply_body(t, k, next_round, slot, xcd_block() * blockDim.x + threadIdx.x, gridDim.x * blockDim.x, &st);
-    stage_flush(st, &t.ctl[K_WL + slot], wl_of(t, slot));
+    ovl_apply_body(t, k, xcd_block() * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
 // The overlap rounds after the first detection in one workgroup: each phase
@@ -1316,7 +1555,7 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(Topo t, TailPlan p) {
         const int k = p.k[j];
         ovl_gather_body(t, k, p.f, p.cap_frac, p.keep, i0, stride);
         TAIL_SYNC();
-        ovl_apply_body(t, k, p.next_round[j], p.slot0[j], i0, stride);
+        ovl_apply_body(t, k, i0, stride);
         TAIL_SYNC();
         int last = -1;
         for (int r = 0; r < p.rounds[j]; ++r) {
@@ -1324,7 +1563,10 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(Topo t, TailPlan p) {
             if (slot >= MAXR) slot -= MAXR;
             const int round = p.next_round[j] + r;
             last = slot;
-            if (rounds_done(t, slot, false)) break;
+            if (r == 0)
+                flip_eval_star_body(t, k, round, slot, i0, stride);
+            else if (rounds_done(t, slot, false))
+                break;
             flip_eval_list_body(t, round, slot, i0, stride);
             TAIL_SYNC();
             if (rounds_done(t, slot, true)) break;
@@ -1338,8 +1580,8 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(Topo t, TailPlan p) {
         // and the detection's, as the last workgroup of the fused launch does
         const int knew = p.k[j + 1];
         wave_sum_add(&t.ctl[K_OVL + knew],
-                     validate_detect_local_body(t, &t.ctl[K_INV + p.rep[j]], k, p.stamp[j + 1] + t.base->vbase,
-                                                p.keep, knew, i0, stride));
+                     validate_detect_local_body(t, &t.ctl[K_INV + p.rep[j]], k, p.next_round[j],
+                                                p.stamp[j + 1] + t.base->vbase, p.keep, knew, i0, stride));
         __syncthreads();
         if (i0 == 0) {
             repair_check_body(t.ctl, p.rep[j], last);
@@ -1452,6 +1694,9 @@ inline int list_grid(const Sim &s) {
     return g < 16 ? 16 : (g > kListGridMax ? kListGridMax : g);
 }
 
+// Workgroups of the launches with one group of lanes per star.
+inline int star_grid(const Sim &s) { return std::min(kStarGridMax, list_grid(s) * kStarLanes); }
+
 }  // namespace
 
 void launch_flip_eval_full(Sim &s, int round, int slot, int reversal) {
@@ -1465,6 +1710,12 @@ void launch_flip_eval_list(Sim &s, int round, int slot) {
     round -= s.rbase;
     Topo t = topo_of(s);
     hipLaunchKernelGGL(k_flip_eval_list, dim3(list_grid(s)), dim3(256), 0, s.stream, t, round, slot);
+}
+
+void launch_flip_eval_star(Sim &s, int k, int round, int slot) {
+    round -= s.rbase;
+    Topo t = topo_of(s);
+    hipLaunchKernelGGL(k_flip_eval_star, dim3(star_grid(s)), dim3(256), 0, s.stream, t, k, round, slot);
 }
 
 void launch_flip_apply(Sim &s, int round, int slot) {
@@ -1484,11 +1735,6 @@ void launch_validate(Sim &s, int rep, int last) {
     hipLaunchKernelGGL(k_validate, dim3(grid_for((s.T + 3) / 4)), dim3(kScanBlock), 0, s.stream, t, rep, last);
 }
 
-void launch_validate_local(Sim &s, int rep, int k, int last) {
-    Topo t = topo_of(s);
-    hipLaunchKernelGGL(k_validate_local, dim3(list_grid(s)), dim3(256), 0, s.stream, t, rep, k, last);
-}
-
 void launch_ovl_detect(Sim &s, int vstamp, int k, int check, int vrep, int vlast) {
     vstamp -= s.vbase;
     Topo t = topo_of(s);
@@ -1496,30 +1742,23 @@ void launch_ovl_detect(Sim &s, int vstamp, int k, int check, int vrep, int vlast
                        1.0 - s.p.contact_tol, k, check, vrep, vlast);
 }
 
-void launch_validate_detect_local(Sim &s, int rep, int k, int last, int vstamp, int knew, int check) {
+void launch_validate_detect_local(Sim &s, int rep, int k, int rfirst, int last, int vstamp, int knew, int check) {
     vstamp -= s.vbase;
+    rfirst -= s.rbase;
     Topo t = topo_of(s);
-    hipLaunchKernelGGL(k_validate_detect_local, dim3(list_grid(s)), dim3(256), 0, s.stream, t, rep, k, last, vstamp,
+    hipLaunchKernelGGL(k_validate_detect_local, dim3(star_grid(s)), dim3(256), 0, s.stream, t, rep, k, rfirst, last, vstamp,
                        1.0 - s.p.contact_tol, knew, check);
-}
-
-void launch_ovl_detect_local(Sim &s, int vstamp, int k, int kprev, int check) {
-    vstamp -= s.vbase;
-    Topo t = topo_of(s);
-    hipLaunchKernelGGL(k_ovl_detect_local, dim3(list_grid(s)), dim3(256), 0, s.stream, t, vstamp,
-                       1.0 - s.p.contact_tol, k, kprev, check);
 }
 
 void launch_ovl_gather(Sim &s, int k) {
     Topo t = topo_of(s);
-    hipLaunchKernelGGL(k_ovl_gather, dim3(list_grid(s)), dim3(256), 0, s.stream, t, k, s.p.overlap_factor,
+    hipLaunchKernelGGL(k_ovl_gather, dim3(star_grid(s)), dim3(256), 0, s.stream, t, k, s.p.overlap_factor,
                        s.p.cap_frac, 1.0 - s.p.contact_tol);
 }
 
-void launch_ovl_apply(Sim &s, int k, int next_round, int slot) {
-    next_round -= s.rbase;
+void launch_ovl_apply(Sim &s, int k) {
     Topo t = topo_of(s);
-    hipLaunchKernelGGL(k_ovl_apply, dim3(list_grid(s)), dim3(256), 0, s.stream, t, k, next_round, slot);
+    hipLaunchKernelGGL(k_ovl_apply, dim3(list_grid(s)), dim3(256), 0, s.stream, t, k);
 }
 
 void launch_tail(Sim &s, const TailPlan &plan) {

@@ -278,11 +278,14 @@ void enqueue_repair(Sim &s, Cursor &c, bool full, bool reversal, int rounds, std
     // the first `multi` rounds (the long worklists) on many workgroups, the rest in one workgroup
     // launch that stops at the first round with nothing to do
     const int m = std::min(rounds, std::max(1, multi));
+    const int rfirst = s.round_id + 1;
     for (int j = 0; j < m; ++j) {
         const int r = ++s.round_id;
         const int slot = c.take_slot();
         if (j == 0 && full)
             launch_flip_eval_full(s, r, slot, reversal ? rev_mode(s) : 0);
+        else if (j == 0)
+            launch_flip_eval_star(s, oround, r, slot);
         else
             launch_flip_eval_list(s, r, slot);
         launch_flip_apply(s, r, slot);
@@ -298,11 +301,9 @@ void enqueue_repair(Sim &s, Cursor &c, bool full, bool reversal, int rounds, std
         launch_repair_rounds(s, r0, slot0, rounds - m, false);
     }
     if (fd && oround >= 0)
-        launch_validate_detect_local(s, rep, oround, last, fd->stamp, fd->k, fd->check);
+        launch_validate_detect_local(s, rep, oround, rfirst, last, fd->stamp, fd->k, fd->check);
     else if (fd)
         launch_ovl_detect(s, fd->stamp, fd->k, fd->check, rep, last);
-    else if (oround >= 0)
-        launch_validate_local(s, rep, oround, last);
     else
         launch_validate(s, rep, last);
 }
@@ -310,11 +311,12 @@ void enqueue_repair(Sim &s, Cursor &c, bool full, bool reversal, int rounds, std
 // ------------------------------------------------------------------ host-driven path
 // Flip rounds with one read-back per round (used to finish a step whose
 // budget ran out, for bd_set_positions and for the kinetic replay).  The
-// first round reads the worklist of slot c.slot unless `full`.  When `snap` is
+// first round scans every edge (`full`), or takes the edges at the disks overlap
+// round `oround` moved, or reads the worklist of slot c.slot (oround < 0).  When `snap` is
 // given and the first evaluation meets an inverted triangle, the topology is
 // copied aside before any flip.  Returns true for a valid triangulation with
 // no edge left to flip.
-bool host_flip_rounds(Sim &s, Cursor &c, bool full, bool reversal, bool *snap) {
+bool host_flip_rounds(Sim &s, Cursor &c, bool full, bool reversal, bool *snap, int oround = -1) {
     if (snap) *snap = false;
     const int budget = s.p.max_flip_rounds > 0 ? s.p.max_flip_rounds : 200;
     bool done = false;
@@ -326,6 +328,8 @@ bool host_flip_rounds(Sim &s, Cursor &c, bool full, bool reversal, bool *snap) {
         zero_ctl(s, K_WL + next_slot(slot));
         if (full)
             launch_flip_eval_full(s, r, slot, reversal && it == 0 ? rev_mode(s) : 0);
+        else if (it == 0 && oround >= 0)
+            launch_flip_eval_star(s, oround, r, slot);
         else
             launch_flip_eval_list(s, r, slot);
         read_ctl(s);
@@ -399,7 +403,7 @@ int kinetic_replay(Sim &s, Cursor &c, MoveFrom from, int oround) {
 // fail, and the move is replayed from the snapshot in sub-steps.
 int host_repair(Sim &s, Cursor &c, bool full, bool reversal, MoveFrom from, int oround) {
     bool snapped = false;
-    if (host_flip_rounds(s, c, full, reversal, &snapped)) return BD_OK;
+    if (host_flip_rounds(s, c, full, reversal, &snapped, full ? -1 : oround)) return BD_OK;
     if (!snapped || s.hctl[K_TOPO] != 0) {
         zero_ctl(s, K_TOPO);
         return host_rebuild(s);
@@ -501,7 +505,7 @@ int host_overlap_loop(Sim &s, Cursor &c, int &rounds) {
         launch_ovl_gather(s, k);
         const int slot = c.slot;
         zero_ctl(s, K_WL + slot);
-        launch_ovl_apply(s, k, s.round_id + 1, slot);
+        launch_ovl_apply(s, k);
         read_ctl(s);
         if (s.hctl[K_STAR] != 0 || s.hctl[K_TOPO] != 0) {
             s.last_error = "vertex star walk failed (corrupt triangulation)";
@@ -633,7 +637,7 @@ void enqueue_rounds(Sim &s, Cursor &c, std::vector<int> &orounds, std::vector<in
         enqueue_repair(s, c, true, true, s.budget.em, &rep_first, -1, &fd, hybrid ? s.multi_em : 1 << 30);
         for (int j = 0; j < per_phase; ++j) {
             launch_ovl_gather(s, k);
-            launch_ovl_apply(s, k, s.round_id + 1, c.slot);
+            launch_ovl_apply(s, k);
             const int knext = c.take_oround();
             orounds.push_back(knext);
             FusedDetect fn{knext, ++s.vround, j + 1 == nover ? 2 : 1};
@@ -678,16 +682,8 @@ void enqueue_rounds(Sim &s, Cursor &c, std::vector<int> &orounds, std::vector<in
         return;
     }
     enqueue_repair(s, c, true, true, s.budget.em, &rep_first);
-    // the first detection after the move scans every edge, later ones only
-    // what round k-1 changed; the detection's last workgroup runs the round's
-    // check (and after the last budgeted round the final check)
-    auto detect = [&](int k, int check) {
-        const int stamp = ++s.vround;
-        if (orounds.size() == 1)
-            launch_ovl_detect(s, stamp, k, check);
-        else
-            launch_ovl_detect_local(s, stamp, k, orounds[orounds.size() - 2], check);
-    };
+    // the first detection after the move scans every edge (in the tail, later ones only what the round
+    // before changed); its last workgroup runs the round's check
     // rounds after the first detection in one workgroup (same slots, stamps and round ids)
     TailPlan plan{};
     plan.nover = nover;
@@ -699,7 +695,7 @@ void enqueue_rounds(Sim &s, Cursor &c, std::vector<int> &orounds, std::vector<in
         orounds.push_back(k);
         plan.k[j] = k;
         if (j == 0) {
-            detect(k, 1);
+            launch_ovl_detect(s, ++s.vround, k, 1);
             plan.stamp[0] = 0;
         } else {
             plan.stamp[j] = ++s.vround - s.vbase;
@@ -1575,7 +1571,7 @@ void free_all(Sim &s) {
     void *ptrs[] = {s.x, s.y, s.xy, s.xo, s.yo, s.th, s.tho, s.rad, s.sp, s.sp_sorted, s.perm, s.key_id, s.sorted_id, s.pos_of, s.pj, s.part,
                     s.tiles, s.chunk_spec, s.reps, s.rep_of, s.Lr, s.Kd, s.fout, s.he_v, s.he_twin, s.vert_he,
                     s.claim, s.tri_stamp, s.moved, s.edge_stamp, s.vstamp, s.wl[0], s.wl[1], s.cand, s.cand_won,
-                    s.touched, s.det_stamp, s.fl_stamp, s.fl, s.vt_stamp, s.vt, s.newpos, s.oldpos, s.snap_v, s.snap_twin,
+                    s.touched, s.det_stamp, s.fl_stamp, s.fl, s.vt_stamp, s.vt, s.newpos, s.oldpos, s.star, s.star_deg, s.snap_v, s.snap_twin,
                     s.snap_vh, s.xa, s.ya, s.xb, s.yb, s.ctl,
                     s.acc, s.nl, s.nl_cnt, s.nl_cand, s.cell_of, s.cell_count, s.cell_start, s.cell_fill, s.cell_items,
                     s.xbuild, s.ybuild, s.fsr, s.scan_bsum, s.stiles, s.xs, s.ys, s.ths};
@@ -1890,6 +1886,10 @@ int init_impl(Sim &s, int R, const int32_t *n_per, const double *xy, const doubl
     s.vt = dalloc<int>(s.T + 64);
     s.newpos = dalloc<double2>(n);
     s.oldpos = dalloc<double2>(n);
+    if (p->overlap_method == BD_OVERLAP_DELAUNAY) {
+        s.star = dalloc<int>(16 * (size_t)n);
+        s.star_deg = dalloc<int>(n);
+    }
     s.snap_v = dalloc<int>(s.H);
     s.snap_twin = dalloc<int>(s.H);
     s.snap_vh = dalloc<int>(nva);
