@@ -122,6 +122,7 @@ struct StepBase {
     int nl_now;      // this step rebuilds them before its force (copied from nl_req when it begins)
 };
 constexpr int kRing = 64;            // most steps queued at once in graph mode
+constexpr int kGraphSteps = 8;       // steps in the longer captured graph
 constexpr size_t kMaxGraphs = 16;    // captured step graphs kept per handle (one per budget setting)
 
 constexpr int MAXACT = 16;    // overlapping partners recorded per disk and round (adjoint tape)
@@ -241,6 +242,7 @@ struct Sim {
     int *sorted_id = nullptr;        // sorted index -> library index (species-sorted)
     int *pos_of = nullptr;           // library index -> sorted index
     void *pj = nullptr;              // float2 / double2 [n], sorted order
+    bool pj_is_xy = false;           // one species in FP64: sorted order is the library's, the force reads xy itself
     void *part = nullptr;            // [nchunks][n] float2 / double2 partial sums
     Tile *tiles = nullptr;           // force tiles, longest first (symmetric form: the adjoint's tiles)
     int ntiles = 0;
@@ -302,7 +304,7 @@ struct Sim {
     StepBase *dbase = nullptr;       // device copy of the bases below
     StepBase *hbase = nullptr;       // pinned staging for it
     int rbase = 0, vbase = 0;        // bases currently on the device; launches pass stamp - base
-    // captured steps (one graph triple per round-budget setting)
+    // captured steps (one set per round-budget setting)
     bool use_graph = false;
     int batch_hint = kRing;          // graph steps queued per batch (adapts to the steps between stops)
     int tail_mode = -1;              // overlap rounds after the first detection: 0 launch per phase,
@@ -316,7 +318,9 @@ struct Sim {
     int touch_prev[MAXO] = {};       // the same over the previous window
     int touch_steps = 0;             // steps in the current window
     struct StepGraph {
-        hipGraphExec_t pre = nullptr, force = nullptr, post = nullptr;
+        hipGraphExec_t one = nullptr, many = nullptr;   // one step; kGraphSteps steps (captured once in steady use)
+        hipGraphExec_t pre = nullptr, force = nullptr, post = nullptr;   // one step cut around its force (timing)
+        int64_t uses = 0;                               // steps replayed
         int r_used = 0, v_used = 0;
         int c_slot = 0, c_rep = 0, c_oround = 0;
         std::vector<int> orounds, rep_first;
@@ -349,10 +353,9 @@ struct Sim {
 
 // ---- kernel launchers (k_*.hip) ------------------------------------------
 void launch_cast(Sim &s);
-void launch_step_begin(Sim &s);                       // clear the control block unless the batch stopped
-void launch_step_begin_cast(Sim &s);                  // both of the above in one launch (all-pairs path)
-void launch_step_end(Sim &s, int r_used, int v_used); // record the control block, advance or stop
-void launch_force(Sim &s);
+void launch_step_begin(Sim &s, const StepBase &b);    // start of a batch: step base, clear control block
+void launch_step_end(Sim &s, int r_used, int v_used); // record the control block, clear it, advance or stop
+void launch_force(Sim &s, const void *src = nullptr);
 int force_max_grid(Sim &s, int per_lane);            // resident workgroups of the persistent launch
 // level > 0: sub-interval `index` of the 2^level halves of the step after edge reversals (Sec. 4.3)
 void launch_em(Sim &s, int level = 0, unsigned index = 0);
@@ -380,7 +383,8 @@ struct NlTailPlan {
 void launch_nl_tail(Sim &s, const NlTailPlan &p);
 // triangulation (slot: round slot in ctl; rep: repair slot)
 // reversal: 0 no test; 1 count reversed edges (Sec. 4.3); 2 count them and flag the step (K_REV) for halving
-void launch_flip_eval_full(Sim &s, int round, int slot, int reversal);
+// snapshot: the same pass copies the topology aside (as launch_snapshot)
+void launch_flip_eval_full(Sim &s, int round, int slot, int reversal, bool snapshot = false);
 void launch_flip_eval_list(Sim &s, int round, int slot);
 // the first evaluation after overlap round k: the edges at the disks it moved (and the slot's worklist)
 void launch_flip_eval_star(Sim &s, int k, int round, int slot);
@@ -414,6 +418,7 @@ struct TailPlan {
     int slot0[MAXTAIL];            // its first round slot
     int rep[MAXTAIL];              // its repair slot
     double f, cap_frac, keep;
+    int end, r_used, v_used;       // end: it also ends the queued step
 };
 void launch_tail(Sim &s, const TailPlan &plan);
 // rounds [round0, round0 + rounds) of a repair in one workgroup (first_evaluated: round0's evaluation ran

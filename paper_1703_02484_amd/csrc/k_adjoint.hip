@@ -278,7 +278,7 @@ void launch_adj_step(Sim &s, int t) {
     // Phi at the positions before the step: kept by the replay, else recomputed
     const size_t vec = s.fp32 ? sizeof(float2) : sizeof(double2);
     const void *phi = tp.phi ? (const char *)tp.phi + (size_t)t * s.part_cap * vec : s.part;
-    if (!tp.phi) launch_force(s);
+    if (!tp.phi) launch_force(s, s.pj);
     if (s.fp32)
         hipLaunchKernelGGL(k_adj_dk_rows<float2>, dim3(nb), dim3(kAdjBlock), 0, s.stream, s.n, s.S,
                            (const float2 *)phi, s.reps, s.rep_of, s.chunk_spec, s.pos_of, a.lam, s.p.dt,

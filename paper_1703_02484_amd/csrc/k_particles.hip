@@ -18,6 +18,7 @@
 
 #include "bd_internal.h"
 #include "geom.h"
+#include "step_end.h"
 
 namespace bd {
 namespace {
@@ -623,68 +624,24 @@ __global__ void k_zero_one(int *p) {
     if (threadIdx.x == 0) *p = 0;
 }
 
-__device__ __forceinline__ void step_begin_body(int *__restrict__ ctl, StepBase *__restrict__ base) {
-    if (base->stop) {   // keep the halted step's control block for the host; no list rebuild
-        if (threadIdx.x == 0) base->nl_now = 0;
-        return;
-    }
+// Start of a batch of queued steps: the step base and a clear control block (the steps' ends keep both).
+__global__ void k_step_begin(int *__restrict__ ctl, StepBase *__restrict__ base, StepBase b) {
     for (int i = threadIdx.x; i < N_CTL; i += blockDim.x) ctl[i] = 0;
-    if (threadIdx.x == 0) {   // a rebuild the last step's skin test asked for happens in this step
-        base->nl_now = base->nl_req;
-        base->nl_req = 0;
-    }
+    if (threadIdx.x == 0) *base = b;
 }
 
-__global__ void k_step_begin(int *__restrict__ ctl, StepBase *__restrict__ base) { step_begin_body(ctl, base); }
-
-// The step's start and the cast in one launch (all-pairs path): workgroup 0 also clears the control
-// block.  Nothing in the cast reads what the clear writes (the control block, the list flags), and
-// the stop flag both read is not written here.
-template <typename T2>
-__global__ void k_step_begin_cast(int *__restrict__ ctl, StepBase *__restrict__ base, int n,
-                                  const double *__restrict__ x, const double *__restrict__ y,
-                                  const int *__restrict__ sorted_id, T2 *__restrict__ pj) {
-    if (blockIdx.x == 0) step_begin_body(ctl, base);
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n || base->stop) return;
-    const int i = sorted_id[k];
-    T2 v;
-    v.x = x[i];
-    v.y = y[i];
-    pj[k] = v;
-}
-
-// End of a queued step, one workgroup: record its control block in the ring,
-// then (after a barrier: every thread has read the step base) either advance
-// the step counter and the stamp bases, or stop the batch when the step halted
-// (the host finishes it) or the ring is full.
-__global__ void k_step_end(const int *__restrict__ ctl, StepBase *__restrict__ base, int *__restrict__ ring,
-                           int r_used, int v_used) {
-    if (base->stop) return;   // uniform: written by this kernel only after the barrier below
-    const int idx = base->batch_idx;
-    for (int i = threadIdx.x; i < N_CTL; i += blockDim.x) ring[(size_t)idx * N_CTL + i] = ctl[i];
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    if (ctl[K_HALT]) {
-        base->stop = 1;
-        return;
-    }
-    base->step += 1;
-    base->rbase += r_used;
-    base->vbase += v_used;
-    base->batch_idx = idx + 1;
-    if (idx + 1 >= kRing) base->stop = 2;
+__global__ void k_step_end(int *ctl, StepBase *base, int *__restrict__ ring, int r_used, int v_used) {
+    step_end_body(ctl, base, ring, r_used, v_used);
 }
 
 }  // namespace
 
-void launch_step_begin(Sim &s) {
-    hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(256), 0, s.stream, s.ctl, s.dbase);
+void launch_step_begin(Sim &s, const StepBase &b) {
+    hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(256), 0, s.stream, s.ctl, s.dbase, b);
 }
 
 void launch_step_end(Sim &s, int r_used, int v_used) {
-    hipLaunchKernelGGL(k_step_end, dim3(1), dim3(256), 0, s.stream, (const int *)s.ctl, s.dbase, s.ring, r_used,
-                       v_used);
+    hipLaunchKernelGGL(k_step_end, dim3(1), dim3(256), 0, s.stream, s.ctl, s.dbase, s.ring, r_used, v_used);
 }
 
 void launch_pack_xy(Sim &s, int m) {
@@ -693,17 +650,10 @@ void launch_pack_xy(Sim &s, int m) {
                            (const double *)s.y, s.xy);
 }
 
-void launch_step_begin_cast(Sim &s) {
-    const int nb = blocks_for(s.n, 256);
-    if (s.fp32)
-        hipLaunchKernelGGL(k_step_begin_cast<float2>, dim3(nb), dim3(256), 0, s.stream, s.ctl, s.dbase, s.n,
-                           (const double *)s.x, (const double *)s.y, (const int *)s.sorted_id, (float2 *)s.pj);
-    else
-        hipLaunchKernelGGL(k_step_begin_cast<double2>, dim3(nb), dim3(256), 0, s.stream, s.ctl, s.dbase, s.n,
-                           (const double *)s.x, (const double *)s.y, (const int *)s.sorted_id, (double2 *)s.pj);
-}
-
+// Positions in sorted order for the all-pairs force (with one species in FP64 that is the (x, y) pairs
+// themselves: no launch).
 void launch_cast(Sim &s) {
+    if (s.pj_is_xy) return;
     const int nb = blocks_for(s.n, 256);
     if (s.fp32)
         hipLaunchKernelGGL(k_cast<float2>, dim3(nb), dim3(256), 0, s.stream, s.n, s.x, s.y, s.sorted_id,
@@ -716,28 +666,28 @@ void launch_cast(Sim &s) {
 namespace {
 
 template <typename T, typename T2, int P, bool FAST>
-void launch_force_t(Sim &s, const LawArgs &law) {
+void launch_force_t(Sim &s, const LawArgs &law, const void *pj) {
     if (s.period > 0.0) {   // periodic box: one workgroup per tile, minimum-image separations
         hipLaunchKernelGGL((k_force<T, T2, P, FAST, true>), dim3(s.ntiles), dim3(kForceBlock), 0, s.stream,
-                           (const T2 *)s.pj, s.tiles, (T2 *)s.part, law, s.dbase);
+                           (const T2 *)pj, s.tiles, (T2 *)s.part, law, s.dbase);
     } else if (FAST && s.persistent == 3) {   // j staged through LDS (inverse-square law)
         hipLaunchKernelGGL((k_force_lds<T, T2, P>), dim3(s.ntiles), dim3(kForceBlock), 0, s.stream,
-                           (const T2 *)s.pj, s.tiles, (T2 *)s.part, s.dbase);
+                           (const T2 *)pj, s.tiles, (T2 *)s.part, s.dbase);
     } else if (s.persistent) {
         hipLaunchKernelGGL((k_force_queue<T, T2, P, FAST>), dim3(s.force_grid), dim3(kForceBlock), 0, s.stream,
-                           (const T2 *)s.pj, s.tiles, s.ntiles, (T2 *)s.part, law, s.ctl + K_FQUEUE, s.dbase);
+                           (const T2 *)pj, s.tiles, s.ntiles, (T2 *)s.part, law, s.ctl + K_FQUEUE, s.dbase);
     } else {
         hipLaunchKernelGGL((k_force<T, T2, P, FAST>), dim3(s.ntiles), dim3(kForceBlock), 0, s.stream,
-                           (const T2 *)s.pj, s.tiles, (T2 *)s.part, law, s.dbase);
+                           (const T2 *)pj, s.tiles, (T2 *)s.part, law, s.dbase);
     }
 }
 
 template <typename T, typename T2, int P>
-void launch_force_p(Sim &s, const LawArgs &law) {
+void launch_force_p(Sim &s, const LawArgs &law, const void *pj) {
     if (s.kind_fast)
-        launch_force_t<T, T2, P, true>(s, law);
+        launch_force_t<T, T2, P, true>(s, law, pj);
     else
-        launch_force_t<T, T2, P, false>(s, law);
+        launch_force_t<T, T2, P, false>(s, law, pj);
 }
 
 template <typename T, typename T2, int P, bool FAST>
@@ -758,7 +708,9 @@ int max_grid_p(bool fast) {
 }  // namespace
 
 // Tiles of 256 * per_lane particles; per_lane is 2 or 4.
-void launch_force(Sim &s) {
+// src: positions in sorted order (null: those of the last cast).
+void launch_force(Sim &s, const void *src) {
+    if (!src) src = s.pj_is_xy ? (const void *)s.xy : s.pj;
     LawArgs law{s.fp.kind, s.fp.q, s.fp.A, s.fp.lambda, s.fp.cutoff, s.period};
     if (s.persistent == 2) {   // symmetric chunk pairs (the host builds them only for the inverse-square law)
         // per_lane 2 / 4: 4 wavefronts (chunks of 512 / 1024); 8: 2 wavefronts (chunks of 1024)
@@ -766,7 +718,7 @@ void launch_force(Sim &s) {
         const SymTile *st = s.stiles;
         const StepBase *base = s.dbase;
         if (s.fp32) {
-            const float2 *pj = (const float2 *)s.pj;
+            const float2 *pj = (const float2 *)src;
             float2 *part = (float2 *)s.part;
             if (s.per_lane == 2)
                 hipLaunchKernelGGL((k_force_sym<float, float2, 2, 4>), g, b4, 0, s.stream, pj, st, part, base);
@@ -775,7 +727,7 @@ void launch_force(Sim &s) {
             else
                 hipLaunchKernelGGL((k_force_sym<float, float2, 8, 2>), g, b2, 0, s.stream, pj, st, part, base);
         } else {
-            const double2 *pj = (const double2 *)s.pj;
+            const double2 *pj = (const double2 *)src;
             double2 *part = (double2 *)s.part;
             if (s.per_lane == 2)
                 hipLaunchKernelGGL((k_force_sym<double, double2, 2, 4>), g, b4, 0, s.stream, pj, st, part, base);
@@ -789,14 +741,14 @@ void launch_force(Sim &s) {
     if (s.persistent == 1) hipLaunchKernelGGL(k_zero_one, dim3(1), dim3(64), 0, s.stream, s.ctl + K_FQUEUE);
     if (s.fp32) {
         if (s.per_lane == 2)
-            launch_force_p<float, float2, 2>(s, law);
+            launch_force_p<float, float2, 2>(s, law, src);
         else
-            launch_force_p<float, float2, 4>(s, law);
+            launch_force_p<float, float2, 4>(s, law, src);
     } else {
         if (s.per_lane == 2)
-            launch_force_p<double, double2, 2>(s, law);
+            launch_force_p<double, double2, 2>(s, law, src);
         else
-            launch_force_p<double, double2, 4>(s, law);
+            launch_force_p<double, double2, 4>(s, law, src);
     }
 }
 

@@ -39,6 +39,7 @@
 
 #include "bd_internal.h"
 #include "geom.h"
+#include "step_end.h"
 
 namespace bd {
 namespace {
@@ -541,9 +542,19 @@ __device__ __forceinline__ void cand_flush(const Topo &t, int slot, CandStage<CA
     for (int i = threadIdx.x; i < n; i += blockDim.x) t.cand[st.base + i] = st.buf[i];
 }
 
-__global__ __launch_bounds__(kEvalBlock) void k_flip_eval_full(Topo t, int round, int slot, int reversal) {
+// snap: where the topology is copied aside (v == null: not): the pass reads all of it anyway.
+struct Snapshot {
+    int *v, *twin, *vh;
+    int nvh;
+};
+
+__global__ __launch_bounds__(kEvalBlock) void k_flip_eval_full(Topo t, int round, int slot, int reversal,
+                                                               Snapshot snap) {
     __shared__ CandStage<kEvalStage> st;
     if (stopped(t.ctl)) return;   // nothing in this launch writes the stop flags: uniform
+    if (snap.v)
+        for (int i = xcd_block() * blockDim.x + threadIdx.x; i < snap.nvh; i += gridDim.x * blockDim.x)
+            snap.vh[i] = t.vert_he[i];
     if (threadIdx.x == 0) st.cnt = 0;
     __syncthreads();
     round += t.base->rbase;
@@ -554,6 +565,13 @@ __global__ __launch_bounds__(kEvalBlock) void k_flip_eval_full(Topo t, int round
         for (int k = 0; k < 3; ++k) {
             v[k] = t.he_v[h0 + k];
             tw[k] = t.he_twin[h0 + k];
+        }
+        if (snap.v) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                snap.v[h0 + k] = v[k];
+                snap.twin[h0 + k] = tw[k];
+            }
         }
         bool own[3], ok = true;
 #pragma unroll
@@ -1542,21 +1560,56 @@ __device__ __forceinline__ bool rounds_done(const Topo &t, int slot, bool evalua
     return ctl_read(t.ctl, (evaluated ? K_CAND : K_WL) + slot) == 0;
 }
 
-__global__ __launch_bounds__(kTailBlock) void k_tail(Topo t, TailPlan p) {
+// Between two phases: true when the step has stopped (the same for every thread).
+__device__ __forceinline__ bool tail_sync(const Topo &t) {
+    __syncthreads();
+    const bool stop = stopped(t.ctl);
+    __syncthreads();
+    return stop;
+}
+
+// Flip rounds [round0, round0 + rounds) of a repair in one workgroup, from
+// slot slot0 on.  first_evaluated: the first round's evaluation already ran in
+// a launch of many workgroups (the repair after the move scans every edge), so
+// it starts with that round's apply; otherwise with the evaluation of the
+// worklist in slot0.  The loop ends at the first round with nothing to do.
+// Returns true when the step has stopped.
+__device__ __forceinline__ bool repair_rounds_body(const Topo &t, int round0, int slot0, int rounds,
+                                                   bool first_evaluated) {
     const int i0 = threadIdx.x, stride = blockDim.x;
-#define TAIL_SYNC()                  \
-    do {                             \
-        __syncthreads();             \
-        if (stopped(t.ctl)) return;  \
-        __syncthreads();             \
-    } while (0)
-    TAIL_SYNC();
+    if (tail_sync(t)) return true;
+    for (int r = 0; r < rounds; ++r) {
+        int slot = slot0 + r;
+        if (slot >= MAXR) slot -= MAXR;
+        const int round = round0 + r;
+        if (r > 0 || !first_evaluated) {
+            if (rounds_done(t, slot, false)) break;
+            flip_eval_list_body(t, round, slot, i0, stride);
+            if (tail_sync(t)) return true;
+        }
+        if (rounds_done(t, slot, true)) break;
+        flip_apply_body(t, round, slot, i0, stride);
+        if (tail_sync(t)) return true;
+        flip_fix_body(t, round, slot, i0, stride);
+        if (tail_sync(t)) return true;
+    }
+    return false;
+}
+
+__global__ __launch_bounds__(kTailBlock) void k_repair_rounds(Topo t, int round0, int slot0, int rounds,
+                                                              int first_evaluated) {
+    repair_rounds_body(t, round0, slot0, rounds, first_evaluated != 0);
+}
+
+__device__ __forceinline__ void tail_body(const Topo &t, const TailPlan &p) {
+    const int i0 = threadIdx.x, stride = blockDim.x;
+    if (tail_sync(t)) return;
     for (int j = 0; j < p.nover; ++j) {
         const int k = p.k[j];
         ovl_gather_body(t, k, p.f, p.cap_frac, p.keep, i0, stride);
-        TAIL_SYNC();
+        if (tail_sync(t)) return;
         ovl_apply_body(t, k, i0, stride);
-        TAIL_SYNC();
+        if (tail_sync(t)) return;
         int last = -1;
         for (int r = 0; r < p.rounds[j]; ++r) {
             int slot = p.slot0[j] + r;
@@ -1568,14 +1621,14 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(Topo t, TailPlan p) {
             else if (rounds_done(t, slot, false))
                 break;
             flip_eval_list_body(t, round, slot, i0, stride);
-            TAIL_SYNC();
+            if (tail_sync(t)) return;
             if (rounds_done(t, slot, true)) break;
             flip_apply_body(t, round, slot, i0, stride);
-            TAIL_SYNC();
+            if (tail_sync(t)) return;
             flip_fix_body(t, round, slot, i0, stride);
-            TAIL_SYNC();
+            if (tail_sync(t)) return;
         }
-        // this repair's validation with the next round's detection, one walk
+        // this repair's validation with the next round's detection, one pass
         // over the stars of the disks round k moved; then the repair's check
         // and the detection's, as the last workgroup of the fused launch does
         const int knew = p.k[j + 1];
@@ -1588,42 +1641,15 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(Topo t, TailPlan p) {
             ovl_check_body(t.ctl, knew, p.stamp[j + 1], t.base);
             if (j + 1 == p.nover) final_check_body(t.ctl, knew);
         }
-        TAIL_SYNC();
+        if (tail_sync(t)) return;
     }
-#undef TAIL_SYNC
 }
 
-// Flip rounds [round0, round0 + rounds) of a repair in one workgroup, from
-// slot slot0 on.  first_evaluated: the first round's evaluation already ran in
-// a launch of many workgroups (the repair after the move scans every edge), so
-// it starts with that round's apply; otherwise with the evaluation of the
-// worklist in slot0.  The loop ends at the first round with nothing to do.
-__global__ __launch_bounds__(kTailBlock) void k_repair_rounds(Topo t, int round0, int slot0, int rounds,
-                                                              int first_evaluated) {
-    const int i0 = threadIdx.x, stride = blockDim.x;
-#define TAIL_SYNC()                  \
-    do {                             \
-        __syncthreads();             \
-        if (stopped(t.ctl)) return;  \
-        __syncthreads();             \
-    } while (0)
-    TAIL_SYNC();
-    for (int r = 0; r < rounds; ++r) {
-        int slot = slot0 + r;
-        if (slot >= MAXR) slot -= MAXR;
-        const int round = round0 + r;
-        if (r > 0 || !first_evaluated) {
-            if (rounds_done(t, slot, false)) break;
-            flip_eval_list_body(t, round, slot, i0, stride);
-            TAIL_SYNC();
-        }
-        if (rounds_done(t, slot, true)) break;
-        flip_apply_body(t, round, slot, i0, stride);
-        TAIL_SYNC();
-        flip_fix_body(t, round, slot, i0, stride);
-        TAIL_SYNC();
-    }
-#undef TAIL_SYNC
+__global__ __launch_bounds__(kTailBlock) void k_tail(Topo t, TailPlan p, StepBase *base, int *ring) {
+    tail_body(t, p);
+    if (!p.end) return;
+    __syncthreads();
+    step_end_body(t.ctl, base, ring, p.r_used, p.v_used);
 }
 
 // Topology snapshot before a repair (skipped once the step has stopped, so the
@@ -1699,11 +1725,12 @@ inline int star_grid(const Sim &s) { return std::min(kStarGridMax, list_grid(s) 
 
 }  // namespace
 
-void launch_flip_eval_full(Sim &s, int round, int slot, int reversal) {
+void launch_flip_eval_full(Sim &s, int round, int slot, int reversal, bool snapshot) {
     round -= s.rbase;
     Topo t = topo_of(s);
+    const Snapshot snap = snapshot ? Snapshot{s.snap_v, s.snap_twin, s.snap_vh, s.nv + s.R} : Snapshot{};
     hipLaunchKernelGGL(k_flip_eval_full, dim3(grid_for((long)(s.T + 3) / 4 * 1024 / kEvalBlock, kEvalGrid)), dim3(kEvalBlock), 0, s.stream, t, round,
-                       slot, reversal);
+                       slot, reversal, snap);
 }
 
 void launch_flip_eval_list(Sim &s, int round, int slot) {
@@ -1763,7 +1790,7 @@ void launch_ovl_apply(Sim &s, int k) {
 
 void launch_tail(Sim &s, const TailPlan &plan) {
     Topo t = topo_of(s);
-    hipLaunchKernelGGL(k_tail, dim3(1), dim3(kTailBlock), 0, s.stream, t, plan);
+    hipLaunchKernelGGL(k_tail, dim3(1), dim3(kTailBlock), 0, s.stream, t, plan, s.dbase, s.ring);
 }
 
 void launch_repair_rounds(Sim &s, int round0, int slot0, int rounds, bool first_evaluated) {

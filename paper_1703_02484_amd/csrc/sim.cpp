@@ -254,7 +254,7 @@ void enqueue_repair(Sim &s, Cursor &c, bool full, bool reversal, int rounds, std
     // positions: a later repair of the same step that fails replays the
     // whole move from there (the Delaunay triangulation of the end positions
     // is unique), so the repairs after overlap rounds need no copy of their own.
-    if (full) launch_snapshot(s);
+    // The copy is taken by the first evaluation, which reads the whole topology.
     const int rep = c.take_rep();
     if (first_slots) first_slots->push_back(c.slot);
     int last = -1;
@@ -262,7 +262,7 @@ void enqueue_repair(Sim &s, Cursor &c, bool full, bool reversal, int rounds, std
         // the first evaluation scans every edge; the rest of the rounds run in one workgroup
         const int r0 = ++s.round_id;
         const int slot0 = c.take_slot();
-        launch_flip_eval_full(s, r0, slot0, reversal ? rev_mode(s) : 0);
+        launch_flip_eval_full(s, r0, slot0, reversal ? rev_mode(s) : 0, true);
         last = slot0;
         for (int j = 1; j < rounds; ++j) {
             ++s.round_id;
@@ -283,7 +283,7 @@ void enqueue_repair(Sim &s, Cursor &c, bool full, bool reversal, int rounds, std
         const int r = ++s.round_id;
         const int slot = c.take_slot();
         if (j == 0 && full)
-            launch_flip_eval_full(s, r, slot, reversal ? rev_mode(s) : 0);
+            launch_flip_eval_full(s, r, slot, reversal ? rev_mode(s) : 0, true);
         else if (j == 0)
             launch_flip_eval_star(s, oround, r, slot);
         else
@@ -421,12 +421,15 @@ void rollback(Sim &s) {
     if (s.ovl_method == 0) host_rebuild(s);
 }
 
-void drop_graphs(Sim &s) {
-    for (auto &e : s.graphs) {
-        if (e.second.pre) (void)hipGraphExecDestroy(e.second.pre);
-        if (e.second.force) (void)hipGraphExecDestroy(e.second.force);
-        if (e.second.post) (void)hipGraphExecDestroy(e.second.post);
+void destroy_graph(Sim::StepGraph &g) {
+    for (hipGraphExec_t *e : {&g.one, &g.many, &g.pre, &g.force, &g.post}) {
+        if (*e) (void)hipGraphExecDestroy(*e);
+        *e = nullptr;
     }
+}
+
+void drop_graphs(Sim &s) {
+    for (auto &e : s.graphs) destroy_graph(e.second);
     s.graphs.clear();
 }
 
@@ -549,19 +552,24 @@ int host_overlap_loop_nl(Sim &s, Cursor &c, int &rounds) {
     }
 }
 
-// Puts the step counter and the stamp bases of the coming step in device
-// memory (stream-ordered); later launches pass stamps relative to them.
+// The step counter and the stamp bases of the coming step.  Kernels read them from device memory; launches pass
+// stamps relative to them.
+StepBase next_base(Sim &s) {
+    StepBase b;
+    b.step = s.step;
+    b.rbase = s.rbase = s.round_id;
+    b.vbase = s.vbase = s.vround;
+    b.stop = 0;
+    b.batch_idx = 0;
+    b.nl_req = 0;   // the host rebuilds lists that are due before it queues steps
+    b.nl_now = 0;
+    return b;
+}
+
+// Puts them in device memory (stream-ordered).
 void write_base(Sim &s) {
-    s.hbase->step = s.step;
-    s.hbase->rbase = s.round_id;
-    s.hbase->vbase = s.vround;
-    s.hbase->stop = 0;
-    s.hbase->batch_idx = 0;
-    s.hbase->nl_req = 0;   // the host rebuilds lists that are due before it queues steps
-    s.hbase->nl_now = 0;
+    *s.hbase = next_base(s);
     check(hipMemcpyAsync(s.dbase, s.hbase, sizeof(StepBase), hipMemcpyHostToDevice, s.stream), "step base");
-    s.rbase = s.round_id;
-    s.vbase = s.vround;
 }
 
 // Overlap rounds enqueued per step: the adaptive budget, never more than the
@@ -618,9 +626,16 @@ bool tail_fused(const Sim &s) { return tail_mode_of(s) == 1; }
 
 // The budgeted part of a step after the update: repair rounds, then overlap
 // rounds each with its repair, the final overlap check, the skin test.
-void enqueue_rounds(Sim &s, Cursor &c, std::vector<int> &orounds, std::vector<int> &rep_first) {
+// end: the caller would end a queued step next; returns true when the last kernel does it.
+bool enqueue_rounds(Sim &s, Cursor &c, std::vector<int> &orounds, std::vector<int> &rep_first, bool end = false) {
     const int nover = overlaps_budget(s);
     const int mode = tail_mode_of(s);
+    const bool tail_ends = end && !s.use_nl;   // with lists the skin test comes after the tail
+    auto end_in_tail = [&](TailPlan &plan) {   // every round and stamp of the step has been handed out
+        plan.end = tail_ends ? 1 : 0;
+        plan.r_used = s.round_id - s.rbase;
+        plan.v_used = s.vround - s.vbase;
+    };
     if (mode != 1 || nover > MAXTAIL || nover == 0) {
         // Each detection runs in the launch that validates the repair before it: the first one
         // scans every triangle (after the repair of the move), later ones the stars of the disks
@@ -676,14 +691,20 @@ void enqueue_rounds(Sim &s, Cursor &c, std::vector<int> &orounds, std::vector<in
             orounds.push_back(k);
             plan.k[plan.nover] = k;
             plan.stamp[plan.nover] = ++s.vround - s.vbase;
+            end_in_tail(plan);
             launch_tail(s, plan);
         }
         skin_check(s, false);
-        return;
+        return per_phase < nover && tail_ends;
     }
-    enqueue_repair(s, c, true, true, s.budget.em, &rep_first);
-    // the first detection after the move scans every edge (in the tail, later ones only what the round
-    // before changed); its last workgroup runs the round's check
+    // The first detection after the move scans every triangle, with the validation of the move's repair (in the
+    // tail, later ones only what the round before changed); its last workgroup runs both checks.  (The repair's
+    // rounds and that scan in the tail's workgroup as well, two launches fewer: equal on 1,024 disks, 85 against
+    // 80 us per step on 2,048, 105 against 92 on 4,096.)
+    int k = c.take_oround();
+    orounds.push_back(k);
+    const FusedDetect fd{k, ++s.vround, 1};
+    enqueue_repair(s, c, true, true, s.budget.em, &rep_first, -1, &fd);
     // rounds after the first detection in one workgroup (same slots, stamps and round ids)
     TailPlan plan{};
     plan.nover = nover;
@@ -691,15 +712,14 @@ void enqueue_rounds(Sim &s, Cursor &c, std::vector<int> &orounds, std::vector<in
     plan.cap_frac = s.p.cap_frac;
     plan.keep = 1.0 - s.p.contact_tol;
     for (int j = 0; j < nover; ++j) {
-        const int k = c.take_oround();
-        orounds.push_back(k);
-        plan.k[j] = k;
-        if (j == 0) {
-            launch_ovl_detect(s, ++s.vround, k, 1);
-            plan.stamp[0] = 0;
-        } else {
+        if (j > 0) {
+            k = c.take_oround();
+            orounds.push_back(k);
             plan.stamp[j] = ++s.vround - s.vbase;
+        } else {
+            plan.stamp[0] = 0;
         }
+        plan.k[j] = k;
         plan.next_round[j] = s.round_id + 1 - s.rbase;
         plan.slot0[j] = c.slot;
         plan.rep[j] = c.take_rep();
@@ -710,12 +730,14 @@ void enqueue_rounds(Sim &s, Cursor &c, std::vector<int> &orounds, std::vector<in
             c.take_slot();
         }
     }
-    const int k = c.take_oround();
+    k = c.take_oround();
     orounds.push_back(k);
     plan.k[nover] = k;
     plan.stamp[nover] = ++s.vround - s.vbase;
+    end_in_tail(plan);
     launch_tail(s, plan);
     skin_check(s, false);
+    return tail_ends;
 }
 
 // The budgeted overlap rounds of the list method: gather and apply per round,
@@ -778,68 +800,97 @@ hipGraphExec_t capture(Sim &s, const std::function<void()> &enqueue) {
     check(hipStreamBeginCapture(s.stream, hipStreamCaptureModeRelaxed), "begin capture");
     enqueue();
     check(hipStreamEndCapture(s.stream, &g), "end capture");
-    hipError_t rc = hipGraphInstantiate(&e, g, nullptr, nullptr, 0);
+    size_t nodes = 0;
+    hipError_t rc = hipGraphGetNodes(g, nullptr, &nodes);
+    if (rc == hipSuccess && nodes > 0) rc = hipGraphInstantiate(&e, g, nullptr, nullptr, 0);   // nothing enqueued: null
     (void)hipGraphDestroy(g);
     check(rc, "graph instantiate");
     return e;
 }
 
 // The captured step for the current round budgets (captured on first use):
-// [clear counters, cast] [force] [update, budgeted rounds, checks].  Stamps
-// inside are relative to the bases of the step being replayed.
+// cast or list rebuild, force, update, budgeted rounds, checks.  One graph holds
+// a step, a second kGraphSteps of them (the device pauses about 8 us between two
+// graphs; captured once the budgets have held for a while, since a change of
+// budgets needs another graph); with kernel timing a step is cut into three around its force,
+// so that events can be recorded there.  Stamps inside are relative to the bases
+// of the step being replayed.
 Sim::StepGraph &step_graph(Sim &s) {
     const int nover = s.ovl_method == 1 ? s.budget.overlaps : overlaps_budget(s);
     std::vector<int> key = {s.budget.em, nover, tail_mode_of(s), s.multi_em, s.multi_ovl, s.ovl_phase, s.nl_phase};
     for (int j = 0; j < nover; ++j) key.push_back(s.budget.ovl[j]);
+    Sim::StepGraph *found = nullptr;
     for (auto &e : s.graphs)
-        if (e.first == key) return e.second;
-    if (s.graphs.size() >= kMaxGraphs) {   // the least recently captured goes (nothing of it is in flight)
-        Sim::StepGraph &old = s.graphs.front().second;
-        (void)hipGraphExecDestroy(old.pre);
-        (void)hipGraphExecDestroy(old.force);
-        (void)hipGraphExecDestroy(old.post);
-        s.graphs.erase(s.graphs.begin());
+        if (e.first == key) found = &e.second;
+    if (!found) {
+        if (s.graphs.size() >= kMaxGraphs) {   // the least recently captured goes (nothing of it is in flight)
+            destroy_graph(s.graphs.front().second);
+            s.graphs.erase(s.graphs.begin());
+        }
+        s.graphs.emplace_back(key, Sim::StepGraph());
+        found = &s.graphs.back().second;
     }
-    Sim::StepGraph g;
-    // stamps inside the graph count from the base of the step it is replayed for
+    Sim::StepGraph &g = *found;
+    constexpr int64_t kSteady = 32;   // steps with the same budgets before the longer graph is captured
+    const bool many = !s.timing && !g.many && g.uses >= kSteady;
+    if (s.timing ? g.post != nullptr : g.one != nullptr && !many) return g;
     const int r0 = s.round_id, v0 = s.vround;
     const int rbase_live = s.rbase, vbase_live = s.vbase;
-    s.rbase = r0;
-    s.vbase = v0;
-    g.pre = capture(s, [&] {
-        if (s.use_nl) {
-            launch_step_begin(s);
+    auto pre = [&] {
+        if (s.use_nl)
             launch_verlet_build_requested(s);
-        } else {
-            launch_step_begin_cast(s);
-        }
-    });
-    g.force = capture(s, [&] {
+        else
+            launch_cast(s);
+    };
+    auto force = [&] {
         if (s.use_nl)
             launch_force_nl(s);
         else
             launch_force(s);
-    });
-    Cursor c;
-    g.post = capture(s, [&] {
+    };
+    auto post = [&] {
+        // stamps inside the graph count from the base of the step it is replayed for
+        s.round_id = s.rbase = r0;
+        s.vround = s.vbase = v0;
+        Cursor c;
+        g.orounds.clear();
+        g.rep_first.clear();
         launch_em(s);
+        bool ended = false;
         if (s.ovl_method == 1)
             enqueue_rounds_nl(s, c, g.orounds);
         else
-            enqueue_rounds(s, c, g.orounds, g.rep_first);
-        launch_step_end(s, s.round_id - r0, s.vround - v0);
-    });
-    g.r_used = s.round_id - r0;
-    g.v_used = s.vround - v0;
-    g.c_slot = c.slot;
-    g.c_rep = c.rep;
-    g.c_oround = c.oround;
+            ended = enqueue_rounds(s, c, g.orounds, g.rep_first, true);
+        g.r_used = s.round_id - r0;
+        g.v_used = s.vround - v0;
+        if (!ended) launch_step_end(s, g.r_used, g.v_used);
+        g.c_slot = c.slot;
+        g.c_rep = c.rep;
+        g.c_oround = c.oround;
+    };
+    auto steps = [&](int count) {
+        return capture(s, [&] {
+            for (int k = 0; k < count; ++k) {
+                pre();
+                force();
+                post();
+            }
+        });
+    };
+    if (s.timing) {
+        g.pre = capture(s, pre);
+        g.force = capture(s, force);
+        g.post = capture(s, post);
+    } else if (many) {
+        g.many = steps(kGraphSteps);
+    } else {
+        g.one = steps(1);
+    }
     s.round_id = r0;   // capturing ran nothing
     s.vround = v0;
     s.rbase = rbase_live;
     s.vbase = vbase_live;
-    s.graphs.emplace_back(key, std::move(g));
-    return s.graphs.back().second;
+    return g;
 }
 
 void timed(Sim &s, const std::function<void()> &work) {
@@ -979,27 +1030,35 @@ int run_graph_steps(Sim &s, int64_t nsteps) {
         // steps queued after one that stops still cost their launches: queue about as many
         // steps as recently ran between stops (neighbour-list rebuilds, budget growth)
         const int m = (int)std::min<int64_t>(nsteps, std::min(kRing, s.batch_hint));
-        write_base(s);
-        for (int k = 0; k < m; ++k) {
-            check(hipGraphLaunch(g.pre, s.stream), "graph launch");
-            timed(s, [&] { check(hipGraphLaunch(g.force, s.stream), "graph launch"); });
-            check(hipGraphLaunch(g.post, s.stream), "graph launch");
+        launch_step_begin(s, next_base(s));
+        for (int k = 0; k < m;) {
+            if (s.timing) {
+                if (g.pre) check(hipGraphLaunch(g.pre, s.stream), "graph launch");
+                timed(s, [&] { check(hipGraphLaunch(g.force, s.stream), "graph launch"); });
+                check(hipGraphLaunch(g.post, s.stream), "graph launch");
+                ++k;
+            } else if (g.many && m - k >= kGraphSteps) {
+                check(hipGraphLaunch(g.many, s.stream), "graph launch");
+                k += kGraphSteps;
+            } else {
+                check(hipGraphLaunch(g.one, s.stream), "graph launch");
+                ++k;
+            }
         }
-        StepBase hb;
-        check(hipMemcpyAsync(&s.hbase->step, &s.dbase->step, sizeof(StepBase), hipMemcpyDeviceToHost, s.stream),
-              "step base");
+        // the records of all queued steps come back with the base: those of steps after a stop are not read
+        check(hipMemcpyAsync(s.hbase, s.dbase, sizeof(StepBase), hipMemcpyDeviceToHost, s.stream), "step base");
+        check(hipMemcpyAsync(s.hring, s.ring, sizeof(int) * N_CTL * m, hipMemcpyDeviceToHost, s.stream), "ring");
         check(hipStreamSynchronize(s.stream), "sync");
-        hb = *s.hbase;
+        const StepBase hb = *s.hbase;
         const int done = hb.batch_idx;
         const int nrec = done + (hb.stop == 1 ? 1 : 0);
+        g.uses += nrec;
         // stops are rare (a halted step; list rebuilds happen inside the queued steps): after one,
         // queue as many steps as ran before it, then double back up to the ring size
         if (hb.stop == 1)
             s.batch_hint = std::max(4, nrec);
         else if (nrec == m)
             s.batch_hint = std::min(kRing, 2 * s.batch_hint);
-        check(hipMemcpyAsync(s.hring, s.ring, sizeof(int) * N_CTL * nrec, hipMemcpyDeviceToHost, s.stream), "ring");
-        check(hipStreamSynchronize(s.stream), "sync");
         StepPlan plan;
         plan.b = s.budget;
         plan.overlaps = s.ovl_method == 1 ? s.budget.overlaps : overlaps_budget(s);
@@ -1031,7 +1090,12 @@ int run_graph_steps(Sim &s, int64_t nsteps) {
             }
         }
         nsteps -= nrec;
-        write_base(s);   // clears the stop flag for later work on this handle
+        if (hb.stop != 0) {
+            write_base(s);   // clears the stop flag for later work on this handle
+        } else {   // the device has advanced the bases itself
+            s.rbase = s.round_id;
+            s.vbase = s.vround;
+        }
     }
     return BD_OK;
 }
@@ -1803,6 +1867,7 @@ int init_impl(Sim &s, int R, const int32_t *n_per, const double *xy, const doubl
     s.fp32 = p->force_precision == BD_PREC_FP32;
     s.kind_fast = (fp->kind == BD_FORCE_POWER && fp->q == 2.0 && !(fp->cutoff > 0)) ? 1 : 0;
     s.use_nl = fp->cutoff > 0;
+    s.pj_is_xy = fp->S == 1 && !s.fp32 && !s.use_nl;
     s.ovl_method = p->overlap_method;
     s.period = p->periodic ? L_per[0] : 0.0;
     check(hipGetDevice(&s.device), "hipGetDevice");

@@ -183,3 +183,26 @@ def test_tail_in_one_workgroup_equals_launch_per_phase(graph):
         h.step(25)
     _same(a, b)
     _same(a, c)
+
+
+@pytest.mark.parametrize("name,over", [("C1", {}), ("C2", {}), ("C3", {}), ("C3", {"overlap": "verlet"})])
+def test_graph_forms_bitwise_equal_eager(name, over):
+    """The captured forms of a step -- one step, several steps in one graph (captured once the budgets have held),
+    and a step cut around its timed force -- against launch by launch, batch sizes that use each of them."""
+    w = synth.make(name, n=1500)
+    a = binding.Sim.from_workload(w, **over)
+    b = binding.Sim.from_workload(w, **over)
+    b.set_graph_mode(True)
+    for k, n in enumerate([1, 40, 3, 33, 8, 70, 5]):
+        if k in (4, 6):
+            b.enable_kernel_timing(k == 4)
+        a.step(n)
+        b.step(n)
+        if k == 4:
+            assert b.kernel_time()[1] == n
+        if "overlap" in over:   # the list method keeps no triangulation
+            xa, ta, sa, _ = a.state()
+            xb, tb, sb, _ = b.state()
+            assert np.array_equal(xa, xb) and np.array_equal(ta, tb) and sa == sb
+        else:
+            _same(a, b)
