@@ -103,7 +103,7 @@ typedef struct bd_params {
                                     by timing the candidate tilings once per workload shape when the pair
                                     count is large (see bd_get_force_config); -1 / -2 / -3: the symmetric
                                     form (inverse-square law only) with chunks of at most 1024 (4 per
-                                    lane) / 512 (2 per lane) / 1024 (8 per lane, 2 wavefronts) */
+                                    lane) / 512 (4 per lane, 2 wavefronts) / 1024 (8 per lane, 2 wavefronts) */
     int32_t force_per_lane;      /* with force_chunk > 0: particles i per lane, 2 or 4 (0: 4); a tile holds
                                     256 * force_per_lane particles i */
     int32_t force_launch;        /* with force_chunk > 0: 0 one workgroup per tile, j as wave-uniform scalar
@@ -129,7 +129,7 @@ typedef struct bd_params {
                                     overlap method keeps the triangulation of the flat torus (2n triangles,
                                     no frame points, no infinite vertex), whose predicates read a triangle
                                     or a quad at the nearest images of its vertices.  One system per
-                                    handle; all-pairs forces in the one-workgroup-per-tile form
+                                    handle; a pinned all-pairs form is the one-workgroup-per-tile form
                                     (force_chunk >= 0, force_launch 0); no adjoint */
 } bd_params;
 
@@ -213,7 +213,8 @@ int bd_batch_layout(bd_sim *sim, int32_t *R_out, int32_t *disk_off, int32_t *fra
 /* Tiling of the all-pairs force kernel in use (measurement and reproducibility). */
 typedef struct bd_force_config {
     int32_t chunk;        /* j per chunk (results depend on it at rounding level) */
-    int32_t per_lane;     /* i per lane; a tile holds 256 * per_lane particles i */
+    int32_t per_lane;     /* i per lane; a tile holds 256 * per_lane particles i (symmetric: with the chunk
+                             it names the form, see force_chunk; 1 with chunks of 256 or 128) */
     int32_t persistent;   /* launch form: 0 one workgroup per tile (i-block x chunk); 1 a fixed grid taking
                              those tiles from a queue; 2 symmetric: one workgroup per pair of chunks,
                              each pair of disks evaluated once and both sums written; 3 one workgroup

@@ -101,7 +101,17 @@ struct Tile {
 // of one system (A before B, or A itself), each pair evaluated once and both
 // sides written: part[pbase_i + i] (i in A, sum over B) and part[pbase_j + j]
 // (j in B, sum over A; not for A itself).
-constexpr int kSymChunk = 1024;   // longest chunk of the symmetric form (256 per_lane, per_lane 2 or 4)
+// Forms of the symmetric launch: longest chunk, and the particles per lane they are known by (tiles of the
+// ordinary form and the adjoint over the same chunks hold 256 min(per_lane, 4)).
+struct SymForm {
+    int chunk, per_lane;
+};
+constexpr SymForm kSymForms[] = {{1024, 4}, {512, 2}, {1024, 8}, {256, 1}, {128, 1}};
+inline bool is_sym_form(int chunk, int per_lane) {
+    for (const SymForm &f : kSymForms)
+        if (f.chunk == chunk && f.per_lane == per_lane) return true;
+    return false;
+}
 struct SymTile {
     int i0, i1, j0, j1;
     long long pbase_i, pbase_j;

@@ -289,7 +289,10 @@ void launch_adj_step(Sim &s, int t) {
                            a.dk_rows);
     hipLaunchKernelGGL(k_adj_dk_blocks, dim3(nblocks((long long)a.dk_blocks * s.S * s.S)), dim3(kAdjBlock), 0,
                        s.stream, s.n, s.S, a.dk_blocks, s.sp, a.dk_rows, a.dk_blk);
-    if (s.per_lane == 2)
+    if (s.per_lane == 1)   // tiles of 256 min(per_lane, 4) particles
+        hipLaunchKernelGGL(k_adj_pairs<1>, dim3(s.ntiles), dim3(kAdjBlock), 0, s.stream, a.pj4, s.sp_sorted, s.tiles,
+                           s.Kd, s.S, a.gpart);
+    else if (s.per_lane == 2)
         hipLaunchKernelGGL(k_adj_pairs<2>, dim3(s.ntiles), dim3(kAdjBlock), 0, s.stream, a.pj4, s.sp_sorted, s.tiles,
                            s.Kd, s.S, a.gpart);
     else

@@ -281,17 +281,28 @@ __global__ __launch_bounds__(kForceBlock) void k_force_queue(const T2 *__restric
 }
 
 // Symmetric form (inverse-square law).  A tile is a pair of chunks A, B of
-// one system (at most 256 P disks each): each of the 4 wavefronts owns up to
+// one system (at most 64 W P disks each): each of the W wavefronts owns up to
 // 64 P particles i of A, P per lane, in registers.  The particles j of B pass through the wavefront in
-// groups of 128 (2 per lane); a group turns around the wavefront one lane per
+// groups of 64 Q (Q per lane); a group turns around the wavefront one lane per
 // step (DPP wave_rol: lane l takes lane l+1's values) for 64 steps, so every
 // lane meets every j of the group once.  g = (r_i - r_j)/d^3 is added to i's
 // sum and subtracted from j's sum, which travels with j; after the 64 steps
-// each j is back in its lane and the wavefront leaves its sums in LDS.  At the
-// end the 4 wavefronts' sums are added in wavefront order (deterministic) and
-// written for B's particles (slot of chunk A).  A chunk paired with itself
+// each j is back in its lane.  With several wavefronts they take the groups
+// staggered, no two the same at a time, and add their sums of a group to one
+// LDS copy in the order they come to it (fixed, so results are deterministic);
+// with one, it writes them out.  A chunk paired with itself
 // (j0 == i0) takes i's side only, with d^2 floored so that i == j adds 0.
-// Padding i (j) sit at +BIG (-BIG): their g underflow to exactly 0.
+// Padding i (j) sit at +BIG (-BIG): their g underflow to exactly 0.  In a
+// periodic box they would have a nearest image: the groups that hold some are
+// evaluated with a test of each pair.
+// VALU-bound: per pair 14 FP64 instructions (1.2 issue slots each as measured),
+// v_rsq_f64 (4.3 slots) and 8 / P DPP moves of a j (half of that in FP32), so P
+// = 4 where registers and waves allow.  One LDS copy of the j sums instead of
+// one per wavefront doubles the waves a CU holds.  FP64, 64 systems of 2,048 to
+// 32,768 disks: 22 slots a pair as 4 per lane on 2 wavefronts, 24 as 2 per lane
+// on 4; FP32, 65,536 disks: 12.7 against 13.8, 4 per lane on 4 wavefronts 13.3.
+// One wavefront per tile where chunks of 512 are too few tiles to fill the
+// device: 16,001 disks FP64 87 us (chunks of 256) against 129.
 template <typename T>
 __device__ __forceinline__ T rot1(T v);
 template <>
@@ -313,22 +324,22 @@ __device__ __forceinline__ float sym_big<float>() { return 1e18f; }   // (2e18)^
 template <>
 __device__ __forceinline__ double sym_big<double>() { return 1e150; }
 
-constexpr int kSymQ = 2;
-
-// The 64 steps of one group of j (every lane active: the rotation reads all lanes).
-template <typename T, int P, bool SELF>
-__device__ __forceinline__ void sym_group(const T (&xi)[P], const T (&yi)[P], T (&fx)[P], T (&fy)[P],
-                                          T (&xj)[kSymQ], T (&yj)[kSymQ], T (&gx)[kSymQ], T (&gy)[kSymQ]) {
+// The 64 steps of one group of j (every lane active: the rotation reads all lanes).  PAD: the group or the
+// wavefront holds padding (periodic box only).
+template <typename T, int P, int Q, bool SELF, bool PER, bool PAD>
+__device__ __forceinline__ void sym_group(const T (&xi)[P], const T (&yi)[P], T (&fx)[P], T (&fy)[P], T (&xj)[Q],
+                                          T (&yj)[Q], T (&gx)[Q], T (&gy)[Q], T per, T inv_per) {
     for (int t = 0; t < 64; ++t) {
 #pragma unroll
-        for (int q = 0; q < kSymQ; ++q) {
+        for (int q = 0; q < Q; ++q) {
 #pragma unroll
             for (int p = 0; p < P; ++p) {
-                const T dx = xi[p] - xj[q];
-                const T dy = yi[p] - yj[q];
+                const T dx = near_image<T, PER>(xi[p] - xj[q], per, inv_per);
+                const T dy = near_image<T, PER>(yi[p] - yj[q], per, inv_per);
                 T d2 = dx * dx + dy * dy;
                 if (SELF) d2 = d2 > self_floor<T>() ? d2 : self_floor<T>();
-                const T inv3 = inv_cube<T>(d2);
+                T inv3 = inv_cube<T>(d2);
+                if (PAD) inv3 = xi[p] == sym_big<T>() || xj[q] == -sym_big<T>() ? (T)0 : inv3;
                 const T ex = dx * inv3, ey = dy * inv3;
                 fx[p] += ex;
                 fy[p] += ey;
@@ -343,59 +354,92 @@ __device__ __forceinline__ void sym_group(const T (&xi)[P], const T (&yi)[P], T 
     }
 }
 
-// W wavefronts per workgroup; a chunk holds at most 64 W P disks.
-template <typename T, typename T2, int P, int W>
+// W wavefronts per workgroup; a chunk holds at most 64 W P disks.  PER: periodic box of side `period`.
+template <typename T, typename T2, int P, int W, int Q, bool PER>
 __global__ __launch_bounds__(64 * W) void k_force_sym(const T2 *__restrict__ pj, const SymTile *__restrict__ tiles,
-                                                      T2 *__restrict__ part, const StepBase *__restrict__ base) {
-    constexpr int kSymP = P;
-    __shared__ T2 jsum[W][64 * W * P];
+                                                      T2 *__restrict__ part, double period,
+                                                      const StepBase *__restrict__ base) {
+    __shared__ T2 jsum[W > 1 ? 64 * W * P : 1];
     if (base->stop) return;
     const SymTile tl = tiles[blockIdx.x];
     const bool self = tl.j0 == tl.i0;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int ni = tl.i1 - tl.i0, nj = tl.j1 - tl.j0;
     const T big = sym_big<T>();
-    T xi[kSymP], yi[kSymP], fx[kSymP], fy[kSymP];
+    const T per = (T)period, inv_per = PER ? (T)(1.0 / period) : (T)0;
+    T xi[P], yi[P], fx[P], fy[P];
 #pragma unroll
-    for (int p = 0; p < kSymP; ++p) {
-        const int k = wave * 64 * kSymP + p * 64 + lane;
+    for (int p = 0; p < P; ++p) {
+        const int k = wave * 64 * P + p * 64 + lane;
         const T2 v = pj[tl.i0 + (k < ni ? k : 0)];
         xi[p] = k < ni ? v.x : big;
         yi[p] = k < ni ? v.y : big;
         fx[p] = (T)0;
         fy[p] = (T)0;
     }
-    for (int jg = 0; jg < nj; jg += 64 * kSymQ) {   // same trip count in every lane
-        T xj[kSymQ], yj[kSymQ], gx[kSymQ], gy[kSymQ];
-#pragma unroll
-        for (int q = 0; q < kSymQ; ++q) {
-            const int k = jg + q * 64 + lane;
-            const T2 v = pj[tl.j0 + (k < nj ? k : 0)];
-            xj[q] = k < nj ? v.x : -big;
-            yj[q] = k < nj ? v.y : -big;
-            gx[q] = (T)0;
-            gy[q] = (T)0;
+    if (W > 1 && !self) {   // uniform in the workgroup
+        for (int k = threadIdx.x; k < nj; k += 64 * W) {
+            T2 z;
+            z.x = z.y = (T)0;
+            jsum[k] = z;
         }
-        if (self)
-            sym_group<T, P, true>(xi, yi, fx, fy, xj, yj, gx, gy);
-        else
-            sym_group<T, P, false>(xi, yi, fx, fy, xj, yj, gx, gy);
-        if (!self) {
+        __syncthreads();
+    }
+    // turn it: wavefront w takes group (it + w * step) mod turns; at least as many turns as wavefronts, so that no
+    // two take the same
+    const int groups = (nj + 64 * Q - 1) / (64 * Q);
+    const int turns = groups > W ? groups : W, step = turns / W;
+    for (int it = 0; it < turns; ++it) {   // same trip count in every lane
+        int g = it + wave * step;
+        if (g >= turns) g -= turns;
+        if (g < groups) {
+            const int jg = g * 64 * Q;
+            T xj[Q], yj[Q], gx[Q], gy[Q];
 #pragma unroll
-            for (int q = 0; q < kSymQ; ++q) {
+            for (int q = 0; q < Q; ++q) {
                 const int k = jg + q * 64 + lane;
-                if (k < nj) {
-                    T2 g;
-                    g.x = gx[q];
-                    g.y = gy[q];
-                    jsum[wave][k] = g;
+                const T2 v = pj[tl.j0 + (k < nj ? k : 0)];
+                xj[q] = k < nj ? v.x : -big;
+                yj[q] = k < nj ? v.y : -big;
+                gx[q] = (T)0;
+                gy[q] = (T)0;
+            }
+            const bool pad = PER && (jg + 64 * Q > nj || (wave + 1) * 64 * P > ni);
+            if (pad) {
+                if (self)
+                    sym_group<T, P, Q, true, PER, PER>(xi, yi, fx, fy, xj, yj, gx, gy, per, inv_per);
+                else
+                    sym_group<T, P, Q, false, PER, PER>(xi, yi, fx, fy, xj, yj, gx, gy, per, inv_per);
+            } else if (self) {
+                sym_group<T, P, Q, true, PER, false>(xi, yi, fx, fy, xj, yj, gx, gy, per, inv_per);
+            } else {
+                sym_group<T, P, Q, false, PER, false>(xi, yi, fx, fy, xj, yj, gx, gy, per, inv_per);
+            }
+            if (!self) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const int k = jg + q * 64 + lane;
+                    if (k < nj) {
+                        T2 v;
+                        v.x = gx[q];
+                        v.y = gy[q];
+                        if (W > 1) {
+                            const T2 a = jsum[k];
+                            v.x += a.x;
+                            v.y += a.y;
+                            jsum[k] = v;
+                        } else {
+                            part[tl.pbase_j + tl.j0 + k] = v;
+                        }
+                    }
                 }
             }
         }
+        if (W > 1 && !self) __syncthreads();   // the sums of this turn's groups are in place
     }
 #pragma unroll
-    for (int p = 0; p < kSymP; ++p) {
-        const int k = wave * 64 * kSymP + p * 64 + lane;
+    for (int p = 0; p < P; ++p) {
+        const int k = wave * 64 * P + p * 64 + lane;
         if (k < ni) {
             T2 v;
             v.x = fx[p];
@@ -403,17 +447,8 @@ __global__ __launch_bounds__(64 * W) void k_force_sym(const T2 *__restrict__ pj,
             part[tl.pbase_i + tl.i0 + k] = v;
         }
     }
-    if (self) return;   // uniform in the workgroup
-    __syncthreads();
-    for (int k = threadIdx.x; k < nj; k += 64 * W) {
-        T2 a = jsum[0][k];
-#pragma unroll
-        for (int w = 1; w < W; ++w) {
-            a.x += jsum[w][k].x;
-            a.y += jsum[w][k].y;
-        }
-        part[tl.pbase_j + tl.j0 + k] = a;
-    }
+    if (self || W == 1) return;   // uniform in the workgroup
+    for (int k = threadIdx.x; k < nj; k += 64 * W) part[tl.pbase_j + tl.j0 + k] = jsum[k];
 }
 
 // F_i = sum_c K[s_i][spec(c)] Phi_{i,c} over the chunks of i's system, FP64,
@@ -713,39 +748,53 @@ void launch_force(Sim &s, const void *src) {
     if (!src) src = s.pj_is_xy ? (const void *)s.xy : s.pj;
     LawArgs law{s.fp.kind, s.fp.q, s.fp.A, s.fp.lambda, s.fp.cutoff, s.period};
     if (s.persistent == 2) {   // symmetric chunk pairs (the host builds them only for the inverse-square law)
-        // per_lane 2 / 4: 4 wavefronts (chunks of 512 / 1024); 8: 2 wavefronts (chunks of 1024)
-        const dim3 g(s.nstiles), b4(256), b2(128);
-        const SymTile *st = s.stiles;
-        const StepBase *base = s.dbase;
+        auto go = [&](auto kern, int waves, auto *pos, auto *part) {
+            hipLaunchKernelGGL(kern, dim3(s.nstiles), dim3(64 * waves), 0, s.stream, pos,
+                               (const SymTile *)s.stiles, part, s.period, (const StepBase *)s.dbase);
+        };
+        // chunks of 1024 (4 per lane, 4 wavefronts; 8 per lane, 2), 512 (4 per lane, 2), 256 (4 per lane, 1) and
+        // 128 (2 per lane, 1)
+#define BD_SYM(T, T2, Q, PER)                                                                    \
+    do {                                                                                         \
+        const T2 *pos = (const T2 *)src;                                                         \
+        T2 *part = (T2 *)s.part;                                                                 \
+        if (s.chunk_len == 128)                                                                  \
+            go(k_force_sym<T, T2, 2, 1, 2, PER>, 1, pos, part);                                  \
+        else if (s.chunk_len == 256)                                                             \
+            go(k_force_sym<T, T2, 4, 1, Q, PER>, 1, pos, part);                                  \
+        else if (s.chunk_len == 512)                                                             \
+            go(k_force_sym<T, T2, 4, 2, Q, PER>, 2, pos, part);                                  \
+        else if (s.per_lane == 4)                                                                \
+            go(k_force_sym<T, T2, 4, 4, Q, PER>, 4, pos, part);                                  \
+        else                                                                                     \
+            go(k_force_sym<T, T2, 8, 2, Q, PER>, 2, pos, part);                                  \
+    } while (0)
         if (s.fp32) {
-            const float2 *pj = (const float2 *)src;
-            float2 *part = (float2 *)s.part;
-            if (s.per_lane == 2)
-                hipLaunchKernelGGL((k_force_sym<float, float2, 2, 4>), g, b4, 0, s.stream, pj, st, part, base);
-            else if (s.per_lane == 4)
-                hipLaunchKernelGGL((k_force_sym<float, float2, 4, 4>), g, b4, 0, s.stream, pj, st, part, base);
+            if (s.period > 0.0)
+                BD_SYM(float, float2, 1, true);
             else
-                hipLaunchKernelGGL((k_force_sym<float, float2, 8, 2>), g, b2, 0, s.stream, pj, st, part, base);
+                BD_SYM(float, float2, 2, false);
         } else {
-            const double2 *pj = (const double2 *)src;
-            double2 *part = (double2 *)s.part;
-            if (s.per_lane == 2)
-                hipLaunchKernelGGL((k_force_sym<double, double2, 2, 4>), g, b4, 0, s.stream, pj, st, part, base);
-            else if (s.per_lane == 4)
-                hipLaunchKernelGGL((k_force_sym<double, double2, 4, 4>), g, b4, 0, s.stream, pj, st, part, base);
+            if (s.period > 0.0)
+                BD_SYM(double, double2, 1, true);
             else
-                hipLaunchKernelGGL((k_force_sym<double, double2, 8, 2>), g, b2, 0, s.stream, pj, st, part, base);
+                BD_SYM(double, double2, 1, false);
         }
+#undef BD_SYM
         return;
     }
     if (s.persistent == 1) hipLaunchKernelGGL(k_zero_one, dim3(1), dim3(64), 0, s.stream, s.ctl + K_FQUEUE);
     if (s.fp32) {
-        if (s.per_lane == 2)
+        if (s.per_lane == 1)
+            launch_force_p<float, float2, 1>(s, law, src);
+        else if (s.per_lane == 2)
             launch_force_p<float, float2, 2>(s, law, src);
         else
             launch_force_p<float, float2, 4>(s, law, src);
     } else {
-        if (s.per_lane == 2)
+        if (s.per_lane == 1)
+            launch_force_p<double, double2, 1>(s, law, src);
+        else if (s.per_lane == 2)
             launch_force_p<double, double2, 2>(s, law, src);
         else
             launch_force_p<double, double2, 4>(s, law, src);
@@ -765,6 +814,8 @@ int force_max_grid(Sim &s, int per_lane) {
     return cus * per_cu;
 }
 
+constexpr int kEmSmall = 32768;
+
 void launch_em(Sim &s, int level, unsigned index) {
     EmArgs a;
     a.n = s.n;
@@ -779,12 +830,14 @@ void launch_em(Sim &s, int level, unsigned index) {
     a.level = level;
     a.index = index;
     a.periodic = s.period > 0.0 ? 1 : 0;
-    const int nb = blocks_for(s.n, 256);
+    // the partial sums of a disk are a chain of loads: small handles spread them over more compute units
+    const int block = s.n <= kEmSmall ? 64 : 256;
+    const int nb = blocks_for(s.n, block);
     const Tape &tp = s.adj.tape;
     signed char *wf = tp.on ? tp.emwf + (size_t)tp.step_idx * 2 * s.n : nullptr;
     const bool bridge = level > 0;
     auto go = [&](auto kern, auto part, const double2 *fdirect) {
-        hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, s.stream, a, (const StepBase *)s.dbase, part, s.reps,
+        hipLaunchKernelGGL(kern, dim3(nb), dim3(block), 0, s.stream, a, (const StepBase *)s.dbase, part, s.reps,
                            s.rep_of, s.chunk_spec, s.Kd, s.pos_of, s.key_id, s.sp, s.rad, s.x, s.y, s.xy, s.xo, s.yo, s.th,
                            s.tho, s.acc, fdirect, wf, (const int *)s.ctl);
     };

@@ -1287,16 +1287,13 @@ struct Tiling {
     long long part_len = 0;
 };
 
-// sym: chunks of at most 256 per_lane and the symmetric form's tile list (every
+// sym: chunks of at most `chunk` and the symmetric form's tile list (every
 // pair of chunks of a system once, then every chunk with itself); the
 // ordinary tiles of the same chunks are kept for the adjoint sweep.
-// Longest chunk of the symmetric form for a per_lane setting (2, 4: 4 wavefronts; 8: 2 wavefronts).
-inline int sym_cap(int per_lane) { return per_lane == 8 ? 1024 : 256 * per_lane; }
-
 Tiling make_tiling(const Sim &s, int chunk, int per_lane, bool sym = false) {
     Tiling t;
     t.reps.resize(s.R);
-    const int ib_len = 256 * std::min(per_lane, 4);   // ordinary tiles (and the adjoint's) hold 2 or 4 per lane
+    const int ib_len = 256 * std::min(per_lane, 4);   // ordinary tiles (and the adjoint's) hold 1, 2 or 4 per lane
     std::vector<int2> ch;
     for (int r = 0; r < s.R; ++r) {
         RepInfo &ri = t.reps[r];
@@ -1311,7 +1308,7 @@ Tiling make_tiling(const Sim &s, int chunk, int per_lane, bool sym = false) {
         for (int b = 0; b < s.S; ++b) {
             ch.clear();
             cut_species(s.bstart_h[r * (s.S + 1) + b], s.bstart_h[r * (s.S + 1) + b + 1],
-                        sym ? sym_cap(per_lane) : chunk, ch, sym);
+                        chunk, ch, sym);
             for (const int2 &c : ch) {
                 all.push_back(c);
                 t.chunk_spec.push_back(b);
@@ -1350,9 +1347,9 @@ void upload_tiling(Sim &s, const Tiling &t, int chunk, int per_lane, int persist
     if ((long long)t.tiles.size() > s.tiles_cap || t.part_len > s.part_cap ||
         (long long)t.stiles.size() > s.stiles_cap || (persistent == 2) != !t.stiles.empty())
         throw DeviceError{hipErrorInvalidValue, "force tiling larger than its buffers"};
-    for (const SymTile &st : t.stiles)   // the kernel holds at most sym_cap(per_lane) particles of each side
-        if (st.i1 - st.i0 > sym_cap(per_lane) || st.j1 - st.j0 > sym_cap(per_lane) || st.i1 <= st.i0 ||
-            st.j1 <= st.j0 || (per_lane != 2 && per_lane != 4 && per_lane != 8))
+    for (const SymTile &st : t.stiles)   // the kernel holds at most a chunk of each side
+        if (st.i1 - st.i0 > chunk || st.j1 - st.j0 > chunk || st.i1 <= st.i0 || st.j1 <= st.j0 ||
+            !is_sym_form(chunk, per_lane))
             throw DeviceError{hipErrorInvalidValue, "symmetric force tile out of shape"};
     if (!t.stiles.empty())
         check(hipMemcpyAsync(s.stiles, t.stiles.data(), sizeof(SymTile) * t.stiles.size(), hipMemcpyHostToDevice,
@@ -1491,6 +1488,29 @@ void alloc_force_buffers(Sim &s, long long max_tiles, long long max_part, long l
     s.stiles_cap = max_stiles;
 }
 
+// The form when nothing is timed.  One system: a small one is short of workgroups, not of arithmetic, so the
+// tiles get smaller (256 particles i, short chunks) until the partial sums the update reads back cost more; from
+// 4,096 disks on the inverse-square law takes the symmetric form with one wavefront per tile.  Measured with graph
+// replay, us per step as 256 per lane 4 and <= 2,048 tiles (the rule for batches) / this rule: FP64 65 / 55 on 500
+// disks, 70 / 63 on 1,024, 79 / 68 on 2,048, 90 / 81 on 3,000, 104 / 92 on 5,003, 144 / 119 on 8,000; periodic 354
+// / 273 on 16,001, 838 / 605 on 32,768.  Chunks of 128 against 256 in a periodic box: 222 / 251 on 12,000 disks,
+// 282 / 273 on 16,001.
+struct FixedForm {
+    int chunk, per_lane;
+    bool sym;
+};
+
+FixedForm fixed_form(const Sim &s, int dchunk) {
+    if (s.R > 1) return {dchunk, 4, false};
+    if (s.n <= 768) return {32, 1, false};
+    if (s.n <= 2560) return {64, 1, false};
+    if (s.n <= 4096) return {128, 1, false};
+    if (!s.kind_fast) return {dchunk, 4, false};
+    if (s.n <= 12288) return {128, 1, true};
+    if (s.n <= 65536) return {256, 1, true};
+    return {1024, 4, true};
+}
+
 void setup_force(Sim &s) {
     const size_t vec = s.fp32 ? sizeof(float2) : sizeof(double2);
     s.reps = dalloc<RepInfo>(s.R);
@@ -1510,21 +1530,29 @@ void setup_force(Sim &s) {
         upload_tiling(s, t, s.p.force_chunk, pl, s.p.force_launch == 1 ? 1 : s.p.force_launch == 2 ? 3 : 0);
         return;
     }
-    if (s.p.force_chunk < 0) {   // the symmetric form, pinned: -1 chunks of 1024 (4 per lane), -2 of 512, -3 1024 (8)
-        const int pl = s.p.force_chunk == -1 ? 4 : s.p.force_chunk == -2 ? 2 : 8;
-        Tiling t = make_tiling(s, sym_cap(pl), pl, true);
+    if (s.p.force_chunk < 0) {   // the symmetric form, pinned
+        const SymForm f = kSymForms[-1 - s.p.force_chunk];
+        Tiling t = make_tiling(s, f.chunk, f.per_lane, true);
         alloc_force_buffers(s, (long long)t.tiles.size(), t.part_len, (long long)t.stiles.size());
-        upload_tiling(s, t, sym_cap(pl), pl, 2);
+        upload_tiling(s, t, f.chunk, f.per_lane, 2);
         return;
     }
     long double pairs = 0;
     for (int r = 0; r < s.R; ++r) pairs += (long double)(s.off_h[r + 1] - s.off_h[r]) * (s.off_h[r + 1] - s.off_h[r]);
     const int dchunk = default_chunk(s);
-    // a periodic box has its own (minimum-image) kernel in the one-workgroup-per-tile form: fixed rule
+    const long long part_limit = (2ll << 30) / (long long)vec;
+    // few pairs, and the periodic box: fixed rule
     if (pairs < (long double)(1 << 26) || s.period > 0.0) {
-        Tiling t = make_tiling(s, dchunk, 4);
-        alloc_force_buffers(s, (long long)t.tiles.size(), t.part_len);
-        upload_tiling(s, t, dchunk, 4, 0);
+        const FixedForm f = fixed_form(s, dchunk);
+        Tiling t = make_tiling(s, f.chunk, f.per_lane, f.sym);
+        if (t.part_len > part_limit && f.sym) {   // too many chunks for the partial sums: the ordinary form
+            t = make_tiling(s, dchunk, 4);
+            alloc_force_buffers(s, (long long)t.tiles.size(), t.part_len);
+            upload_tiling(s, t, dchunk, 4, 0);
+            return;
+        }
+        alloc_force_buffers(s, (long long)t.tiles.size(), t.part_len, (long long)t.stiles.size());
+        upload_tiling(s, t, f.chunk, f.per_lane, f.sym ? 2 : 0);
         return;
     }
     const std::string key = tune_key(s);
@@ -1546,7 +1574,6 @@ void setup_force(Sim &s) {
     std::vector<int> chunks{dchunk};   // the fixed rule is always a candidate
     for (int c = std::max(256, dchunk / 8); c <= std::min(65536, dchunk * 4); c *= 2)
         if (c != dchunk) chunks.push_back(c);
-    const long long part_limit = (2ll << 30) / (long long)vec;
     long long max_tiles = 0, max_part = 0;
     std::vector<std::pair<int, int>> cands;   // (chunk, per_lane)
     for (int c : chunks)
@@ -1565,12 +1592,15 @@ void setup_force(Sim &s) {
     }
     // the symmetric form (inverse-square law): every pair of chunks once
     long long max_stiles = 0;
-    std::vector<int> sym_pl;   // symmetric candidates: chunks of 512 (2 per lane) or 1024 (4 or 8 per lane)
+    std::vector<SymForm> sym;
     if (s.kind_fast)
-        for (int pl : {2, 4, 8}) {
-            Tiling t = make_tiling(s, sym_cap(pl), pl, true);
+        for (const SymForm &f : kSymForms) {
+            // chunks below 512 fill the device for one system of up to some 30,000 disks; in a batch the systems
+            // do, and a system stepped alone can be pinned to the batch's form
+            if (f.chunk < 512 && (s.R > 1 || s.n > 40000)) continue;
+            Tiling t = make_tiling(s, f.chunk, f.per_lane, true);
             if (t.part_len > part_limit) continue;
-            sym_pl.push_back(pl);
+            sym.push_back(f);
             max_tiles = std::max(max_tiles, (long long)t.tiles.size());
             max_part = std::max(max_part, t.part_len);
             max_stiles = std::max(max_stiles, (long long)t.stiles.size());
@@ -1606,9 +1636,9 @@ void setup_force(Sim &s) {
             scored.push_back(TuneChoice{cp.first, cp.second, pers, time_force(s, 5)});
         }
     }
-    for (int pl : sym_pl) {
-        upload_tiling(s, make_tiling(s, sym_cap(pl), pl, true), sym_cap(pl), pl, 2);
-        scored.push_back(TuneChoice{sym_cap(pl), pl, 2, time_force(s, 5)});
+    for (const SymForm &f : sym) {
+        upload_tiling(s, make_tiling(s, f.chunk, f.per_lane, true), f.chunk, f.per_lane, 2);
+        scored.push_back(TuneChoice{f.chunk, f.per_lane, 2, time_force(s, 5)});
     }
     std::sort(scored.begin(), scored.end(), [](const TuneChoice &x, const TuneChoice &y) { return x.ms < y.ms; });
     TuneChoice best{0, 0, 0, 1e30};

@@ -104,3 +104,23 @@ def test_symmetric_form_needs_the_inverse_square_law():
     w = synth.make("C1", n=300)
     with pytest.raises(binding.BDError):
         binding.Sim.from_workload(w, force_chunk=-1, kind="power", q=6.0)
+
+
+@pytest.mark.parametrize("n", [700, 769, 2561, 4097, 5003, 12289])
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("periodic", [False, True])
+def test_fixed_rule_forms_match_oracle(n, fp32, periodic):
+    """The forms the library takes without timing, at the sizes where they change: small ordinary tiles, then one
+    wavefront per pair of chunks of 128 (and 256 in a periodic box), with ragged last chunks of three species whose
+    padding must not act (in a periodic box padding has a nearest image)."""
+    w = synth.make("C1", n=n, periodic=periodic)
+    species = (np.arange(n) % 5 % 3).astype(np.int32)
+    K = np.array([[1e-2, -5e-3, 4e-3], [2e-3, 1e-2, 0.0], [-1e-3, 3e-3, 7e-3]])
+    g = binding.Sim(w.xy, w.radii, species, None, K, L=w.L, fp32=fp32, periodic=periodic)
+    cfg = g.force_config()
+    if cfg["tuned"] == 0:
+        assert cfg["persistent"] == (2 if n > 4096 else 0)
+    idx = np.unique(np.concatenate([[0, n - 1], np.random.default_rng(1).integers(0, n, 500)])).astype(np.int32)
+    fo = oracle.forces(w.xy, species, K, idx=idx, period=w.L if periodic else 0.0)
+    tol = 1e-4 if fp32 else 1e-12
+    assert np.abs(g.forces()[idx] - fo).max() <= tol * _scale(fo)
