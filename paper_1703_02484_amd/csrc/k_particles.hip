@@ -666,7 +666,7 @@ __global__ void k_step_begin(int *__restrict__ ctl, StepBase *__restrict__ base,
 }
 
 __global__ void k_step_end(int *ctl, StepBase *base, int *__restrict__ ring, int r_used, int v_used) {
-    step_end_body(ctl, base, ring, r_used, v_used);
+    step_end_body(ctl, ctl, base, ring, r_used, v_used);
 }
 
 }  // namespace

@@ -136,6 +136,15 @@ Topo topo_of(Sim &s) {
     return t;
 }
 
+// The box kind at compile time: the kernels that read geometry are instantiated for walls and for the periodic
+// box, so that the wall-box code holds no minimum images (an FP64 division each).  A kernel's code is read through a
+// cache of 64 KiB shared by two compute units, and a one-workgroup kernel that walks through more than that waits
+// for its instructions.
+template <bool PER>
+struct TopoP : Topo {
+    static constexpr bool kPer = PER;
+};
+
 __device__ __forceinline__ bool stopped(const int *ctl) { return (ctl[K_HALT] | ctl[K_DONE]) != 0; }
 // Read of a counter that other workgroups of the running launch update with atomics.
 __device__ __forceinline__ int ctl_read(const int *ctl, int i) {
@@ -156,28 +165,23 @@ __device__ __forceinline__ void topo_err(const Topo &t) { atomicAdd(&t.ctl[K_TOP
 // frame of its first vertex, every other vertex at its nearest image: every
 // edge of the torus triangulation is far shorter than P / 2, so that image is
 // the one the triangle spans.
-__device__ __forceinline__ double sep_p(double v, double P) { return P > 0.0 ? bd_min_image(v, P) : v; }
+template <class TP>
+__device__ __forceinline__ double sep_p(const TP &t, double v) { return TP::kPer ? bd_min_image(v, t.P) : v; }
 
-__device__ __forceinline__ int flip_rule_at(const Topo &t, int a, int b, int c, int d, double2 pa, double2 pb,
+template <class TP>
+__device__ __forceinline__ int flip_rule_at(const TP &t, int a, int b, int c, int d, double2 pa, double2 pb,
                                             double2 pc, double2 pd, bool *inverted) {
-    if (t.P <= 0.0) return bd_flip_rule_xy(a, b, c, d, t.inf, pa.x, pa.y, pb.x, pb.y, pc.x, pc.y, pd.x, pd.y, true, inverted);
-    return bd_flip_rule_quad(0.0, 0.0, sep_p(pb.x - pa.x, t.P), sep_p(pb.y - pa.y, t.P), sep_p(pc.x - pa.x, t.P),
-                             sep_p(pc.y - pa.y, t.P), sep_p(pd.x - pa.x, t.P), sep_p(pd.y - pa.y, t.P), true,
-                             inverted);
+    if (!TP::kPer)
+        return bd_flip_rule_xy(a, b, c, d, t.inf, pa.x, pa.y, pb.x, pb.y, pc.x, pc.y, pd.x, pd.y, true, inverted);
+    return bd_flip_rule_quad(0.0, 0.0, sep_p(t, pb.x - pa.x), sep_p(t, pb.y - pa.y), sep_p(t, pc.x - pa.x),
+                             sep_p(t, pc.y - pa.y), sep_p(t, pd.x - pa.x), sep_p(t, pd.y - pa.y), true, inverted);
 }
 
-__device__ __forceinline__ int flip_rule_of(const Topo &t, int a, int b, int c, int d, bool *inverted) {
-    return flip_rule_at(t, a, b, c, d, t.xy[a], t.xy[b], t.xy[c], t.xy[d], inverted);
-}
-
-__device__ __forceinline__ double orient_at(const Topo &t, double2 pa, double2 pb, double2 pc) {
-    if (t.P <= 0.0) return bd_orient(pa.x, pa.y, pb.x, pb.y, pc.x, pc.y);
-    return bd_orient(0.0, 0.0, sep_p(pb.x - pa.x, t.P), sep_p(pb.y - pa.y, t.P), sep_p(pc.x - pa.x, t.P),
-                     sep_p(pc.y - pa.y, t.P));
-}
-
-__device__ __forceinline__ double orient_of(const Topo &t, int a, int b, int c) {
-    return orient_at(t, t.xy[a], t.xy[b], t.xy[c]);
+template <class TP>
+__device__ __forceinline__ double orient_at(const TP &t, double2 pa, double2 pb, double2 pc) {
+    if (!TP::kPer) return bd_orient(pa.x, pa.y, pb.x, pb.y, pc.x, pc.y);
+    return bd_orient(0.0, 0.0, sep_p(t, pb.x - pa.x), sep_p(t, pb.y - pa.y), sep_p(t, pc.x - pa.x),
+                     sep_p(t, pc.y - pa.y));
 }
 
 __device__ __forceinline__ unsigned long long claim_key(int round, int e) {
@@ -353,20 +357,32 @@ __device__ __forceinline__ bool adjacent(const Topo &t, int c, int d) {
     }
 }
 
-// Stars, one per kStarLanes lanes.  The star of a disk is its outgoing half-edges in counter-clockwise order from
-// vert_he; lane q of the group holds half-edges q and q + kStarLanes with their far vertices.  Finding it is a
-// chain of dependent loads (each half-edge from the one before), walked from both ends at once by the whole group
-// (same addresses); everything after it is one load per lane.  Stars above kStarMax are left to one lane.
-constexpr int kStarLanes = 8, kStarMax = 16;
+// Stars, one per kStarLanes lanes.  The star of a disk is its outgoing
+// half-edges in counter-clockwise order from vert_he; lane q of the group holds
+// half-edges q and q + kStarLanes with their far vertices.  Finding it is a
+// chain of dependent loads (each half-edge from the one before), walked from
+// both ends at once by the whole group (same addresses); everything after it is
+// one load per lane.  Stars above kStarMax are left to one lane.  (Sixteen lanes
+// in the one-workgroup tail, one half-edge each: 2% faster rounds below 64 stars,
+// but twice the passes above: 272 against 247 us a step at 16,000 disks.)
+constexpr int kStarLanes = 8;
+constexpr int kStarMax = 2 * kStarLanes;
+constexpr int kStarLarge = -1;
 
 struct Star {
     int deg;         // kStarLarge: more than kStarMax; 0: the walk met an index out of range
     int h[2], w[2];
 };
-constexpr int kStarLarge = -1;
+struct StarPos {   // positions of the disk and of the far vertices a lane holds
+    double2 pv, pw[2];
+};
 
 __device__ __forceinline__ int star_base() { return (int)__lane_id() & ~(kStarLanes - 1); }
 __device__ __forceinline__ int star_lane() { return (int)__lane_id() & (kStarLanes - 1); }
+// Whether `any` holds in a lane of this lane's group (every lane of the group is here).
+__device__ __forceinline__ bool star_any(bool any) {
+    return ((__ballot(any) >> star_base()) & ((1ull << kStarLanes) - 1ull)) != 0;
+}
 // Value held for half-edge i of the star (two: some star of the wavefront has more than kStarLanes).
 template <typename T>
 __device__ __forceinline__ T star_get(const T (&x)[2], int i, bool two) {
@@ -377,14 +393,21 @@ __device__ __forceinline__ T star_get(const T (&x)[2], int i, bool two) {
     return i < kStarLanes ? a : b;
 }
 __device__ __forceinline__ double2 star_get2(const double2 (&x)[2], int i, bool two) {
-    const double ax[2] = {x[0].x, x[1].x}, ay[2] = {x[0].y, x[1].y};
+    double ax[2], ay[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        ax[u] = x[u].x;
+        ay[u] = x[u].y;
+    }
     return make_double2(star_get(ax, i, two), star_get(ay, i, two));
 }
+__device__ __forceinline__ bool star_two(const Star &s) { return __ballot(s.deg > kStarLanes) != 0; }
 
 __device__ __forceinline__ Star star_walk(const Topo &t, int v) {
     Star s;
     s.deg = 0;
-    s.h[0] = s.h[1] = s.w[0] = s.w[1] = -1;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) s.h[u] = s.w[u] = -1;
     const int q = star_lane();
     const int h0 = t.vert_he[v];
     if (bad_he(t, h0)) return s;
@@ -399,11 +422,12 @@ __device__ __forceinline__ Star star_walk(const Topo &t, int v) {
         if (bad_he(t, tf)) return s;
         if (tf == hb) break;
         if (bad_he(t, tb)) return s;
-        if (nf + nb >= kStarMax) {
+        const int cw = bd_next(tb);
+        const bool meet = cw == tf;
+        if (nf + nb + (meet ? 1 : 2) > kStarMax) {
             s.deg = kStarLarge;
             return s;
         }
-        const int cw = bd_next(tb);
         if (q == (nf & (kStarLanes - 1))) {
             const int w = t.he_v[bd_next(tf)];
             if (nf < kStarLanes) {
@@ -415,11 +439,7 @@ __device__ __forceinline__ Star star_walk(const Topo &t, int v) {
             }
         }
         ++nf;
-        if (cw == tf) break;
-        if (nf + nb >= kStarMax) {
-            s.deg = kStarLarge;
-            return s;
-        }
+        if (meet) break;
         if (q == nb) {
             bh = cw;
             bw = t.he_v[bd_next(cw)];
@@ -429,6 +449,7 @@ __device__ __forceinline__ Star star_walk(const Topo &t, int v) {
         hb = cw;
     }
     const int deg = nf + nb;
+    bool ok = true;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {   // half-edge i >= nf is the (deg - 1 - i)-th clockwise one
         const int i = q + u * kStarLanes;
@@ -438,13 +459,38 @@ __device__ __forceinline__ Star star_walk(const Topo &t, int v) {
             s.h[u] = h;
             s.w[u] = w;
         }
+        if (i < deg && bad_v(t, s.w[u])) ok = false;
     }
-    bool ok = true;
+    s.deg = star_any(!ok) ? 0 : deg;
+    return s;
+}
+
+// The star that the current round's gather recorded for the disk queued at idx; with `rewritten`, whether a flip
+// round rfirst or later (absolute) rewrote the triangle of a half-edge this lane holds.  Two dependent loads deep:
+// the record has room for kStarMax whatever the degree, and lanes past the degree read the tables' first entries.
+__device__ __forceinline__ Star star_recorded(const Topo &t, int idx, int rfirst = 0, bool *rewritten = nullptr) {
+    Star s;
+    const int *rec = t.star + (size_t)idx * kStarMax + star_lane();
+    s.deg = t.star_deg[idx];
+    s.h[0] = rec[0];
+    s.h[1] = -1;
+    const bool two = star_two(s);
+    if (two) s.h[1] = rec[kStarLanes];
+    int w[2] = {-1, -1}, stamp[2] = {0, 0};
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-        if (q + u * kStarLanes < deg && bad_v(t, s.w[u])) ok = false;
-    const unsigned long long group = ((1ull << kStarLanes) - 1ull) << star_base();
-    s.deg = (__ballot(!ok) & group) != 0 ? 0 : deg;
+    for (int u = 0; u < 2; ++u) {
+        if (u == 1 && !two) continue;
+        const int h = star_lane() + u * kStarLanes < s.deg ? s.h[u] : 0;
+        w[u] = t.he_v[bd_next(h)];
+        if (rewritten) stamp[u] = t.tri_stamp[h / 3];
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const bool held = star_lane() + u * kStarLanes < s.deg;
+        if (!held) s.h[u] = -1;
+        s.w[u] = held ? w[u] : -1;
+        if (rewritten && held && stamp[u] >= rfirst) *rewritten = true;
+    }
     return s;
 }
 
@@ -497,27 +543,14 @@ __device__ __forceinline__ void register_flip(const Topo &t, int h, int tw, int 
 
 // Evaluates the canonical edge h (h < twin) and, if it must flip, registers
 // it as a candidate of round slot `slot` and claims its two triangles.
-template <int CAP = 1>
-__device__ __forceinline__ void eval_edge(const Topo &t, int h, int tw, int round, int slot, int reversal,
-                                          CandStage<CAP> *st = nullptr) {
+template <int CAP, class TP>
+__device__ __forceinline__ void eval_edge(const TP &t, int h, int tw, int round, int slot, CandStage<CAP> *st) {
     if (bad_he(t, tw)) return topo_err(t);
     const int a = t.he_v[h], b = t.he_v[bd_next(h)], c = t.he_v[bd_prev(h)];
     const int d = t.he_v[bd_prev(tw)];
     if (bad_v(t, a) || bad_v(t, b) || bad_v(t, c) || bad_v(t, d)) return topo_err(t);
-    if (reversal) {
-        // Sec. 4.3: the pair passed through each other if the edge vector reversed
-        bool rev = false;
-        if (a < t.n && b < t.n) {
-            const double ox = sep_p(t.xo[b] - t.xo[a], t.P), oy = sep_p(t.yo[b] - t.yo[a], t.P);
-            const double2 pa = t.xy[a], pb = t.xy[b];
-            const double mx = sep_p(pb.x - pa.x, t.P), my = sep_p(pb.y - pa.y, t.P);
-            rev = ox * mx + oy * my < 0.0;
-        }
-        wave_count64(&t.acc[A_REVERSALS], rev);
-        if (reversal == 2) wave_count(&t.ctl[K_REV], rev);
-    }
     bool inverted = false;
-    const int rule = flip_rule_of(t, a, b, c, d, &inverted);
+    const int rule = flip_rule_at(t, a, b, c, d, t.xy[a], t.xy[b], t.xy[c], t.xy[d], &inverted);
     register_flip<CAP>(t, h, tw, c, d, rule, inverted, round, slot, st);
 }
 
@@ -548,7 +581,8 @@ struct Snapshot {
     int nvh;
 };
 
-__global__ __launch_bounds__(kEvalBlock) void k_flip_eval_full(Topo t, int round, int slot, int reversal,
+template <class TP>
+__global__ __launch_bounds__(kEvalBlock) void k_flip_eval_full(TP t, int round, int slot, int reversal,
                                                                Snapshot snap) {
     __shared__ CandStage<kEvalStage> st;
     if (stopped(t.ctl)) return;   // nothing in this launch writes the stop flags: uniform
@@ -613,8 +647,8 @@ __global__ __launch_bounds__(kEvalBlock) void k_flip_eval_full(Topo t, int round
                 const int k1 = k == 2 ? 0 : k + 1;
                 bool rev = false;
                 if (own[k] && v[k] < t.n && v[k1] < t.n) {
-                    const double rx = sep_p(ox[k1] - ox[k], t.P), ry = sep_p(oy[k1] - oy[k], t.P);
-                    const double mx = sep_p(px[k1] - px[k], t.P), my = sep_p(py[k1] - py[k], t.P);
+                    const double rx = sep_p(t, ox[k1] - ox[k]), ry = sep_p(t, oy[k1] - oy[k]);
+                    const double mx = sep_p(t, px[k1] - px[k]), my = sep_p(t, py[k1] - py[k]);
                     rev = rx * mx + ry * my < 0.0;
                 }
                 wave_count64(&t.acc[A_REVERSALS], rev);
@@ -628,11 +662,11 @@ __global__ __launch_bounds__(kEvalBlock) void k_flip_eval_full(Topo t, int round
             const int a = v[k], b = v[k1], c = v[k2];
             bool inverted = false;
             int rule;
-            if (t.P > 0.0) {
+            if (TP::kPer) {
                 const double ax = px[k], ay = py[k];
-                rule = bd_flip_rule_quad(0.0, 0.0, sep_p(px[k1] - ax, t.P), sep_p(py[k1] - ay, t.P),
-                                         sep_p(px[k2] - ax, t.P), sep_p(py[k2] - ay, t.P), sep_p(qx[k] - ax, t.P),
-                                         sep_p(qy[k] - ay, t.P), true, &inverted);
+                rule = bd_flip_rule_quad(0.0, 0.0, sep_p(t, px[k1] - ax), sep_p(t, py[k1] - ay),
+                                         sep_p(t, px[k2] - ax), sep_p(t, py[k2] - ay), sep_p(t, qx[k] - ax),
+                                         sep_p(t, qy[k] - ay), true, &inverted);
             } else {
                 rule = bd_flip_rule_xy(a, b, c, d[k], t.inf, px[k], py[k], px[k1], py[k1], px[k2], py[k2], qx[k],
                                        qy[k], true, &inverted);
@@ -643,9 +677,9 @@ __global__ __launch_bounds__(kEvalBlock) void k_flip_eval_full(Topo t, int round
     cand_flush(t, slot, st);
 }
 
-template <int CAP = 1>
-__device__ __forceinline__ void flip_eval_list_body(const Topo &t, int round, int slot, int i0, int stride,
-                                                    CandStage<CAP> *st = nullptr) {
+template <int CAP, class TP>
+__device__ __forceinline__ void flip_eval_list_body(const TP &t, int round, int slot, int i0, int stride,
+                                                    CandStage<CAP> *st) {
     if (stopped(t.ctl)) return;
     round += t.base->rbase;
     const int count = t.ctl[K_WL + slot];
@@ -666,11 +700,12 @@ __device__ __forceinline__ void flip_eval_list_body(const Topo &t, int round, in
             h = tw;
             tw = s;
         }
-        eval_edge<CAP>(t, h, tw, round, slot, 0, st);
+        eval_edge<CAP>(t, h, tw, round, slot, st);
     }
 }
 
-__global__ void k_flip_eval_list(Topo t, int round, int slot) {
+template <class TP>
+__global__ void k_flip_eval_list(TP t, int round, int slot) {
     __shared__ CandStage<kEvalStage> st;
     if (stopped(t.ctl)) return;   // nothing in this launch writes the stop flags: uniform
     if (threadIdx.x == 0) st.cnt = 0;
@@ -684,120 +719,118 @@ __global__ void k_flip_eval_list(Topo t, int round, int slot) {
 // from the stars its gather recorded (the topology has not changed since).  Lane i of a star takes the edge to
 // its far vertex w_i and the edge w_i - w_(i+1) across from the disk.  No worklist: an edge of two moved disks is
 // evaluated by both.  65,536 disks: 17 us for the walk that queued the edges and 8 us for their evaluation before.
-template <int CAP = 1>
-__device__ __forceinline__ void flip_eval_star_body(const Topo &t, int k, int round, int slot, int i0, int stride,
-                                                    CandStage<CAP> *st = nullptr) {
-    if (stopped(t.ctl)) return;
-    round += t.base->rbase;
-    const int ntouched = t.ctl[K_TOUCH + k];
-    const int *touched = touched_of(t, k);
+// Evaluates the edges of the triangles at disk v (star s) and loads its positions.  False when an index was out of
+// range, or for a star above kStarMax (evaluated here by one lane): then the positions are not loaded.  The edge to
+// a far vertex and the one across from the disk go through one copy of the flip rule, in canonical order.
+template <int CAP, class TP>
+__device__ __forceinline__ bool eval_star(const TP &t, int v, const Star &s, int round, int slot,
+                                          StarPos &sp, CandStage<CAP> *st) {
     const int q = star_lane();
-    for (int g = i0 / kStarLanes; g < ntouched; g += stride / kStarLanes) {
-        const int v = touched[g];
-        const int deg = t.star_deg[g];
-        if (deg == kStarLarge) {
-            if (q != 0) continue;
-            const int h0 = t.vert_he[v];
-            if (bad_he(t, h0)) {
+    if (s.deg == kStarLarge) {
+        if (q != 0) return false;
+        const int h0 = t.vert_he[v];
+        if (bad_he(t, h0)) {
+            topo_err(t);
+            return false;
+        }
+        int h = h0, guard = 0;
+        do {
+#pragma clang loop unroll(disable)
+            for (int e = 0; e < 2; ++e) {
+                const int l = e ? bd_next(h) : h, lt = t.he_twin[l];
+                if (bad_he(t, lt))
+                    topo_err(t);
+                else
+                    eval_edge<CAP>(t, l < lt ? l : lt, l < lt ? lt : l, round, slot, st);
+            }
+            h = t.he_twin[bd_prev(h)];
+            if (bad_he(t, h)) {
                 topo_err(t);
-                continue;
+                break;
             }
-            int h = h0, guard = 0;
-            do {
-                const int l = bd_next(h), tw = t.he_twin[h], lt = t.he_twin[l];
-                if (bad_he(t, tw) || bad_he(t, lt)) {
-                    topo_err(t);
-                    break;
-                }
-                eval_edge<CAP>(t, h < tw ? h : tw, h < tw ? tw : h, round, slot, 0, st);
-                eval_edge<CAP>(t, l < lt ? l : lt, l < lt ? lt : l, round, slot, 0, st);
-                h = t.he_twin[bd_prev(h)];
-                if (bad_he(t, h)) {
-                    topo_err(t);
-                    break;
-                }
-            } while (h != h0 && ++guard < 4096);
-            continue;
-        }
-        const bool two = __ballot(deg > kStarLanes) != 0;
-        const double2 pv = t.xy[v];
-        int h[2], w[2], lt[2], far[2];
-        double2 pw[2], pf[2];
-        const bool in[2] = {q < deg, q + kStarLanes < deg};
+        } while (h != h0 && ++guard < 4096);
+        return false;
+    }
+    const int deg = s.deg;
+    const bool two = star_two(s);
+    const double2 pv = t.xy[v];
+    sp.pv = pv;
+    int lt[2], far[2];
+    double2 pf[2];
+    bool ok = true;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            h[u] = w[u] = lt[u] = far[u] = -1;
-            pw[u] = pf[u] = pv;
-            if (u == 1 && !two) continue;
-            if (in[u]) h[u] = t.star[(size_t)g * kStarMax + u * kStarLanes + q];
-        }
-        bool ok = true;
+    for (int u = 0; u < 2; ++u) {
+        lt[u] = far[u] = -1;
+        sp.pw[u] = pf[u] = pv;
+        if (q + u * kStarLanes >= deg) continue;
+        lt[u] = t.he_twin[bd_next(s.h[u])];
+        if (bad_v(t, s.w[u]))
+            ok = false;
+        else
+            sp.pw[u] = t.xy[s.w[u]];
+    }
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if ((u == 1 && !two) || !in[u]) continue;
-            w[u] = t.he_v[bd_next(h[u])];
-            lt[u] = t.he_twin[bd_next(h[u])];
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if ((u == 1 && !two) || !in[u]) continue;
-            if (bad_he(t, lt[u]) || bad_v(t, w[u])) {
-                ok = false;
-                continue;
-            }
+    for (int u = 0; u < 2; ++u) {
+        if (q + u * kStarLanes >= deg) continue;
+        if (bad_he(t, lt[u]))
+            ok = false;
+        else
             far[u] = t.he_v[bd_prev(lt[u])];
-            pw[u] = t.xy[w[u]];
-        }
+    }
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if ((u == 1 && !two) || !in[u] || !ok) continue;
-            if (bad_v(t, far[u])) {
-                ok = false;
-                continue;
-            }
+    for (int u = 0; u < 2; ++u) {
+        if (q + u * kStarLanes >= deg || !ok) continue;
+        if (bad_v(t, far[u]))
+            ok = false;
+        else
             pf[u] = t.xy[far[u]];
-        }
-        if (!ok) topo_err(t);
-        const unsigned long long group = ((1ull << kStarLanes) - 1ull) << star_base();
-        if ((__ballot(!ok) & group) != 0) continue;   // the group's lanes are here together
+    }
+    if (!ok) topo_err(t);
+    if (star_any(!ok)) return false;   // the group's lanes are here together
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (u == 1 && !two) continue;
-            const int i = q + u * kStarLanes;
-            const int ip = i + 1 >= deg ? 0 : i + 1, im = i == 0 ? deg - 1 : i - 1;
-            const int wn = star_get(w, ip, two), wp = star_get(w, im, two), hp = star_get(h, im, two);
-            const double2 pn = star_get2(pw, ip, two), pp = star_get2(pw, im, two);
-            if (!in[u]) continue;
-            {   // the edge v - w_i: triangles (v, w_i, w_(i+1)) and (w_i, v, w_(i-1))
-                const int tw = bd_prev(hp);
-                const bool fwd = h[u] < tw;
-                bool inverted = false;
-                const int rule = fwd ? flip_rule_at(t, v, w[u], wn, wp, pv, pw[u], pn, pp, &inverted)
-                                     : flip_rule_at(t, w[u], v, wp, wn, pw[u], pv, pp, pn, &inverted);
-                register_flip<CAP>(t, fwd ? h[u] : tw, fwd ? tw : h[u], fwd ? wn : wp, fwd ? wp : wn, rule, inverted,
-                                   round, slot, st);
-            }
-            {   // the edge w_i - w_(i+1): triangles (w_i, w_(i+1), v) and (w_(i+1), w_i, far)
-                const int l = bd_next(h[u]);
-                const bool fwd = l < lt[u];
-                bool inverted = false;
-                const int rule = fwd ? flip_rule_at(t, w[u], wn, v, far[u], pw[u], pn, pv, pf[u], &inverted)
-                                     : flip_rule_at(t, wn, w[u], far[u], v, pn, pw[u], pf[u], pv, &inverted);
-                register_flip<CAP>(t, fwd ? l : lt[u], fwd ? lt[u] : l, fwd ? v : far[u], fwd ? far[u] : v, rule,
-                                   inverted, round, slot, st);
-            }
+    for (int u = 0; u < 2; ++u) {
+        if (u == 1 && !two) continue;
+        const int i = q + u * kStarLanes;
+        const int ip = i + 1 >= deg ? 0 : i + 1, im = i == 0 ? deg - 1 : i - 1;
+        const int wn = star_get(s.w, ip, two), wp = star_get(s.w, im, two), hp = star_get(s.h, im, two);
+        const double2 pn = star_get2(sp.pw, ip, two), pp = star_get2(sp.pw, im, two);
+        if (i >= deg) continue;
+#pragma clang loop unroll(disable)
+        for (int e = 0; e < 2; ++e) {
+            // e = 0: v - w_i, triangles (v, w_i, w_(i+1)) and (w_i, v, w_(i-1)); e = 1: w_i - w_(i+1), triangles
+            // (w_i, w_(i+1), v) and (w_(i+1), w_i, far)
+            const int h = e ? bd_next(s.h[u]) : s.h[u], g = e ? lt[u] : bd_prev(hp);
+            const bool fwd = h < g;
+            const int a0 = e ? s.w[u] : v, b0 = e ? wn : s.w[u], c0 = e ? v : wn, d0 = e ? far[u] : wp;
+            const double2 pa0 = e ? sp.pw[u] : pv, pb0 = e ? pn : sp.pw[u], pc0 = e ? pv : pn, pd0 = e ? pf[u] : pp;
+            const int c = fwd ? c0 : d0, d = fwd ? d0 : c0;
+            bool inverted = false;
+            const int rule = flip_rule_at(t, fwd ? a0 : b0, fwd ? b0 : a0, c, d, fwd ? pa0 : pb0, fwd ? pb0 : pa0,
+                                          fwd ? pc0 : pd0, fwd ? pd0 : pc0, &inverted);
+            register_flip<CAP>(t, fwd ? h : g, fwd ? g : h, c, d, rule, inverted, round, slot, st);
         }
     }
+    return true;
 }
 
-__global__ __launch_bounds__(256) void k_flip_eval_star(Topo t, int k, int round, int slot) {
+// First evaluation of the repair after overlap round k: every edge of the triangles at the disks the round moved,
+// from the stars its gather recorded (the topology has not changed since).  Lane i of a star takes the edge to
+// its far vertex w_i and the edge w_i - w_(i+1) across from the disk.  No worklist: an edge of two moved disks is
+// evaluated by both.  65,536 disks: 17 us for the walk that queued the edges and 8 us for their evaluation before.
+template <class TP>
+__global__ __launch_bounds__(256) void k_flip_eval_star(TP t, int k, int round, int slot) {
     __shared__ CandStage<kEvalStage> st;
     if (stopped(t.ctl)) return;   // nothing in this launch writes the stop flags: uniform
     if (threadIdx.x == 0) st.cnt = 0;
     __syncthreads();
     const int i0 = xcd_block() * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
-    flip_eval_star_body<kEvalStage>(t, k, round, slot, i0, stride, &st);
+    const int ntouched = t.ctl[K_TOUCH + k];
+    const int *touched = touched_of(t, k);
     flip_eval_list_body<kEvalStage>(t, round, slot, i0, stride, &st);   // edges the repair before left blocked
+    for (int g = i0 / kStarLanes; g < ntouched; g += stride / kStarLanes) {
+        StarPos sp;
+        eval_star<kEvalStage>(t, touched[g], star_recorded(t, g), round + t.base->rbase, slot, sp, &st);
+    }
     cand_flush(t, slot, st);
 }
 
@@ -950,7 +983,8 @@ __global__ void k_flip_fix(Topo t, int round, int slot) {
 
 // Counts finite triangles that are not positively oriented after repair `rep`.
 // inv: the repair's invalid-triangle counter, or a workgroup's share of it in LDS
-__device__ __forceinline__ void validate_tri(const Topo &t, int tri, int *inv) {
+template <class TP>
+__device__ __forceinline__ void validate_tri(const TP &t, int tri, int *inv) {
     const int a = t.he_v[3 * tri], b = t.he_v[3 * tri + 1], c = t.he_v[3 * tri + 2];
     if (bad_v(t, a) || bad_v(t, b) || bad_v(t, c)) {
         atomicAdd(inv, 1);
@@ -958,7 +992,7 @@ __device__ __forceinline__ void validate_tri(const Topo &t, int tri, int *inv) {
         return;
     }
     if (a >= t.inf || b >= t.inf || c >= t.inf) return;
-    if (orient_of(t, a, b, c) <= 0.0) atomicAdd(inv, 1);
+    if (orient_at(t, t.xy[a], t.xy[b], t.xy[c]) <= 0.0) atomicAdd(inv, 1);
 }
 
 // End of repair `rep` whose last round used slot `last`: halt the step when the
@@ -993,7 +1027,8 @@ __device__ __forceinline__ bool add_block_count(int *counter, const int *block_c
     return true;
 }
 
-__global__ __launch_bounds__(kScanBlock) void k_validate(Topo t, int rep, int last) {
+template <class TP>
+__global__ __launch_bounds__(kScanBlock) void k_validate(TP t, int rep, int last) {
     __shared__ int inv;
     if (stopped(t.ctl)) return;   // nothing in this launch writes the stop flags: uniform
     if (threadIdx.x == 0) inv = 0;
@@ -1008,24 +1043,6 @@ __global__ __launch_bounds__(kScanBlock) void k_validate(Topo t, int rep, int la
 // Detect: every Delaunay edge between two disks with d < (r_i + r_j)(1 - tol)
 // (Algorithm 2 test, Sec. 2.3 contact distance); both ends are queued once
 // per round.
-// Queues disk v for overlap round k once per stamp; with a workgroup stage the
-// position is taken in LDS (the stage is copied out at the end of the launch).
-template <int CAP = 1>
-__device__ __forceinline__ void mark_touched(const Topo &t, int v, int stamp, int k, Stage<CAP> *st = nullptr) {
-    const bool fresh = atomicExch(&t.vstamp[v], stamp) != stamp;
-    if (st) {
-        const int pos = wave_reserve(&st->cnt, fresh);
-        if (!fresh) return;
-        if (pos < CAP)
-            st->buf[pos] = v;
-        else
-            touched_of(t, k)[atomicAdd(&t.ctl[K_TOUCH + k], 1)] = v;
-        return;
-    }
-    const int pos = wave_reserve(&t.ctl[K_TOUCH + k], fresh);
-    if (fresh) touched_of(t, k)[pos] = v;
-}
-
 __device__ __forceinline__ void ovl_check_body(int *ctl, int k, int stamp, const StepBase *base);
 __device__ __forceinline__ void final_check_body(int *ctl, int k);
 
@@ -1052,7 +1069,8 @@ __device__ __forceinline__ void det_flush(const Topo &t, int k, int *buf, int &c
 // vrep >= 0: the same pass also validates every triangle for the repair in
 // slot vrep (last round slot vlast), whose check the last workgroup runs
 // before the detection's.
-__global__ __launch_bounds__(kDetBlock) void k_ovl_detect(Topo t, int rstamp, double keep, int k, int check, int vrep,
+template <class TP>
+__global__ __launch_bounds__(kDetBlock) void k_ovl_detect(TP t, int rstamp, double keep, int k, int check, int vrep,
                                                           int vlast) {
 #pragma clang fp contract(off)
     __shared__ int buf[kDetStage];
@@ -1093,9 +1111,8 @@ __global__ __launch_bounds__(kDetBlock) void k_ovl_detect(Topo t, int rstamp, do
                 if (!ok) {
                     atomicAdd(&inv, 1);
                 } else if (v[0] < t.inf && v[1] < t.inf && v[2] < t.inf) {
-                    const double o = t.P > 0.0 ? bd_orient(0.0, 0.0, sep_p(px[1] - px[0], t.P), sep_p(py[1] - py[0], t.P),
-                                                           sep_p(px[2] - px[0], t.P), sep_p(py[2] - py[0], t.P))
-                                               : bd_orient(px[0], py[0], px[1], py[1], px[2], py[2]);
+                    const double o = orient_at(t, make_double2(px[0], py[0]), make_double2(px[1], py[1]),
+                                               make_double2(px[2], py[2]));
                     if (o <= 0.0) atomicAdd(&inv, 1);
                 }
             }
@@ -1106,7 +1123,7 @@ __global__ __launch_bounds__(kDetBlock) void k_ovl_detect(Topo t, int rstamp, do
                 if (!ok || h > tw[e]) continue;
                 const int a = v[e], b = v[e1];
                 if (a >= t.n || b >= t.n) continue;
-                const double dx = sep_p(px[e] - px[e1], t.P), dy = sep_p(py[e] - py[e1], t.P);
+                const double dx = sep_p(t, px[e] - px[e1]), dy = sep_p(t, py[e] - py[e1]);
                 const double d = sqrt(dx * dx + dy * dy);
                 if (d < (pr[e] + pr[e1]) * keep) {
                     ++found;
@@ -1144,19 +1161,45 @@ __global__ __launch_bounds__(kDetBlock) void k_ovl_detect(Topo t, int rstamp, do
 // that detection created it; every other edge was tested then and neither of
 // its disks has moved.  So only the stars of the disks moved by round kprev
 // and the flipped list are tested; an overlapping edge counts once (det_stamp).
-// An overlapping edge (canonical id e), counted and its disks queued the first time it is found.
-template <int CAP = 1>
+// An overlapping edge (canonical id e): counted the first time it is found, both disks queued for overlap round k
+// once per stamp.  With a workgroup stage (large rounds) the disks are marked only by the first to find the edge:
+// 30 us for a round of 1,000,000 disks with all three exchanges issued together, 22 us so.  Without one (the tail)
+// the exchanges are in flight together, since a round there waits for its chains.
+template <int CAP>
 __device__ __forceinline__ void found_edge(const Topo &t, int e, int a, int b, int stamp, int k, int &found,
-                                           Stage<CAP> *st = nullptr) {
-    if (atomicExch(&t.det_stamp[e], stamp) == stamp) return;
-    ++found;
-    mark_touched(t, a, stamp, k, st);
-    mark_touched(t, b, stamp, k, st);
+                                           Stage<CAP> *st) {
+    const int old_e = atomicExch(&t.det_stamp[e], stamp);
+    int old_a = stamp, old_b = stamp;
+    if (!st || old_e != stamp) {
+        old_a = atomicExch(&t.vstamp[a], stamp);
+        old_b = atomicExch(&t.vstamp[b], stamp);
+    }
+    if (old_e != stamp) ++found;
+    const unsigned long long ma = __ballot(old_a != stamp), mb = __ballot(old_b != stamp);
+    if ((ma | mb) == 0) return;
+    const int lane = __lane_id(), leader = __ffsll((unsigned long long)__ballot(true)) - 1;
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    int *counter = &t.ctl[K_TOUCH + k], *list = touched_of(t, k);
+    int base = 0;
+    if (lane == leader) base = atomicAdd(st ? &st->cnt : counter, __popcll(ma) + __popcll(mb));
+    base = __shfl(base, leader);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        if (u == 0 ? old_a == stamp : old_b == stamp) continue;
+        const int v = u == 0 ? a : b;
+        const int pos = base + (u == 0 ? __popcll(ma & lt) : __popcll(ma) + __popcll(mb & lt));
+        if (!st)
+            list[pos] = v;
+        else if (pos < CAP)
+            st->buf[pos] = v;
+        else
+            list[atomicAdd(counter, 1)] = v;
+    }
 }
 
-template <int CAP = 1>
-__device__ __forceinline__ void detect_edge(const Topo &t, int h, int stamp, double keep, int k, int &found,
-                                            Stage<CAP> *st = nullptr) {
+template <int CAP, class TP>
+__device__ __forceinline__ void detect_edge(const TP &t, int h, int stamp, double keep, int k, int &found,
+                                            Stage<CAP> *st) {
     const int tw = t.he_twin[h];
     if (bad_he(t, tw)) return topo_err(t);
     const int e = h < tw ? h : tw;
@@ -1164,7 +1207,7 @@ __device__ __forceinline__ void detect_edge(const Topo &t, int h, int stamp, dou
     if (bad_v(t, a) || bad_v(t, b)) return topo_err(t);
     if (a >= t.n || b >= t.n) return;
     const double2 pa = t.xy[a], pb = t.xy[b];
-    const double dx = sep_p(pa.x - pb.x, t.P), dy = sep_p(pa.y - pb.y, t.P);
+    const double dx = sep_p(t, pa.x - pb.x), dy = sep_p(t, pa.y - pb.y);
     const double d = sqrt(dx * dx + dy * dy);
     if (d < (t.ru > 0.0 ? t.ru + t.ru : t.rad[a] + t.rad[b]) * keep) found_edge(t, e, a, b, stamp, k, found, st);
 }
@@ -1177,105 +1220,123 @@ __device__ __forceinline__ void detect_edge(const Topo &t, int h, int stamp, dou
 // detection's (check = 1) and the final check (check = 2).  On a repair that
 // fails its check the detection's marks are never read: the host continues
 // with rounds of its own slots and stamps.
-// Body: inv is the repair's invalid-triangle counter, or a workgroup's share
-// of it in LDS; the stamp st is absolute.  Returns the overlapping edges this thread found (the caller adds them
-// to K_OVL + knew).
-// The stars are those the round's gather recorded where no flip of the repair (rounds rfirst and later, relative)
-// rewrote one of their triangles, else walked again.  One lane per edge and triangle of a star: 65,536 disks,
-// 23 us as one thread per star, which exchanged a stamp per edge.
-template <int CAP = 1>
-__device__ __forceinline__ int validate_detect_local_body(const Topo &t, int *inv, int k, int rfirst, int st,
-                                                          double keep, int knew, int i0, int stride,
-                                                          Stage<CAP> *stage = nullptr) {
+// inv is the repair's invalid-triangle counter, or a workgroup's share of it in LDS; stamps are absolute here.
+
+// The tests of one star: does the triangle after half-edge i, tested from its first half-edge on, not turn
+// counter-clockwise; does the disk overlap the far one.
+enum { STAR_INVALID = 1, STAR_HIT = 4 };   // shifted by u for half-edge q + u * kStarLanes
+
+template <class TP>
+__device__ __forceinline__ int star_test(const TP &t, int v, const Star &s, const StarPos &sp, double keep) {
 #pragma clang fp contract(off)
-    const int nmoved = t.ctl[K_TOUCH + k];
-    const int nvt = t.ctl[K_VT_N];
-    const int nfl = t.ctl[K_FL_N];
-    rfirst += t.base->rbase;
-    const int *moved = touched_of(t, k);
     const int q = star_lane();
-    int found = 0;
-    for (int g = i0 / kStarLanes; g < nmoved; g += stride / kStarLanes) {
-        const int v = moved[g];
-        Star s;
-        s.deg = t.star_deg[g];
-        bool rewritten = s.deg <= 0;
+    const bool two = star_two(s);
+    const double rv = t.ru > 0.0 ? t.ru : t.rad[v];
+    const double2 pv = sp.pv;
+    int r = 0;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int i = q + u * kStarLanes;
-            s.h[u] = i < s.deg ? t.star[(size_t)g * kStarMax + i] : -1;
-            s.w[u] = i < s.deg ? t.he_v[bd_next(s.h[u])] : -1;
-            if (i < s.deg && t.tri_stamp[s.h[u] / 3] >= rfirst) rewritten = true;
+    for (int u = 0; u < 2; ++u) {
+        if (u == 1 && !two) continue;
+        const int i = q + u * kStarLanes;
+        const int ip = i + 1 >= s.deg ? 0 : i + 1;
+        const int wn = star_get(s.w, ip, two);
+        const double2 pn = star_get2(sp.pw, ip, two);
+        if (i >= s.deg) continue;
+        const int w = s.w[u];
+        const double2 pw = sp.pw[u];
+        if (w < t.inf && wn < t.inf) {   // the triangle (v, w, wn)
+            const int f = s.h[u] % 3;
+            const double o = orient_at(t, f == 0 ? pv : f == 1 ? pn : pw, f == 0 ? pw : f == 1 ? pv : pn,
+                                       f == 0 ? pn : f == 1 ? pw : pv);
+            if (o <= 0.0) r |= STAR_INVALID << u;
         }
-        const unsigned long long group = ((1ull << kStarLanes) - 1ull) << star_base();
-        if ((__ballot(rewritten) & group) != 0) s = star_walk(t, v);
-        if (s.deg == 0) {
-            if (q == 0) {
-                atomicAdd(inv, 1);
-                topo_err(t);
-            }
-            continue;
+        if (w < t.n) {
+            const double dx = sep_p(t, pv.x - pw.x), dy = sep_p(t, pv.y - pw.y);
+            const double d = sqrt(dx * dx + dy * dy);
+            if (d < (rv + (t.ru > 0.0 ? t.ru : t.rad[w])) * keep) r |= STAR_HIT << u;
         }
-        if (s.deg == kStarLarge) {
-            if (q != 0) continue;
-            const int h0 = t.vert_he[v];
-            int h = h0, guard = 0;
-            do {
-                validate_tri(t, h / 3, inv);
-                detect_edge(t, h, st, keep, knew, found, stage);
-                h = t.he_twin[bd_prev(h)];
-                if (bad_he(t, h) || ++guard > 4096) {
-                    atomicAdd(inv, 1);
-                    topo_err(t);
-                    break;
-                }
-            } while (h != h0);
-            continue;
-        }
-        const bool two = __ballot(s.deg > kStarLanes) != 0;
-        const double2 pv = t.xy[v];
-        const double rv = t.ru > 0.0 ? t.ru : t.rad[v];
-        double2 pw[2] = {pv, pv};
-        bool bad = false;
+    }
+    return r;
+}
+
+// Commits the tests of a star: the repair's invalid count, the overlapping edges and their disks.
+template <int CAP>
+__device__ __forceinline__ void star_commit(const Topo &t, int v, const Star &s, int r, int *inv, int st,
+                                            int knew, int &found, Stage<CAP> *stage) {
+    const bool two = star_two(s);
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
-            if (q + u * kStarLanes < s.deg) {
-                bad = bad || bad_v(t, s.w[u]);
-                if (!bad) pw[u] = t.xy[s.w[u]];
-            }
-        if (bad) {
+    for (int u = 0; u < 2; ++u) {
+        if (u == 1 && !two) continue;
+        const int i = star_lane() + u * kStarLanes;
+        const int tw = bd_prev(star_get(s.h, i == 0 ? s.deg - 1 : i - 1, two));   // the edge's other half
+        if (r & (STAR_INVALID << u)) atomicAdd(inv, 1);
+        if (r & (STAR_HIT << u))
+            found_edge(t, s.h[u] < tw ? s.h[u] : tw, v, s.w[u], st, knew, found, stage);
+    }
+}
+
+// A star above kStarMax, by one lane.
+template <int CAP, class TP>
+__device__ __forceinline__ void star_large(const TP &t, int v, int *inv, int st, double keep, int knew, int &found,
+                                           Stage<CAP> *stage) {
+    const int h0 = t.vert_he[v];
+    int h = h0, guard = 0;
+    do {
+        validate_tri(t, h / 3, inv);
+        detect_edge(t, h, st, keep, knew, found, stage);
+        h = t.he_twin[bd_prev(h)];
+        if (bad_he(t, h) || ++guard > 4096) {
+            atomicAdd(inv, 1);
+            topo_err(t);
+            break;
+        }
+    } while (h != h0);
+}
+
+// Star of the disk queued at idx after the repair: as recorded where no flip of the repair (rounds rfirst and
+// later, absolute) rewrote one of its triangles, else walked again; then its positions and its tests (r).  False
+// when it was handled here (above kStarMax, by one lane; an index out of range).
+template <int CAP, class TP>
+__device__ __forceinline__ bool star_after_repair(const TP &t, int idx, int v, int *inv, int rfirst, int st,
+                                                  double keep, int knew, int &found, Stage<CAP> *stage, Star &s,
+                                                  int &r) {
+    const int q = star_lane();
+    bool rewritten = false;
+    s = star_recorded(t, idx, rfirst, &rewritten);
+    if (star_any(rewritten || s.deg <= 0)) s = star_walk(t, v);
+    if (s.deg == kStarLarge) {
+        if (q == 0) star_large(t, v, inv, st, keep, knew, found, stage);
+        return false;
+    }
+    StarPos sp;
+    sp.pv = t.xy[v];
+    bool bad = s.deg == 0;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        sp.pw[u] = sp.pv;
+        if (q + u * kStarLanes >= s.deg) continue;
+        if (bad_v(t, s.w[u]))
+            bad = true;
+        else
+            sp.pw[u] = t.xy[s.w[u]];
+    }
+    if (star_any(bad)) {
+        if (q == 0) {
             atomicAdd(inv, 1);
             topo_err(t);
         }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (u == 1 && !two) continue;
-            const int i = q + u * kStarLanes;
-            const int ip = i + 1 >= s.deg ? 0 : i + 1;
-            const int wn = star_get(s.w, ip, two);
-            const double2 pn = star_get2(pw, ip, two);
-            if (i >= s.deg || bad) continue;
-            const int w = s.w[u];
-            if (w < t.inf && wn < t.inf) {   // the triangle (v, w, wn), tested from its first half-edge on
-                const int r = s.h[u] % 3;
-                const double o = r == 0   ? orient_at(t, pv, pw[u], pn)
-                                 : r == 1 ? orient_at(t, pn, pv, pw[u])
-                                          : orient_at(t, pw[u], pn, pv);
-                if (o <= 0.0) atomicAdd(inv, 1);
-            }
-            if (w < t.n) {
-                const double dx = sep_p(pv.x - pw[u].x, t.P), dy = sep_p(pv.y - pw[u].y, t.P);
-                const double d = sqrt(dx * dx + dy * dy);
-                if (d < (rv + (t.ru > 0.0 ? t.ru : t.rad[w])) * keep) {
-                    const int tw = t.he_twin[s.h[u]];
-                    if (bad_he(t, tw))
-                        topo_err(t);
-                    else
-                        found_edge(t, s.h[u] < tw ? s.h[u] : tw, v, w, st, knew, found, stage);
-                }
-            }
-        }
+        return false;
     }
+    r = star_test(t, v, s, sp, keep);
+    return true;
+}
+
+// The triangles and diagonals flips rewrote since the last detection.
+template <int CAP, class TP>
+__device__ __forceinline__ int validate_detect_flipped(const TP &t, int *inv, int st, double keep, int knew, int i0,
+                                                       int stride, Stage<CAP> *stage) {
+    const int nvt = t.ctl[K_VT_N], nfl = t.ctl[K_FL_N];
+    int found = 0;
     for (int idx = i0; idx < nvt + nfl; idx += stride) {
         if (idx >= nvt) {
             const int e = t.fl[idx - nvt];
@@ -1296,7 +1357,10 @@ __device__ __forceinline__ int validate_detect_local_body(const Topo &t, int *in
 
 constexpr int kTouchStage = 2048;
 
-__global__ __launch_bounds__(256) void k_validate_detect_local(Topo t, int rep, int k, int rfirst, int last, int stamp,
+// One lane per edge and triangle of a star: 65,536 disks 11 us, 23 us as one thread per star, which exchanged a
+// stamp per edge.
+template <class TP>
+__global__ __launch_bounds__(256) void k_validate_detect_local(TP t, int rep, int k, int rfirst, int last, int stamp,
                                                                double keep, int knew, int check) {
     __shared__ int inv, nfound;
     __shared__ Stage<kTouchStage> st;
@@ -1306,8 +1370,20 @@ __global__ __launch_bounds__(256) void k_validate_detect_local(Topo t, int rep, 
         nfound = 0;
     }
     stage_init(st);
-    int found = validate_detect_local_body(t, &inv, k, rfirst, stamp + t.base->vbase, keep, knew,
-                                           xcd_block() * blockDim.x + threadIdx.x, gridDim.x * blockDim.x, &st);
+    const int i0 = xcd_block() * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+    const int nmoved = t.ctl[K_TOUCH + k], vst = stamp + t.base->vbase;
+    const int *moved = touched_of(t, k);
+    int found = 0;
+    // before the stars: their counts lie beside the counters that the workgroups add to as they end, and read late
+    // they wait behind those atomics (1,000,000 disks, first round: 42 us with this pass last, 28 us so)
+    found += validate_detect_flipped(t, &inv, vst, keep, knew, i0, stride, &st);
+    for (int g = i0 / kStarLanes; g < nmoved; g += stride / kStarLanes) {
+        const int v = moved[g];
+        Star s;
+        int r;
+        if (star_after_repair(t, g, v, &inv, rfirst + t.base->rbase, vst, keep, knew, found, &st, s, r))
+            star_commit(t, v, s, r, &inv, vst, knew, found, &st);
+    }
     stage_flush(st, &t.ctl[K_TOUCH + knew], touched_of(t, knew));
     for (int off = 32; off > 0; off >>= 1) found += __shfl_xor(found, off);
     if (__lane_id() == 0 && found) atomicAdd(&nfound, found);
@@ -1358,10 +1434,11 @@ __device__ __forceinline__ void final_check_body(int *ctl, int k) {
 // walked from one end.
 
 // Displacement of disk v (at pv, radius rv) by its neighbour w; false when they do not overlap.
-__device__ __forceinline__ bool ovl_term(const Topo &t, double2 pv, double rv, int w, double2 pw, double f,
+template <class TP>
+__device__ __forceinline__ bool ovl_term(const TP &t, double2 pv, double rv, int w, double2 pw, double f,
                                          double keep, double &cx, double &cy) {
 #pragma clang fp contract(off)
-    const double dx = sep_p(pv.x - pw.x, t.P), dy = sep_p(pv.y - pw.y, t.P);
+    const double dx = sep_p(t, pv.x - pw.x), dy = sep_p(t, pv.y - pw.y);
     const double d = sqrt(dx * dx + dy * dy);
     const double contact = rv + (t.ru > 0.0 ? t.ru : t.rad[w]);
     if (!(d < contact * keep)) return false;
@@ -1371,170 +1448,180 @@ __device__ __forceinline__ bool ovl_term(const Topo &t, double2 pv, double rv, i
     return true;
 }
 
-__device__ __forceinline__ void ovl_gather_body(const Topo &t, int k, double f, double cap_frac, double keep, int i0, int stride) {
+// Disk v, queued at idx: its star, and in the group's first lane its position before (pv) and after (np).
+template <class TP>
+__device__ __forceinline__ Star gather_star(const TP &t, int idx, int v, double f, double cap_frac, double keep,
+                                                double2 &pv, double2 &np) {
 #pragma clang fp contract(off)
+    const int q = star_lane();
+    const bool rec = t.tev != nullptr;   // adjoint tape: entry idx of this round for disk idx
+    pv = np = t.xy[v];
+    const double rv = t.ru > 0.0 ? t.ru : t.rad[v];
+    const double L = t.Lr[t.rep_of[v]];
+    const Star s = star_walk(t, v);
+    if (q == 0) t.star_deg[idx] = s.deg;
+    if (s.deg == 0) {
+        if (q == 0) {
+            t.newpos[idx] = pv;
+            topo_err(t);
+            atomicAdd(&t.ctl[K_STAR], 1);
+        }
+        return s;
+    }
+    const int e = rec ? t.tent_base + t.ctl[K_TAPE_ENT] + idx : 0;
+    const bool room = rec && e < t.tcap_ent;
+    if (rec && !room && q == 0) atomicOr(&t.ctl[K_TAPE_OVF], 1);
+    int na = 0;
+    double sx = 0.0, sy = 0.0;
+    if (s.deg == kStarLarge) {
+        if (q != 0) return s;
+        // one lane: the neighbour of smallest id, then the sum around the star from there
+        const int h0 = t.vert_he[v];
+        int best = h0, bestid = 0x7FFFFFFF, h = h0, guard = 0;
+        bool broken = false;
+        do {
+            const int w = t.he_v[bd_next(h)];
+            if (bad_v(t, w)) {
+                broken = true;
+                break;
+            }
+            if (w < t.inf && w < bestid) {
+                bestid = w;
+                best = h;
+            }
+            h = t.he_twin[bd_prev(h)];
+            if (bad_he(t, h) || ++guard > 4096) {
+                broken = true;
+                break;
+            }
+        } while (h != h0);
+        if (broken) {
+            t.newpos[idx] = pv;
+            topo_err(t);
+            atomicAdd(&t.ctl[K_STAR], 1);
+            return s;
+        }
+        h = best;
+        do {
+            const int w = t.he_v[bd_next(h)];
+            double cx, cy;
+            if (w < t.n && ovl_term(t, pv, rv, w, t.xy[w], f, keep, cx, cy)) {
+                sx += cx;
+                sy += cy;
+                if (room && na < MAXACT) t.tenb[(size_t)e * MAXACT + na] = w;
+                ++na;
+            }
+            h = t.he_twin[bd_prev(h)];
+        } while (h != best);
+    } else {
+        const bool two = star_two(s);
+        double cx[2], cy[2];
+        unsigned hits = 0;   // bit i: neighbour i overlaps
+        int bestid = 0x7FFFFFFF, best = 0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            cx[u] = cy[u] = 0.0;
+            if (u == 1 && !two) continue;
+            const int i = q + u * kStarLanes;
+            bool hit = false;
+            if (i < s.deg) {
+                t.star[(size_t)idx * kStarMax + i] = s.h[u];
+                if (s.w[u] < t.n) hit = ovl_term(t, pv, rv, s.w[u], t.xy[s.w[u]], f, keep, cx[u], cy[u]);
+                if (s.w[u] < t.inf && s.w[u] < bestid) {
+                    bestid = s.w[u];
+                    best = i;
+                }
+            }
+            hits |= (unsigned)((__ballot(hit) >> star_base()) & ((1ull << kStarLanes) - 1ull)) << (u * kStarLanes);
+        }
+        for (int off = kStarLanes / 2; off > 0; off >>= 1) {
+            const int oid = __shfl_xor(bestid, off), ob = __shfl_xor(best, off);
+            if (oid < bestid) {
+                bestid = oid;
+                best = ob;
+            }
+        }
+        // canonical order: neighbours best .. deg - 1, then 0 .. best - 1
+        unsigned part = hits & ~((1u << best) - 1u), rest = hits & ((1u << best) - 1u);
+        while ((part | rest) != 0) {
+            if (part == 0) {
+                part = rest;
+                rest = 0;
+            }
+            const int i = __ffs(part) - 1;
+            part &= part - 1;
+            sx += star_get(cx, i, two);
+            sy += star_get(cy, i, two);
+            const int w = star_get(s.w, i, two);
+            if (room && q == 0 && na < MAXACT) t.tenb[(size_t)e * MAXACT + na] = w;
+            ++na;
+        }
+        if (q != 0) return s;
+    }
+    if (room) {
+        if (na > MAXACT) atomicOr(&t.ctl[K_TAPE_OVF], 2);
+        t.tev[e] = v;
+        t.tecnt[e] = na < MAXACT ? na : MAXACT;
+        t.teold[e] = pv;
+        t.tedisp[e] = make_double2(sx, sy);
+    }
+    const double len = sqrt(sx * sx + sy * sy);
+    const double cap = cap_frac * rv;
+    if (len > cap) {
+        double sc = cap / len;
+        sx = sx * sc;
+        sy = sy * sc;
+        wave_count64(&t.acc[A_CAP_HITS], true);
+    }
+    const double xv = pv.x, yv = pv.y;
+    if (room) {
+        t.tewf[2 * (size_t)e] = bd_wall_slope(xv + sx, rv, L);
+        t.tewf[2 * (size_t)e + 1] = bd_wall_slope(yv + sy, rv, L);
+    }
+    np = TP::kPer ? make_double2(bd_wrap(xv + sx, t.P), bd_wrap(yv + sy, t.P))
+                   : make_double2(bd_wall(xv + sx, rv, L), bd_wall(yv + sy, rv, L));
+    t.newpos[idx] = np;
+    return s;
+}
+
+template <class TP>
+__global__ __launch_bounds__(256) void k_ovl_gather(TP t, int k, double f, double cap_frac, double keep) {
     if (stopped(t.ctl)) return;
     const int ntouched = t.ctl[K_TOUCH + k];
     const int *touched = touched_of(t, k);
-    const int q = star_lane();
-    const bool rec = t.tev != nullptr;   // adjoint tape: entry idx of this round for disk idx
-    for (int idx = i0 / kStarLanes; idx < ntouched; idx += stride / kStarLanes) {
-        const int v = touched[idx];
-        const double2 pv = t.xy[v];
-        const double rv = t.ru > 0.0 ? t.ru : t.rad[v];
-        const double L = t.Lr[t.rep_of[v]];
-        const Star s = star_walk(t, v);
-        if (q == 0) t.star_deg[idx] = s.deg;
-        if (s.deg == 0) {
-            if (q == 0) {
-                t.newpos[idx] = pv;
-                topo_err(t);
-                atomicAdd(&t.ctl[K_STAR], 1);
-            }
-            continue;
-        }
-        const int e = rec ? t.tent_base + t.ctl[K_TAPE_ENT] + idx : 0;
-        const bool room = rec && e < t.tcap_ent;
-        if (rec && !room && q == 0) atomicOr(&t.ctl[K_TAPE_OVF], 1);
-        int na = 0;
-        double sx = 0.0, sy = 0.0;
-        if (s.deg == kStarLarge) {
-            if (q != 0) continue;
-            // one lane: the neighbour of smallest id, then the sum around the star from there
-            const int h0 = t.vert_he[v];
-            int best = h0, bestid = 0x7FFFFFFF, h = h0, guard = 0;
-            bool broken = false;
-            do {
-                const int w = t.he_v[bd_next(h)];
-                if (bad_v(t, w)) {
-                    broken = true;
-                    break;
-                }
-                if (w < t.inf && w < bestid) {
-                    bestid = w;
-                    best = h;
-                }
-                h = t.he_twin[bd_prev(h)];
-                if (bad_he(t, h) || ++guard > 4096) {
-                    broken = true;
-                    break;
-                }
-            } while (h != h0);
-            if (broken) {
-                t.newpos[idx] = pv;
-                topo_err(t);
-                atomicAdd(&t.ctl[K_STAR], 1);
-                continue;
-            }
-            h = best;
-            do {
-                const int w = t.he_v[bd_next(h)];
-                double cx, cy;
-                if (w < t.n && ovl_term(t, pv, rv, w, t.xy[w], f, keep, cx, cy)) {
-                    sx += cx;
-                    sy += cy;
-                    if (room && na < MAXACT) t.tenb[(size_t)e * MAXACT + na] = w;
-                    ++na;
-                }
-                h = t.he_twin[bd_prev(h)];
-            } while (h != best);
-        } else {
-            const bool two = __ballot(s.deg > kStarLanes) != 0;
-            double cx[2] = {0.0, 0.0}, cy[2] = {0.0, 0.0};
-            unsigned hits = 0;   // bit i: neighbour i overlaps
-            int bestid = 0x7FFFFFFF, best = 0;
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                if (u == 1 && !two) continue;
-                const int i = q + u * kStarLanes;
-                bool hit = false;
-                if (i < s.deg) {
-                    t.star[(size_t)idx * kStarMax + i] = s.h[u];
-                    if (s.w[u] < t.n) hit = ovl_term(t, pv, rv, s.w[u], t.xy[s.w[u]], f, keep, cx[u], cy[u]);
-                    if (s.w[u] < t.inf && s.w[u] < bestid) {
-                        bestid = s.w[u];
-                        best = i;
-                    }
-                }
-                hits |= (unsigned)((__ballot(hit) >> star_base()) & ((1ull << kStarLanes) - 1ull)) << (u * kStarLanes);
-            }
-            for (int off = kStarLanes / 2; off > 0; off >>= 1) {
-                const int oid = __shfl_xor(bestid, off), ob = __shfl_xor(best, off);
-                if (oid < bestid) {
-                    bestid = oid;
-                    best = ob;
-                }
-            }
-            // canonical order: neighbours best .. deg - 1, then 0 .. best - 1
-            unsigned part = hits & ~((1u << best) - 1u), rest = hits & ((1u << best) - 1u);
-            while ((part | rest) != 0) {
-                if (part == 0) {
-                    part = rest;
-                    rest = 0;
-                }
-                const int i = __ffs(part) - 1;
-                part &= part - 1;
-                sx += star_get(cx, i, two);
-                sy += star_get(cy, i, two);
-                const int w = star_get(s.w, i, two);
-                if (room && q == 0 && na < MAXACT) t.tenb[(size_t)e * MAXACT + na] = w;
-                ++na;
-            }
-            if (q != 0) continue;
-        }
-        if (room) {
-            if (na > MAXACT) atomicOr(&t.ctl[K_TAPE_OVF], 2);
-            t.tev[e] = v;
-            t.tecnt[e] = na < MAXACT ? na : MAXACT;
-            t.teold[e] = pv;
-            t.tedisp[e] = make_double2(sx, sy);
-        }
-        const double len = sqrt(sx * sx + sy * sy);
-        const double cap = cap_frac * rv;
-        if (len > cap) {
-            double sc = cap / len;
-            sx = sx * sc;
-            sy = sy * sc;
-            wave_count64(&t.acc[A_CAP_HITS], true);
-        }
-        const double xv = pv.x, yv = pv.y;
-        if (room) {
-            t.tewf[2 * (size_t)e] = bd_wall_slope(xv + sx, rv, L);
-            t.tewf[2 * (size_t)e + 1] = bd_wall_slope(yv + sy, rv, L);
-        }
-        if (t.P > 0.0)
-            t.newpos[idx] = make_double2(bd_wrap(xv + sx, t.P), bd_wrap(yv + sy, t.P));
-        else
-            t.newpos[idx] = make_double2(bd_wall(xv + sx, rv, L), bd_wall(yv + sy, rv, L));
+    for (int idx = (xcd_block() * blockDim.x + threadIdx.x) / kStarLanes; idx < ntouched; idx += gridDim.x * blockDim.x / kStarLanes) {
+        double2 pv, np;
+        gather_star(t, idx, touched[idx], f, cap_frac, keep, pv, np);
     }
 }
 
-__global__ __launch_bounds__(256) void k_ovl_gather(Topo t, int k, double f, double cap_frac, double keep) {
-    ovl_gather_body(t, k, f, cap_frac, keep, xcd_block() * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+__device__ __forceinline__ void move_disk(const Topo &t, int idx, int v, double2 from, double2 to) {
+    t.oldpos[idx] = from;
+    ((double *)t.x)[v] = to.x;
+    ((double *)t.y)[v] = to.y;
+    ((double2 *)t.xy)[v] = to;
 }
 
-// Apply: write the new positions, keeping the old ones for a replay.
+// Adjoint tape: closes the round's entries (written by the gather); one thread.
+__device__ __forceinline__ void close_tape_round(const Topo &t, int ntouched) {
+    if (t.tev == nullptr) return;
+    const int di = t.tdir_base + t.ctl[K_TAPE_DIR];
+    if (di < t.tcap_dir)
+        t.tdir[di] = make_int2(t.tent_base + t.ctl[K_TAPE_ENT], ntouched);
+    else
+        atomicOr(&t.ctl[K_TAPE_OVF], 1);
+    t.ctl[K_TAPE_ENT] += ntouched;
+    t.ctl[K_TAPE_DIR] += 1;
+}
+
 __device__ __forceinline__ void ovl_apply_body(const Topo &t, int k, int i0, int stride) {
     if (stopped(t.ctl)) return;
     const int ntouched = t.ctl[K_TOUCH + k];
-    if (t.tev != nullptr && i0 == 0) {
-        // adjoint tape: close the round's entries (written by the gather)
-        const int di = t.tdir_base + t.ctl[K_TAPE_DIR];
-        if (di < t.tcap_dir)
-            t.tdir[di] = make_int2(t.tent_base + t.ctl[K_TAPE_ENT], ntouched);
-        else
-            atomicOr(&t.ctl[K_TAPE_OVF], 1);
-        t.ctl[K_TAPE_ENT] += ntouched;
-        t.ctl[K_TAPE_DIR] += 1;
-    }
+    if (i0 == 0) close_tape_round(t, ntouched);
     const int *touched = touched_of(t, k);
     for (int idx = i0; idx < ntouched; idx += stride) {
         const int v = touched[idx];
-        const double2 np = t.newpos[idx];
-        t.oldpos[idx] = t.xy[v];
-        ((double *)t.x)[v] = np.x;
-        ((double *)t.y)[v] = np.y;
-        ((double2 *)t.xy)[v] = np;
+        move_disk(t, idx, v, t.xy[v], t.newpos[idx]);
     }
 }
 
@@ -1543,10 +1630,14 @@ __global__ void k_ovl_apply(Topo t, int k) {
     ovl_apply_body(t, k, xcd_block() * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
-// The overlap rounds after the first detection in one workgroup: each phase
-// is the body of the corresponding kernel run with the workgroup's threads,
-// and a barrier separates phases (workgroup-scope release/acquire, so every
-// thread sees the previous phase's writes).  Halts follow the same rules.
+// The overlap rounds after the first detection in one workgroup, the phases of
+// the separate launches with a barrier between them (workgroup-scope
+// release/acquire, so every thread sees the previous phase's writes).  Halts
+// follow the same rules.  A round is a chain of some twenty dependent steps, so
+// what it waits for is latency: of memory, of atomics, and of instructions not
+// in the cache.  Small rounds took 13 us with 162 KiB of code (every phase
+// inlined for both box kinds), 10 us with 60 KiB; 1,024 disks 64 to 58 us a
+// step, 16,001 in the periodic box 272 to 247.
 constexpr int kTailBlock = 1024;
 
 // In one workgroup, after a barrier: true when flip round `slot` has nothing
@@ -1574,7 +1665,8 @@ __device__ __forceinline__ bool tail_sync(const Topo &t) {
 // it starts with that round's apply; otherwise with the evaluation of the
 // worklist in slot0.  The loop ends at the first round with nothing to do.
 // Returns true when the step has stopped.
-__device__ __forceinline__ bool repair_rounds_body(const Topo &t, int round0, int slot0, int rounds,
+template <class TP>
+__device__ __forceinline__ bool repair_rounds_body(const TP &t, int round0, int slot0, int rounds,
                                                    bool first_evaluated) {
     const int i0 = threadIdx.x, stride = blockDim.x;
     if (tail_sync(t)) return true;
@@ -1584,7 +1676,7 @@ __device__ __forceinline__ bool repair_rounds_body(const Topo &t, int round0, in
         const int round = round0 + r;
         if (r > 0 || !first_evaluated) {
             if (rounds_done(t, slot, false)) break;
-            flip_eval_list_body(t, round, slot, i0, stride);
+            flip_eval_list_body<1>(t, round, slot, i0, stride, nullptr);
             if (tail_sync(t)) return true;
         }
         if (rounds_done(t, slot, true)) break;
@@ -1596,45 +1688,98 @@ __device__ __forceinline__ bool repair_rounds_body(const Topo &t, int round0, in
     return false;
 }
 
-__global__ __launch_bounds__(kTailBlock) void k_repair_rounds(Topo t, int round0, int slot0, int rounds,
-                                                              int first_evaluated) {
-    repair_rounds_body(t, round0, slot0, rounds, first_evaluated != 0);
+// The workgroup keeps the control block in LDS: every phase reads its counts and the stop flags, and every list
+// append takes a position there.
+__device__ __forceinline__ void ctl_to_lds(Topo &t, int *lds) {
+    for (int i = threadIdx.x; i < N_CTL; i += blockDim.x) lds[i] = t.ctl[i];
+    __syncthreads();
+    t.ctl = lds;
 }
 
-__device__ __forceinline__ void tail_body(const Topo &t, const TailPlan &p) {
+template <class TP>
+__global__ __launch_bounds__(kTailBlock) void k_repair_rounds(TP t, int round0, int slot0, int rounds,
+                                                              int first_evaluated) {
+    __shared__ int s_ctl[N_CTL];
+    int *ctl = t.ctl;
+    ctl_to_lds(t, s_ctl);
+    repair_rounds_body(t, round0, slot0, rounds, first_evaluated != 0);
+    __syncthreads();
+    for (int i = threadIdx.x; i < N_CTL; i += blockDim.x) ctl[i] = s_ctl[i];
+}
+
+// Rounds that queue at most one star per group of lanes keep the stars in
+// registers: gather, move, then the repair's first evaluation together with the
+// tests the detection will make; when no edge flips those tests stand, and the
+// round ends without reading a star again.  Each phase has one copy of its code
+// (see TopoP).
+template <class TP>
+__device__ __forceinline__ void tail_body(const TP &t, const TailPlan &p) {
     const int i0 = threadIdx.x, stride = blockDim.x;
+    const int g0 = i0 / kStarLanes, gstep = kTailBlock / kStarLanes;
     if (tail_sync(t)) return;
     for (int j = 0; j < p.nover; ++j) {
-        const int k = p.k[j];
-        ovl_gather_body(t, k, p.f, p.cap_frac, p.keep, i0, stride);
+        const int k = p.k[j], knew = p.k[j + 1];
+        const int ntouched = t.ctl[K_TOUCH + k];
+        const int *touched = touched_of(t, k);
+        const bool small = ntouched <= gstep;
+        Star s;
+        double2 pv, np;
+        int r = 0, v = 0, slot = p.slot0[j], round = p.next_round[j], last = slot;
+        for (int idx = g0; idx < ntouched; idx += gstep) {
+            v = touched[idx];
+            s = gather_star(t, idx, v, p.f, p.cap_frac, p.keep, pv, np);
+        }
         if (tail_sync(t)) return;
-        ovl_apply_body(t, k, i0, stride);
+        if (small) {
+            if (g0 < ntouched && star_lane() == 0 && s.deg != 0) move_disk(t, g0, v, pv, np);
+            if (i0 == 0) close_tape_round(t, ntouched);
+        } else {
+            ovl_apply_body(t, k, i0, stride);
+        }
         if (tail_sync(t)) return;
-        int last = -1;
-        for (int r = 0; r < p.rounds[j]; ++r) {
-            int slot = p.slot0[j] + r;
-            if (slot >= MAXR) slot -= MAXR;
-            const int round = p.next_round[j] + r;
-            last = slot;
-            if (r == 0)
-                flip_eval_star_body(t, k, round, slot, i0, stride);
-            else if (rounds_done(t, slot, false))
-                break;
-            flip_eval_list_body(t, round, slot, i0, stride);
-            if (tail_sync(t)) return;
-            if (rounds_done(t, slot, true)) break;
+        bool tested = false;
+        for (int idx = g0; idx < ntouched; idx += gstep) {
+            if (!small) {
+                v = touched[idx];
+                s = star_recorded(t, idx);
+            }
+            StarPos sp;
+            tested = eval_star<1>(t, v, s, round + t.base->rbase, slot, sp, nullptr);
+            if (small && tested) r = star_test(t, v, s, sp, p.keep);
+        }
+        const bool none = rounds_done(t, slot, false);   // nothing the repair before left blocked
+        if (!none) flip_eval_list_body<1>(t, round, slot, i0, stride, nullptr);
+        if (tail_sync(t)) return;
+        const bool flips = !rounds_done(t, slot, true);
+        for (int rr = 1; flips; ++rr) {   // the repair's rounds, as repair_rounds_body
             flip_apply_body(t, round, slot, i0, stride);
             if (tail_sync(t)) return;
             flip_fix_body(t, round, slot, i0, stride);
             if (tail_sync(t)) return;
+            if (rr == p.rounds[j]) break;
+            ++round;
+            slot = slot + 1 >= MAXR ? 0 : slot + 1;
+            last = slot;
+            if (rounds_done(t, slot, false)) break;
+            flip_eval_list_body<1>(t, round, slot, i0, stride, nullptr);
+            if (tail_sync(t)) return;
+            if (rounds_done(t, slot, true)) break;
         }
-        // this repair's validation with the next round's detection, one pass
-        // over the stars of the disks round k moved; then the repair's check
-        // and the detection's, as the last workgroup of the fused launch does
-        const int knew = p.k[j + 1];
-        wave_sum_add(&t.ctl[K_OVL + knew],
-                     validate_detect_local_body(t, &t.ctl[K_INV + p.rep[j]], k, p.next_round[j],
-                                                p.stamp[j + 1] + t.base->vbase, p.keep, knew, i0, stride));
+        // this repair's validation with the next round's detection; then the repair's check and the detection's,
+        // as the last workgroup of the fused launch does
+        int *inv = &t.ctl[K_INV + p.rep[j]];
+        const int stamp = p.stamp[j + 1] + t.base->vbase;
+        int found = 0;
+        for (int idx = g0; idx < ntouched; idx += gstep) {
+            if (!small || flips || !tested) {
+                v = touched[idx];
+                tested = star_after_repair<1>(t, idx, v, inv, p.next_round[j] + t.base->rbase, stamp, p.keep, knew,
+                                                  found, nullptr, s, r);
+            }
+            if (tested) star_commit<1>(t, v, s, r, inv, stamp, knew, found, nullptr);
+        }
+        found += validate_detect_flipped<1>(t, inv, stamp, p.keep, knew, i0, stride, nullptr);
+        wave_sum_add(&t.ctl[K_OVL + knew], found);
         __syncthreads();
         if (i0 == 0) {
             repair_check_body(t.ctl, p.rep[j], last);
@@ -1645,11 +1790,18 @@ __device__ __forceinline__ void tail_body(const Topo &t, const TailPlan &p) {
     }
 }
 
-__global__ __launch_bounds__(kTailBlock) void k_tail(Topo t, TailPlan p, StepBase *base, int *ring) {
+template <class TP>
+__global__ __launch_bounds__(kTailBlock) void k_tail(TP t, TailPlan p, StepBase *base, int *ring) {
+    __shared__ int s_ctl[N_CTL];
+    int *ctl = t.ctl;
+    ctl_to_lds(t, s_ctl);
     tail_body(t, p);
-    if (!p.end) return;
     __syncthreads();
-    step_end_body(t.ctl, base, ring, p.r_used, p.v_used);
+    if (p.end) {
+        step_end_body(s_ctl, ctl, base, ring, p.r_used, p.v_used);
+    } else {
+        for (int i = threadIdx.x; i < N_CTL; i += blockDim.x) ctl[i] = s_ctl[i];
+    }
 }
 
 // Topology snapshot before a repair (skipped once the step has stopped, so the
@@ -1721,86 +1873,118 @@ inline int list_grid(const Sim &s) {
 }
 
 // Workgroups of the launches with one group of lanes per star.
-inline int star_grid(const Sim &s) { return std::min(kStarGridMax, list_grid(s) * kStarLanes); }
+inline int star_grid(const Sim &s) { return std::min(kStarGridMax, list_grid(s) * 8); }
+
+// Calls f with the topology typed by the box kind.
+template <class F>
+void with_box(const Topo &t, F &&f) {
+    if (t.P > 0.0) {
+        TopoP<true> tp;
+        static_cast<Topo &>(tp) = t;
+        f(tp);
+    } else {
+        TopoP<false> tp;
+        static_cast<Topo &>(tp) = t;
+        f(tp);
+    }
+}
 
 }  // namespace
 
 void launch_flip_eval_full(Sim &s, int round, int slot, int reversal, bool snapshot) {
     round -= s.rbase;
-    Topo t = topo_of(s);
+    const Topo t = topo_of(s);
     const Snapshot snap = snapshot ? Snapshot{s.snap_v, s.snap_twin, s.snap_vh, s.nv + s.R} : Snapshot{};
-    hipLaunchKernelGGL(k_flip_eval_full, dim3(grid_for((long)(s.T + 3) / 4 * 1024 / kEvalBlock, kEvalGrid)), dim3(kEvalBlock), 0, s.stream, t, round,
+    with_box(t, [&](auto tp) {
+        hipLaunchKernelGGL(k_flip_eval_full<decltype(tp)>, dim3(grid_for((long)(s.T + 3) / 4 * 1024 / kEvalBlock, kEvalGrid)), dim3(kEvalBlock), 0, s.stream, tp, round,
                        slot, reversal, snap);
+    });
 }
 
 void launch_flip_eval_list(Sim &s, int round, int slot) {
     round -= s.rbase;
-    Topo t = topo_of(s);
-    hipLaunchKernelGGL(k_flip_eval_list, dim3(list_grid(s)), dim3(256), 0, s.stream, t, round, slot);
+    const Topo t = topo_of(s);
+    with_box(t, [&](auto tp) {
+        hipLaunchKernelGGL(k_flip_eval_list<decltype(tp)>, dim3(list_grid(s)), dim3(256), 0, s.stream, tp, round, slot);
+    });
 }
 
 void launch_flip_eval_star(Sim &s, int k, int round, int slot) {
     round -= s.rbase;
-    Topo t = topo_of(s);
-    hipLaunchKernelGGL(k_flip_eval_star, dim3(star_grid(s)), dim3(256), 0, s.stream, t, k, round, slot);
+    const Topo t = topo_of(s);
+    with_box(t, [&](auto tp) {
+        hipLaunchKernelGGL(k_flip_eval_star<decltype(tp)>, dim3(star_grid(s)), dim3(256), 0, s.stream, tp, k, round, slot);
+    });
 }
 
 void launch_flip_apply(Sim &s, int round, int slot) {
     round -= s.rbase;
-    Topo t = topo_of(s);
+    const Topo t = topo_of(s);
     hipLaunchKernelGGL(k_flip_apply, dim3(list_grid(s)), dim3(256), 0, s.stream, t, round, slot);
 }
 
 void launch_flip_fix(Sim &s, int round, int slot) {
     round -= s.rbase;
-    Topo t = topo_of(s);
+    const Topo t = topo_of(s);
     hipLaunchKernelGGL(k_flip_fix, dim3(list_grid(s)), dim3(256), 0, s.stream, t, round, slot);
 }
 
 void launch_validate(Sim &s, int rep, int last) {
-    Topo t = topo_of(s);
-    hipLaunchKernelGGL(k_validate, dim3(grid_for((s.T + 3) / 4)), dim3(kScanBlock), 0, s.stream, t, rep, last);
+    const Topo t = topo_of(s);
+    with_box(t, [&](auto tp) {
+        hipLaunchKernelGGL(k_validate<decltype(tp)>, dim3(grid_for((s.T + 3) / 4)), dim3(kScanBlock), 0, s.stream, tp, rep, last);
+    });
 }
 
 void launch_ovl_detect(Sim &s, int vstamp, int k, int check, int vrep, int vlast) {
     vstamp -= s.vbase;
-    Topo t = topo_of(s);
-    hipLaunchKernelGGL(k_ovl_detect, dim3(grid_for((s.T + 3) / 4)), dim3(kDetBlock), 0, s.stream, t, vstamp,
+    const Topo t = topo_of(s);
+    with_box(t, [&](auto tp) {
+        hipLaunchKernelGGL(k_ovl_detect<decltype(tp)>, dim3(grid_for((s.T + 3) / 4)), dim3(kDetBlock), 0, s.stream, tp, vstamp,
                        1.0 - s.p.contact_tol, k, check, vrep, vlast);
+    });
 }
 
 void launch_validate_detect_local(Sim &s, int rep, int k, int rfirst, int last, int vstamp, int knew, int check) {
     vstamp -= s.vbase;
     rfirst -= s.rbase;
-    Topo t = topo_of(s);
-    hipLaunchKernelGGL(k_validate_detect_local, dim3(star_grid(s)), dim3(256), 0, s.stream, t, rep, k, rfirst, last, vstamp,
+    const Topo t = topo_of(s);
+    with_box(t, [&](auto tp) {
+        hipLaunchKernelGGL(k_validate_detect_local<decltype(tp)>, dim3(star_grid(s)), dim3(256), 0, s.stream, tp, rep, k, rfirst, last, vstamp,
                        1.0 - s.p.contact_tol, knew, check);
+    });
 }
 
 void launch_ovl_gather(Sim &s, int k) {
-    Topo t = topo_of(s);
-    hipLaunchKernelGGL(k_ovl_gather, dim3(star_grid(s)), dim3(256), 0, s.stream, t, k, s.p.overlap_factor,
+    const Topo t = topo_of(s);
+    with_box(t, [&](auto tp) {
+        hipLaunchKernelGGL(k_ovl_gather<decltype(tp)>, dim3(star_grid(s)), dim3(256), 0, s.stream, tp, k, s.p.overlap_factor,
                        s.p.cap_frac, 1.0 - s.p.contact_tol);
+    });
 }
 
 void launch_ovl_apply(Sim &s, int k) {
-    Topo t = topo_of(s);
+    const Topo t = topo_of(s);
     hipLaunchKernelGGL(k_ovl_apply, dim3(list_grid(s)), dim3(256), 0, s.stream, t, k);
 }
 
 void launch_tail(Sim &s, const TailPlan &plan) {
-    Topo t = topo_of(s);
-    hipLaunchKernelGGL(k_tail, dim3(1), dim3(kTailBlock), 0, s.stream, t, plan, s.dbase, s.ring);
+    const Topo t = topo_of(s);
+    with_box(t, [&](auto tp) {
+        hipLaunchKernelGGL(k_tail<decltype(tp)>, dim3(1), dim3(kTailBlock), 0, s.stream, tp, plan, s.dbase, s.ring);
+    });
 }
 
 void launch_repair_rounds(Sim &s, int round0, int slot0, int rounds, bool first_evaluated) {
-    Topo t = topo_of(s);
-    hipLaunchKernelGGL(k_repair_rounds, dim3(1), dim3(kTailBlock), 0, s.stream, t, round0 - s.rbase, slot0, rounds,
+    const Topo t = topo_of(s);
+    with_box(t, [&](auto tp) {
+        hipLaunchKernelGGL(k_repair_rounds<decltype(tp)>, dim3(1), dim3(kTailBlock), 0, s.stream, tp, round0 - s.rbase, slot0, rounds,
                        first_evaluated ? 1 : 0);
+    });
 }
 
 void launch_snapshot(Sim &s) {
-    Topo t = topo_of(s);
+    const Topo t = topo_of(s);
     const void *p[] = {s.he_v, s.he_twin, s.vert_he, s.snap_v, s.snap_twin, s.snap_vh};
     int vec = 1;
     for (const void *q : p) vec &= ((uintptr_t)q % 16 == 0) ? 1 : 0;
@@ -1809,7 +1993,7 @@ void launch_snapshot(Sim &s) {
 }
 
 void launch_scatter_oldpos(Sim &s, int k) {
-    Topo t = topo_of(s);
+    const Topo t = topo_of(s);
     hipLaunchKernelGGL(k_scatter_oldpos, dim3(grid_for(s.n)), dim3(256), 0, s.stream, t, k, s.xa, s.ya);
 }
 

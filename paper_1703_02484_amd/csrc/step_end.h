@@ -8,16 +8,18 @@ namespace bd {
 // Records the step's control block in the ring, then either advances the step counter and the stamp bases and
 // clears the control block for the next step (a list rebuild this step's skin test asked for happens there), or
 // stops the batch when the step halted (the host finishes it, from the control block as it stands) or the ring is
-// full.  Every thread of the workgroup calls it, after a barrier; the stop flag is written only after the barrier
-// inside.
-__device__ __forceinline__ void step_end_body(int *ctl, StepBase *base, int *ring, int r_used, int v_used) {
+// full.  now: the control block as the step left it (ctl itself, or the workgroup's copy of it in LDS).  Every
+// thread of the workgroup calls it, after a barrier; the stop flag is written only after the barrier inside.
+__device__ __forceinline__ void step_end_body(const int *now, int *ctl, StepBase *base, int *ring, int r_used,
+                                              int v_used) {
     if (base->stop) return;
     const int idx = base->batch_idx;
-    const int halt = ctl[K_HALT];
+    const int halt = now[K_HALT];
     __syncthreads();   // every thread has read it
     for (int i = threadIdx.x; i < N_CTL; i += blockDim.x) {
-        ring[(size_t)idx * N_CTL + i] = ctl[i];
-        if (!halt) ctl[i] = 0;
+        const int c = now[i];
+        ring[(size_t)idx * N_CTL + i] = c;
+        ctl[i] = halt ? c : 0;
     }
     if (threadIdx.x != 0) return;
     if (halt) {

@@ -54,3 +54,30 @@ def test_high_degree_stars_match_oracle(m, tail_mode):
     assert tri_set(g.triangles()) == tri_set(o.triangles())
     sg, so = g.state()[3], o.state()[3]
     assert sg["overlap_rounds_total"] == so["overlap_rounds_total"] > 0
+
+
+@pytest.mark.parametrize("pairs", [1, 63, 64, 65, 150])
+@pytest.mark.parametrize("periodic", [False, True])
+def test_tail_rounds_around_one_star_per_group_match_oracle(pairs, periodic):
+    """Rounds of 2 * pairs disks in the one-workgroup tail: below, at and above the 128 stars it keeps in registers."""
+    k = 40
+    L = 2.3 * k
+    rng = np.random.default_rng(pairs)
+    xy = np.array([[1.15 + 2.3 * i, 1.15 + 2.3 * j] for i in range(k) for j in range(k)])
+    xy += rng.uniform(-0.1, 0.1, xy.shape)
+    odd = rng.choice(np.arange(k // 2) * 2 * k + 1, k // 2, replace=False)   # rows 0, 2, ...: pairs along y
+    first = np.concatenate([odd + 4 * c for c in range(k // 4 - 1)])[:pairs]
+    assert len(first) == pairs
+    xy[first + 1] = xy[first] + [0.0, 2.0 + 1e-6]   # each pair pulled 0.02 into an overlap by every step; no other forces
+    n = len(xy)
+    kw = dict(L=L, D=1.0, dt=1e-7, seed=pairs, overlap_factor=0.5, periodic=periodic, cutoff=2.05)
+    sp, K = np.zeros(n, np.int32), np.array([[-4e5]])
+    g = binding.Sim(xy, np.ones(n), sp, None, K, **kw)
+    g.set_tail_mode(2)
+    o = oracle.OracleSim(xy, np.ones(n), sp, None, K, **kw)
+    g.step(3)
+    o.step(3)
+    assert rel_err(g.state()[0], o.state()[0]) <= 1e-9
+    assert tri_set(g.triangles()) == tri_set(o.triangles())
+    sg, so = g.state()[3], o.state()[3]
+    assert sg["overlap_rounds_total"] == so["overlap_rounds_total"] > 0
