@@ -258,6 +258,7 @@ struct Sim {
     int ntiles = 0;
     SymTile *stiles = nullptr;       // symmetric form: chunk pairs, then each chunk with itself
     int nstiles = 0;
+    int nch_max = 0;   // most chunks of one system in the tiling
     long long stiles_cap = 0;
     int *chunk_spec = nullptr;       // species of each chunk
     long long part_cap = 0;          // elements allocated for part

@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 
 #include "bd_internal.h"
+#include "gather.h"
 #include "geom.h"
 #include "step_end.h"
 
@@ -451,42 +452,6 @@ __global__ __launch_bounds__(64 * W) void k_force_sym(const T2 *__restrict__ pj,
     for (int k = threadIdx.x; k < nj; k += 64 * W) part[tl.pbase_j + tl.j0 + k] = jsum[k];
 }
 
-// F_i = sum_c K[s_i][spec(c)] Phi_{i,c} over the chunks of i's system, FP64,
-// fixed chunk order; k is i's sorted index.
-template <typename T2>
-__device__ __forceinline__ void gather_force(const T2 *__restrict__ part, const RepInfo &ri,
-                                             const int *__restrict__ chunk_spec, const double *__restrict__ K,
-                                             int S, int si, int k, double &fx, double &fy) {
-    fx = 0.0;
-    fy = 0.0;
-    const long long row = ri.poff + (k - ri.off);
-    const double *Ki = K + si * S;
-    int c = 0;
-    // 16 chunks at a time: the loads are all issued before the sums, which keep the chunk order (one
-    // particle per thread, so the loads in flight per thread set how much of the latency is hidden)
-    constexpr int kB = 16;
-    for (; c + kB <= ri.nch; c += kB) {
-        T2 v[kB];
-        double w[kB];
-#pragma unroll
-        for (int u = 0; u < kB; ++u) {
-            v[u] = part[row + (long long)(c + u) * ri.n];
-            w[u] = Ki[chunk_spec[ri.cfirst + c + u]];
-        }
-#pragma unroll
-        for (int u = 0; u < kB; ++u) {
-            fx += w[u] * (double)v[u].x;
-            fy += w[u] * (double)v[u].y;
-        }
-    }
-    for (; c < ri.nch; ++c) {
-        const double w = Ki[chunk_spec[ri.cfirst + c]];
-        const T2 v = part[row + (long long)c * ri.n];
-        fx += w * (double)v.x;
-        fy += w * (double)v.y;
-    }
-}
-
 // ---------------------------------------------------------------- noise
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two 32x32
 // multiplies whose high halves are mixed with the other counter words and the
@@ -544,7 +509,8 @@ struct EmArgs {
 // DIRECT: the forces come in fdirect (the list force), else as partial sums to reduce with K.
 // BRIDGE: a sub-interval of a halved step (level > 0); the bridge draws hold about twice the registers
 // of the rest, so the whole steps (level 0) run an instance without them at twice the waves per SIMD.
-template <typename T2, bool DIRECT, bool BRIDGE>
+// W > 1: W wavefronts gather the forces of 64 disks (gather.h), the first one does the rest.
+template <typename T2, bool DIRECT, bool BRIDGE, int W>
 __global__ __launch_bounds__(256) void k_em(EmArgs a, const StepBase *__restrict__ base, const T2 *__restrict__ part,
                                             const RepInfo *__restrict__ reps,
                                             const int *__restrict__ rep_of, const int *__restrict__ chunk_spec,
@@ -558,17 +524,19 @@ __global__ __launch_bounds__(256) void k_em(EmArgs a, const StepBase *__restrict
                                             unsigned long long *__restrict__ acc, const double2 *__restrict__ fdirect,
                                             signed char *__restrict__ wf, const int *__restrict__ ctl) {
 #pragma clang fp contract(off)
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = W > 1 ? blockIdx.x * 64 + (threadIdx.x & 63) : blockIdx.x * blockDim.x + threadIdx.x;
+    const bool valid = i < a.n;
     int clamps = 0;
     if (base->stop || ctl[K_HALT]) return;   // K_HALT this early: the step's neighbour lists overflowed
-    if (i < a.n) {
+    double fx = 0.0, fy = 0.0;
+    if (!DIRECT)
+        gather_force<T2, W>(part, reps, valid ? rep_of[i] : 0, chunk_spec, K, a.S, valid ? sp[i] : 0,
+                            valid ? pos_of[i] : 0, valid, fx, fy);
+    if (valid && (W == 1 || threadIdx.x < 64)) {
         const RepInfo ri = reps[rep_of[i]];
-        double fx, fy;
         if (DIRECT) {
             fx = fdirect[i].x;
             fy = fdirect[i].y;
-        } else {
-            gather_force<T2>(part, ri, chunk_spec, K, a.S, sp[i], pos_of[i], fx, fy);
         }
         // noise keyed by the system's seed and the caller's index of the disk inside its system
         const unsigned id = (unsigned)key_id[i];
@@ -640,15 +608,17 @@ __global__ __launch_bounds__(256) void k_em(EmArgs a, const StepBase *__restrict
         atomicAdd(&acc[A_CLAMP_BASE + (blockIdx.x % A_CLAMP_SLOTS) * A_CLAMP_STRIDE], (unsigned long long)wg_clamps);
 }
 
-template <typename T2>
+template <typename T2, int W>
 __global__ void k_reduce_forces(int n, int S, const T2 *__restrict__ part, const RepInfo *__restrict__ reps,
                                 const int *__restrict__ rep_of, const int *__restrict__ chunk_spec,
                                 const double *__restrict__ K, const int *__restrict__ pos_of,
                                 const int *__restrict__ sp, double *__restrict__ out) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    const int i = W > 1 ? blockIdx.x * 64 + (threadIdx.x & 63) : blockIdx.x * blockDim.x + threadIdx.x;
+    const bool valid = i < n;
     double fx, fy;
-    gather_force<T2>(part, reps[rep_of[i]], chunk_spec, K, S, sp[i], pos_of[i], fx, fy);
+    gather_force<T2, W>(part, reps, valid ? rep_of[i] : 0, chunk_spec, K, S, valid ? sp[i] : 0, valid ? pos_of[i] : 0,
+                        valid, fx, fy);
+    if (!valid || (W > 1 && threadIdx.x >= 64)) return;
     out[2 * i] = fx;
     out[2 * i + 1] = fy;
 }
@@ -814,8 +784,6 @@ int force_max_grid(Sim &s, int per_lane) {
     return cus * per_cu;
 }
 
-constexpr int kEmSmall = 32768;
-
 void launch_em(Sim &s, int level, unsigned index) {
     EmArgs a;
     a.n = s.n;
@@ -830,9 +798,9 @@ void launch_em(Sim &s, int level, unsigned index) {
     a.level = level;
     a.index = index;
     a.periodic = s.period > 0.0 ? 1 : 0;
-    // the partial sums of a disk are a chain of loads: small handles spread them over more compute units
-    const int block = s.n <= kEmSmall ? 64 : 256;
-    const int nb = blocks_for(s.n, block);
+    const bool split = !s.use_nl && gather_split(s);
+    const int disks = s.n <= kGatherSmall ? 64 : 256, block = split ? 256 : disks;
+    const int nb = blocks_for(s.n, disks);
     const Tape &tp = s.adj.tape;
     signed char *wf = tp.on ? tp.emwf + (size_t)tp.step_idx * 2 * s.n : nullptr;
     const bool bridge = level > 0;
@@ -844,21 +812,29 @@ void launch_em(Sim &s, int level, unsigned index) {
     const float2 *p32 = (const float2 *)s.part;
     const double2 *p64 = (const double2 *)s.part, *none = nullptr, *fsr = (const double2 *)s.fsr;
     if (s.use_nl)
-        bridge ? go(k_em<float2, true, true>, p32, fsr) : go(k_em<float2, true, false>, p32, fsr);
+        bridge ? go(k_em<float2, true, true, 1>, p32, fsr) : go(k_em<float2, true, false, 1>, p32, fsr);
+    else if (s.fp32 && split)
+        bridge ? go(k_em<float2, false, true, 4>, p32, none) : go(k_em<float2, false, false, 4>, p32, none);
     else if (s.fp32)
-        bridge ? go(k_em<float2, false, true>, p32, none) : go(k_em<float2, false, false>, p32, none);
+        bridge ? go(k_em<float2, false, true, 1>, p32, none) : go(k_em<float2, false, false, 1>, p32, none);
+    else if (split)
+        bridge ? go(k_em<double2, false, true, 4>, p64, none) : go(k_em<double2, false, false, 4>, p64, none);
     else
-        bridge ? go(k_em<double2, false, true>, p64, none) : go(k_em<double2, false, false>, p64, none);
+        bridge ? go(k_em<double2, false, true, 1>, p64, none) : go(k_em<double2, false, false, 1>, p64, none);
 }
 
 void launch_reduce_forces(Sim &s) {
-    const int nb = blocks_for(s.n, 256);
+    const bool split = gather_split(s);
+    auto go = [&](auto kern, auto part) {
+        hipLaunchKernelGGL(kern, dim3(blocks_for(s.n, split ? 64 : 256)), dim3(256), 0, s.stream, s.n, s.S, part,
+                           s.reps, s.rep_of, s.chunk_spec, s.Kd, s.pos_of, s.sp, s.fout);
+    };
+    const float2 *p32 = (const float2 *)s.part;
+    const double2 *p64 = (const double2 *)s.part;
     if (s.fp32)
-        hipLaunchKernelGGL(k_reduce_forces<float2>, dim3(nb), dim3(256), 0, s.stream, s.n, s.S,
-                           (const float2 *)s.part, s.reps, s.rep_of, s.chunk_spec, s.Kd, s.pos_of, s.sp, s.fout);
+        split ? go(k_reduce_forces<float2, 4>, p32) : go(k_reduce_forces<float2, 1>, p32);
     else
-        hipLaunchKernelGGL(k_reduce_forces<double2>, dim3(nb), dim3(256), 0, s.stream, s.n, s.S,
-                           (const double2 *)s.part, s.reps, s.rep_of, s.chunk_spec, s.Kd, s.pos_of, s.sp, s.fout);
+        split ? go(k_reduce_forces<double2, 4>, p64) : go(k_reduce_forces<double2, 1>, p64);
 }
 
 }  // namespace bd

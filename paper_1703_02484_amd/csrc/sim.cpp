@@ -1364,6 +1364,8 @@ void upload_tiling(Sim &s, const Tiling &t, int chunk, int per_lane, int persist
     check(hipMemcpyAsync(s.reps, t.reps.data(), sizeof(RepInfo) * s.R, hipMemcpyHostToDevice, s.stream), "reps");
     check(hipStreamSynchronize(s.stream), "tiling upload");
     s.ntiles = (int)t.tiles.size();
+    s.nch_max = 0;
+    for (const RepInfo &ri : t.reps) s.nch_max = std::max(s.nch_max, ri.nch);
     s.chunk_len = chunk;
     s.per_lane = per_lane;
     s.persistent = persistent;

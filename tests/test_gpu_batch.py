@@ -222,3 +222,33 @@ def test_batch_of_tiny_systems():
         o = oracle.OracleSim(xs[r], np.ones(3), np.zeros(3, np.int32), None, K, L=Ls[r], seed=r, **kw)
         o.step(20)
         assert rel_err(xb[doff[r]:doff[r + 1]], o.state()[0]) <= 1e-9, r
+
+
+@pytest.mark.parametrize("copies", [1, 12])
+@pytest.mark.parametrize("fp32", [False, True])
+def test_force_sums_do_not_depend_on_the_batch(copies, fp32):
+    """Systems below and above 32 chunks of partial sums, alone (one or four wavefronts per 64 disks), in a handle of
+    up to 32,768 disks and in a larger one: the same bits, and the oracle's forces.  Three species, one system a
+    boundary in the middle of a wavefront."""
+    rng = np.random.default_rng(4)
+    K = np.array([[1e-2, -5e-3, 4e-3], [2e-3, 1e-2, 0.0], [-1e-3, 3e-3, 7e-3]])
+    xs, sps, Ls = [], [], []
+    for n in [300, 2005, 2111] + [2999] * copies:
+        L = synth.box_side(n, 0.3)
+        xs.append(synth.rsa(n, L, 1.0, seed=n))
+        sps.append(rng.integers(0, 3, n).astype(np.int32))
+        Ls.append(L)
+    kw = dict(fp32=fp32, force_chunk=64, dt=1e-4)
+    b = binding.Sim.batch(xs, [np.ones(len(x)) for x in xs], sps, None, Ls, list(range(len(xs))), K, **kw)
+    off = np.concatenate([[0], np.cumsum([len(x) for x in xs])])
+    fb = b.forces()
+    b.step(2)
+    xb = b.state()[0]
+    for r in range(4):
+        sl = slice(off[r], off[r + 1])
+        fo = oracle.forces(xs[r], sps[r], K)
+        assert np.abs(fb[sl] - fo).max() <= (1e-4 if fp32 else 1e-12) * np.abs(fo).max()
+        s = binding.Sim(xs[r], np.ones(len(xs[r])), sps[r], None, K, L=Ls[r], seed=r, **kw)
+        assert np.array_equal(fb[sl], s.forces())
+        s.step(2)
+        assert np.array_equal(xb[sl], s.state()[0])
