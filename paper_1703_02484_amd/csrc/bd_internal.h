@@ -186,12 +186,11 @@ struct AdjState {
     int every = 0;
     std::vector<Checkpoint> ck;            // at t0, t0 + every, ..., then the final state
     Tape tape;
-    double2 *lam = nullptr, *nu = nullptr; // adjoint of the positions; round scratch
-    double *bx = nullptr, *by = nullptr;   // positions before a round, by disk id
+    double2 *lam = nullptr;                // adjoint of the positions
+    double4 *nub = nullptr;                // round scratch by disk id: nu, position before the round
     double4 *pj4 = nullptr;                // sorted (x, y, lambda) of one step
     double2 *gpart = nullptr;              // [part_cap] per-chunk adjoint force contributions
-    double *dk_rows = nullptr;             // [n][S] one step's dL/dK row of each particle
-    double *dk_blk = nullptr;              // [blocks][S*S] partial sums of dL/dK
+    double *dk_blk = nullptr;              // [blocks of 64 disks][S*S] partial sums of dL/dK
     double *dk = nullptr;                  // [S*S]
     int dk_blocks = 0;
 };
@@ -437,7 +436,7 @@ void launch_tail(Sim &s, const TailPlan &plan);
 void launch_repair_rounds(Sim &s, int round0, int slot0, int rounds, bool first_evaluated = true);
 
 // adjoint sweep (k_adjoint.hip)
-void launch_adj_round(Sim &s, int first_entry, int count);     // one recorded overlap round, reversed
+void launch_adj_rounds(Sim &s, const int2 *dir, int r0, int r1);   // recorded overlap rounds, reversed
 void launch_adj_step(Sim &s, int t);                           // move of recorded step t, reversed
 void launch_adj_dk_final(Sim &s);
 

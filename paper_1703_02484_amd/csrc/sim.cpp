@@ -2168,7 +2168,7 @@ void adj_free(Sim &s) {
     AdjState &a = s.adj;
     for (auto &c : a.ck) ck_free(c);
     tape_free(a.tape);
-    void *ptrs[] = {a.lam, a.nu, a.bx, a.by, a.pj4, a.gpart, a.dk_rows, a.dk_blk, a.dk};
+    void *ptrs[] = {a.lam, a.nub, a.pj4, a.gpart, a.dk_blk, a.dk};
     for (void *p : ptrs)
         dfree(p);
     a = AdjState();
@@ -2206,13 +2206,10 @@ int adjoint_begin(Sim &s, int64_t nsteps, int every) {
     ck_save(s, a.ck[nseg]);
     const int n = s.n;
     a.lam = dalloc<double2>(n);
-    a.nu = dalloc<double2>(n);
-    a.bx = dalloc<double>(n);
-    a.by = dalloc<double>(n);
+    a.nub = dalloc<double4>(n);
     a.pj4 = dalloc<double4>(n);
     a.gpart = dalloc<double2>((size_t)s.part_cap);
-    a.dk_blocks = (n + 255) / 256;
-    a.dk_rows = dalloc<double>((size_t)n * s.S);
+    a.dk_blocks = (n + 63) / 64;
     a.dk_blk = dalloc<double>((size_t)a.dk_blocks * s.S * s.S);
     a.dk = dalloc<double>(s.S * s.S);
     Tape &tp = a.tape;
@@ -2308,7 +2305,7 @@ int adjoint_backward(Sim &s, const double *gT, double *g0, double *gK, bool dev 
         check(hipStreamSynchronize(s.stream), "sync");
         for (int t = len - 1; t >= 0; --t) {
             const int r0 = t == 0 ? 0 : tp.step_dir_end[t - 1], r1 = tp.step_dir_end[t];
-            for (int r = r1 - 1; r >= r0; --r) launch_adj_round(s, dir[r].x, dir[r].y);
+            launch_adj_rounds(s, dir.data(), r0, r1);
             launch_adj_step(s, t);
         }
     }

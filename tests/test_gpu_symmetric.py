@@ -124,3 +124,43 @@ def test_fixed_rule_forms_match_oracle(n, fp32, periodic):
     fo = oracle.forces(w.xy, species, K, idx=idx, period=w.L if periodic else 0.0)
     tol = 1e-4 if fp32 else 1e-12
     assert np.abs(g.forces()[idx] - fo).max() <= tol * _scale(fo)
+
+
+@pytest.mark.parametrize("pin, sizes", [(-1, (129, 1023, 2050)), (-2, (129, 1023, 2050)), (-3, (129, 1023, 2050)),
+                                        (0, (4100,)), (0, (12301,))])
+def test_symmetric_adjoint_matches_ordinary_tiles(pin, sizes):
+    """Ragged chunks (one disk over, one short) of two species in every symmetric form (0: the library's, of 128 and
+    256), against the ordered pair sum."""
+    ws = [synth.make("C5", n=n, seed=n) for n in sizes]
+    rng = np.random.default_rng(5)
+    lam = rng.normal(size=(sum(w.n for w in ws), 2))
+    out = []
+    for chunk in (pin, 256):
+        b = binding.Sim.from_workloads(ws, force_chunk=chunk)
+        b.adjoint_begin(5, 2)
+        out.append(b.adjoint_backward(lam))
+    for got, ref in zip(*out):   # the two trajectories differ by the rounding of their force sums
+        assert np.abs(got - ref).max() <= 1e-9 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("n", [1500, 14000])
+def test_adjoint_of_large_overlap_rounds_matches_oracle_jvp(n):
+    """A first round of some hundred, and of more than 4,096 moved disks (with later ones of fewer than 1,024)."""
+    L = synth.box_side(n, 0.5)
+    xy = synth.rsa(n, L, 1.0, seed=8)
+    sp = (np.arange(n) % 2).astype(np.int32)
+    w = synth.Workload("dense", xy, np.ones(n), sp, np.zeros(n), 2, np.array([[0.05, -0.02], [0.03, 0.04]]), L=L,
+                       D=1.0, dt=2e-2, seed=2)
+    g = binding.Sim.from_workload(w)
+    g.adjoint_begin(1, 1)
+    o = oracle.OracleSim.from_workload(w)
+    rng = np.random.default_rng(2)
+    v, tK = rng.normal(size=(n, 2)), rng.normal(size=(2, 2))
+    o.set_tangent(v, tK)
+    o.step(1)
+    assert np.abs(g.state()[0] - o.state()[0]).max() <= 1e-9 * w.L
+    lam = rng.normal(size=(n, 2))
+    g0, gK = g.adjoint_backward(lam)
+    lhs = np.sum(g0 * v) + np.sum(gK * tK)
+    rhs = np.sum(lam * o.tangent())
+    assert abs(lhs - rhs) <= 1e-10 * max(abs(rhs), np.abs(lam * o.tangent()).sum() * 1e-2)
