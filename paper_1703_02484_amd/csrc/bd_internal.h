@@ -15,9 +15,9 @@ namespace bd {
 // Device control block (int32 ctl[]): flags and per-slot work counts.  A step
 // is enqueued as a budgeted sequence of rounds; every round uses its own count
 // slots, so no count is reset or read back between launches.
-constexpr int MAXR = 160;     // flip-round slots (even: worklists alternate by slot parity)
-constexpr int MAXREP = 48;    // repair slots
-constexpr int MAXO = 48;      // overlap-round slots
+constexpr int MAXR = 256;     // flip-round slots (even: worklists alternate by slot parity)
+constexpr int MAXREP = 64;    // repair slots
+constexpr int MAXO = 64;      // overlap-round slots
 enum Ctl {
     K_HALT = 0,        // nonzero: stop; the host finishes the step
     K_REASON = 1,      // HaltReason
@@ -418,7 +418,7 @@ void launch_interp(Sim &s, int i, int k);             // x = xa + (i/k)(xb - xa)
 // The overlap rounds of a step after the first detection, run by one
 // workgroup (phases separated by workgroup barriers instead of launches);
 // the same rounds, slots and stamps as the launch-per-phase sequence.
-constexpr int MAXTAIL = 24;
+constexpr int MAXTAIL = 48;
 struct TailPlan {
     int nover;                     // budgeted overlap rounds
     int rounds[MAXTAIL];           // flip rounds of the repair after round j

@@ -572,12 +572,21 @@ void write_base(Sim &s) {
     check(hipMemcpyAsync(s.dbase, s.hbase, sizeof(StepBase), hipMemcpyHostToDevice, s.stream), "step base");
 }
 
-// Overlap rounds enqueued per step: the adaptive budget, never more than the
-// caller's round cap (the host loop enforces the cap beyond that) nor more
-// than the step's flip-round slots hold.
+// Overlap rounds enqueued per step, never more than the caller's round cap (the
+// host loop enforces the cap beyond that) nor more than the step's flip-round
+// slots hold.  Rounds launched per phase cost their launches whether or not the
+// step needs them: the adaptive budget.  The one-workgroup tail leaves at the
+// first detection that finds nothing, so it gets all the rounds it holds: a step
+// the host has to continue costs some 100 us per round.  16,384 disks with the
+// contact factor 1/2 need up to 25 rounds a step and now and then 41; ten steps
+// with their reverse sweep, first pass of a handle 14.7 to 16.4 ms with a budget
+// that followed the rounds (at most 24), 11.3 to 13.6 so; later passes with a
+// step of 41 rounds 15.3 to 18.0 and 12.5 to 13.0.
+constexpr int kMaxLaunchedRounds = 24;
+
 int overlaps_budget(const Sim &s) {
     const int cap = s.p.max_overlap_rounds > 0 ? s.p.max_overlap_rounds : 10000;
-    const int nover = std::min(s.budget.overlaps, cap);
+    const int nover = std::min(tail_mode_of(s) == 0 ? s.budget.overlaps : MAXTAIL, cap);
     int slots = s.budget.em;
     for (int j = 0; j < nover; ++j) {
         if (slots + s.budget.ovl[j] > MAXR) return j;
@@ -1212,8 +1221,7 @@ int finish_step(Sim &s, const int *h_in, const StepPlan &plan) {
             used = used_rounds(r, plan.b.ovl[j]);
         adapt(s.budget.ovl[j], used, s.slack_ovl[j]);
     }
-    s.budget.overlaps = std::max(s.budget.overlaps, plan.overlaps);
-    adapt(s.budget.overlaps, rounds, s.slack_over, MAXO / 2);   // contact-factor runs need ~20 rounds
+    adapt(s.budget.overlaps, rounds, s.slack_over, kMaxLaunchedRounds);   // contact-factor runs need ~20 rounds
     update_ovl_phase(s, h, plan.orounds, std::min(rounds, plan.overlaps));
     s.st.overlap_rounds_total += rounds;
     if (rounds > s.st.overlap_rounds_max) s.st.overlap_rounds_max = rounds;
@@ -1248,7 +1256,7 @@ int finish_step_nl(Sim &s, const int *h_in, const StepPlan &plan) {
     int &budget = s.budget.overlaps;
     budget = plan.b.overlaps;
     if (rounds >= budget) {
-        budget = std::min(MAXO / 2, rounds + 1);
+        budget = std::min(kMaxLaunchedRounds, rounds + 1);
         s.slack_over = 0;
     } else if (rounds + 1 < budget) {
         if (++s.slack_over >= kShrinkAfter) {
@@ -1288,8 +1296,7 @@ struct Tiling {
 };
 
 // sym: chunks of at most `chunk` and the symmetric form's tile list (every
-// pair of chunks of a system once, then every chunk with itself); the
-// ordinary tiles of the same chunks are kept for the adjoint sweep.
+// pair of chunks of a system once, then every chunk with itself).
 Tiling make_tiling(const Sim &s, int chunk, int per_lane, bool sym = false) {
     Tiling t;
     t.reps.resize(s.R);
