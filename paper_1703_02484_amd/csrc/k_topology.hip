@@ -560,9 +560,12 @@ __device__ __forceinline__ void eval_edge(const TP &t, int h, int tw, int round,
 // issues its loads in three dependent waves instead of one chain per edge.
 // The decisions are those of eval_edge.
 constexpr int kEvalStage = 2048;
-// Workgroup and grid of the full evaluation: 256-, 512- and 1024-thread workgroups with the same number
-// of threads in the grid measured within 3 % of each other on 1M disks.
-constexpr int kEvalBlock = 1024, kEvalGrid = 512;
+// Workgroup and grid of the full evaluation: bound by the rate of its scattered loads (some twenty a triangle), so by
+// the wavefronts a compute unit holds.  80 registers let six wavefronts of a SIMD run, which workgroups of 1024
+// threads cannot fill; five workgroups of 256 per compute unit are all resident at once.  1,000,000 disks 73 us as
+// 512 x 1024, 66 so, 81 as 1536 x 256 (some wait for a place and run alone); 16,001 disks 16.0 and 11.5; 64 systems
+// of 2,048 to 32,768 74 and 63.
+constexpr int kEvalBlock = 256, kEvalGrid = 1280;
 
 // Every thread of the workgroup calls it once, at the end: the staged
 // candidates are reserved in the round's list with one atomic and copied out.

@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 import oracle
-from paper_1703_02484_amd import binding
+from paper_1703_02484_amd import binding, synth
 from tests._checks import rel_err, tri_set
 from tests.conftest import gpu_available
 
@@ -81,3 +81,25 @@ def test_tail_rounds_around_one_star_per_group_match_oracle(pairs, periodic):
     assert tri_set(g.triangles()) == tri_set(o.triangles())
     sg, so = g.state()[3], o.state()[3]
     assert sg["overlap_rounds_total"] == so["overlap_rounds_total"] > 0
+
+
+@pytest.mark.parametrize("tail_mode", [0, 1, 2])
+@pytest.mark.parametrize("graph", [False, True])
+def test_many_overlap_rounds_match_oracle(tail_mode, graph):
+    """Steps of 35 to 60 rounds: within and beyond what one launch of the tail holds (48)."""
+    n = 300
+    L = synth.box_side(n, 0.5)
+    xy = synth.rsa(n, L, 1.0, seed=3)
+    kw = dict(L=L, dt=2e-3, seed=1, overlap_factor=0.4)
+    sp, K = np.zeros(n, np.int32), np.array([[1e-2]])
+    g = binding.Sim(xy, np.ones(n), sp, None, K, **kw)
+    g.set_tail_mode(tail_mode)
+    g.set_graph_mode(graph)
+    o = oracle.OracleSim(xy, np.ones(n), sp, None, K, **kw)
+    g.step(8)
+    o.step(8)
+    assert rel_err(g.state()[0], o.state()[0]) <= 1e-9
+    sg, so = g.state()[3], o.state()[3]
+    assert so["overlap_rounds_max"] > 48
+    for k in ("overlap_rounds_total", "overlap_rounds_max", "overlap_edges_total"):
+        assert sg[k] == so[k]
