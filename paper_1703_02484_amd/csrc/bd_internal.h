@@ -279,7 +279,7 @@ struct Sim {
     int *nl = nullptr, *nl_cnt = nullptr;
     int *nl_cand = nullptr;          // disks of a one-workgroup list round
     int nl_phase = 1;                // list overlap rounds launched as full passes before the one-workgroup rest
-    int *cell_of = nullptr, *cell_count = nullptr, *cell_start = nullptr, *cell_fill = nullptr, *cell_items = nullptr;
+    int *cell_rows = nullptr, *cell_more = nullptr, *cell_next = nullptr;   // empty between builds (k_verlet.hip)
     double *xbuild = nullptr, *ybuild = nullptr;
     double2 *fsr = nullptr;          // short-range forces, caller order
     int ovl_method = 0;              // 0: overlap rounds over Delaunay edges; 1: over the neighbour lists
@@ -287,7 +287,6 @@ struct Sim {
     double rad_uni = 0.0;            // > 0: every disk has this radius
     double nl_margin = 0.0;          // lists hold every pair closer than contact while no disk moved farther
                                      // than this since the build: (cutoff + skin - 2 r_max) / 2
-    int *scan_bsum = nullptr;        // per-block totals of the cell-count scan
     // triangulation (half-edge SoA, ghosts included)
     int *he_v = nullptr, *he_twin = nullptr, *vert_he = nullptr;
     unsigned long long *claim = nullptr;
@@ -371,7 +370,7 @@ int force_max_grid(Sim &s, int per_lane);            // resident workgroups of t
 void launch_em(Sim &s, int level = 0, unsigned index = 0);
 void launch_reduce_forces(Sim &s);
 // short-range path (k_verlet.hip)
-int verlet_scan_blocks(int ncells);
+size_t verlet_row_ints(int ncell);   // ints in the rows of ncell cells
 void launch_verlet_build(Sim &s);
 void launch_verlet_build_requested(Sim &s);   // the same kernels, each doing nothing unless the step asks (graph mode)
 void launch_force_nl(Sim &s);

@@ -6,12 +6,14 @@
 // time, in a fixed order (cells of the 3 x 3 block in turn, ids ascending
 // inside a cell), stored slot-major (nl[k * n + i]) for coalesced reads.
 // They stay valid while no disk has moved more than skin / 2 since the build:
-// then every pair with d <= r_cut at force time is in the list.  The build is a
-// counting sort of the disks by cell (count, exclusive scan, scatter, sort of
-// each cell's few ids) followed by one thread per disk scanning the 3 x 3
-// cells around it.  In graph mode the build kernels are part of every
-// queued step and do nothing unless the previous step's skin test asked for
-// new lists (`req` points at the step's flag; null: always build).
+// then every pair with d <= r_cut at force time is in the list.  The build is
+// two launches: every disk enters its cell's row, then one thread per disk scans
+// the 3 x 3 rows around it, each row's few ids sorted in registers.  In graph
+// mode both are part of every queued step and do nothing unless the previous
+// step's skin test asked for new lists (`req` points at the step's flag; null:
+// always build), so what they cost is their launches: as a counting sort (count,
+// two scans, scatter, sort, build) six launches took 27 us of every step, now 9,
+// and a build of 1,000,000 disks 166 us, now 104.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -42,152 +44,132 @@ constexpr int kNlBatch = 2;
 // once, and a launch of few workgroups costs less.
 constexpr int kBuildGrid = 512;
 
-__global__ void k_cell_count(int n, const double *__restrict__ x, const double *__restrict__ y, double inv_cell,
-                             int nc, int *__restrict__ cell_of, int *__restrict__ cell_count, const int *req) {
+// A cell's row: the number of disks, then the first seven ids, in the order they came; one 32-byte sector.  Further
+// disks hang on the cell's chain (cell_more: the last one + 1, cell_next: the one before, by id).  Rows and chains are
+// empty between builds: whoever reads the new lists first clears them.
+constexpr int kCellIds = 7;
+constexpr int kCellRow = kCellIds + 1;
+
+__global__ void k_cell_insert(int n, const double2 *__restrict__ xy, double inv_cell, int nc, int *__restrict__ rows,
+                              int *__restrict__ more, int *__restrict__ next, const int *req) {
     if (req && !*req) return;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        int c = cell_coord(y[i], inv_cell, nc) * nc + cell_coord(x[i], inv_cell, nc);
-        cell_of[i] = c;
-        atomicAdd(&cell_count[c], 1);
+        const double2 p = xy[i];
+        const int c = cell_coord(p.y, inv_cell, nc) * nc + cell_coord(p.x, inv_cell, nc);
+        const int k = atomicAdd(&rows[(size_t)c * kCellRow], 1);
+        if (k < kCellIds)
+            rows[(size_t)c * kCellRow + 1 + k] = i;
+        else
+            next[i] = atomicExch(&more[c], i + 1);
     }
 }
 
-// Exclusive scan of the cell counts (m = cells + 1 entries; the last count is
-// 0, so start[m - 1] = n): each 1024-entry block scans in LDS and records its
-// total, then every block adds the totals of the blocks before it.
-constexpr int kScanBlk = 1024;
-
-// Segments of kScanBlk entries, each scanned by one workgroup at a time (a
-// workgroup takes segments blockIdx.x, blockIdx.x + gridDim.x, ...).
-__global__ __launch_bounds__(kScanBlk) void k_scan_local(int m, const int *__restrict__ cnt, int *__restrict__ start,
-                                                         int *__restrict__ bsum, const int *req) {
-    __shared__ int buf[kScanBlk];
-    if (req && !*req) return;
-    const int nseg = (m + kScanBlk - 1) / kScanBlk;
-    for (int seg = blockIdx.x; seg < nseg; seg += gridDim.x) {
-        const int i = seg * kScanBlk + threadIdx.x;
-        const int v = i < m ? cnt[i] : 0;
-        __syncthreads();   // the previous segment's reads of buf are done
-        buf[threadIdx.x] = v;
-        __syncthreads();
-        for (int off = 1; off < kScanBlk; off <<= 1) {
-            const int add = threadIdx.x >= (unsigned)off ? buf[threadIdx.x - off] : 0;
-            __syncthreads();
-            buf[threadIdx.x] += add;
-            __syncthreads();
-        }
-        if (i < m) start[i] = buf[threadIdx.x] - v;
-        if (threadIdx.x == kScanBlk - 1) bsum[seg] = buf[threadIdx.x];
-    }
-}
-
-__global__ __launch_bounds__(kScanBlk) void k_scan_offsets(int m, int *__restrict__ start,
-                                                           const int *__restrict__ bsum, const int *req) {
-    __shared__ int total;
-    if (req && !*req) return;
-    const int nseg = (m + kScanBlk - 1) / kScanBlk;
-    for (int seg = blockIdx.x; seg < nseg; seg += gridDim.x) {
-        if (seg == 0) continue;   // uniform in the workgroup
-        __syncthreads();          // the previous segment's read of total is done
-        if (threadIdx.x == 0) total = 0;
-        __syncthreads();
-        int acc = 0;
-        for (int b = threadIdx.x; b < seg; b += kScanBlk) acc += bsum[b];
-        if (acc) atomicAdd(&total, acc);
-        __syncthreads();
-        const int i = seg * kScanBlk + threadIdx.x;
-        if (i < m) start[i] += total;
-    }
-}
-
-__global__ void k_cell_scatter(int n, const int *__restrict__ cell_of, const int *__restrict__ cell_start,
-                               int *__restrict__ cell_fill, int *__restrict__ cell_items, const int *req) {
-    if (req && !*req) return;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        int c = cell_of[i];
-        cell_items[cell_start[c] + atomicAdd(&cell_fill[c], 1)] = i;
-    }
-}
-
-// One thread per cell: the scatter filled each cell in arbitrary order; sort
-// it by id (cells hold a few disks) so that the lists below are deterministic.
-// The cell's count and fill counter are zeroed for the next build.
-__global__ void k_cell_sort(int ncell, const int *__restrict__ cell_start, int *__restrict__ cell_items,
-                            int *__restrict__ cell_count, int *__restrict__ cell_fill, const int *req) {
-    if (req && !*req) return;
-    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < ncell; c += gridDim.x * blockDim.x) {
-        cell_count[c] = 0;
-        cell_fill[c] = 0;
-        const int b = cell_start[c], e = cell_start[c + 1];
-        for (int p = b + 1; p < e; ++p) {
-            const int v = cell_items[p];
-            int q = p;
-            while (q > b && cell_items[q - 1] > v) {
-                cell_items[q] = cell_items[q - 1];
-                --q;
-            }
-            cell_items[q] = v;
-        }
-    }
-}
-
-// One thread per disk: neighbours within r_list from the 3 x 3 cells, in cell
+// The list of disk i: neighbours within r_list from the 3 x 3 cells, in cell
 // order and by id inside a cell, written straight to the slot-major list (at
-// most CAP; the largest count above CAP is reported so the caller can grow the
+// most cap; the largest count above cap is reported so the caller can grow the
 // lists).  The position at build time is kept for the skin test.
-// The list of disk i (see k_nl_build).
-template <int CAP>
-__device__ __forceinline__ void nl_build_one(int i, int n, const double *__restrict__ x, const double *__restrict__ y,
-                                             double inv_cell, int nc, double rl2, const int *__restrict__ cell_start,
-                                             const int *__restrict__ cell_items, int *__restrict__ nl,
-                                             int *__restrict__ nl_cnt, double *__restrict__ xb,
-                                             double *__restrict__ yb, int *__restrict__ overflow, double P) {
+struct BuildArgs {
+    int n, nc, cap;
+    double inv_cell, rl2, P;
+    const double2 *xy;
+    const int4 *rows;
+    const int *more, *next;
+    int *nl, *nl_cnt, *overflow;
+    double *xb, *yb;
+};
+
+template <bool PER>
+__device__ __forceinline__ void nl_build_one(const BuildArgs &a, int i) {
 #pragma clang fp contract(off)
-    const double xi = x[i], yi = y[i];
-    const int cx = cell_coord(xi, inv_cell, nc), cy = cell_coord(yi, inv_cell, nc);
+    const double2 pi = a.xy[i];
+    const int nc = a.nc;
+    const int cx = cell_coord(pi.x, a.inv_cell, nc), cy = cell_coord(pi.y, a.inv_cell, nc);
     int cnt = 0;
-    // periodic box (P > 0): the 3 x 3 block wraps around (at least 3 cells a row, so no cell twice)
+    auto test = [&](int j, double2 pj) {
+        const double dx = sep_k<PER>(pi.x - pj.x, a.P), dy = sep_k<PER>(pi.y - pj.y, a.P);
+        if (j == i || dx * dx + dy * dy > a.rl2) return;
+        if (cnt < a.cap) a.nl[(size_t)cnt * a.n + i] = j;
+        ++cnt;
+    };
+    // periodic box: the 3 x 3 block wraps around (at least 3 cells a row, so no cell twice)
     for (int oy = -1; oy <= 1; ++oy) {
         int gy = cy + oy;
-        if (P > 0.0)
+        if (PER)
             gy = gy < 0 ? gy + nc : (gy >= nc ? gy - nc : gy);
         else if (gy < 0 || gy >= nc)
             continue;
-        for (int ox = -1; ox <= 1; ++ox) {
-            int gx = cx + ox;
-            if (P > 0.0)
-                gx = gx < 0 ? gx + nc : (gx >= nc ? gx - nc : gx);
-            else if (gx < 0 || gx >= nc)
+        int c[3];
+        int4 lo[3], hi[3];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {   // the three rows are loaded together
+            int gx = cx + u - 1;
+            if (PER) gx = gx < 0 ? gx + nc : (gx >= nc ? gx - nc : gx);
+            c[u] = gx < 0 || gx >= nc ? -1 : gy * nc + gx;
+            const int cu = c[u] < 0 ? gy * nc + cx : c[u];
+            lo[u] = a.rows[2 * (size_t)cu];
+            hi[u] = a.rows[2 * (size_t)cu + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            const int m = c[u] < 0 ? 0 : lo[u].x;
+            int id[kCellIds] = {lo[u].y, lo[u].z, lo[u].w, hi[u].x, hi[u].y, hi[u].z, hi[u].w};
+            if (m > kCellIds) {   // also on the chain: the smallest id above the last one, m times
+                int last = -1;
+                for (int k = 0; k < m; ++k) {
+                    int best = 0x7FFFFFFF;
+#pragma unroll
+                    for (int q = 0; q < kCellIds; ++q)
+                        if (id[q] > last && id[q] < best) best = id[q];
+                    for (int e = a.more[c[u]]; e != 0; e = a.next[e - 1])
+                        if (e - 1 > last && e - 1 < best) best = e - 1;
+                    last = best;
+                    test(best, a.xy[best]);
+                }
                 continue;
-            const int c = gy * nc + gx;
-            for (int p = cell_start[c]; p < cell_start[c + 1]; ++p) {
-                const int j = cell_items[p];
-                if (j == i) continue;
-                const double dx = sep(xi - x[j], P), dy = sep(yi - y[j], P);
-                if (dx * dx + dy * dy > rl2) continue;
-                if (cnt < CAP) nl[(size_t)cnt * n + i] = j;
-                ++cnt;
             }
+#pragma unroll
+            for (int q = 0; q < kCellIds; ++q)
+                if (q >= m) id[q] = 0x7FFFFFFF;
+#pragma unroll
+            for (int r = 0; r < kCellIds; ++r)   // odd-even transposition: as many rounds as ids
+#pragma unroll
+                for (int q = r & 1; q + 1 < kCellIds; q += 2) {
+                    const int x = id[q], y = id[q + 1];
+                    id[q] = x < y ? x : y;
+                    id[q + 1] = x < y ? y : x;
+                }
+            double2 p[kCellIds];
+#pragma unroll
+            for (int q = 0; q < kCellIds; ++q)
+                if (q < m) p[q] = a.xy[id[q]];
+#pragma unroll
+            for (int q = 0; q < kCellIds; ++q)
+                if (q < m) test(id[q], p[q]);
         }
     }
-    if (cnt > CAP) atomicMax(overflow, cnt);
-    nl_cnt[i] = cnt < CAP ? cnt : CAP;
-    xb[i] = xi;
-    yb[i] = yi;
+    if (cnt > a.cap) atomicMax(a.overflow, cnt);
+    a.nl_cnt[i] = cnt < a.cap ? cnt : a.cap;
+    a.xb[i] = pi.x;
+    a.yb[i] = pi.y;
 }
 
-template <int CAP>
-__global__ __launch_bounds__(256) void k_nl_build(int n, const double *__restrict__ x, const double *__restrict__ y,
-                                                  double inv_cell, int nc, double rl2,
-                                                  const int *__restrict__ cell_start,
-                                                  const int *__restrict__ cell_items, int *__restrict__ nl,
-                                                  int *__restrict__ nl_cnt, double *__restrict__ xb,
-                                                  double *__restrict__ yb, int *__restrict__ overflow, const int *req,
-                                                  double P) {
-#pragma clang fp contract(off)
+template <bool PER>
+__global__ __launch_bounds__(256) void k_nl_build(BuildArgs a, const int *req) {
     if (req && !*req) return;
-    for (int i = xcd_block() * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        nl_build_one<CAP>(i, n, x, y, inv_cell, nc, rl2, cell_start, cell_items, nl, nl_cnt, xb, yb, overflow, P);
+    for (int i = xcd_block() * blockDim.x + threadIdx.x; i < a.n; i += gridDim.x * blockDim.x) nl_build_one<PER>(a, i);
+}
+
+// Empties the cell of a disk at p (cells may be many more than disks, so by disk).
+__device__ __forceinline__ void cell_clear(double2 p, double inv_cell, int nc, int *rows, int *more) {
+    const int c = cell_coord(p.y, inv_cell, nc) * nc + cell_coord(p.x, inv_cell, nc);
+    rows[(size_t)c * kCellRow] = 0;
+    more[c] = 0;
+}
+
+__global__ void k_cells_clear(int n, const double2 *__restrict__ xy, double inv_cell, int nc, int *__restrict__ rows,
+                              int *__restrict__ more) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) cell_clear(xy[i], inv_cell, nc, rows, more);
 }
 
 // Pair force over the list: F_i = sum_j K[s_i][s_j] g(d) (r_i - r_j)/d for
@@ -200,7 +182,8 @@ __global__ __launch_bounds__(256) void k_force_nl(int n, const double2 *__restri
                                                   int kind, double q, double A, double lam, double rc,
                                                   const int *__restrict__ nl, const int *__restrict__ nl_cnt,
                                                   double2 *__restrict__ f, const StepBase *__restrict__ base,
-                                                  int *__restrict__ ctl, double P) {
+                                                  int *__restrict__ ctl, double inv_cell, int nc,
+                                                  int *__restrict__ rows, int *__restrict__ more, double P) {
 #pragma clang fp contract(off)
     int i = xcd_block() * blockDim.x + threadIdx.x;
     if (base->stop) return;
@@ -216,6 +199,7 @@ __global__ __launch_bounds__(256) void k_force_nl(int n, const double2 *__restri
             ctl[K_HALT] = 1;
         }
     }
+    if (built && i < n) cell_clear(xy[i], inv_cell, nc, rows, more);
     if (over || i >= n) return;
     const double2 pi = xy[i];
     const double xi = pi.x, yi = pi.y;
@@ -631,46 +615,53 @@ NlArgs nl_args(const Sim &s) {
 
 }  // namespace
 
-// Blocks of the cell-count scan (cells + 1 entries); sizes its per-block totals.
-int verlet_scan_blocks(int ncells) { return (ncells + 1 + kScanBlk - 1) / kScanBlk; }
-
 namespace {
 
-// The build kernels; req = null builds unconditionally (the caller zeroed
-// cell_count, cell_fill and the overflow flag), else only when *req != 0.
+// The build kernels; req = null builds unconditionally, else only when *req != 0.
 void enqueue_build(Sim &s, const int *req) {
-    const double inv_cell = (double)s.nl_nc / s.L_h[0];
-    const int m = s.nl_ncell + 1;
-    hipLaunchKernelGGL(k_cell_count, dim3(capped(blocks(s.n))), dim3(256), 0, s.stream, s.n, s.x, s.y, inv_cell, s.nl_nc,
-                       s.cell_of, s.cell_count, req);
-    hipLaunchKernelGGL(k_scan_local, dim3(capped(verlet_scan_blocks(s.nl_ncell), 256)), dim3(kScanBlk), 0, s.stream, m,
-                       (const int *)s.cell_count, s.cell_start, s.scan_bsum, req);
-    hipLaunchKernelGGL(k_scan_offsets, dim3(capped(verlet_scan_blocks(s.nl_ncell), 256)), dim3(kScanBlk), 0, s.stream, m,
-                       s.cell_start, (const int *)s.scan_bsum, req);
-    hipLaunchKernelGGL(k_cell_scatter, dim3(capped(blocks(s.n))), dim3(256), 0, s.stream, s.n, s.cell_of, s.cell_start,
-                       s.cell_fill, s.cell_items, req);
-    hipLaunchKernelGGL(k_cell_sort, dim3(capped(blocks(s.nl_ncell))), dim3(256), 0, s.stream, s.nl_ncell, s.cell_start,
-                       s.cell_items, s.cell_count, s.cell_fill, req);
     const double rl = s.fp.cutoff + s.fp.skin;
-    if (s.nl_cap <= 32)
-        hipLaunchKernelGGL(k_nl_build<32>, dim3(capped(blocks(s.n), 2 * kBuildGrid)), dim3(256), 0, s.stream, s.n, s.x, s.y, inv_cell,
-                           s.nl_nc, rl * rl, s.cell_start, s.cell_items, s.nl, s.nl_cnt, s.xbuild, s.ybuild,
-                           s.ctl + K_NL_OVERFLOW, req, s.period);
-    else
-        hipLaunchKernelGGL(k_nl_build<96>, dim3(capped(blocks(s.n), 2 * kBuildGrid)), dim3(256), 0, s.stream, s.n, s.x, s.y, inv_cell,
-                           s.nl_nc, rl * rl, s.cell_start, s.cell_items, s.nl, s.nl_cnt, s.xbuild, s.ybuild,
-                           s.ctl + K_NL_OVERFLOW, req, s.period);
+    BuildArgs a;
+    a.n = s.n;
+    a.nc = s.nl_nc;
+    a.cap = s.nl_cap;
+    a.inv_cell = (double)s.nl_nc / s.L_h[0];
+    a.rl2 = rl * rl;
+    a.P = s.period;
+    a.xy = s.xy;
+    a.rows = (const int4 *)s.cell_rows;
+    a.more = s.cell_more;
+    a.next = s.cell_next;
+    a.nl = s.nl;
+    a.nl_cnt = s.nl_cnt;
+    a.overflow = s.ctl + K_NL_OVERFLOW;
+    a.xb = s.xbuild;
+    a.yb = s.ybuild;
+    hipLaunchKernelGGL(k_cell_insert, dim3(capped(blocks(s.n))), dim3(256), 0, s.stream, s.n, a.xy, a.inv_cell, a.nc,
+                       s.cell_rows, s.cell_more, s.cell_next, req);
+    hipLaunchKernelGGL(s.period > 0.0 ? k_nl_build<true> : k_nl_build<false>, dim3(capped(blocks(s.n), 2 * kBuildGrid)),
+                       dim3(256), 0, s.stream, a, req);
 }
 
 }  // namespace
 
-// Rebuilds the lists from the current positions.  The caller zeroed
-// cell_count, cell_fill and the overflow flag.
-void launch_verlet_build(Sim &s) { enqueue_build(s, nullptr); }
+// Ints in the rows of ncell cells.
+size_t verlet_row_ints(int ncell) { return (size_t)ncell * kCellRow; }
+
+static void launch_cells_clear(Sim &s) {
+    hipLaunchKernelGGL(k_cells_clear, dim3(blocks(s.n)), dim3(256), 0, s.stream, s.n, (const double2 *)s.xy,
+                       (double)s.nl_nc / s.L_h[0], s.nl_nc, s.cell_rows, s.cell_more);
+}
+
+// Rebuilds the lists from the current positions (the caller zeroed the overflow flag) and empties the cells.
+void launch_verlet_build(Sim &s) {
+    enqueue_build(s, nullptr);
+    launch_cells_clear(s);
+}
 
 void launch_verlet_build_requested(Sim &s) {
     StepBase *b = (StepBase *)s.dbase;
-    enqueue_build(s, &b->nl_now);   // the force kernel that follows records the rebuild and checks its capacity
+    // the force kernel that follows records the rebuild, checks its capacity and empties the cells
+    enqueue_build(s, &b->nl_now);
 }
 
 void launch_force_nl(Sim &s) {
@@ -679,7 +670,8 @@ void launch_force_nl(Sim &s) {
         hipLaunchKernelGGL(kern, dim3(blocks(s.n)), dim3(256), 0, s.stream, s.n, (const double2 *)s.xy,
                            (const int *)s.sp, (const double *)s.Kd, s.S, s.fp.kind, s.fp.q,
                            s.fp.A, s.fp.lambda, s.fp.cutoff, (const int *)s.nl, (const int *)s.nl_cnt, s.fsr,
-                           (const StepBase *)s.dbase, s.ctl, s.period);
+                           (const StepBase *)s.dbase, s.ctl, (double)s.nl_nc / s.L_h[0], s.nl_nc, s.cell_rows,
+                           s.cell_more, s.period);
     };
     if (s.fp32)
         per ? (s.S == 1 ? go(k_force_nl<float, true, true>) : go(k_force_nl<float, false, true>))

@@ -437,8 +437,6 @@ void drop_graphs(Sim &s) {
 // check the list capacity; grows it once if a disk has too many neighbours).
 void verlet_rebuild(Sim &s) {
     for (int attempt = 0; attempt < 2; ++attempt) {
-        fill_int(s, s.cell_count, s.nl_ncell + 1, 0);
-        fill_int(s, s.cell_fill, s.nl_ncell, 0);
         zero_ctl(s, K_NL_OVERFLOW);
         launch_verlet_build(s);
         read_ctl(s);
@@ -1676,8 +1674,8 @@ void free_all(Sim &s) {
                     s.claim, s.tri_stamp, s.moved, s.edge_stamp, s.vstamp, s.wl[0], s.wl[1], s.cand, s.cand_won,
                     s.touched, s.det_stamp, s.fl_stamp, s.fl, s.vt_stamp, s.vt, s.newpos, s.oldpos, s.star, s.star_deg, s.snap_v, s.snap_twin,
                     s.snap_vh, s.xa, s.ya, s.xb, s.yb, s.ctl,
-                    s.acc, s.nl, s.nl_cnt, s.nl_cand, s.cell_of, s.cell_count, s.cell_start, s.cell_fill, s.cell_items,
-                    s.xbuild, s.ybuild, s.fsr, s.scan_bsum, s.stiles, s.xs, s.ys, s.ths};
+                    s.acc, s.nl, s.nl_cnt, s.nl_cand, s.cell_rows, s.cell_more, s.cell_next,
+                    s.xbuild, s.ybuild, s.fsr, s.stiles, s.xs, s.ys, s.ths};
     for (void *p : ptrs)
         dfree(p);
     drop_graphs(s);
@@ -2009,24 +2007,23 @@ int init_impl(Sim &s, int R, const int32_t *n_per, const double *xy, const doubl
     if (hipHostMalloc((void **)&s.hbase, sizeof(StepBase), hipHostMallocDefault) != hipSuccess) throw std::bad_alloc();
     if (s.use_nl) {
         const double rl = fp->cutoff + fp->skin;
-        s.nl_nc = std::max(1, std::min(46000, (int)std::floor(L_per[0] / rl)));
+        // cells of side r_list, wider where the box would hold more than 2^26 of them (and 8 per disk)
+        const double most = std::sqrt(std::max(67108864.0, 8.0 * n));
+        s.nl_nc = (int)std::max(1.0, std::min({46000.0, std::floor(most), std::floor(L_per[0] / rl)}));
         if (s.period > 0.0 && s.nl_nc < 3) {
             s.last_error = "a periodic box needs a side of at least 3 (cutoff + skin) for its cell grid";
             return BD_ERR_INVALID_ARG;
         }
         s.nl_ncell = s.nl_nc * s.nl_nc;
-        s.cell_count = dalloc<int>(s.nl_ncell + 1);
-        s.cell_start = dalloc<int>(s.nl_ncell + 1);
-        s.cell_fill = dalloc<int>(s.nl_ncell);
-        s.cell_of = dalloc<int>(n);
-        s.cell_items = dalloc<int>(n);
+        s.cell_rows = dalloc<int>(verlet_row_ints(s.nl_ncell));
+        s.cell_more = dalloc<int>(s.nl_ncell);
+        s.cell_next = dalloc<int>(n);
         s.nl = dalloc<int>((size_t)s.nl_cap * n);
         s.nl_cnt = dalloc<int>(n);
         s.nl_cand = dalloc<int>(n);
         s.xbuild = dalloc<double>(n);
         s.ybuild = dalloc<double>(n);
         s.fsr = dalloc<double2>(n);
-        s.scan_bsum = dalloc<int>(verlet_scan_blocks(s.nl_ncell));
     }
     s.acc = dalloc<unsigned long long>(N_ACC);
     if (hipHostMalloc((void **)&s.hctl, sizeof(int) * N_CTL, hipHostMallocDefault) != hipSuccess)
@@ -2053,6 +2050,10 @@ int init_impl(Sim &s, int R, const int32_t *n_per, const double *xy, const doubl
     check(hipMemcpyAsync(s.sorted_id, sorted.data(), sizeof(int) * n, hipMemcpyHostToDevice, s.stream), "sorted");
     check(hipMemcpyAsync(s.pos_of, pos.data(), sizeof(int) * n, hipMemcpyHostToDevice, s.stream), "pos");
     check(hipMemcpyAsync(s.Kd, s.K.data(), sizeof(double) * s.S * s.S, hipMemcpyHostToDevice, s.stream), "K");
+    if (s.use_nl) {
+        check(hipMemsetAsync(s.cell_rows, 0, sizeof(int) * verlet_row_ints(s.nl_ncell), s.stream), "cell rows");
+        check(hipMemsetAsync(s.cell_more, 0, sizeof(int) * s.nl_ncell, s.stream), "cell chains");
+    }
     check(hipMemsetAsync(s.claim, 0, sizeof(unsigned long long) * s.T, s.stream), "claim");
     check(hipMemsetAsync(s.tri_stamp, 0, sizeof(int) * s.T, s.stream), "tri_stamp");
     check(hipMemsetAsync(s.edge_stamp, 0, sizeof(int) * s.H, s.stream), "edge_stamp");

@@ -142,3 +142,30 @@ def test_full_size_c3_verlet_overlap():
     assert step == 3 and np.all(x >= 1.0) and np.all(x <= w.L - 1.0)
     assert count_overlaps(x) == 0
     assert st["overlap_rounds_total"] > 0
+
+
+@pytest.mark.parametrize("periodic", [False, True])
+@pytest.mark.parametrize("spacing", [1.2, 1.1, 0.9])
+def test_lists_of_crowded_and_empty_cells_match_oracle(periodic, spacing):
+    """Cells of six to a dozen disks (a cell's row holds seven, the rest hang on its chain) beside cells of one or two
+    and empty ones, with the lists rebuilt inside queued steps."""
+    side = int(21.0 / spacing)
+    a = np.array([[1.0 + spacing * i, 1.0 + spacing * j] for i in range(side) for j in range(side)])
+    b = np.array([[24.0 + 2.2 * i, 1.0 + 2.2 * j] for i in range(10) for j in range(9)])
+    rng = np.random.default_rng(7)
+    xy = np.concatenate([a, b]) + rng.uniform(0.0, 0.15, (len(a) + len(b), 2))
+    n, L = len(xy), 48.0
+    per_cell = np.bincount((xy[:, 1] // 3.0).astype(int) * 16 + (xy[:, 0] // 3.0).astype(int), minlength=256)
+    assert per_cell.max() >= (7 if spacing > 1.15 else 8) and (per_cell == 0).any() and (per_cell == 1).any()
+    kw = dict(L=L, dt=2e-3, seed=3, kind="screened", A=1.0, lam=0.5, cutoff=2.5, skin=0.5, periodic=periodic,
+              overlap="verlet")
+    sp, K, rad = np.zeros(n, np.int32), np.array([[0.1]]), np.full(n, 0.3)
+    g = binding.Sim(xy, rad, sp, None, K, **kw)
+    g.set_graph_mode(True)
+    fo = oracle.forces(xy, sp, K, kind="screened", A=1.0, lam=0.5, cutoff=2.5, period=L if periodic else 0.0)
+    assert np.abs(g.forces() - fo).max() <= 1e-12 * _scale(fo)
+    o = oracle.OracleSim(xy, rad, sp, None, K, **{k: v for k, v in kw.items() if k != "skin"})
+    g.step(24)
+    o.step(24)
+    assert rel_err(g.state()[0], o.state()[0]) <= 1e-9
+    assert g.state()[3]["verlet_rebuilds"] >= 3
