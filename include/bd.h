@@ -388,15 +388,17 @@ int bd_kernel_time(bd_sim *sim, double *force_ms, int64_t *force_launches);
  * q = 2, no cutoff); BD_ERR_INVALID_ARG otherwise.
  *
  * bd_adjoint_begin advances nsteps >= 1 steps exactly like bd_step while
- * keeping a device copy of the state every checkpoint_every >= 1 steps; the
- * handle is then at the final step (read it with bd_get_state).
+ * keeping a device copy of the state every checkpoint_every >= 1 steps, and
+ * records the last segment as it runs; the handle is then at the final step
+ * (read it with bd_get_state).
  *
  * bd_adjoint_backward takes grad_xy = dL/dx at the final step (2n doubles,
  * caller order) and writes grad_xy0 = dL/dx at the first step through the
  * dynamics (2n doubles, may be NULL) and grad_K = dL/dK (S*S doubles,
  * row-major, may be NULL).  It replays each segment between checkpoints
- * from its checkpoint (recomputation instead of storing every step), records
- * what the reverse sweep needs, and sweeps it backwards; the handle is left
+ * from its checkpoint (recomputation instead of storing every step) unless
+ * the record holds it, records what the reverse sweep needs, and sweeps it
+ * backwards; the handle is left
  * at the final step with its counters unchanged.  It may be called again
  * with another grad_xy.  Device memory: one checkpoint per segment, the
  * positions of one segment and, when they fit in 8 GiB, the force partial

@@ -186,6 +186,7 @@ struct AdjState {
     int every = 0;
     std::vector<Checkpoint> ck;            // at t0, t0 + every, ..., then the final state
     Tape tape;
+    int tape_seg = -1;                     // segment the tape holds; -1: none
     double2 *lam = nullptr;                // adjoint of the positions
     double4 *nub = nullptr;                // round scratch by disk id: nu, position before the round
     double4 *pj4 = nullptr;                // sorted (x, y, lambda) of one step

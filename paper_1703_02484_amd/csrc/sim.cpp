@@ -1006,14 +1006,21 @@ int one_step(Sim &s) {
         check(hipMemcpyAsync(tp.px + off, s.x, bytes, hipMemcpyDeviceToDevice, s.stream), "tape x");
         check(hipMemcpyAsync(tp.py + off, s.y, bytes, hipMemcpyDeviceToDevice, s.stream), "tape y");
     }
-    compute_forces(s);
-    if (s.adj.tape.on && s.adj.tape.phi) {   // adjoint tape: the step's force partial sums
-        const size_t bytes = (size_t)s.part_cap * (s.fp32 ? sizeof(float2) : sizeof(double2));
-        check(hipMemcpyAsync((char *)s.adj.tape.phi + (size_t)s.adj.tape.step_idx * bytes, s.part, bytes,
-                             hipMemcpyDeviceToDevice, s.stream),
-              "tape phi");
+    {
+        // adjoint tape: the force's partial sums of the step are made in their place on the tape
+        struct PartOnTape {
+            Sim &s;
+            void *part;
+            explicit PartOnTape(Sim &sim) : s(sim), part(sim.part) {
+                const size_t bytes = (size_t)s.part_cap * (s.fp32 ? sizeof(float2) : sizeof(double2));
+                if (s.adj.tape.on && s.adj.tape.phi)
+                    s.part = (char *)s.adj.tape.phi + (size_t)s.adj.tape.step_idx * bytes;
+            }
+            ~PartOnTape() { s.part = part; }
+        } on_tape(s);
+        compute_forces(s);
+        launch_em(s);
     }
-    launch_em(s);
     plan.b = s.budget;
     if (s.ovl_method == 1) {
         plan.overlaps = s.budget.overlaps;
@@ -2182,36 +2189,13 @@ void adj_free(Sim &s) {
     a = AdjState();
 }
 
-int adjoint_begin(Sim &s, int64_t nsteps, int every) {
-    if (!s.kind_fast || s.use_nl) {
-        s.last_error = "the adjoint covers the all-pairs inverse-square force only";
-        return BD_ERR_INVALID_ARG;
-    }
-    if (s.p.max_dt_halvings > 0) {
-        s.last_error = "the adjoint does not cover steps halved after an edge reversal";
-        return BD_ERR_INVALID_ARG;
-    }
-    if (s.period > 0.0) {
-        s.last_error = "the adjoint covers the box with walls only";
-        return BD_ERR_INVALID_ARG;
-    }
-    adj_free(s);
+// Buffers of a rollout; on failure the caller frees them.
+void adj_alloc(Sim &s, int64_t nsteps, int every) {
     AdjState &a = s.adj;
-    a.t0 = s.step;
     a.nsteps = nsteps;
     a.every = every;
-    const int nseg = (int)((nsteps + every - 1) / every);
-    a.ck.resize(nseg + 1);
+    a.ck.resize((nsteps + every - 1) / every + 1);
     for (auto &c : a.ck) ck_alloc(s, c);
-    for (int64_t t = 0; t < nsteps; ++t) {
-        if (t % every == 0) ck_save(s, a.ck[t / every]);
-        int rc = one_step(s);
-        if (rc != BD_OK) {
-            adj_free(s);
-            return rc;
-        }
-    }
-    ck_save(s, a.ck[nseg]);
     const int n = s.n;
     a.lam = dalloc<double2>(n);
     a.nub = dalloc<double4>(n);
@@ -2235,6 +2219,91 @@ int adjoint_begin(Sim &s, int64_t nsteps, int every) {
             tp.phi = nullptr;
         }
     }
+}
+
+// A recording; the tape is off when it goes.
+struct Recording {
+    Sim &s;
+    int seg = -1;
+    bool grow = false;       // the tape was too small
+    bool partners = false;   // a disk had more partners in one round than it records
+    explicit Recording(Sim &sim) : s(sim) {}
+    ~Recording() { s.adj.tape.on = false; }
+};
+
+void tape_start(Sim &s, int seg, int len, Recording &r) {
+    Tape &tp = s.adj.tape;
+    s.adj.tape_seg = -1;
+    r.seg = seg;
+    tp.on = true;
+    tp.ent_base = 0;
+    tp.dir_base = 0;
+    tp.step_dir_end.assign(len, 0);
+}
+
+// Step t of the segment being recorded.
+int record_step(Sim &s, int t, Recording &r) {
+    Tape &tp = s.adj.tape;
+    tp.step_idx = t;
+    const int64_t continued = s.st.host_continued;
+    int rc = one_step(s);
+    if (rc != BD_OK) return rc;
+    if (s.st.host_continued != continued) read_ctl(s);   // else the step's own copy still stands
+    const int *h = s.hctl;
+    if (h[K_TAPE_OVF] & 2) r.partners = true;
+    if (h[K_TAPE_OVF] & 1) r.grow = true;
+    tp.ent_base += h[K_TAPE_ENT];
+    tp.dir_base += h[K_TAPE_DIR];
+    tp.step_dir_end[t] = tp.dir_base;
+    return BD_OK;
+}
+
+// Ends a recording: the tape then holds its segment, or has grown for the next attempt.
+void tape_end(Sim &s, const Recording &r) {
+    Tape &tp = s.adj.tape;
+    tp.on = false;
+    if (r.grow)
+        tape_alloc_rounds(tp, std::max(tp.cap_ent, 2 * tp.ent_base), std::max(tp.cap_dir, 2 * tp.dir_base));
+    else if (!r.partners)
+        s.adj.tape_seg = r.seg;
+}
+
+int adjoint_begin(Sim &s, int64_t nsteps, int every) {
+    if (!s.kind_fast || s.use_nl) {
+        s.last_error = "the adjoint covers the all-pairs inverse-square force only";
+        return BD_ERR_INVALID_ARG;
+    }
+    if (s.p.max_dt_halvings > 0) {
+        s.last_error = "the adjoint does not cover steps halved after an edge reversal";
+        return BD_ERR_INVALID_ARG;
+    }
+    if (s.period > 0.0) {
+        s.last_error = "the adjoint covers the box with walls only";
+        return BD_ERR_INVALID_ARG;
+    }
+    // a rollout of the same shape as the last one keeps its buffers
+    AdjState &a = s.adj;
+    if (!a.ready || a.nsteps != nsteps || a.every != every) {
+        adj_free(s);
+        adj_alloc(s, nsteps, every);
+    }
+    a.ready = false;
+    a.t0 = s.step;
+    const int nseg = (int)a.ck.size() - 1;
+    // the last segment, which the sweep needs first, is recorded as it runs
+    const int64_t last = (int64_t)(nseg - 1) * every;
+    Recording tape(s);
+    for (int64_t t = 0; t < nsteps; ++t) {
+        if (t % every == 0) ck_save(s, a.ck[t / every]);
+        if (t == last) tape_start(s, nseg - 1, (int)(nsteps - last), tape);
+        int rc = t < last ? one_step(s) : record_step(s, (int)(t - last), tape);
+        if (rc != BD_OK) {
+            adj_free(s);
+            return rc;
+        }
+    }
+    tape_end(s, tape);
+    ck_save(s, a.ck[nseg]);
     a.ready = true;
     return BD_OK;
 }
@@ -2243,36 +2312,20 @@ int adjoint_begin(Sim &s, int64_t nsteps, int every) {
 // or an error (state left at the segment's end).
 int record_segment(Sim &s, int seg, int len) {
     AdjState &a = s.adj;
-    Tape &tp = a.tape;
     for (int attempt = 0; attempt < 3; ++attempt) {
         ck_restore(s, a.ck[seg]);
-        tp.on = true;
-        tp.ent_base = 0;
-        tp.dir_base = 0;
-        tp.step_dir_end.assign(len, 0);
-        bool grow = false;
+        Recording tape(s);
+        tape_start(s, seg, len, tape);
         for (int t = 0; t < len; ++t) {
-            tp.step_idx = t;
-            int rc = one_step(s);
-            if (rc != BD_OK) {
-                tp.on = false;
-                return rc;
-            }
-            read_ctl(s);
-            const int *h = s.hctl;
-            if (h[K_TAPE_OVF] & 2) {
-                tp.on = false;
+            int rc = record_step(s, t, tape);
+            if (rc != BD_OK) return rc;
+            if (tape.partners) {
                 s.last_error = "a disk overlapped more partners in one round than the adjoint tape records";
                 return BD_ERR_INVALID_ARG;
             }
-            if (h[K_TAPE_OVF]) grow = true;
-            tp.ent_base += h[K_TAPE_ENT];
-            tp.dir_base += h[K_TAPE_DIR];
-            tp.step_dir_end[t] = tp.dir_base;
         }
-        tp.on = false;
-        if (!grow) return BD_OK;
-        tape_alloc_rounds(tp, std::max(tp.cap_ent, 2 * tp.ent_base), std::max(tp.cap_dir, 2 * tp.dir_base));
+        tape_end(s, tape);
+        if (a.tape_seg == seg) return BD_OK;
     }
     s.last_error = "adjoint tape could not be sized";
     return BD_ERR_DEVICE;
@@ -2304,7 +2357,7 @@ int adjoint_backward(Sim &s, const double *gT, double *g0, double *gK, bool dev 
     std::vector<int2> dir;
     for (int seg = nseg - 1; seg >= 0 && rc == BD_OK; --seg) {
         const int len = (int)std::min<int64_t>(a.every, a.nsteps - (int64_t)seg * a.every);
-        rc = record_segment(s, seg, len);
+        if (a.tape_seg != seg) rc = record_segment(s, seg, len);
         if (rc != BD_OK) break;
         dir.resize(tp.dir_base);
         if (tp.dir_base > 0)

@@ -264,3 +264,34 @@ def test_spec_named_calls_equal_the_library_calls():
     assert step.value == 4 and np.array_equal(xy, c.state()[0])
     lib.bd_batch_destroy(d._h)
     d._h = None
+
+
+@pytest.mark.parametrize("steps, every", [(7, 3), (6, 3), (4, 9)])
+def test_recorded_last_segment_equals_replayed(steps, every):
+    """The last segment is recorded as it runs: a second sweep (which replays it where there are others), a sweep after
+    more steps, and rollouts of the same and of another shape on the same handle give the same bits."""
+    w = synth.make("C5", n=700)
+    lam = np.random.default_rng(1).normal(size=(w.n, 2))
+
+    def fresh(skip, n, e):
+        g = binding.Sim.from_workload(w)
+        if skip:
+            g.step(skip)
+        g.adjoint_begin(n, e)
+        return g.adjoint_backward(lam)
+
+    g = binding.Sim.from_workload(w)
+    g.adjoint_begin(steps, every)
+    first = g.adjoint_backward(lam)
+    again = g.adjoint_backward(lam)
+    g.step(2)
+    later = g.adjoint_backward(lam)   # back at the end of the rollout
+    for got in (again, later):
+        assert np.array_equal(got[0], first[0]) and np.array_equal(got[1], first[1])
+    assert g.state()[2] == steps
+    g.adjoint_begin(steps, every)   # the same shape, from the first one's end
+    got, ref = g.adjoint_backward(lam), fresh(steps, steps, every)
+    assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
+    g.adjoint_begin(steps + 1, every)
+    got, ref = g.adjoint_backward(lam), fresh(2 * steps, steps + 1, every)
+    assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
