@@ -3,8 +3,8 @@
 // for positions and species that live in device memory owned by the caller,
 // with no simulation handle.
 //
-// Two layouts, chosen from n, the precision and whether there is a cutoff
-// (pf_plan), bound by the VALU in both:
+// Three layouts, chosen from n, the precision and whether there is a cutoff
+// (pf_plan); rows and tiles are bound by the VALU:
 //   rows   (few particles) one wavefront per particle i, its lanes over the
 //          j; the 64 partial sums are added across the wavefront in FP64.  One launch, no working memory: with few
 //          particles the time is the launch and the chain of one lane's j.
@@ -16,9 +16,14 @@
 //          the pair loop: it weights the sum over each species' part of the
 //          block.  part[split][i] holds the weighted sums; a second kernel
 //          adds the J splits in FP64 in split order.
-// Neither depends on the launch timing.  The only device memory beyond the
+//   cells  (a cutoff) the particles are put into square cells of the cutoff's
+//          side and each is taken against its 3 x 3 cells: launches of a few
+//          us each instead of n^2 distance tests.  Positions it cannot bin, and
+//          ones so crowded that most pairs would be tested anyway, go to the
+//          tiles, which are launched behind it and do nothing otherwise.
+// None depends on the launch timing.  The only device memory beyond the
 // caller's inputs and outputs is `part` (J * n * 2 values of the working
-// precision).
+// precision) or the cells' arrays.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -309,9 +314,11 @@ __device__ __forceinline__ void pf_block_cut(const PfStage<T> &st, short (&hit)[
 template <typename T, int LAW, bool CUT, int P>
 __global__ __launch_bounds__(kPfBlock) void k_pf_tiles(int n, int J, const double *__restrict__ xy,
                                                        const int32_t *__restrict__ species, PfLaw law,
-                                                       typename Vec2<T>::type *__restrict__ part) {
+                                                       typename Vec2<T>::type *__restrict__ part,
+                                                       const int *__restrict__ crowded) {
     using T2 = typename Vec2<T>::type;
     __shared__ PfStage<T> st;
+    if (crowded && !*crowded) return;   // the cells have done it
     __shared__ T kw[BD_MAX_SPECIES * BD_MAX_SPECIES];
     __shared__ short hit[CUT ? P : 1][CUT ? kPfHits : 1][CUT ? kPfBlock : 1];
     const int S = law.S;
@@ -399,9 +406,10 @@ __global__ __launch_bounds__(kPfBlock) void k_pf_tiles(int n, int J, const doubl
 
 // f[2i], f[2i+1] = sum over the splits in split order, in FP64.
 template <typename T>
-__global__ void k_pf_reduce(int n, int J, const typename Vec2<T>::type *__restrict__ part, double *__restrict__ f) {
+__global__ void k_pf_reduce(int n, int J, const typename Vec2<T>::type *__restrict__ part, double *__restrict__ f,
+                            const int *__restrict__ crowded) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    if (i >= n || (crowded && !*crowded)) return;
     double fx = 0.0, fy = 0.0;
 #pragma unroll 8
     for (int s = 0; s < J; ++s) {
@@ -411,6 +419,209 @@ __global__ void k_pf_reduce(int n, int J, const typename Vec2<T>::type *__restri
     }
     f[2 * (size_t)i] = fx;
     f[2 * (size_t)i + 1] = fy;
+}
+
+// ---------------------------------------------------------------- cells
+// Cells of side h, a hair over the cutoff, on a torus of kGrid x kGrid: cell (floor(x / h) mod kGrid, ...), so no
+// bounding box is needed; particles a multiple of kGrid cells apart share cells and fail the distance test.  Two
+// particles whose working-precision separation passes the cutoff test lie in neighbouring cells: the hair is wider
+// than the rounding of that test and of x / h up to kMaxCell cells from the origin.  Inside a cell the particles are
+// in ascending order of their index, so the sums do not depend on scheduling.
+constexpr int kGrid = 128;
+constexpr int kCells = kGrid * kGrid;   // 64 KiB of counters in LDS
+constexpr double kMaxCell = 1048576.0;
+constexpr int kBinBlock = 1024;
+
+template <typename T>
+struct PfCells {
+    using T2 = typename Vec2<T>::type;
+    int *crowded;           // set: the tiles run instead
+    int *start;             // [kCells + 1]
+    int *ids;               // [n] particles by cell, in any order
+    int *sid, *sp;          // [n] particle and species by cell, ascending
+    unsigned short *cell;   // [n] cell of each particle
+    T2 *pos;                // [n] as sid
+    double inv_h;
+};
+
+template <typename T>
+__device__ __forceinline__ int pf_cell(T x, T y, double inv_h, bool &ok) {
+    const double sx = (double)x * inv_h, sy = (double)y * inv_h;
+    ok = fabs(sx) < kMaxCell && fabs(sy) < kMaxCell;   // neither for what is not a number
+    return ok ? ((int)floor(sy) & (kGrid - 1)) * kGrid + ((int)floor(sx) & (kGrid - 1)) : 0;
+}
+
+// Counting sort by cell in one workgroup: at these sizes a launch costs more than the spread over more compute units
+// would save.  kBinAhead particles of a thread are in flight.
+constexpr int kBinAhead = 8;
+
+template <typename T>
+__global__ __launch_bounds__(kBinBlock) void k_pf_bin(int n, const double *__restrict__ xy, PfCells<T> a) {
+    __shared__ int cnt[kCells];
+    __shared__ int wsum[kBinBlock / 64], bad;
+    __shared__ unsigned long long crowd;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int c = tid; c < kCells; c += kBinBlock) cnt[c] = 0;
+    if (tid == 0) {
+        bad = 0;
+        crowd = 0;
+    }
+    __syncthreads();
+    for (int i0 = tid; i0 < n; i0 += kBinBlock * kBinAhead) {
+        T x[kBinAhead], y[kBinAhead];
+#pragma unroll
+        for (int u = 0; u < kBinAhead; ++u) {
+            const int i = min(i0 + u * kBinBlock, n - 1);
+            x[u] = (T)xy[2 * (size_t)i];
+            y[u] = (T)xy[2 * (size_t)i + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < kBinAhead; ++u) {
+            const int i = i0 + u * kBinBlock;
+            if (i >= n) continue;
+            bool ok;
+            const int c = pf_cell(x[u], y[u], a.inv_h, ok);
+            if (!ok) bad = 1;
+            a.cell[i] = (unsigned short)c;
+            atomicAdd(&cnt[c], 1);
+        }
+    }
+    __syncthreads();
+    constexpr int kOwn = kCells / kBinBlock;   // consecutive cells of a thread
+    int own[kOwn], sum = 0;
+    unsigned long long sq = 0;
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u) {
+        own[u] = cnt[tid * kOwn + u];
+        sum += own[u];
+        sq += (unsigned long long)own[u] * own[u];
+    }
+    int incl = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(incl, off);
+        if (lane >= off) incl += v;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    if (sq) atomicAdd(&crowd, sq);
+    __syncthreads();
+    int at = incl - sum;
+    for (int w = 0; w < wave; ++w) at += wsum[w];
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u) {
+        a.start[tid * kOwn + u] = at;
+        cnt[tid * kOwn + u] = at;
+        at += own[u];
+    }
+    if (tid == kBinBlock - 1) a.start[kCells] = n;
+    // nine cells around each particle: about nine times the sum of the squared counts
+    const bool crowded = bad || 27 * crowd > (unsigned long long)n * n;
+    if (tid == 0) *a.crowded = crowded ? 1 : 0;
+    if (crowded) return;   // uniform in the workgroup
+    __syncthreads();
+    for (int i0 = tid; i0 < n; i0 += kBinBlock * kBinAhead) {
+        int c[kBinAhead];
+#pragma unroll
+        for (int u = 0; u < kBinAhead; ++u) c[u] = a.cell[min(i0 + u * kBinBlock, n - 1)];
+#pragma unroll
+        for (int u = 0; u < kBinAhead; ++u)
+            if (i0 + u * kBinBlock < n) a.ids[atomicAdd(&cnt[c[u]], 1)] = i0 + u * kBinBlock;
+    }
+}
+
+// Each particle to its place: its cell's start and the number of smaller indices in the cell.
+template <typename T>
+__global__ __launch_bounds__(kPfBlock) void k_pf_place(int n, const double *__restrict__ xy,
+                                                       const int32_t *__restrict__ species, PfCells<T> a) {
+    const int e = blockIdx.x * kPfBlock + threadIdx.x;
+    if (e >= n || *a.crowded) return;
+    const int i = a.ids[e], c = a.cell[i];
+    const int b = a.start[c], end = a.start[c + 1];
+    int at = b;
+#pragma unroll 8
+    for (int k = b; k < end; ++k) at += a.ids[k] < i ? 1 : 0;
+    typename Vec2<T>::type v;
+    v.x = (T)xy[2 * (size_t)i];
+    v.y = (T)xy[2 * (size_t)i + 1];
+    a.pos[at] = v;
+    a.sid[at] = i;
+    a.sp[at] = species[i];
+}
+
+// LANES lanes per particle, each every LANES-th one of its 3 x 3 cells (three runs of consecutive particles, or up to
+// six where the torus closes).  A third of them is in range and a law costs many times the test, so hits are noted and
+// evaluated together as in the tiles; a lane's sum keeps their order, the lanes are added in FP64.
+// Waits for its chains of loads, so small calls take more lanes: 20,011 particles, screened law, FP64, whole call 61 us
+// with 4 lanes, 50 with 8, 47 with 16, 51 with 32 (140 us by tiles); 65,536 109, 104, 110 and 126 (970 by tiles).
+constexpr int kCellsWide = 32768;   // 16 lanes up to here, 8 above
+
+template <typename T, int LAW, int LANES>
+__global__ __launch_bounds__(kPfBlock) void k_pf_cells(int n, PfCells<T> a, PfLaw law, double *__restrict__ f) {
+    __shared__ T kw[BD_MAX_SPECIES * BD_MAX_SPECIES];
+    __shared__ int hit[kPfHits][kPfBlock];
+    if (*a.crowded) return;
+    const int S = law.S, tid = threadIdx.x;
+    for (int k = tid; k < S * S; k += kPfBlock) kw[k] = (T)law.K[k];
+    __syncthreads();
+    const PfConst<T> c(law);
+    const int g = blockIdx.x * (kPfBlock / LANES) + tid / LANES, lane = tid & (LANES - 1);
+    const int i = min(g, n - 1);
+    const auto pi = a.pos[i];
+    const int si = a.sp[i] * S;
+    bool ok;
+    const int ci = pf_cell(pi.x, pi.y, a.inv_h, ok), cx = ci & (kGrid - 1), cy = ci / kGrid;
+    T ax = (T)0, ay = (T)0;
+    int cnt = 0;
+    auto evaluate = [&]() {
+        for (int h = 0; __ballot(h < cnt) != 0; ++h) {
+            if (h < cnt) {
+                const int k = hit[h][tid];
+                const auto q = a.pos[k];
+                const T dx = pi.x - q.x, dy = pi.y - q.y;
+                const int sj = a.sp[k];   // out of range: not counted, as in the tiles
+                const T w = (unsigned)sj < (unsigned)S ? kw[si + sj] * law_factor<LAW>(dx * dx + dy * dy, c) : (T)0;
+                ax += dx * w;
+                ay += dy * w;
+            }
+        }
+        cnt = 0;
+    };
+    auto run = [&](int k, int end) {   // every lane is here; a run may be empty
+        constexpr int kU = 4;
+        for (; __ballot(k < end) != 0; k += kU * LANES) {
+            typename Vec2<T>::type q[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) q[u] = a.pos[k + u * LANES < end ? k + u * LANES : i];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int ku = k + u * LANES;
+                const T dx = pi.x - q[u].x, dy = pi.y - q[u].y;
+                const bool in = ku < end && ku != i && !(dx * dx + dy * dy > c.cut2);
+                if (in) hit[cnt++][tid] = ku;
+                if (__ballot(cnt == kPfHits) != 0) evaluate();
+            }
+        }
+    };
+    const bool split = cx == 0 || cx == kGrid - 1;
+    for (int r = -1; r <= 1; ++r) {
+        const int *row = a.start + ((cy + r) & (kGrid - 1)) * kGrid;
+        const int x0 = cx == 0 ? 0 : cx - 1, x1 = cx == kGrid - 1 ? cx : cx + 1;
+        run(row[x0] + lane, row[x1 + 1]);
+        if (__ballot(split) != 0) {   // the cell on the other side
+            const int x = cx == 0 ? kGrid - 1 : 0;
+            run(row[x] + lane, split ? row[x + 1] : 0);
+        }
+    }
+    evaluate();
+    double fx = (double)ax, fy = (double)ay;
+    for (int off = 1; off < LANES; off <<= 1) {
+        fx += __shfl_xor(fx, off);
+        fy += __shfl_xor(fy, off);
+    }
+    if (lane == 0 && g < n) {
+        const size_t o = 2 * (size_t)a.sid[i];
+        f[o] = fx;
+        f[o + 1] = fy;
+    }
 }
 
 size_t pf_value_bytes(int precision) { return precision == BD_PREC_FP32 ? sizeof(float2) : sizeof(double2); }
@@ -441,12 +652,38 @@ int pf_check(int32_t n, const double *xy, const int32_t *species, const bd_force
 
 // How a call runs; depends on n, the precision and the law only.
 struct PfPlan {
-    bool rows;   // rows layout
-    int J;       // tiles layout: j splits
+    bool rows;    // rows layout
+    bool cells;   // cells, with the tiles behind them
+    int J;        // tiles layout: j splits
     size_t bytes;
 };
 
+constexpr size_t pf_align(size_t b) { return (b + 255) / 256 * 256; }
+
+// Places of the cells' arrays in the working memory, the flag first (the tiles' sums, if it comes to them, take what
+// follows it); returns the bytes.
+template <typename T>
+size_t pf_cells_at(int n, const PfLaw &law, unsigned char *base, PfCells<T> &a) {
+    size_t o = 256;
+    auto take = [&](auto *&p, size_t count) {
+        p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(base + o);
+        o += pf_align(count * sizeof(*p));
+    };
+    a.crowded = reinterpret_cast<int *>(base);
+    take(a.start, kCells + 1);
+    take(a.ids, n);
+    take(a.sid, n);
+    take(a.sp, n);
+    take(a.cell, n);
+    take(a.pos, n);
+    a.inv_h = 1.0 / (law.cutoff * (sizeof(T) == 4 ? 1.0 + 1e-5 : 1.0 + 1e-9));
+    return o;
+}
+
 constexpr size_t kPfPartBytes = size_t(32) << 20;   // most working memory of a call that more than one split needs
+
+// Most particles of the cells layout: its sort is one workgroup's, its arrays stay below kPfPartBytes.
+constexpr int kCellsMax = 262144;
 
 // Particles i per lane of the tiles: one LDS read of a j serves them all.  Four for the shortest pair loop
 // (FP32 inverse square: 9 instructions); two where a pair is longer or notes its hits.
@@ -458,12 +695,14 @@ PfPlan pf_plan(int n, int precision, const PfLaw &law) {
     const bool cut = law.cutoff > 0.0;
     // Rows up to these sizes.  Measured, rows against tiles, two species, us: no cutoff, inverse square, FP64
     // 27 / 33 at 5,000, 36 / 47 at 6,000, 60 / 49 at 8,192, FP32 25 / 34 at 6,000, 49 / 35 at 8,192; screened FP64
-    // 72 / 80 at 5,000, 165 / 137 at 8,192.  With a cutoff (12, 0.4 of the area covered), where rows evaluates the
-    // law for the lanes out of range too: screened FP64 43 / 47 at 3,300, 52 / 44 at 4,096, FP32 32 / 43 at 4,096,
-    // inverse square 22 / 42 at 4,096.
-    p.rows = n <= (cut ? 4096 : 6144);
+    // 72 / 80 at 5,000, 165 / 137 at 8,192.  Rows against cells (cutoff 12, 0.45 of the area covered, three species),
+    // where rows evaluates the law for the lanes out of range too: inverse square FP64 23 / 27 at 4,000, FP32 22 / 29;
+    // screened FP64 20 / 30 at 2,000, 36 / 30 at 3,000, FP32 26 / 33 at 3,000, 37 / 33 at 4,000.
+    const bool q2 = law.kind == BD_FORCE_POWER && law.q == 2.0;
+    p.rows = n <= (!cut ? 6144 : q2 ? 4096 : precision == BD_PREC_FP32 ? 3600 : 2800);
     if (p.rows) return p;
-    const bool four = precision == BD_PREC_FP32 && law.kind == BD_FORCE_POWER && law.q == 2.0 && !cut;
+    p.cells = cut && n <= kCellsMax;
+    const bool four = precision == BD_PREC_FP32 && q2 && !cut;
     const long long per_group = (long long)kPfBlock * (four ? 4 : 2), nb = (n + per_group - 1) / per_group;
     // enough splits to fill the device, of at least kPfBlock j, as far as the working memory reaches
     long long J = (kPfTargetGroups + nb - 1) / nb;
@@ -472,6 +711,14 @@ PfPlan pf_plan(int n, int precision, const PfLaw &law) {
                   (long long)(kPfPartBytes / row)});
     p.J = (int)std::max(1ll, J);
     p.bytes = p.J * row;
+    if (p.cells) {
+        PfCells<float> a32;
+        PfCells<double> a64;
+        const size_t c = precision == BD_PREC_FP32 ? pf_cells_at(n, law, nullptr, a32) : pf_cells_at(n, law, nullptr, a64);
+        const size_t most = kPfPartBytes - 256;
+        p.J = std::min(p.J, (int)(most / row));
+        p.bytes = std::max(256 + p.J * row, c);
+    }
     return p;
 }
 
@@ -488,8 +735,26 @@ void pf_launch(int n, const double *xy, const int32_t *species, const PfLaw &law
     }
     constexpr int P = pf_per_lane<T, LAW, CUT>();
     const dim3 grid((n + kPfBlock * P - 1) / (kPfBlock * P), p.J);
-    hipLaunchKernelGGL((k_pf_tiles<T, LAW, CUT, P>), grid, block, 0, stream, n, p.J, xy, species, law, (T2 *)part);
-    hipLaunchKernelGGL(k_pf_reduce<T>, dim3((n + 255) / 256), dim3(256), 0, stream, n, p.J, (const T2 *)part, f_out);
+    const int *crowded = nullptr;
+    if constexpr (CUT) {
+        if (p.cells) {
+            PfCells<T> a;
+            pf_cells_at(n, law, (unsigned char *)part, a);
+            hipLaunchKernelGGL(k_pf_bin<T>, dim3(1), dim3(kBinBlock), 0, stream, n, xy, a);
+            hipLaunchKernelGGL(k_pf_place<T>, dim3((n + kPfBlock - 1) / kPfBlock), block, 0, stream, n, xy, species, a);
+            auto sums = [&](auto kern, int lanes) {
+                const int per = kPfBlock / lanes;
+                hipLaunchKernelGGL(kern, dim3((n + per - 1) / per), block, 0, stream, n, a, law, f_out);
+            };
+            n <= kCellsWide ? sums(k_pf_cells<T, LAW, 16>, 16) : sums(k_pf_cells<T, LAW, 8>, 8);
+            crowded = a.crowded;
+            part = (unsigned char *)part + 256;
+        }
+    }
+    hipLaunchKernelGGL((k_pf_tiles<T, LAW, CUT, P>), grid, block, 0, stream, n, p.J, xy, species, law, (T2 *)part,
+                       crowded);
+    hipLaunchKernelGGL(k_pf_reduce<T>, dim3((n + 255) / 256), dim3(256), 0, stream, n, p.J, (const T2 *)part, f_out,
+                       crowded);
 }
 
 template <typename T>

@@ -119,3 +119,68 @@ def test_pair_forces_dev_singular_positions(n, law, fp32):
     f = binding.pair_forces_dev(torch.from_numpy(xy).cuda(), sp, K, fp32=fp32, **LAWS[law]).cpu().numpy()
     rest = np.arange(n) != 5
     assert np.isnan(f[:, 0]).all() and np.isfinite(f[rest, 1]).all()
+
+
+@pytest.mark.parametrize("law", ["q2", "q6", "screened"])
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("n", [2801, 3601, 4097, 32768, 32769])
+def test_pair_forces_dev_cells_match_oracle(law, fp32, n):
+    """With a cutoff: cells around the origin (both signs of the coordinates), more of them than the grid has (the
+    torus closes), and beside an empty half; three species; the edges of the layout's sizes."""
+    rng = np.random.default_rng(n)
+    m = int(np.ceil(np.sqrt(n)))
+    k = rng.permutation(m * m)[:n]
+    xy = np.stack([k % m, k // m], 1) * 2.5 + rng.uniform(-0.4, 0.4, (n, 2)) - [0.5 * 2.5 * m, 300.0]
+    xy[xy[:, 0] > 0.0] += [5000.0, 0.0]
+    species = rng.integers(0, 3, n).astype(np.int32)
+    K = np.array([[1e-2, -5e-3, 4e-3], [2e-3, 1e-2, 0.0], [-1e-3, 3e-3, 7e-3]])
+    kw = dict(cutoff=7.0, **{"q2": dict(kind="power", q=2.0), "q6": dict(kind="power", q=6.0),
+                             "screened": dict(kind="screened", A=1.0, lam=2.0)}[law])
+    import torch
+
+    f = binding.pair_forces_dev(torch.from_numpy(xy).cuda(), torch.from_numpy(species).cuda(), K, fp32=fp32, **kw)
+    g = binding.pair_forces_dev(torch.from_numpy(xy).cuda(), torch.from_numpy(species).cuda(), K, fp32=fp32,
+                                noalloc=True, **kw)
+    f = f.cpu().numpy()
+    assert np.array_equal(f, g.cpu().numpy())   # the order in which particles reach their cells does not show
+    idx = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, 400)])).astype(np.int32)
+    # FP32 rounds the positions (to 2.4e-4 at 5,000) and a pair within that of the cutoff may fall on either side
+    fo = oracle.forces(xy.astype(np.float32).astype(np.float64) if fp32 else xy, species, K, idx=idx, **kw)
+    edge = np.zeros(len(idx), bool)
+    if fp32:
+        xr = xy.astype(np.float32).astype(np.float64)
+        for a, i in enumerate(idx):
+            d = np.hypot(*(xr - xr[i]).T)
+            edge[a] = (np.abs(d - 7.0) < 1e-3).any()
+        assert edge.mean() < 0.5
+    tol = 1e-4 if fp32 else 1e-12
+    assert np.abs(f[idx] - fo)[~edge].max() <= tol * np.abs(fo).max()
+
+
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("how", ["one_cell", "far_away", "cluster"])
+def test_pair_forces_dev_cells_fall_back(how, fp32):
+    """Positions the cells leave to the all-pairs tiles: within the cutoff of one another, too far from the origin to
+    bin, and most of them in a few cells."""
+    import torch
+
+    n = 5000
+    rng = np.random.default_rng(3)
+    w = synth.make("C1", n=n)
+    xy, cutoff = w.xy.copy(), 6.0
+    if how == "one_cell":
+        cutoff = 4.0 * w.L
+    elif how == "far_away":
+        xy = np.round((xy + 2.0**23 - 1000.0) * 2.0) / 2.0   # halves: exact in FP32 too
+    else:
+        xy[: n // 2] *= 0.05
+    species = rng.integers(0, 2, n).astype(np.int32)
+    K = np.array([[1e-2, -5e-3], [2e-3, 1e-2]])
+    kw = dict(kind="screened", A=1.0, lam=2.0, cutoff=cutoff)
+    f = binding.pair_forces_dev(torch.from_numpy(xy).cuda(), torch.from_numpy(species).cuda(), K, fp32=fp32, **kw)
+    f = f.cpu().numpy()
+    idx = rng.integers(0, n, 300).astype(np.int32)
+    fo = oracle.forces(xy, species, K, idx=idx, **kw)
+    ok = np.isfinite(fo).all(1)
+    assert ok.sum() > 100 and np.array_equal(np.isfinite(f[idx]).all(1), ok)
+    assert np.abs(f[idx] - fo)[ok].max() <= (2e-4 if fp32 else 1e-12) * np.abs(fo[ok]).max()
