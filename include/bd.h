@@ -242,8 +242,8 @@ int bd_forces(bd_sim *sim, double *f_out);
  * Pair forces of the Sec. 2.2 law for positions the caller holds in device
  * memory, without a handle:
  *   F_i = sum_{j != i} K[s_i][s_j] g(d_ij) (r_i - r_j) / d_ij
- * with g and the cutoff from fp (fp->skin is ignored; all pairs are
- * evaluated, no neighbour lists).
+ * with g and the cutoff from fp (fp->skin is ignored; larger calls with a
+ * cutoff find the pairs within it through cells, made anew by each call).
  *   n          number of particles, >= 1
  *   xy         device, 2n doubles, x and y interleaved (caller order)
  *   species    device, n int32 in 0..fp->S-1 (not checked on the device)
@@ -253,7 +253,8 @@ int bd_forces(bd_sim *sim, double *f_out);
  *   f_out      device, 2n doubles (Fx, Fy interleaved), written
  *   stream     hipStream_t of the current device to run on (NULL: the null stream)
  * All device pointers belong to the current device.  The call allocates its
- * working memory (the per-split sums, J * n * 16 bytes at most, J <= 64),
+ * working memory (the per-split sums, J * n * 16 bytes at most, J <= 64, or
+ * with a cutoff about 30 bytes per particle if that is more),
  * runs on `stream`, synchronises it, frees the memory and returns.  Two
  * distinct particles at the same position give non-finite forces.
  * BD_ERR_INVALID_ARG for bad arguments, BD_ERR_OOM if the working memory

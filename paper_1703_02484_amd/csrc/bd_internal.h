@@ -316,7 +316,7 @@ struct Sim {
     int rbase = 0, vbase = 0;        // bases currently on the device; launches pass stamp - base
     // captured steps (one set per round-budget setting)
     bool use_graph = false;
-    int batch_hint = kRing;          // graph steps queued per batch (adapts to the steps between stops)
+    int batch_hint = 0;              // graph steps queued per batch (adapts to the steps between stops); 0: none yet
     int tail_mode = -1;              // overlap rounds after the first detection: 0 launch per phase,
                                      // 1 one workgroup, 2 the large first rounds launched per phase and the
                                      // rest in one workgroup, -1 chosen from the problem size

@@ -1042,7 +1042,11 @@ int run_graph_steps(Sim &s, int64_t nsteps) {
         if (s.use_nl && s.need_rebuild) verlet_rebuild(s);
         Sim::StepGraph &g = step_graph(s);
         // steps queued after one that stops still cost their launches: queue about as many
-        // steps as recently ran between stops (neighbour-list rebuilds, budget growth)
+        // steps as recently ran between stops (neighbour-list rebuilds, budget growth).  A large
+        // handle starts with one step, which shows the rounds to launch on many workgroups:
+        // 1,000,000 disks, a handle's first 20 steps 11.8 ms with all of them queued, 9.5 so
+        // (list method 8.5 and 5.7); 65,536 disks 17.9 and 18.0
+        if (s.batch_hint == 0) s.batch_hint = s.n > 262144 ? 1 : kRing;
         const int m = (int)std::min<int64_t>(nsteps, std::min(kRing, s.batch_hint));
         launch_step_begin(s, next_base(s));
         for (int k = 0; k < m;) {
