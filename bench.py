@@ -34,9 +34,9 @@ PEAK_FP64_TFLOPS = 78.6
 # (FETCH_SIZE, WRITE_SIZE), each scaled by the same counter's reading for a plain
 # 1 GiB copy; valid only for the force kernel's source it was measured on (sha1 of
 # the force section of k_particles.hip, see force_source_sha1).
-MEASURED_TRAFFIC = {"sha1": "6bb720c9c1b32473e48c7b3a46cc513746b3524c", "workload": "C2", "n": 65536,
-                    "force_config": {"chunk": 1024, "per_lane": 4, "persistent": 2},
-                    "bytes_per_launch": 2.0 * 2205.0 * 1024 + 1.0 * 32768.0 * 1024}
+MEASURED_TRAFFIC = {"sha1": "15abe188d582a64abfbd38b3ce161634e5fa1bb8", "workload": "C2", "n": 65536,
+                    "force_config": {"chunk": 512, "per_lane": 2, "persistent": 2},
+                    "bytes_per_launch": 2.0 * 2601.6 * 1024 + 1.0 * 65536.0 * 1024}
 
 
 FORCE_KERNELS = {0: "k_force", 1: "k_force_queue", 2: "k_force_sym"}
@@ -44,7 +44,14 @@ FORCE_KERNELS = {0: "k_force", 1: "k_force_queue", 2: "k_force_sym"}
 # ordinary forms, per ordered pair: 2 sub, mul + FMA for d^2, v_rsq, 2 mul for d^-3, 2 FMA;
 # symmetric form (FP32), per unordered pair: the same, 2 FMA for j's side, and one DPP move
 # (a step moves x, y and both sums of each of a lane's 2 j: 8 moves for its 8 pairs)
-VALU_PER_PAIR = {0: 9.0, 1: 9.0}   # symmetric form: 11 + 4 / per_lane (the 4 moves per j are shared by per_lane i)
+VALU_PER_PAIR = {0: 9.0, 1: 9.0}   # symmetric form: 11 + 4 / P (the 4 moves per j are shared by a lane's P i)
+
+
+def sym_per_lane(fcfg):
+    """Disks i per lane of the symmetric form: two in chunks of 128, eight in its 8-per-lane variant, else four."""
+    return 2 if fcfg["chunk"] == 128 else 8 if fcfg["per_lane"] == 8 else 4
+
+
 LANE_ISSUE_PER_S = 256 * 4 * 16 * 2.4e9   # CUs x SIMDs x lanes x clock: one VALU lane-op per slot
 
 
@@ -54,7 +61,7 @@ def valu_issue_frac(fcfg, n, seconds, fp32):
         return None
     form = fcfg["persistent"]
     pairs = n * (n - 1) / 2 if form == 2 else n * (n - 1)
-    per_pair = 11.0 + 4.0 / fcfg["per_lane"] if form == 2 else VALU_PER_PAIR[form]
+    per_pair = 11.0 + 4.0 / sym_per_lane(fcfg) if form == 2 else VALU_PER_PAIR[form]
     return per_pair * pairs / seconds / LANE_ISSUE_PER_S
 
 
@@ -66,7 +73,7 @@ def force_source_sha1():
     with open(src) as fh:
         text = fh.read()
     a = text.index("// ---------------------------------------------------------------- forces")
-    b = text.index("// F_i = sum_c K[s_i][spec(c)] Phi_{i,c} over the chunks")
+    b = text.index("// ---------------------------------------------------------------- noise")
     return hashlib.sha1(text[a:b].encode()).hexdigest()
 
 
@@ -84,13 +91,13 @@ def measured_traffic(workload, n, fcfg):
 # rocprofv3 --pmc passes (FETCH_SIZE x 2, WRITE_SIZE x 1, calibrated on a plain copy), beside the algorithmic
 # bytes; valid for the kernel sources they were counted on (sha1 of the three kernel files, see
 # c3_source_sha1).  MB = 1e6 bytes.
-C3_TRAFFIC = {"sha1": "a3d772a99d6da0544405237dc6d1be9af153ea52", "kernels": {
-    "k_flip_eval_full": {"measured_MB": 100.2, "algorithmic_MB": 84.1},
-    "k_ovl_detect": {"measured_MB": 72.0, "algorithmic_MB": 67.4},
+C3_TRAFFIC = {"sha1": "2b821970bf98872b2fa30d56c193280034cc3477", "kernels": {
+    "k_flip_eval_full": {"measured_MB": 186.9, "algorithmic_MB": 143.2},   # with the topology snapshot
+    "k_ovl_detect": {"measured_MB": 71.9, "algorithmic_MB": 67.4},
     "k_em": {"measured_MB": 101.0, "algorithmic_MB": 100.7},
     "k_force_nl": {"measured_MB": 61.9, "algorithmic_MB": 54.5},
-    "k_skin_check": {"measured_MB": 33.6, "algorithmic_MB": 33.6},
-    "k_snapshot": {"measured_MB": 109.6, "algorithmic_MB": 109.6}}}
+    "k_ovl_nl_gather": {"measured_MB": 71.5, "algorithmic_MB": 62.9},
+    "k_skin_check": {"measured_MB": 33.6, "algorithmic_MB": 33.6}}}
 
 
 def c3_source_sha1():
