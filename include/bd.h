@@ -253,8 +253,9 @@ int bd_forces(bd_sim *sim, double *f_out);
  *   f_out      device, 2n doubles (Fx, Fy interleaved), written
  *   stream     hipStream_t of the current device to run on (NULL: the null stream)
  * All device pointers belong to the current device.  The call allocates its
- * working memory (the per-split sums, J * n * 16 bytes at most, J <= 64, or
- * with a cutoff about 30 bytes per particle if that is more),
+ * working memory (the per-split sums, J * n * 16 bytes at most, J <= 64; with
+ * a cutoff about 30 bytes per particle if that is more; from 16,000 particles
+ * of the inverse-square law without a cutoff up to 32 MiB of chunk sums),
  * runs on `stream`, synchronises it, frees the memory and returns.  Two
  * distinct particles at the same position give non-finite forces.
  * BD_ERR_INVALID_ARG for bad arguments, BD_ERR_OOM if the working memory

@@ -3,8 +3,8 @@
 // for positions and species that live in device memory owned by the caller,
 // with no simulation handle.
 //
-// Three layouts, chosen from n, the precision and whether there is a cutoff
-// (pf_plan); rows and tiles are bound by the VALU:
+// Four layouts, chosen from n, the precision, the law and whether there is a
+// cutoff (pf_plan); all but cells are bound by the VALU:
 //   rows   (few particles) one wavefront per particle i, its lanes over the
 //          j; the 64 partial sums are added across the wavefront in FP64.  One launch, no working memory: with few
 //          particles the time is the launch and the chain of one lane's j.
@@ -16,6 +16,9 @@
 //          the pair loop: it weights the sum over each species' part of the
 //          block.  part[split][i] holds the weighted sums; a second kernel
 //          adds the J splits in FP64 in split order.
+//   sym    (inverse square, no cutoff, larger n) the particles are sorted by
+//          species and every pair of chunks of them is taken once, both sides
+//          from one evaluation.
 //   cells  (a cutoff) the particles are put into square cells of the cutoff's
 //          side and each is taken against its 3 x 3 cells: launches of a few
 //          us each instead of n^2 distance tests.  Positions it cannot bin, and
@@ -421,6 +424,266 @@ __global__ void k_pf_reduce(int n, int J, const typename Vec2<T>::type *__restri
     f[2 * (size_t)i + 1] = fy;
 }
 
+// ---------------------------------------------------------------- sym
+// Particles sorted by species (ascending index inside one), in chunks of at most C of one species (a species' range cut
+// into equal parts).  part[c * n + k]: the sum of sorted particle k over chunk c, without the strength.
+template <typename T>
+struct PfSym {
+    using T2 = typename Vec2<T>::type;
+    int *count;    // [blocks of kSortBlock][BD_MAX_SPECIES] particles of each species
+    int *total;    // [BD_MAX_SPECIES]
+    int *sid;      // [n] particle at each place
+    T2 *pos;       // [n]
+    T2 *part;      // [rows][n]
+};
+
+constexpr int kSortBlock = 1024;
+
+// Counts of a block's species, wave by wave: in LDS for the block's own places, summed in `count` for the others.
+__device__ __forceinline__ int pf_wave_count(int s, int S, int (*wcnt)[BD_MAX_SPECIES]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int rank = 0;
+    for (int b = 0; b < S; ++b) {
+        const unsigned long long m = __ballot(s == b);
+        if (s == b) rank = __popcll(m & ((1ull << lane) - 1ull));
+        if (lane == 0) wcnt[wave][b] = __popcll(m);
+    }
+    __syncthreads();
+    return rank;
+}
+
+__global__ __launch_bounds__(kSortBlock) void k_pf_count(int n, int S, const int32_t *__restrict__ species,
+                                                         int *__restrict__ count) {
+    __shared__ int wcnt[kSortBlock / 64][BD_MAX_SPECIES];
+    const int i = blockIdx.x * kSortBlock + threadIdx.x;
+    pf_wave_count(i < n ? species[i] : -1, S, wcnt);
+    if (threadIdx.x < S) {
+        int c = 0;
+        for (int w = 0; w < kSortBlock / 64; ++w) c += wcnt[w][threadIdx.x];
+        count[blockIdx.x * BD_MAX_SPECIES + threadIdx.x] = c;
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kSortBlock) void k_pf_sort(int n, int S, const double *__restrict__ xy,
+                                                        const int32_t *__restrict__ species, PfSym<T> a) {
+    __shared__ int wcnt[kSortBlock / 64][BD_MAX_SPECIES];
+    __shared__ int before[BD_MAX_SPECIES], total[BD_MAX_SPECIES];
+    if (threadIdx.x < BD_MAX_SPECIES) before[threadIdx.x] = total[threadIdx.x] = 0;
+    const int i = blockIdx.x * kSortBlock + threadIdx.x;
+    const int s = i < n ? species[i] : -1;
+    const int rank = pf_wave_count(s, S, wcnt);
+    for (int k = threadIdx.x; k < (int)gridDim.x * BD_MAX_SPECIES; k += kSortBlock) {
+        const int b = k % BD_MAX_SPECIES;
+        if (b >= S) continue;
+        const int c = a.count[k];
+        atomicAdd(&total[b], c);
+        if (k / BD_MAX_SPECIES < (int)blockIdx.x) atomicAdd(&before[b], c);
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x < BD_MAX_SPECIES) a.total[threadIdx.x] = total[threadIdx.x];
+    if ((unsigned)s >= (unsigned)S) return;
+    int at = before[s] + rank;
+    for (int b = 0; b < s; ++b) at += total[b];
+    for (int w = 0; w < (int)threadIdx.x >> 6; ++w) at += wcnt[w][s];
+    typename Vec2<T>::type v;
+    v.x = (T)xy[2 * (size_t)i];
+    v.y = (T)xy[2 * (size_t)i + 1];
+    a.pos[at] = v;
+    a.sid[at] = i;
+}
+
+// Number of chunks, and the range and species of chunk c.
+__device__ __forceinline__ int pf_chunks(const int *total, int S, int C) {
+    int nc = 0;
+    for (int b = 0; b < S; ++b) nc += (total[b] + C - 1) / C;
+    return nc;
+}
+__device__ __forceinline__ int pf_chunk(const int *total, int S, int C, int c, int &k0, int &k1) {
+    int base = 0;
+    for (int b = 0; b < S; ++b) {
+        const int m = total[b], nb = (m + C - 1) / C;
+        if (c < nb) {
+            k0 = base + (int)((long long)m * c / nb);
+            k1 = base + (int)((long long)m * (c + 1) / nb);
+            return b;
+        }
+        c -= nb;
+        base += m;
+    }
+    k0 = k1 = 0;
+    return 0;
+}
+
+template <typename T>
+__device__ __forceinline__ T pf_rot(T v) {   // lane l takes lane l + 1's value
+    if constexpr (sizeof(T) == 4) {
+        return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x134, 0xF, 0xF, true));
+    } else {
+        const long long b = __double_as_longlong(v);
+        const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffll), 0x134, 0xF, 0xF, true);
+        const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x134, 0xF, 0xF, true);
+        return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+    }
+}
+
+// 64 steps of a group of 64 Q particles j, Q per lane, turning around the wavefront with their sums.  SELF: the chunk
+// with itself, where at step 0 place p of the lane meets itself in place p - same of the group.  PAD: places past the
+// chunk's end (lane + 64 p >= ni, j >= nj) do not act.
+template <typename T, int P, int Q, bool SELF, bool PAD>
+__device__ __forceinline__ void pf_sym_group(const PfConst<T> &c, const T (&xi)[P], const T (&yi)[P], T (&fx)[P],
+                                             T (&fy)[P], T (&xj)[Q], T (&yj)[Q], T (&gx)[Q], T (&gy)[Q], int same,
+                                             int ni, int nj) {
+    const int lane = threadIdx.x & 63;
+    for (int t = 0; t < 64; ++t) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                const T dx = xi[p] - xj[q], dy = yi[p] - yj[q];
+                T g = law_factor<PF_Q2>(dx * dx + dy * dy, c);
+                if (SELF) g = t == 0 && p - same == q ? (T)0 : g;
+                if (PAD) g = p * 64 + lane < ni && q * 64 + ((lane + t) & 63) < nj ? g : (T)0;
+                const T ex = dx * g, ey = dy * g;
+                fx[p] += ex;
+                fy[p] += ey;
+                gx[q] -= ex;
+                gy[q] -= ey;
+            }
+            xj[q] = pf_rot(xj[q]);
+            yj[q] = pf_rot(yj[q]);
+            gx[q] = pf_rot(gx[q]);
+            gy[q] = pf_rot(gy[q]);
+        }
+    }
+}
+
+// One pair of chunks A <= B per workgroup of W wavefronts: the wavefront's 64 P particles of A in registers, those of B
+// in groups that the wavefronts take staggered, adding a group's sums to one LDS copy in a fixed order.
+// VALU-bound, per unordered pair 11 instructions and 4 / P moves in FP32 against 2 x 9 with both orders: 65,536
+// particles, the whole call 0.78 ms (sort and reduction 0.02 of it), 0.95 with both orders.
+template <typename T, int P, int W, int Q>
+__global__ __launch_bounds__(64 * W) void k_pf_sym(int n, PfLaw law, PfSym<T> a) {
+    using T2 = typename Vec2<T>::type;
+    constexpr int C = 64 * P * W;
+    __shared__ T2 jsum[C];
+    const int nc = pf_chunks(a.total, law.S, C);
+    const int tile = blockIdx.x;
+    if ((long long)tile >= (long long)nc * (nc + 1) / 2) return;   // uniform in the workgroup
+    int cb = (int)((sqrt(8.0 * tile + 1.0) - 1.0) * 0.5);
+    while ((long long)cb * (cb + 1) / 2 > tile) --cb;
+    while ((long long)(cb + 1) * (cb + 2) / 2 <= tile) ++cb;
+    const int ca = tile - (int)((long long)cb * (cb + 1) / 2);
+    int i0, i1, j0, j1;
+    pf_chunk(a.total, law.S, C, ca, i0, i1);
+    pf_chunk(a.total, law.S, C, cb, j0, j1);
+    const bool self = ca == cb;
+    const PfConst<T> c(law);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int ni = i1 - i0, nj = j1 - j0, iw = wave * 64 * P;
+    T xi[P], yi[P], fx[P], fy[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int k = iw + p * 64 + lane;
+        const T2 v = a.pos[i0 + (k < ni ? k : 0)];
+        xi[p] = v.x;
+        yi[p] = v.y;
+        fx[p] = fy[p] = (T)0;
+    }
+    if (!self)
+        for (int k = threadIdx.x; k < nj; k += 64 * W) {
+            T2 z;
+            z.x = z.y = (T)0;
+            jsum[k] = z;
+        }
+    __syncthreads();
+    const int groups = (nj + 64 * Q - 1) / (64 * Q);
+    const int turns = groups > W ? groups : W, step = turns / W;   // no two wavefronts on one group at a time
+    for (int it = 0; it < turns; ++it) {   // same trip count in every lane
+        int g = it + wave * step;
+        if (g >= turns) g -= turns;
+        if (g < groups && iw < ni) {
+            const int jg = g * 64 * Q;
+            T xj[Q], yj[Q], gx[Q], gy[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int k = jg + q * 64 + lane;
+                const T2 v = a.pos[j0 + (k < nj ? k : 0)];
+                xj[q] = v.x;
+                yj[q] = v.y;
+                gx[q] = gy[q] = (T)0;
+            }
+            const int same = (jg - iw) / 64;   // multiples of 64 both
+            const bool pad = jg + 64 * Q > nj || iw + 64 * P > ni;
+            if (self) {
+                if (pad)
+                    pf_sym_group<T, P, Q, true, true>(c, xi, yi, fx, fy, xj, yj, gx, gy, same, ni - iw, nj - jg);
+                else
+                    pf_sym_group<T, P, Q, true, false>(c, xi, yi, fx, fy, xj, yj, gx, gy, same, 0, 0);
+            } else if (pad) {
+                pf_sym_group<T, P, Q, false, true>(c, xi, yi, fx, fy, xj, yj, gx, gy, 0, ni - iw, nj - jg);
+            } else {
+                pf_sym_group<T, P, Q, false, false>(c, xi, yi, fx, fy, xj, yj, gx, gy, 0, 0, 0);
+            }
+            if (!self) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const int k = jg + q * 64 + lane;
+                    if (k < nj) {
+                        T2 v = jsum[k];
+                        v.x += gx[q];
+                        v.y += gy[q];
+                        jsum[k] = v;
+                    }
+                }
+            }
+        }
+        __syncthreads();   // the sums of this turn's groups are in place
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int k = iw + p * 64 + lane;
+        if (k < ni) {
+            T2 v;
+            v.x = fx[p];
+            v.y = fy[p];
+            a.part[(size_t)cb * n + i0 + k] = v;
+        }
+    }
+    if (!self)
+        for (int k = threadIdx.x; k < nj; k += 64 * W) a.part[(size_t)ca * n + j0 + k] = jsum[k];
+}
+
+// F of sorted particle k: its sums over the chunks of each species, weighted, in FP64 and chunk order.
+template <typename T>
+__global__ void k_pf_sym_reduce(int n, int C, PfLaw law, PfSym<T> a, double *__restrict__ f) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    int s = -1, base = 0;   // the species at place k
+    for (int b = 0; b < law.S; ++b) {
+        if (k >= base && k < base + a.total[b]) s = b;
+        base += a.total[b];
+    }
+    if (s < 0) return;   // past the last particle
+    double fx = 0.0, fy = 0.0;
+    int c = 0;
+    for (int b = 0; b < law.S; ++b) {
+        const int end = c + (a.total[b] + C - 1) / C;
+        double sx = 0.0, sy = 0.0;
+#pragma unroll 16
+        for (; c < end; ++c) {
+            const auto v = a.part[(size_t)c * n + k];
+            sx += (double)v.x;
+            sy += (double)v.y;
+        }
+        const double w = law.K[s * law.S + b];
+        fx += w * sx;
+        fy += w * sy;
+    }
+    const size_t o = 2 * (size_t)a.sid[k];
+    f[o] = fx;
+    f[o + 1] = fy;
+}
+
 // ---------------------------------------------------------------- cells
 // Cells of side h, a hair over the cutoff, on a torus of kGrid x kGrid: cell (floor(x / h) mod kGrid, ...), so no
 // bounding box is needed; particles a multiple of kGrid cells apart share cells and fail the distance test.  Two
@@ -653,10 +916,13 @@ int pf_check(int32_t n, const double *xy, const int32_t *species, const bd_force
 // How a call runs; depends on n, the precision and the law only.
 struct PfPlan {
     bool rows;    // rows layout
+    int sym;      // chunk length of the sym layout (0: another layout)
     bool cells;   // cells, with the tiles behind them
     int J;        // tiles layout: j splits
     size_t bytes;
 };
+
+constexpr int kSymMin = 16000;
 
 constexpr size_t pf_align(size_t b) { return (b + 255) / 256 * 256; }
 
@@ -687,6 +953,21 @@ constexpr int kCellsMax = 262144;
 
 // Particles i per lane of the tiles: one LDS read of a j serves them all.  Four for the shortest pair loop
 // (FP32 inverse square: 9 instructions); two where a pair is longer or notes its hits.
+template <typename T>
+size_t pf_sym_at(int n, int S, int C, unsigned char *base, PfSym<T> &a) {
+    size_t o = 0;
+    auto take = [&](auto *&p, size_t count) {
+        p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(base + o);
+        o += pf_align(count * sizeof(*p));
+    };
+    take(a.count, (size_t)((n + kSortBlock - 1) / kSortBlock) * BD_MAX_SPECIES);
+    take(a.total, BD_MAX_SPECIES);
+    take(a.sid, n);
+    take(a.pos, n);
+    take(a.part, (size_t)(n / C + S) * n);
+    return o;
+}
+
 template <typename T, int LAW, bool CUT>
 constexpr int pf_per_lane() { return sizeof(T) == 4 && LAW == PF_Q2 && !CUT ? 4 : 2; }
 
@@ -701,6 +982,24 @@ PfPlan pf_plan(int n, int precision, const PfLaw &law) {
     const bool q2 = law.kind == BD_FORCE_POWER && law.q == 2.0;
     p.rows = n <= (!cut ? 6144 : q2 ? 4096 : precision == BD_PREC_FP32 ? 3600 : 2800);
     if (p.rows) return p;
+    // Every pair once from some 16,000 particles on, where the chunks' sums fit the working memory: the smallest chunk
+    // that lets them (smaller tiles leave fewer compute units waiting at the end).  Tiles against sym, two species, us:
+    // FP32 87 / 93 at 16,000, 119 / 117 at 20,011, 245 / 178 at 30,000 (chunks of 256), 475 / 357 at 43,000 (512),
+    // 941 / 685 at 62,000 (1024), 953 / 776 at 65,536 (1280, 963 with four particles a lane, which leave a second round
+    // of workgroups); FP64 157 / 155 at 16,000, 239 / 199 at 20,011, 513 / 363 at 30,000, 1002 / 751 at 43,000, and
+    // above 44,000, where chunks of 1280 fill the device unevenly, 1309 / 1424 at 49,000.
+    const bool fp32 = precision == BD_PREC_FP32;
+    if (q2 && !cut && n > kSymMin) {
+        for (int C : {256, 512, 1024, 1280}) {
+            PfSym<float> a32;
+            PfSym<double> a64;
+            const size_t b = fp32 ? pf_sym_at(n, law.S, C, nullptr, a32) : pf_sym_at(n, law.S, C, nullptr, a64);
+            if (b > kPfPartBytes || (!fp32 && C > 1024)) continue;
+            p.sym = C;
+            p.bytes = b;
+            return p;
+        }
+    }
     p.cells = cut && n <= kCellsMax;
     const bool four = precision == BD_PREC_FP32 && q2 && !cut;
     const long long per_group = (long long)kPfBlock * (four ? 4 : 2), nb = (n + per_group - 1) / per_group;
@@ -732,6 +1031,29 @@ void pf_launch(int n, const double *xy, const int32_t *species, const PfLaw &law
         hipLaunchKernelGGL((k_pf_rows<T, LAW, CUT>), dim3((n + kWaves - 1) / kWaves), block, 0, stream, n, xy,
                            species, law, f_out);
         return;
+    }
+    if constexpr (LAW == PF_Q2 && !CUT) {
+        if (p.sym) {
+            constexpr int Q = sizeof(T) == 4 ? 2 : 1;
+            const int C = p.sym, nc = n / C + law.S, nb = (n + kSortBlock - 1) / kSortBlock;
+            PfSym<T> a;
+            pf_sym_at(n, law.S, C, (unsigned char *)part, a);
+            hipLaunchKernelGGL(k_pf_count, dim3(nb), dim3(kSortBlock), 0, stream, n, law.S, species, a.count);
+            hipLaunchKernelGGL(k_pf_sort<T>, dim3(nb), dim3(kSortBlock), 0, stream, n, law.S, xy, species, a);
+            auto tiles = [&](auto kern, int waves) {
+                hipLaunchKernelGGL(kern, dim3(nc * (nc + 1) / 2), dim3(64 * waves), 0, stream, n, law, a);
+            };
+            if (C == 256)
+                tiles(k_pf_sym<T, 4, 1, Q>, 1);
+            else if (C == 512)
+                tiles(k_pf_sym<T, 4, 2, Q>, 2);
+            else if (C == 1024)
+                tiles(k_pf_sym<T, 4, 4, Q>, 4);
+            else if constexpr (sizeof(T) == 4)   // five per lane: six workgroups on a compute unit
+                tiles(k_pf_sym<T, 5, 4, Q>, 4);
+            hipLaunchKernelGGL(k_pf_sym_reduce<T>, dim3((n + 255) / 256), dim3(256), 0, stream, n, C, law, a, f_out);
+            return;
+        }
     }
     constexpr int P = pf_per_lane<T, LAW, CUT>();
     const dim3 grid((n + kPfBlock * P - 1) / (kPfBlock * P), p.J);

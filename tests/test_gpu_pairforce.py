@@ -184,3 +184,49 @@ def test_pair_forces_dev_cells_fall_back(how, fp32):
     ok = np.isfinite(fo).all(1)
     assert ok.sum() > 100 and np.array_equal(np.isfinite(f[idx]).all(1), ok)
     assert np.abs(f[idx] - fo)[ok].max() <= (2e-4 if fp32 else 1e-12) * np.abs(fo[ok]).max()
+
+
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("n, S", [(16001, 1), (20001, 8), (20480, 2), (31001, 3), (46001, 2), (64001, 2)])
+def test_pair_forces_dev_every_pair_once_matches_oracle(n, S, fp32):
+    """The inverse-square law without a cutoff above the rows: every chunk length, ragged last chunks, species of
+    uneven number with one absent, and sizes whose sums do not fit and stay with the tiles (64,001 in FP64)."""
+    import torch
+
+    w = synth.make("C1", n=n)
+    rng = np.random.default_rng(n)
+    species = np.minimum(rng.integers(0, 4 * S, n), S - 1).astype(np.int32)   # the last one holds most
+    if S == 8:
+        species[species == 2] = 3
+    K = rng.normal(size=(S, S)) * 1e-2
+    xy, sp = torch.from_numpy(np.ascontiguousarray(w.xy)).cuda(), torch.from_numpy(species).cuda()
+    f = binding.pair_forces_dev(xy, sp, K, fp32=fp32)
+    g = binding.pair_forces_dev(xy, sp, K, fp32=fp32, noalloc=True)
+    f = f.cpu().numpy()
+    assert np.array_equal(f, g.cpu().numpy())
+    idx = np.unique(np.concatenate([[0, n // 2, n - 1], rng.integers(0, n, 300)])).astype(np.int32)
+    fo = oracle.forces(w.xy, species, K, idx=idx)
+    assert np.abs(f[idx] - fo).max() <= (1e-4 if fp32 else 1e-12) * np.abs(fo).max()
+
+
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("n", [20100, 20480])
+def test_pair_forces_dev_every_pair_once_singular(n, fp32):
+    """Two particles at one place give non-finite forces to both, within one chunk and across two, and to nobody else;
+    a particle at infinity gives 0 * inf along x."""
+    import torch
+
+    w = synth.make("C1", n=n)
+    sp = torch.zeros(n, dtype=torch.int32, device="cuda")
+    for a, b in ((3, 4), (0, n - 1), (100, 100 + 64)):
+        xy = w.xy.copy()
+        xy[b] = xy[a]
+        f = binding.pair_forces_dev(torch.from_numpy(xy).cuda(), sp, np.array([[1.0]]), fp32=fp32).cpu().numpy()
+        bad = np.zeros(n, bool)
+        bad[[a, b]] = True
+        assert not np.isfinite(f[bad]).any() and np.isfinite(f[~bad]).all()
+    xy = w.xy.copy()
+    xy[n - 1, 0] = np.inf
+    f = binding.pair_forces_dev(torch.from_numpy(xy).cuda(), sp, np.array([[1.0]]), fp32=fp32).cpu().numpy()
+    rest = np.arange(n) != n - 1
+    assert np.isnan(f[:, 0]).all() and np.isfinite(f[rest, 1]).all()
