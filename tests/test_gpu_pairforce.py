@@ -230,3 +230,34 @@ def test_pair_forces_dev_every_pair_once_singular(n, fp32):
     f = binding.pair_forces_dev(torch.from_numpy(xy).cuda(), sp, np.array([[1.0]]), fp32=fp32).cpu().numpy()
     rest = np.arange(n) != n - 1
     assert np.isnan(f[:, 0]).all() and np.isfinite(f[rest, 1]).all()
+
+
+@pytest.mark.parametrize("n, cutoff", [(5000, 0.0), (9000, 6.0), (9000, 0.0), (17000, 0.0)])
+def test_noalloc_layouts_in_a_graph(n, cutoff):
+    """Each layout captured once and replayed with other positions in the same buffers, among them ones the cells leave
+    to the tiles, with eager work between the replays: bitwise the eager forces."""
+    import torch
+
+    w = synth.make("C1", n=n)
+    sp = torch.from_numpy((np.arange(n) % 2).astype(np.int32)).cuda()
+    K = np.array([[1e-2, -5e-3], [2e-3, 1e-2]])
+    xy = torch.from_numpy(np.ascontiguousarray(w.xy)).cuda()
+    out = torch.empty_like(xy)
+    kw = dict(kind="power", q=2.0, cutoff=cutoff, noalloc=True)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        binding.pair_forces_dev(xy, sp, K, out=out, **kw)
+    torch.cuda.current_stream().wait_stream(s)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        binding.pair_forces_dev(xy, sp, K, out=out, **kw)
+    base = xy.clone()
+    for scale in (1.0, 0.02, 1.3, 1.0):   # 0.02: most pairs within the cutoff
+        xy.copy_(base * scale)
+        g.replay()
+        torch.cuda.synchronize()
+        got = out.clone()
+        ref = binding.pair_forces_dev(xy, sp, K, **{**kw, "noalloc": False})
+        torch.cuda.synchronize()
+        assert torch.equal(got, ref), scale
