@@ -718,6 +718,15 @@ __device__ __forceinline__ int pf_cell(T x, T y, double inv_h, bool &ok) {
 // would save.  kBinAhead particles of a thread are in flight.
 constexpr int kBinAhead = 8;
 
+// Too crowded for the cells: nine cells around each particle hold about 9 sum(count^2) pairs in all; above n^2 / 4.7
+// (FP64) or n^2 / 6.2 (FP32) of them the tiles are faster.  Evenly filled boxes of r cutoffs a side, tiles and cells,
+// us: screened FP64 9,000 particles 96 / 98 at r = 6, 89 / 80 at 7, 20,011 356 / 335 at 5.3, 323 / 255 at 6; inverse
+// square FP32 9,000 62 / 67 at 7, 62 / 61 at 8, 20,011 164 / 172 at 6, 156 / 133 at 7.
+template <typename T>
+__device__ __forceinline__ bool pf_crowded(unsigned long long squares, unsigned long long n) {
+    return (sizeof(T) == 4 ? 56 : 42) * squares > n * n;
+}
+
 template <typename T>
 __global__ __launch_bounds__(kBinBlock) void k_pf_bin(int n, const double *__restrict__ xy, PfCells<T> a) {
     __shared__ int cnt[kCells];
@@ -730,6 +739,24 @@ __global__ __launch_bounds__(kBinBlock) void k_pf_bin(int n, const double *__res
         crowd = 0;
     }
     __syncthreads();
+    {   // a particle per thread shows a crowd before all are counted (m samples: m^2 sum p^2 + m squares)
+        const int i = (int)((long long)n * tid / kBinBlock);
+        bool ok;
+        const int c = pf_cell((T)xy[2 * (size_t)i], (T)xy[2 * (size_t)i + 1], a.inv_h, ok);
+        if (!ok) bad = 1;
+        const int before = atomicAdd(&cnt[c], 1);   // sum over the samples of 2 before + 1 = sum of the squares
+        unsigned sq = 2u * (unsigned)before;
+        for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
+        if (lane == 0) atomicAdd(&crowd, (unsigned long long)sq);
+        __syncthreads();
+        const bool stop = bad || pf_crowded<T>(crowd, kBinBlock);
+        if (stop && tid == 0) *a.crowded = 1;
+        if (stop) return;   // uniform in the workgroup
+        __syncthreads();
+        cnt[c] = 0;
+        if (tid == 0) crowd = 0;
+        __syncthreads();
+    }
     for (int i0 = tid; i0 < n; i0 += kBinBlock * kBinAhead) {
         T x[kBinAhead], y[kBinAhead];
 #pragma unroll
@@ -776,8 +803,7 @@ __global__ __launch_bounds__(kBinBlock) void k_pf_bin(int n, const double *__res
         at += own[u];
     }
     if (tid == kBinBlock - 1) a.start[kCells] = n;
-    // nine cells around each particle: about nine times the sum of the squared counts
-    const bool crowded = bad || 27 * crowd > (unsigned long long)n * n;
+    const bool crowded = bad || pf_crowded<T>(crowd, (unsigned long long)n);
     if (tid == 0) *a.crowded = crowded ? 1 : 0;
     if (crowded) return;   // uniform in the workgroup
     __syncthreads();
@@ -976,11 +1002,12 @@ PfPlan pf_plan(int n, int precision, const PfLaw &law) {
     const bool cut = law.cutoff > 0.0;
     // Rows up to these sizes.  Measured, rows against tiles, two species, us: no cutoff, inverse square, FP64
     // 27 / 33 at 5,000, 36 / 47 at 6,000, 60 / 49 at 8,192, FP32 25 / 34 at 6,000, 49 / 35 at 8,192; screened FP64
-    // 72 / 80 at 5,000, 165 / 137 at 8,192.  Rows against cells (cutoff 12, 0.45 of the area covered, three species),
-    // where rows evaluates the law for the lanes out of range too: inverse square FP64 23 / 27 at 4,000, FP32 22 / 29;
-    // screened FP64 20 / 30 at 2,000, 36 / 30 at 3,000, FP32 26 / 33 at 3,000, 37 / 33 at 4,000.
+    // 72 / 80 at 5,000, 165 / 137 at 8,192.  With a cutoff, where rows evaluates the law for the lanes out of range
+    // too, rows against cells (cutoff 12, 0.45 of the area covered, three species): inverse square FP64 23 / 27 at
+    // 4,000, FP32 22 / 29; screened FP64 20 / 30 at 2,000, 55 / 31 at 4,000, FP32 37 / 33 at 4,000; but with cutoffs
+    // of a fifth of the box and more, which the cells leave to the tiles, rows 53 / 89 to 121 at 3,700.
     const bool q2 = law.kind == BD_FORCE_POWER && law.q == 2.0;
-    p.rows = n <= (!cut ? 6144 : q2 ? 4096 : precision == BD_PREC_FP32 ? 3600 : 2800);
+    p.rows = n <= (cut ? 4096 : 6144);
     if (p.rows) return p;
     // Every pair once from some 16,000 particles on, where the chunks' sums fit the working memory: the smallest chunk
     // that lets them (smaller tiles leave fewer compute units waiting at the end).  Tiles against sym, two species, us:
