@@ -254,7 +254,7 @@ int bd_forces(bd_sim *sim, double *f_out);
  *   stream     hipStream_t of the current device to run on (NULL: the null stream)
  * All device pointers belong to the current device.  The call allocates its
  * working memory (the per-split sums, J * n * 16 bytes at most, J <= 64; with
- * a cutoff about 30 bytes per particle if that is more; from 16,000 particles
+ * a cutoff about 30 bytes per particle if that is more; above 16,384 particles
  * of the inverse-square law without a cutoff up to 32 MiB of chunk sums),
  * runs on `stream`, synchronises it, frees the memory and returns.  Two
  * distinct particles at the same position give non-finite forces.

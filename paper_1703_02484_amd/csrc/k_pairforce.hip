@@ -561,7 +561,7 @@ __device__ __forceinline__ void pf_sym_group(const PfConst<T> &c, const T (&xi)[
 // One pair of chunks A <= B per workgroup of W wavefronts: the wavefront's 64 P particles of A in registers, those of B
 // in groups that the wavefronts take staggered, adding a group's sums to one LDS copy in a fixed order.
 // VALU-bound, per unordered pair 11 instructions and 4 / P moves in FP32 against 2 x 9 with both orders: 65,536
-// particles, the whole call 0.78 ms (sort and reduction 0.02 of it), 0.95 with both orders.
+// particles, the whole call 0.75 ms (sort and reduction 0.02 of it), 0.96 with both orders.
 template <typename T, int P, int W, int Q>
 __global__ __launch_bounds__(64 * W) void k_pf_sym(int n, PfLaw law, PfSym<T> a) {
     using T2 = typename Vec2<T>::type;
@@ -573,10 +573,20 @@ __global__ __launch_bounds__(64 * W) void k_pf_sym(int n, PfLaw law, PfSym<T> a)
     int cb = (int)((sqrt(8.0 * tile + 1.0) - 1.0) * 0.5);
     while ((long long)cb * (cb + 1) / 2 > tile) --cb;
     while ((long long)(cb + 1) * (cb + 2) / 2 <= tile) ++cb;
-    const int ca = tile - (int)((long long)cb * (cb + 1) / 2);
+    int ca = tile - (int)((long long)cb * (cb + 1) / 2);
     int i0, i1, j0, j1;
     pf_chunk(a.total, law.S, C, ca, i0, i1);
     pf_chunk(a.total, law.S, C, cb, j0, j1);
+    if (i1 - i0 < j1 - j0) {   // the longer one in registers: the time is the number of groups of the other
+        auto swap = [](int &x, int &y) {
+            const int z = x;
+            x = y;
+            y = z;
+        };
+        swap(ca, cb);
+        swap(i0, j0);
+        swap(i1, j1);
+    }
     const bool self = ca == cb;
     const PfConst<T> c(law);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -948,7 +958,7 @@ struct PfPlan {
     size_t bytes;
 };
 
-constexpr int kSymMin = 16000;
+constexpr int kSymMin = 16384;
 
 constexpr size_t pf_align(size_t b) { return (b + 255) / 256 * 256; }
 
@@ -1009,12 +1019,13 @@ PfPlan pf_plan(int n, int precision, const PfLaw &law) {
     const bool q2 = law.kind == BD_FORCE_POWER && law.q == 2.0;
     p.rows = n <= (cut ? 4096 : 6144);
     if (p.rows) return p;
-    // Every pair once from some 16,000 particles on, where the chunks' sums fit the working memory: the smallest chunk
-    // that lets them (smaller tiles leave fewer compute units waiting at the end).  Tiles against sym, two species, us:
-    // FP32 87 / 93 at 16,000, 119 / 117 at 20,011, 245 / 178 at 30,000 (chunks of 256), 475 / 357 at 43,000 (512),
-    // 941 / 685 at 62,000 (1024), 953 / 776 at 65,536 (1280, 963 with four particles a lane, which leave a second round
-    // of workgroups); FP64 157 / 155 at 16,000, 239 / 199 at 20,011, 513 / 363 at 30,000, 1002 / 751 at 43,000, and
-    // above 44,000, where chunks of 1280 fill the device unevenly, 1309 / 1424 at 49,000.
+    // Every pair once above 16,384 particles, where the chunks' sums fit the working memory: the smallest chunk that
+    // lets them (smaller tiles leave fewer compute units waiting at the end).  Tiles against sym, three species, us:
+    // FP32 86 / 94 at 16,001, 130 / 98 at 18,000, 118 / 117 at 20,011, 245 / 176 at 30,000 (chunks of 256), 472 / 363
+    // at 43,000 (512), 941 / 685 at 62,000 (1024), 957 / 754 at 65,536 (1280, 963 with four particles a lane, which
+    // leave a second round of workgroups); FP64 149 / 156 at 16,001, 195 / 161 at 18,000, 235 / 205 at 20,011, 506 /
+    // 372 at 30,000, 1006 / 701 at 43,000, and above 44,000, where chunks of 1280 fill the device unevenly, 1309 /
+    // 1424 at 49,000.
     const bool fp32 = precision == BD_PREC_FP32;
     if (q2 && !cut && n > kSymMin) {
         for (int C : {256, 512, 1024, 1280}) {

@@ -187,7 +187,7 @@ def test_pair_forces_dev_cells_fall_back(how, fp32):
 
 
 @pytest.mark.parametrize("fp32", [False, True])
-@pytest.mark.parametrize("n, S", [(16001, 1), (20001, 8), (20480, 2), (31001, 3), (46001, 2), (64001, 2)])
+@pytest.mark.parametrize("n, S", [(16385, 1), (20001, 8), (20480, 2), (31001, 3), (46001, 2), (64001, 2)])
 def test_pair_forces_dev_every_pair_once_matches_oracle(n, S, fp32):
     """The inverse-square law without a cutoff above the rows: every chunk length, ragged last chunks, species of
     uneven number with one absent, and sizes whose sums do not fit and stay with the tiles (64,001 in FP64)."""
