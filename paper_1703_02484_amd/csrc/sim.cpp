@@ -839,8 +839,10 @@ Sim::StepGraph &step_graph(Sim &s) {
     }
     Sim::StepGraph &g = *found;
     constexpr int64_t kSteady = 32;   // steps with the same budgets before the longer graph is captured
-    const bool many = !s.timing && !g.many && g.uses >= kSteady;
-    if (s.timing ? g.post != nullptr : g.one != nullptr && !many) return g;
+    // a batch whose steps are not a multiple of kGraphSteps needs `one` beside `many`, also where the uses so far were
+    // timed steps, which capture neither
+    const bool one = !s.timing && !g.one, many = !s.timing && !g.many && g.uses >= kSteady;
+    if (s.timing ? g.post != nullptr : !one && !many) return g;
     const int r0 = s.round_id, v0 = s.vround;
     const int rbase_live = s.rbase, vbase_live = s.vbase;
     auto pre = [&] {
@@ -888,11 +890,9 @@ Sim::StepGraph &step_graph(Sim &s) {
         g.pre = capture(s, pre);
         g.force = capture(s, force);
         g.post = capture(s, post);
-    } else if (many) {
-        g.many = steps(kGraphSteps);
-    } else {
-        g.one = steps(1);
     }
+    if (one) g.one = steps(1);
+    if (many) g.many = steps(kGraphSteps);
     s.round_id = r0;   // capturing ran nothing
     s.vround = v0;
     s.rbase = rbase_live;

@@ -206,3 +206,25 @@ def test_graph_forms_bitwise_equal_eager(name, over):
             assert np.array_equal(xa, xb) and np.array_equal(ta, tb) and sa == sb
         else:
             _same(a, b)
+
+
+@pytest.mark.parametrize("name,over", [("C2", {}), ("C3", {}), ("C3", {"overlap": "verlet"})])
+def test_untimed_steps_after_a_handles_first_steps_were_timed(name, over):
+    """A fresh handle whose first steps all run cut around their timed force, with moves so small that the round
+    budgets settle and hold (they shrink by one after 64 steps that needed less), and then untimed batches that need
+    single steps (3), both graphs (11) and several in one graph (8)."""
+    w = synth.make(name, n=600)
+    a = binding.Sim.from_workload(w, dt=1e-9, **over)
+    b = binding.Sim.from_workload(w, dt=1e-9, **over)
+    b.set_graph_mode(True)
+    b.enable_kernel_timing(True)
+    a.step(600)
+    b.step(600)
+    assert b.kernel_time()[1] == 600
+    b.enable_kernel_timing(False)
+    for n in (3, 11, 8):
+        a.step(n)
+        b.step(n)
+        xa, ta, sa, _ = a.state()
+        xb, tb, sb, _ = b.state()
+        assert np.array_equal(xa, xb) and np.array_equal(ta, tb) and sa == sb
