@@ -28,7 +28,7 @@ enum Ctl {
     K_OVL_ROUNDS = 6,  // overlap rounds that moved disks in the budgeted sequence
     K_LAST = 7,        // last round slot of the repair that halted
     K_NL_REBUILD = 8,  // a disk moved more than skin/2 since the neighbour lists were built
-    K_NL_OVERFLOW = 9, // largest neighbour count when it exceeded the list capacity
+    K_REV = 9,         // Delaunay edges reversed by this step's move, counted when a reversal halves the step
     K_FQUEUE = 10,     // next tile of the persistent all-pairs force launch
     K_TAPE_ENT = 11,   // adjoint tape: entries recorded by the overlap rounds of this step
     K_TAPE_DIR = 12,   // adjoint tape: overlap rounds recorded in this step
@@ -39,8 +39,10 @@ enum Ctl {
     K_TICKET = 17,     // workgroups finished in the current launch (last-workgroup checks; back to 0 after)
     K_NL_BUILT = 18,   // the neighbour lists were rebuilt on the device at the start of this step
     K_NL_STALE = 19,   // list overlap detection: a disk moved so far since the build that a pair may be missing
-    K_REV = 20,        // Delaunay edges reversed by this step's move, counted when a reversal halves the step
-    K_CAND = 21,                     // [MAXR] flip candidates of round slot j
+    K_NL_OVERFLOW = 20, // list build: largest neighbour count when it exceeded the list capacity
+    K_NL_LONG = 21,    // list build: cells of more disks than a row holds
+    K_NL_IDS = 22,     // list build: room taken for their ids
+    K_CAND = 23,                     // [MAXR] flip candidates of round slot j
     K_WL = K_CAND + MAXR,            // [MAXR] worklist length read by round slot j
     K_INVQ = K_WL + MAXR,            // [MAXR] evaluated quads holding an inverted triangle
     K_INV = K_INVQ + MAXR,           // [MAXREP] invalid triangles after repair j
@@ -53,7 +55,8 @@ enum HaltReason {
     HALT_INVALID = 2,
     HALT_TOPOLOGY = 3,
     HALT_OVERLAP_BUDGET = 4,
-    HALT_NL_CAPACITY = 5,  // a rebuild inside a queued step found more neighbours than the lists hold
+    HALT_NL_CAPACITY = 5,  // a rebuild inside a queued step found more neighbours than the lists hold, or a cell of
+                           // more disks than its row holds in a step queued without the sort of such cells
     HALT_NL_STALE = 6,     // list overlap detection: the lists may miss a pair (rebuild, then continue)
     HALT_REVERSAL = 7      // the move reversed a Delaunay edge: the host redoes the step in halves
 };
@@ -281,6 +284,9 @@ struct Sim {
     int *nl_cand = nullptr;          // disks of a one-workgroup list round
     int nl_phase = 1;                // list overlap rounds launched as full passes before the one-workgroup rest
     int *cell_rows = nullptr, *cell_more = nullptr, *cell_next = nullptr;   // empty between builds (k_verlet.hip)
+    int *cell_long = nullptr;        // [n / 8 + 1] cells of more disks than a row holds
+    int *cell_ids = nullptr;         // [2 n] their ids, in the order of the chain and sorted
+    bool nl_sort = false;            // such cells have been met: queued steps sort them too
     double *xbuild = nullptr, *ybuild = nullptr;
     double2 *fsr = nullptr;          // short-range forces, caller order
     int ovl_method = 0;              // 0: overlap rounds over Delaunay edges; 1: over the neighbour lists
@@ -373,7 +379,8 @@ void launch_reduce_forces(Sim &s);
 // short-range path (k_verlet.hip)
 size_t verlet_row_ints(int ncell);   // ints in the rows of ncell cells
 void launch_verlet_build(Sim &s);
-void launch_verlet_build_requested(Sim &s);   // the same kernels, each doing nothing unless the step asks (graph mode)
+// the same kernels, each doing nothing unless the step asks (graph mode); the sort of long cells where s.nl_sort
+void launch_verlet_build_requested(Sim &s);
 void launch_force_nl(Sim &s);
 // xy[0, m) = (x, y)[0, m): after a copy into x, y
 void launch_pack_xy(Sim &s, int m);

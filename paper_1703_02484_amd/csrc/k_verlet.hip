@@ -8,12 +8,15 @@
 // They stay valid while no disk has moved more than skin / 2 since the build:
 // then every pair with d <= r_cut at force time is in the list.  The build is
 // two launches: every disk enters its cell's row, then one thread per disk scans
-// the 3 x 3 rows around it, each row's few ids sorted in registers.  In graph
-// mode both are part of every queued step and do nothing unless the previous
-// step's skin test asked for new lists (`req` points at the step's flag; null:
-// always build), so what they cost is their launches: as a counting sort (count,
-// two scans, scatter, sort, build) six launches took 27 us of every step, now 9,
-// and a build of 1,000,000 disks 166 us, now 104.
+// the 3 x 3 rows around it, each row's few ids sorted in registers.  Cells of
+// more disks than a row holds are sorted once by a launch between the two: by
+// every build of the host, and in queued steps from the first such cell on (a
+// step queued before halts at its force, and the host runs it again).  In graph
+// mode the launches are part of every queued step and do nothing unless the
+// previous step's skin test asked for new lists (`req` points at the step's
+// flag; null: always build), so what they cost is their launches: as a counting
+// sort (count, two scans, scatter, sort, build) six launches took 27 us of every
+// step, now 9, and a build of 1,000,000 disks 166 us, now 104.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -45,22 +48,94 @@ constexpr int kNlBatch = 2;
 constexpr int kBuildGrid = 512;
 
 // A cell's row: the number of disks, then the first seven ids, in the order they came; one 32-byte sector.  Further
-// disks hang on the cell's chain (cell_more: the last one + 1, cell_next: the one before, by id).  Rows and chains are
-// empty between builds: whoever reads the new lists first clears them.
+// disks hang on the cell's chain (cell_more: the last one + 1, cell_next: the one before, by id), and the eighth enters
+// the cell in the list of long cells.  Rows and chains are empty between builds: whoever reads the new lists first
+// clears them.
 constexpr int kCellIds = 7;
 constexpr int kCellRow = kCellIds + 1;
 
+struct LongCells {
+    int *list;   // cells of more than kCellIds disks, in the order they came
+    int *ids;
+    int *ctl;    // K_NL_LONG of them, K_NL_IDS of ids taken
+};
+
 __global__ void k_cell_insert(int n, const double2 *__restrict__ xy, double inv_cell, int nc, int *__restrict__ rows,
-                              int *__restrict__ more, int *__restrict__ next, const int *req) {
+                              int *__restrict__ more, int *__restrict__ next, LongCells lc, const int *req) {
     if (req && !*req) return;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const double2 p = xy[i];
         const int c = cell_coord(p.y, inv_cell, nc) * nc + cell_coord(p.x, inv_cell, nc);
         const int k = atomicAdd(&rows[(size_t)c * kCellRow], 1);
-        if (k < kCellIds)
+        if (k < kCellIds) {
             rows[(size_t)c * kCellRow + 1 + k] = i;
-        else
-            next[i] = atomicExch(&more[c], i + 1);
+            continue;
+        }
+        const unsigned long long eighth = __ballot(k == kCellIds);   // one reservation for the wavefront
+        if (eighth != 0) {
+            const int lane = __lane_id(), leader = __ffsll(eighth) - 1;
+            int at = 0;
+            if (lane == leader) at = atomicAdd(&lc.ctl[K_NL_LONG], __popcll(eighth));
+            at = __shfl(at, leader);
+            if (k == kCellIds) lc.list[at + __popcll(eighth & ((1ull << lane) - 1ull))] = c;
+        }
+        next[i] = atomicExch(&more[c], i + 1);
+    }
+}
+
+// The ids of each long cell in ascending order, kSortLanes lanes a cell: gathered from the row and the chain, then each
+// to the place that the number of smaller ones gives.  cell_more becomes the start of the sorted ids.  The time is the
+// walk of the chain; room is taken with one atomic for all cells of a workgroup's turn (262,144 disks, 11 a cell, with
+// an atomic per cell here and in the insert 399 us a build, so 151).  Unit disks at area fraction 0.5, us a build with
+// every disk selecting a long cell's next id from its chain / sorted once (and as a counting sort of all cells): 262,144
+// with lists of radius 3 37 / 37 (52), 5.5 75 / 63 (90), 8.5 278 / 151 (190), 12.5 1158 / 271 (408); 40,009 with 12.5
+// 670 / 95 (224).
+constexpr int kSortBlock = 256, kSortLanes = 8, kSortCells = kSortBlock / kSortLanes;
+
+__global__ __launch_bounds__(kSortBlock) void k_cells_sort(const int *__restrict__ rows, int *__restrict__ more,
+                                                           const int *__restrict__ next, LongCells lc,
+                                                           const int *req) {
+    __shared__ int start[kSortCells];
+    if (req && !*req) return;
+    const int g = threadIdx.x / kSortLanes, lane = threadIdx.x & (kSortLanes - 1), count = lc.ctl[K_NL_LONG];
+    for (int w0 = blockIdx.x * kSortCells; w0 < count; w0 += gridDim.x * kSortCells) {   // uniform in the workgroup
+        const bool valid = w0 + g < count;
+        const int c = valid ? lc.list[w0 + g] : 0;
+        const int *row = rows + (size_t)c * kCellRow;
+        const int m = valid ? row[0] : 0;
+        __syncthreads();   // the turn before has read its starts
+        if (lane == 0) start[g] = 2 * m;
+        __syncthreads();
+        if (threadIdx.x < kSortCells) {   // one wavefront
+            const int own = start[threadIdx.x];
+            int incl = own;
+            for (int off = 1; off < kSortCells; off <<= 1) {
+                const int v = __shfl_up(incl, off, kSortCells);
+                if ((int)threadIdx.x >= off) incl += v;
+            }
+            int at = 0;
+            if (threadIdx.x == kSortCells - 1) at = atomicAdd(&lc.ctl[K_NL_IDS], incl);
+            start[threadIdx.x] = __shfl(at, kSortCells - 1, kSortCells) + incl - own;
+        }
+        __syncthreads();
+        int *came = lc.ids + start[g], *sorted = came + m;
+        if (valid) {
+            if (lane < kCellIds) came[lane] = row[1 + lane];
+            int e = more[c];
+            for (int k = kCellIds; k < m; ++k) {   // the same in the cell's lanes
+                if (lane == 0) came[k] = e - 1;
+                e = next[e - 1];
+            }
+        }
+        __syncthreads();   // the ids that other lanes wrote
+        for (int k = lane; k < m; k += kSortLanes) {
+            const int id = came[k];
+            int smaller = 0;
+#pragma unroll 8
+            for (int q = 0; q < m; ++q) smaller += came[q] < id ? 1 : 0;
+            sorted[smaller] = id;
+        }
+        if (valid && lane == 0) more[c] = start[g] + m;
     }
 }
 
@@ -73,7 +148,7 @@ struct BuildArgs {
     double inv_cell, rl2, P;
     const double2 *xy;
     const int4 *rows;
-    const int *more, *next;
+    const int *more, *ids;   // ids: the sorted ids of the long cells (null: they are not sorted)
     int *nl, *nl_cnt, *overflow;
     double *xb, *yb;
 };
@@ -113,17 +188,19 @@ __device__ __forceinline__ void nl_build_one(const BuildArgs &a, int i) {
         for (int u = 0; u < 3; ++u) {
             const int m = c[u] < 0 ? 0 : lo[u].x;
             int id[kCellIds] = {lo[u].y, lo[u].z, lo[u].w, hi[u].x, hi[u].y, hi[u].z, hi[u].w};
-            if (m > kCellIds) {   // also on the chain: the smallest id above the last one, m times
-                int last = -1;
-                for (int k = 0; k < m; ++k) {
-                    int best = 0x7FFFFFFF;
+            if (m > kCellIds) {
+                if (!a.ids) continue;   // the step halts before its lists are read
+                const int *ids = a.ids + a.more[c[u]];
+                constexpr int kB = 8;
+                for (int k = 0; k < m; k += kB) {
+                    int j[kB];
+                    double2 pj[kB];
 #pragma unroll
-                    for (int q = 0; q < kCellIds; ++q)
-                        if (id[q] > last && id[q] < best) best = id[q];
-                    for (int e = a.more[c[u]]; e != 0; e = a.next[e - 1])
-                        if (e - 1 > last && e - 1 < best) best = e - 1;
-                    last = best;
-                    test(best, a.xy[best]);
+                    for (int q = 0; q < kB; ++q) j[q] = k + q < m ? ids[k + q] : i;   // disk i is not its own neighbour
+#pragma unroll
+                    for (int q = 0; q < kB; ++q) pj[q] = a.xy[j[q]];
+#pragma unroll
+                    for (int q = 0; q < kB; ++q) test(j[q], pj[q]);
                 }
                 continue;
             }
@@ -183,14 +260,16 @@ __global__ __launch_bounds__(256) void k_force_nl(int n, const double2 *__restri
                                                   const int *__restrict__ nl, const int *__restrict__ nl_cnt,
                                                   double2 *__restrict__ f, const StepBase *__restrict__ base,
                                                   int *__restrict__ ctl, double inv_cell, int nc,
-                                                  int *__restrict__ rows, int *__restrict__ more, double P) {
+                                                  int *__restrict__ rows, int *__restrict__ more, bool sorted,
+                                                  double P) {
 #pragma clang fp contract(off)
     int i = xcd_block() * blockDim.x + threadIdx.x;
     if (base->stop) return;
     // after a rebuild inside a queued step: count it, and stop the step here if a disk had more
-    // neighbours than the lists hold (the host grows them and runs the step again)
+    // neighbours than the lists hold or a cell was long and not sorted (the host grows the lists, sorts, and runs the
+    // step again)
     const bool built = base->nl_now != 0;
-    const bool over = built && ctl[K_NL_OVERFLOW] > 0;
+    const bool over = built && (ctl[K_NL_OVERFLOW] > 0 || (!sorted && ctl[K_NL_LONG] > 0));
     if (built && blockIdx.x == 0 && threadIdx.x == 0) {
         ctl[K_NL_BUILT] = 1;
         if (over) {
@@ -618,7 +697,7 @@ NlArgs nl_args(const Sim &s) {
 namespace {
 
 // The build kernels; req = null builds unconditionally, else only when *req != 0.
-void enqueue_build(Sim &s, const int *req) {
+void enqueue_build(Sim &s, const int *req, bool sort) {
     const double rl = s.fp.cutoff + s.fp.skin;
     BuildArgs a;
     a.n = s.n;
@@ -630,14 +709,18 @@ void enqueue_build(Sim &s, const int *req) {
     a.xy = s.xy;
     a.rows = (const int4 *)s.cell_rows;
     a.more = s.cell_more;
-    a.next = s.cell_next;
+    a.ids = sort ? s.cell_ids : nullptr;
     a.nl = s.nl;
     a.nl_cnt = s.nl_cnt;
     a.overflow = s.ctl + K_NL_OVERFLOW;
     a.xb = s.xbuild;
     a.yb = s.ybuild;
+    const LongCells lc{s.cell_long, s.cell_ids, s.ctl};
     hipLaunchKernelGGL(k_cell_insert, dim3(capped(blocks(s.n))), dim3(256), 0, s.stream, s.n, a.xy, a.inv_cell, a.nc,
-                       s.cell_rows, s.cell_more, s.cell_next, req);
+                       s.cell_rows, s.cell_more, s.cell_next, lc, req);
+    if (sort)
+        hipLaunchKernelGGL(k_cells_sort, dim3(capped(s.n / 8 / kSortCells + 1, 2 * kBuildGrid)), dim3(kSortBlock), 0,
+                           s.stream, (const int *)s.cell_rows, s.cell_more, (const int *)s.cell_next, lc, req);
     hipLaunchKernelGGL(s.period > 0.0 ? k_nl_build<true> : k_nl_build<false>, dim3(capped(blocks(s.n), 2 * kBuildGrid)),
                        dim3(256), 0, s.stream, a, req);
 }
@@ -652,16 +735,16 @@ static void launch_cells_clear(Sim &s) {
                        (double)s.nl_nc / s.L_h[0], s.nl_nc, s.cell_rows, s.cell_more);
 }
 
-// Rebuilds the lists from the current positions (the caller zeroed the overflow flag) and empties the cells.
+// Rebuilds the lists from the current positions (the caller zeroed the build's counters) and empties the cells.
 void launch_verlet_build(Sim &s) {
-    enqueue_build(s, nullptr);
+    enqueue_build(s, nullptr, true);
     launch_cells_clear(s);
 }
 
 void launch_verlet_build_requested(Sim &s) {
     StepBase *b = (StepBase *)s.dbase;
     // the force kernel that follows records the rebuild, checks its capacity and empties the cells
-    enqueue_build(s, &b->nl_now);
+    enqueue_build(s, &b->nl_now, s.nl_sort);
 }
 
 void launch_force_nl(Sim &s) {
@@ -671,7 +754,7 @@ void launch_force_nl(Sim &s) {
                            (const int *)s.sp, (const double *)s.Kd, s.S, s.fp.kind, s.fp.q,
                            s.fp.A, s.fp.lambda, s.fp.cutoff, (const int *)s.nl, (const int *)s.nl_cnt, s.fsr,
                            (const StepBase *)s.dbase, s.ctl, (double)s.nl_nc / s.L_h[0], s.nl_nc, s.cell_rows,
-                           s.cell_more, s.period);
+                           s.cell_more, s.nl_sort, s.period);
     };
     if (s.fp32)
         per ? (s.S == 1 ? go(k_force_nl<float, true, true>) : go(k_force_nl<float, false, true>))

@@ -437,10 +437,12 @@ void drop_graphs(Sim &s) {
 // check the list capacity; grows it once if a disk has too many neighbours).
 void verlet_rebuild(Sim &s) {
     for (int attempt = 0; attempt < 2; ++attempt) {
-        zero_ctl(s, K_NL_OVERFLOW);
+        static_assert(K_NL_LONG == K_NL_OVERFLOW + 1 && K_NL_IDS == K_NL_OVERFLOW + 2, "cleared together");
+        fill_int(s, s.ctl + K_NL_OVERFLOW, 3, 0);
         launch_verlet_build(s);
         read_ctl(s);
         const int need = s.hctl[K_NL_OVERFLOW];
+        if (s.hctl[K_NL_LONG] > 0) s.nl_sort = true;
         if (need == 0) {
             ++s.st.verlet_rebuilds;
             s.need_rebuild = false;
@@ -824,7 +826,8 @@ hipGraphExec_t capture(Sim &s, const std::function<void()> &enqueue) {
 // of the step being replayed.
 Sim::StepGraph &step_graph(Sim &s) {
     const int nover = s.ovl_method == 1 ? s.budget.overlaps : overlaps_budget(s);
-    std::vector<int> key = {s.budget.em, nover, tail_mode_of(s), s.multi_em, s.multi_ovl, s.ovl_phase, s.nl_phase};
+    std::vector<int> key = {s.budget.em, nover, tail_mode_of(s), s.multi_em, s.multi_ovl, s.ovl_phase, s.nl_phase,
+                            s.nl_sort ? 1 : 0};
     for (int j = 0; j < nover; ++j) key.push_back(s.budget.ovl[j]);
     Sim::StepGraph *found = nullptr;
     for (auto &e : s.graphs)
@@ -1685,7 +1688,7 @@ void free_all(Sim &s) {
                     s.claim, s.tri_stamp, s.moved, s.edge_stamp, s.vstamp, s.wl[0], s.wl[1], s.cand, s.cand_won,
                     s.touched, s.det_stamp, s.fl_stamp, s.fl, s.vt_stamp, s.vt, s.newpos, s.oldpos, s.star, s.star_deg, s.snap_v, s.snap_twin,
                     s.snap_vh, s.xa, s.ya, s.xb, s.yb, s.ctl,
-                    s.acc, s.nl, s.nl_cnt, s.nl_cand, s.cell_rows, s.cell_more, s.cell_next,
+                    s.acc, s.nl, s.nl_cnt, s.nl_cand, s.cell_rows, s.cell_more, s.cell_next, s.cell_long, s.cell_ids,
                     s.xbuild, s.ybuild, s.fsr, s.stiles, s.xs, s.ys, s.ths};
     for (void *p : ptrs)
         dfree(p);
@@ -2029,6 +2032,8 @@ int init_impl(Sim &s, int R, const int32_t *n_per, const double *xy, const doubl
         s.cell_rows = dalloc<int>(verlet_row_ints(s.nl_ncell));
         s.cell_more = dalloc<int>(s.nl_ncell);
         s.cell_next = dalloc<int>(n);
+        s.cell_long = dalloc<int>(n / 8 + 1);
+        s.cell_ids = dalloc<int>(2 * (size_t)n);
         s.nl = dalloc<int>((size_t)s.nl_cap * n);
         s.nl_cnt = dalloc<int>(n);
         s.nl_cand = dalloc<int>(n);
