@@ -575,7 +575,8 @@ void write_base(Sim &s) {
 // Overlap rounds enqueued per step, never more than the caller's round cap (the
 // host loop enforces the cap beyond that) nor more than the step's flip-round
 // slots hold.  Rounds launched per phase cost their launches whether or not the
-// step needs them: the adaptive budget.  The one-workgroup tail leaves at the
+// step needs them: the adaptive budget in mode 0, those that recently queued many
+// disks in mode 2 (update_ovl_phase).  The one-workgroup tail leaves at the
 // first detection that finds nothing, so it gets all the rounds it holds: a step
 // the host has to continue costs some 100 us per round.  16,384 disks with the
 // contact factor 1/2 need up to 25 rounds a step and now and then 41; ten steps
@@ -613,7 +614,9 @@ int tail_mode_of(const Sim &s) {
 // Mode 2: overlap rounds launched per phase before the one-workgroup tail.  Rounds 0, 1, ... are,
 // up to the first round whose detection queued at most kTailItems disks (half of what the tail's
 // workgroup of 1024 threads takes in one pass of each phase) in the current and the previous
-// window of kTouchWindow steps; that round and the later ones run in the tail.  Measured per step
+// window of kTouchWindow steps; that round and the later ones run in the tail.  Rounds past kMaxLaunchedRounds are
+// launched only after a step that itself queued so many disks there (all of them: each number of rounds is a
+// graph of its own): one such step would cost the next 64 to 128 up to 24 empty rounds more.  Measured per step
 // with graph replay: 512 and 128 within 1 % of each other on 65,536 and 1M disks and on 16,384
 // disks with the contact factor; 2048 is 25-40 % slower on the first two.
 void update_ovl_phase(Sim &s, const int *h, const std::vector<int> &orounds, int rounds) {
@@ -626,7 +629,9 @@ void update_ovl_phase(Sim &s, const int *h, const std::vector<int> &orounds, int
         s.touch_steps = 0;
     }
     int phase = 0;
-    while (phase < MAXO && std::max(s.touch_hi[phase], s.touch_prev[phase]) > kTailItems) ++phase;
+    while (phase < kMaxLaunchedRounds && std::max(s.touch_hi[phase], s.touch_prev[phase]) > kTailItems) ++phase;
+    const bool many = rounds > phase && rounds <= (int)orounds.size() && h[K_TOUCH + orounds[phase]] > kTailItems;
+    if (phase == kMaxLaunchedRounds && many) phase = MAXTAIL;
     s.ovl_phase = phase;
 }
 

@@ -228,3 +228,40 @@ def test_untimed_steps_after_a_handles_first_steps_were_timed(name, over):
         xa, ta, sa, _ = a.state()
         xb, tb, sb, _ = b.state()
         assert np.array_equal(xa, xb) and np.array_equal(ta, tb) and sa == sb
+
+
+def test_rounds_launched_per_phase_after_a_step_of_many():
+    """Launch form 2 launches the overlap rounds that recently moved many disks.  After one step of more than a
+    hundred rounds of thousands of disks the next one launches all 48 that a step holds, those after it 24; the
+    results are those of the other forms."""
+    torch = pytest.importorskip("torch")
+    from torch.profiler import ProfilerActivity, profile
+
+    m, c = 12, 12   # c x c patches of m x m disks on a hexagonal lattice
+
+    def patches(d):
+        p = d * np.array([[i + 0.5 * (j & 1) - m / 2, 0.8660254 * (j - m / 2)] for i in range(m) for j in range(m)])
+        return np.concatenate([p + [20.0 + 32.0 * a, 20.0 + 32.0 * b] for a in range(c) for b in range(c)])
+
+    xy0 = patches(2.1)
+    n = len(xy0)
+    xy = patches(1.99) + np.random.default_rng(3).uniform(0, 0.001, (n, 2))
+    launched = {}
+    sims = []
+    for mode in (1, 2):
+        g = binding.Sim(xy0, np.ones(n), np.zeros(n, np.int32), None, np.array([[0.0]]), L=32.0 * c + 8, D=0.0,
+                        dt=1e-6, seed=1, overlap_factor=0.5, contact_tol=1e-4)
+        g.set_tail_mode(mode)
+        g.set_positions(xy)
+        g.step(1)
+        assert g.state()[3]["overlap_rounds_max"] > 100
+        for _ in range(3):
+            with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
+                g.step(1)
+                torch.cuda.synchronize()
+            names = [e.name for e in prof.events()]
+            assert any("k_em" in k for k in names)   # the trace holds this library's kernels
+            launched.setdefault(mode, []).append(sum("k_ovl_gather" in k for k in names))
+        sims.append(g)
+    assert launched == {1: [0, 0, 0], 2: [48, 24, 24]}
+    _same(*sims)
