@@ -111,26 +111,34 @@ def c3_source_sha1():
     return h.hexdigest()
 
 
-def _short_range_once(w, steps, warmup, overlap):
+def timed_steps(sim, steps, warmup):
+    """`warmup` untimed steps, then `steps` timed ones: (seconds, force seconds per launch, force launches, counters
+    before).  Kernel timing is on in both: with it a step is captured in its own form, which belongs to the warm-up."""
     import torch
 
-    from paper_1703_02484_amd import binding
-
-    sim = binding.Sim.from_workload(w, overlap=overlap)
-    sim.set_graph_mode(True)
+    sim.enable_kernel_timing(True)
     sim.step(warmup)
     st0 = sim.state()[3]
-    sim.enable_kernel_timing(True)
+    sim.enable_kernel_timing(True)   # from zero
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     sim.step(steps)
     torch.cuda.synchronize()   # every stream of the device, the library's included
     elapsed = time.perf_counter() - t0
     force_ms, launches = sim.kernel_time()
+    return elapsed, force_ms / 1e3 / max(launches, 1), launches, st0
+
+
+def _short_range_once(w, steps, warmup, overlap):
+    from paper_1703_02484_amd import binding
+
+    sim = binding.Sim.from_workload(w, overlap=overlap)
+    sim.set_graph_mode(True)
+    elapsed, force_s, _, st0 = timed_steps(sim, steps, warmup)
     st1 = sim.state()[3]
     sim.close()
     d = {k: st1[k] - st0[k] for k in st1}
-    return elapsed, force_ms / 1e3 / max(launches, 1), d
+    return elapsed, force_s, d
 
 
 def run_short_range(steps, warmup):
@@ -197,19 +205,10 @@ def run_batched(steps, warmup, loop_steps):
     b = binding.Sim.from_workloads(ws)
     b.set_graph_mode(True)
     cfg = b.force_config()
-    b.step(warmup)
-    st0 = b.state()[3]
-    b.enable_kernel_timing(True)
-    torch.cuda.synchronize()
-    t0 = time.perf_counter()
-    b.step(steps)
-    torch.cuda.synchronize()
-    elapsed = time.perf_counter() - t0
-    force_ms, launches = b.kernel_time()
+    elapsed, avg_s, _, st0 = timed_steps(b, steps, warmup)
     xb, _, step_b, st1 = b.state()
     _, doff, _ = b.layout()
     b.close()
-    avg_s = force_ms / 1e3 / max(launches, 1)
     tflops = FLOPS_PER_PAIR * pairs / avg_s / 1e12
     out = {"workload": f"C4: {len(ws)} systems, N_r log-uniform in [2048, 32768] (sum {ntot}), phi_r ~ U[0.2, 0.5], "
                        f"FP64 all-pairs inverse-square K=1e-2, dt=1e-4, seed_r=r",
@@ -222,17 +221,9 @@ def run_batched(steps, warmup, loop_steps):
     # the same batch with FP32 pair sums (positions and predicates stay FP64)
     b32 = binding.Sim.from_workloads(ws, fp32=True)
     b32.set_graph_mode(True)
-    b32.step(warmup)
-    b32.enable_kernel_timing(True)
-    torch.cuda.synchronize()
-    t0 = time.perf_counter()
-    b32.step(steps)
-    torch.cuda.synchronize()
-    el32 = time.perf_counter() - t0
-    f32_ms, f32_launches = b32.kernel_time()
+    el32, f32_s, _, _ = timed_steps(b32, steps, warmup)
     out["fp32"] = {"value": ntot * steps / el32, "unit": "particle-steps/s", "ms_per_step": 1e3 * el32 / steps,
-                   "force_ms": f32_ms / max(f32_launches, 1),
-                   "force_tflops": FLOPS_PER_PAIR * pairs / (f32_ms / 1e3 / max(f32_launches, 1)) / 1e12,
+                   "force_ms": f32_s * 1e3, "force_tflops": FLOPS_PER_PAIR * pairs / f32_s / 1e12,
                    "force_config": b32.force_config()}
     b32.close()
     # the same systems, one handle each (pinned to the batch's force form), stepped one after another
@@ -446,15 +437,7 @@ def main():
     torch.cuda.synchronize()
     eager_ms = 1e3 * (time.perf_counter() - t0) / max(1, args.steps // 4)
     sim.set_graph_mode(not args.no_graph)
-    sim.step(args.warmup)
-    st0 = sim.state()[3]
-    sim.enable_kernel_timing(True)
-    torch.cuda.synchronize()
-    t0 = time.perf_counter()
-    sim.step(args.steps)
-    torch.cuda.synchronize()   # every stream of the device, the library's included
-    elapsed = time.perf_counter() - t0
-    force_ms, launches = sim.kernel_time()
+    elapsed, avg_force_s, launches, st0 = timed_steps(sim, args.steps, args.warmup)
     st1 = sim.state()[3]
     fcfg = sim.force_config()
 
@@ -462,7 +445,6 @@ def main():
     ms_per_step = 1e3 * elapsed / args.steps
     value = n * args.steps / elapsed
     pairs = n * (n - 1)
-    avg_force_s = force_ms / 1e3 / max(launches, 1)
     achieved = FLOPS_PER_PAIR * pairs / avg_force_s / 1e12
     peak = PEAK_FP32_TFLOPS if w.fp32_forces else PEAK_FP64_TFLOPS
     d = {k: st1[k] - st0[k] for k in st1}
@@ -485,8 +467,8 @@ def main():
                         f"hard walls, Delaunay overlap correction",
             "N": n,
             "pair_interactions_per_s": pairs / avg_force_s,
-            "force_ms_per_step": force_ms / max(launches, 1),
-            "other_ms_per_step": ms_per_step - force_ms / max(launches, 1),
+            "force_ms_per_step": avg_force_s * 1e3,
+            "other_ms_per_step": ms_per_step - avg_force_s * 1e3,
             "graph_mode": not args.no_graph,
             "eager_ms_per_step": eager_ms,
             "overlap_rounds_per_step": d["overlap_rounds_total"] / args.steps,
