@@ -261,3 +261,53 @@ def test_noalloc_layouts_in_a_graph(n, cutoff):
         ref = binding.pair_forces_dev(xy, sp, K, **{**kw, "noalloc": False})
         torch.cuda.synchronize()
         assert torch.equal(got, ref), scale
+
+
+@pytest.mark.parametrize("fp32, n, S", [(True, 40001, 1), (True, 60001, 2), (True, 64101, 2), (True, 71600, 2),
+                                        (True, 66001, 8), (False, 28001, 2), (False, 44001, 2)])
+def test_pair_forces_dev_every_pair_once_in_long_chunks(fp32, n, S):
+    """Chunks of 512, 1,024 and (FP32) 1,280 particles, whose wavefronts add into one copy of the sums: against the
+    oracle, with two particles at one place (neighbours, in different wavefronts of a chunk, in different chunks), with
+    one at infinity, and captured and replayed with other positions, bitwise the eager forces."""
+    import torch
+
+    w = synth.make("C1", n=n)
+    rng = np.random.default_rng(n)
+    species = np.minimum(rng.integers(0, 4 * S, n), S - 1).astype(np.int32)
+    K = rng.normal(size=(S, S)) * 1e-2
+    base, sp = torch.from_numpy(np.ascontiguousarray(w.xy)).cuda(), torch.from_numpy(species).cuda()
+    f = binding.pair_forces_dev(base, sp, K, fp32=fp32).cpu().numpy()
+    idx = np.unique(np.concatenate([[0, n // 2, n - 1], rng.integers(0, n, 300)])).astype(np.int32)
+    fo = oracle.forces(w.xy, species, K, idx=idx)
+    assert np.abs(f[idx] - fo).max() <= (1e-4 if fp32 else 1e-12) * np.abs(fo).max()
+
+    for a, b in ((3, 4), (0, n - 1), (100, 100 + 450)):
+        xy = base.clone()
+        xy[b] = xy[a]
+        f = binding.pair_forces_dev(xy, sp, K, fp32=fp32).cpu().numpy()
+        bad = np.zeros(n, bool)
+        bad[[a, b]] = True
+        assert not np.isfinite(f[bad]).any() and np.isfinite(f[~bad]).all()
+    xy = base.clone()
+    xy[n - 1, 0] = np.inf
+    f = binding.pair_forces_dev(xy, sp, K, fp32=fp32).cpu().numpy()
+    rest = np.arange(n) != n - 1
+    assert np.isnan(f[:, 0]).all() and np.isfinite(f[rest, 1]).all()
+
+    xy = base.clone()
+    out = torch.empty_like(xy)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        binding.pair_forces_dev(xy, sp, K, fp32=fp32, out=out, noalloc=True)
+    torch.cuda.current_stream().wait_stream(s)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        binding.pair_forces_dev(xy, sp, K, fp32=fp32, out=out, noalloc=True)
+    for scale in (1.0, 1.3, 0.9, 1.0):
+        xy.copy_(base * scale)
+        g.replay()
+        torch.cuda.synchronize()
+        got = out.clone()
+        ref = binding.pair_forces_dev(xy, sp, K, fp32=fp32)
+        assert torch.equal(got, ref), scale
