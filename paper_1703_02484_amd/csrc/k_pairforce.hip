@@ -26,7 +26,7 @@
 //          tiles, which are launched behind it and do nothing otherwise.
 // None depends on the launch timing.  The only device memory beyond the
 // caller's inputs and outputs is `part` (J * n * 2 values of the working
-// precision) or the cells' arrays.
+// precision), the sorted particles and chunk sums of sym, or the cells' arrays.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -233,8 +233,9 @@ __device__ __forceinline__ void pf_stage(PfStage<T> &st, int S, int jb, int m, c
     __syncthreads();
 }
 
-// Adds the staged j [k0, k1) to the sums of P particles i.  SELF: the block may hold i itself (at index own[p]).
-template <typename T, int LAW, int P, bool SELF>
+// Adds the staged j [k0, k1) to the sums of P particles i.  SELF: the block may hold i itself (at index own[p]).  CUT:
+// pairs beyond the cutoff add 0.
+template <typename T, int LAW, int P, bool SELF, bool CUT>
 __device__ __forceinline__ void pf_block(const PfStage<T> &st, int k0, int k1, const PfConst<T> &c, const T (&xi)[P],
                                          const T (&yi)[P], const int (&own)[P], T (&ax)[P], T (&ay)[P]) {
 #pragma unroll 4
@@ -247,14 +248,15 @@ __device__ __forceinline__ void pf_block(const PfStage<T> &st, int k0, int k1, c
             const T d2 = dx * dx + dy * dy;
             T g = law_factor<LAW>(d2, c);
             if (SELF) g = own[p] == jk ? (T)0 : g;
+            if (CUT) g = d2 > c.cut2 ? (T)0 : g;
             ax[p] += dx * g;
             ay[p] += dy * g;
         }
     }
 }
 
-// The same with a cutoff.  Most pairs are beyond it and a law costs many times the test, so a lane only notes the
-// staged j inside its cutoff (kPfHits per particle at most) and the wavefront evaluates the noted pairs together,
+// The same for blocks most of whose pairs are beyond the cutoff.  A law costs many times the test, so a lane only notes
+// the staged j inside its cutoff (kPfHits per particle at most) and the wavefront evaluates the noted pairs together,
 // when a lane's list is full and at the end of the part: each lane still adds its pairs in staged order.
 constexpr int kPfHits = 16;
 
@@ -309,16 +311,35 @@ __device__ __forceinline__ void pf_block_cut(const PfStage<T> &st, short (&hit)[
     for (int p = 0; p < P; ++p) evaluate(p, ax[p], ay[p]);
 }
 
-// VALU-bound.  65,536 particles, two species, FP32 inverse square: 0.99 ms, 9 instructions an ordered pair at 0.99
-// of the issue rate (4.1 ms with the strength and the self test in the pair loop and an IEEE square root and
-// division).  20,011 particles, screened law, cutoff 12, FP64: 0.11 ms (0.41 ms evaluating the law wherever one of
-// the wavefront's lanes was in range).
+// Pairs of the wavefront inside the cutoff, of its 64 P kPfProbe with kPfProbe of the block's m staged j.
+constexpr int kPfProbe = 8;
+
+template <typename T, int P>
+__device__ __forceinline__ int pf_inside(const PfStage<T> &st, int m, const PfConst<T> &c, const T (&xi)[P],
+                                         const T (&yi)[P]) {
+    int inside = 0;
+#pragma unroll
+    for (int u = 0; u < kPfProbe; ++u) {
+        const auto q = st.pos[u * m / kPfProbe];
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const T dx = xi[p] - q.x, dy = yi[p] - q.y;
+            inside += __popcll(__ballot(!(dx * dx + dy * dy > c.cut2)));
+        }
+    }
+    return inside;
+}
+
+// VALU-bound.  110,000 particles, FP32 inverse square, no cutoff: 2.9 ms, 9 instructions an ordered pair at 0.96 of the
+// issue rate (11.8 ms with the strength and the self test in the pair loop and an IEEE square root and division).
+// Screened law, FP64, 110,000: without a cutoff 22.8 ms (29.5), cutoff 0.3 of the box 15.4 (29.3, the law evaluated
+// wherever one of the wavefront's lanes was in range), beyond the box 23.8 (29.6; 32.1 noting every pair).  That law in
+// FP64 with a cutoff is held to 128 registers for four wavefronts a SIMD: 129 and three cost 7 %.
 // grid (ceil(n / (256 P)), J); part[split * n + i] = sum over the split's j of K[s_i][s_j] g (r_i - r_j) / d.
 template <typename T, int LAW, bool CUT, int P>
-__global__ __launch_bounds__(kPfBlock) void k_pf_tiles(int n, int J, const double *__restrict__ xy,
-                                                       const int32_t *__restrict__ species, PfLaw law,
-                                                       typename Vec2<T>::type *__restrict__ part,
-                                                       const int *__restrict__ crowded) {
+__global__ __launch_bounds__(kPfBlock, sizeof(T) == 8 && LAW == PF_SCREENED && CUT ? 4 : 1) void k_pf_tiles(
+    int n, int J, const double *__restrict__ xy, const int32_t *__restrict__ species, PfLaw law,
+    typename Vec2<T>::type *__restrict__ part, const int *__restrict__ crowded) {
     using T2 = typename Vec2<T>::type;
     __shared__ PfStage<T> st;
     if (crowded && !*crowded) return;   // the cells have done it
@@ -343,9 +364,10 @@ __global__ __launch_bounds__(kPfBlock) void k_pf_tiles(int n, int J, const doubl
     }
     // with a cutoff the pairs beyond it are skipped: a coordinate at infinity, whose pairs all lie beyond it but give
     // 0 * inf, is found here instead (0 * x is 0 for every finite x)
-    __shared__ int at_infinity;
+    __shared__ int at_infinity, inside[2];
+    int turn = 0;
     T zx = (T)0, zy = (T)0;
-    if (CUT && threadIdx.x == 0) at_infinity = 0;   // read after pf_stage's barriers
+    if (CUT && threadIdx.x == 0) at_infinity = inside[0] = 0;   // read after pf_stage's barriers
     const long long per = ((long long)n + J - 1) / J;
     const int j0 = (int)min((long long)n, per * blockIdx.y);
     const int j1 = (int)min((long long)n, per * (blockIdx.y + 1));
@@ -361,21 +383,36 @@ __global__ __launch_bounds__(kPfBlock) void k_pf_tiles(int n, int J, const doubl
         int own[P];
 #pragma unroll
         for (int p = 0; p < P; ++p) own[p] = ii[p] - jb;
+        // Noting pays where less than kLine / 64 of the pairs are inside.  40,001 particles, us noting with a share of
+        // 0.23 and of 0.48 / pair by pair: screened FP32 1217, 2070 / 1940, FP64 2190, 3851 / 3400; q = 6 FP32 2698,
+        // 5176 / 5500, FP64 4813, 9259 / 9350; inverse square FP64 1114, 1605 / 1080, FP32 804, 1094 / 640 (never).
+        // The wavefronts wait for one another at the next block, so they decide together.
+        constexpr int kLine = !CUT ? 0 : LAW == PF_POWER ? 33 : LAW == PF_SCREENED ? 27 : sizeof(T) == 8 ? 20 : 0;
+        bool note = false;
+        if (kLine > 0) {
+            const int in = pf_inside<T, P>(st, m, c, xi, yi);
+            if ((threadIdx.x & 63) == 0) atomicAdd(&inside[turn], in);
+            __syncthreads();
+            note = inside[turn] < kLine * P * kPfProbe * (kPfBlock / 64);
+            turn ^= 1;   // the other one was read before the last block was staged
+            if (threadIdx.x == 0) inside[turn] = 0;
+        }
         for (int s = 0; s < S; ++s) {
             const int k0 = __builtin_amdgcn_readfirstlane(st.seg[s]), k1 = __builtin_amdgcn_readfirstlane(st.seg[s + 1]);
             T ax[P], ay[P];
 #pragma unroll
             for (int p = 0; p < P; ++p) ax[p] = ay[p] = (T)0;
-            if constexpr (CUT) {
-                if (self)
-                    pf_block_cut<T, LAW, P, true>(st, hit, k0, k1, c, xi, yi, own, ax, ay);
-                else
-                    pf_block_cut<T, LAW, P, false>(st, hit, k0, k1, c, xi, yi, own, ax, ay);
+            if (note) {
+                if constexpr (CUT) {
+                    if (self)
+                        pf_block_cut<T, LAW, P, true>(st, hit, k0, k1, c, xi, yi, own, ax, ay);
+                    else
+                        pf_block_cut<T, LAW, P, false>(st, hit, k0, k1, c, xi, yi, own, ax, ay);
+                }
+            } else if (self) {
+                pf_block<T, LAW, P, true, CUT>(st, k0, k1, c, xi, yi, own, ax, ay);
             } else {
-                if (self)
-                    pf_block<T, LAW, P, true>(st, k0, k1, c, xi, yi, own, ax, ay);
-                else
-                    pf_block<T, LAW, P, false>(st, k0, k1, c, xi, yi, own, ax, ay);
+                pf_block<T, LAW, P, false, CUT>(st, k0, k1, c, xi, yi, own, ax, ay);
             }
 #pragma unroll
             for (int p = 0; p < P; ++p) {
@@ -730,8 +767,10 @@ constexpr int kBinAhead = 8;
 
 // Too crowded for the cells: nine cells around each particle hold about 9 sum(count^2) pairs in all; above n^2 / 4.7
 // (FP64) or n^2 / 6.2 (FP32) of them the tiles are faster.  Evenly filled boxes of r cutoffs a side, tiles and cells,
-// us: screened FP64 9,000 particles 96 / 98 at r = 6, 89 / 80 at 7, 20,011 356 / 335 at 5.3, 323 / 255 at 6; inverse
-// square FP32 9,000 62 / 67 at 7, 62 / 61 at 8, 20,011 164 / 172 at 6, 156 / 133 at 7.
+// us: screened FP64 9,000 particles 107 / 102 at r = 6, 97 / 83 at 7, 20,011 362 / 341 at 5.3, 332 / 259 at 6; inverse
+// square FP32 9,000 64 / 68 at 7, 64 / 60 at 8, 20,011 173 / 173 at 6, 173 / 136 at 7.  The line is that of the smaller
+// calls; at 100,000 the two meet at r = 4 (screened FP64 10.3 / 10.1 ms, 7.0 / 5.2 at 6) and at 5 (inverse square FP32
+// 3.3 / 4.0 at 4.6, 3.3 / 3.0 at 5.3).
 template <typename T>
 __device__ __forceinline__ bool pf_crowded(unsigned long long squares, unsigned long long n) {
     return (sizeof(T) == 4 ? 56 : 42) * squares > n * n;
@@ -987,8 +1026,7 @@ constexpr size_t kPfPartBytes = size_t(32) << 20;   // most working memory of a 
 // Most particles of the cells layout: its sort is one workgroup's, its arrays stay below kPfPartBytes.
 constexpr int kCellsMax = 262144;
 
-// Particles i per lane of the tiles: one LDS read of a j serves them all.  Four for the shortest pair loop
-// (FP32 inverse square: 9 instructions); two where a pair is longer or notes its hits.
+// Places of the sym layout's arrays; returns the bytes.
 template <typename T>
 size_t pf_sym_at(int n, int S, int C, unsigned char *base, PfSym<T> &a) {
     size_t o = 0;
@@ -1004,6 +1042,8 @@ size_t pf_sym_at(int n, int S, int C, unsigned char *base, PfSym<T> &a) {
     return o;
 }
 
+// Particles i per lane of the tiles: one LDS read of a j serves them all.  Four for the shortest pair loop
+// (FP32 inverse square: 9 instructions); two where a pair is longer or notes its hits.
 template <typename T, int LAW, bool CUT>
 constexpr int pf_per_lane() { return sizeof(T) == 4 && LAW == PF_Q2 && !CUT ? 4 : 2; }
 
@@ -1015,17 +1055,19 @@ PfPlan pf_plan(int n, int precision, const PfLaw &law) {
     // 72 / 80 at 5,000, 165 / 137 at 8,192.  With a cutoff, where rows evaluates the law for the lanes out of range
     // too, rows against cells (cutoff 12, 0.45 of the area covered, three species): inverse square FP64 23 / 27 at
     // 4,000, FP32 22 / 29; screened FP64 20 / 30 at 2,000, 55 / 31 at 4,000, FP32 37 / 33 at 4,000; but with cutoffs
-    // of a fifth of the box and more, which the cells leave to the tiles, rows 53 / 89 to 121 at 3,700.
+    // of a fifth of the box and more, which the cells leave to the tiles, rows 53 / 89 to 139 at 3,700 (screened FP64).
     const bool q2 = law.kind == BD_FORCE_POWER && law.q == 2.0;
     p.rows = n <= (cut ? 4096 : 6144);
     if (p.rows) return p;
     // Every pair once above 16,384 particles, where the chunks' sums fit the working memory: the smallest chunk that
     // lets them (smaller tiles leave fewer compute units waiting at the end).  Tiles against sym, three species, us:
     // FP32 86 / 94 at 16,001, 130 / 98 at 18,000, 118 / 117 at 20,011, 245 / 176 at 30,000 (chunks of 256), 472 / 363
-    // at 43,000 (512), 941 / 685 at 62,000 (1024), 957 / 754 at 65,536 (1280, 963 with four particles a lane, which
-    // leave a second round of workgroups); FP64 149 / 156 at 16,001, 195 / 161 at 18,000, 235 / 205 at 20,011, 506 /
-    // 372 at 30,000, 1006 / 701 at 43,000, and above 44,000, where chunks of 1280 fill the device unevenly, 1309 /
-    // 1424 at 49,000.
+    // at 43,000 (512), 941 / 685 at 62,000 (1024), 957 / 754 at 65,536 (1280; 963 with four particles a lane, which
+    // leave a second round of workgroups there).  Chunks of 1280, FP32 only, are the last that fit, with two species
+    // for 64,031 to 71,680: 1059 / 802 at 64,100, 1148 / 809 at 67,000, 1276 / 905 at 70,500, 1289 / 910 at 71,600; one
+    // species 1188 / 822 at 68,000, eight 1135 / 913 at 66,000.  FP64 149 / 156 at 16,001, 195 / 161 at 18,000, 235 /
+    // 205 at 20,011, 506 / 372 at 30,000, 1006 / 701 at 43,000, 1107 / 752 at 44,500, and above, where chunks of 1280
+    // fill the device unevenly, 1309 / 1424 at 49,000.
     const bool fp32 = precision == BD_PREC_FP32;
     if (q2 && !cut && n > kSymMin) {
         for (int C : {256, 512, 1024, 1280}) {

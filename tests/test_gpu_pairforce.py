@@ -311,3 +311,57 @@ def test_pair_forces_dev_every_pair_once_in_long_chunks(fp32, n, S):
         got = out.clone()
         ref = binding.pair_forces_dev(xy, sp, K, fp32=fp32)
         assert torch.equal(got, ref), scale
+
+
+@pytest.mark.parametrize("law", ["q2", "q6", "screened"])
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("frac", [0.35, 0.5, 2.0])
+def test_pair_forces_dev_wide_cutoffs_match_oracle(law, fp32, frac):
+    """Cutoffs that the cells leave to the tiles, with a quarter to all of the pairs inside: blocks whose pairs are
+    noted and blocks evaluated pair by pair, particles in no order in space and in rows."""
+    import torch
+
+    n = 9001
+    w = synth.make("C1", n=n)
+    rng = np.random.default_rng(2)
+    cutoff = frac * w.L
+    kw = dict(cutoff=cutoff, **{"q2": dict(kind="power", q=2.0), "q6": dict(kind="power", q=6.0),
+                                "screened": dict(kind="screened", A=1.0, lam=20.0)}[law])
+    K = np.array([[1e-2, -5e-3, 4e-3], [2e-3, 1e-2, 0.0], [-1e-3, 3e-3, 7e-3]])
+    species = rng.integers(0, 3, n).astype(np.int32)
+    for xy in (w.xy, w.xy[np.argsort(w.xy[:, 1])]):
+        x = np.ascontiguousarray(xy.astype(np.float32).astype(np.float64) if fp32 else xy)
+        f = binding.pair_forces_dev(torch.from_numpy(x).cuda(), torch.from_numpy(species).cuda(), K, fp32=fp32, **kw)
+        f = f.cpu().numpy()
+        idx = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, 300)])).astype(np.int32)
+        fo = oracle.forces(x, species, K, idx=idx, **kw)
+        edge = np.array([(np.abs(np.hypot(*(x - x[i]).T) - cutoff) < (1e-3 if fp32 else 1e-9)).any() for i in idx])
+        assert edge.mean() < 0.9
+        assert np.abs(f[idx] - fo)[~edge].max() <= (1e-4 if fp32 else 1e-12) * np.abs(fo).max()
+
+
+@pytest.mark.parametrize("fp32", [False, True])
+def test_pair_forces_dev_cutoff_beyond_the_system_costs_no_more(fp32):
+    """With every pair inside the cutoff the call does the work of the one without, and the tests of the distances: of
+    some 30 instructions a pair 2 more, 7 %; the limit is twice that."""
+    import time
+
+    import torch
+
+    n = 40001
+    w = synth.make("C1", n=n)
+    xy, sp = torch.from_numpy(np.ascontiguousarray(w.xy)).cuda(), torch.zeros(n, dtype=torch.int32, device="cuda")
+    out = torch.empty_like(xy)
+
+    def best(cutoff):
+        ts = []
+        for _ in range(12):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            binding.pair_forces_dev(xy, sp, np.array([[1.0]]), kind="screened", A=1.0, lam=0.5, fp32=fp32,
+                                    cutoff=cutoff, out=out)
+            ts.append(time.perf_counter() - t)
+        return min(ts[2:])
+
+    t0, t1 = best(0.0), best(2.0 * w.L)
+    assert t1 <= 1.14 * t0, (t0, t1)
