@@ -1050,11 +1050,13 @@ int run_graph_steps(Sim &s, int64_t nsteps) {
         if (s.use_nl && s.need_rebuild) verlet_rebuild(s);
         Sim::StepGraph &g = step_graph(s);
         // steps queued after one that stops still cost their launches: queue about as many
-        // steps as recently ran between stops (neighbour-list rebuilds, budget growth).  A large
-        // handle starts with one step, which shows the rounds to launch on many workgroups:
-        // 1,000,000 disks, a handle's first 20 steps 11.8 ms with all of them queued, 9.5 so
-        // (list method 8.5 and 5.7); 65,536 disks 17.9 and 18.0
-        if (s.batch_hint == 0) s.batch_hint = s.n > 262144 ? 1 : kRing;
+        // steps as recently ran between stops (neighbour-list rebuilds, budget growth).  Where rounds are launched on
+        // many workgroups (form 2) a handle starts with one step, which shows how many: until then the tail's one
+        // workgroup runs them all.  A handle's first 20 steps, ms with all of them queued / so: 66,000 disks at area
+        // fraction 0.5 with moves of 0.2 and 0.06 radii 36.4 / 14.7 and 9.2 / 6.8, 200,000 42.5 / 29.5 and 20.5 / 10.2;
+        // 50,000 by the list method 2.66 / 1.50, 1,000,000 8.5 / 5.7; few overlaps, a graph more to capture: 17,000
+        // disks of the all-pairs workload 3.95 / 4.41, 65,536 17.9 / 18.0
+        if (s.batch_hint == 0) s.batch_hint = tail_mode_of(s) == 2 ? 1 : kRing;
         const int m = (int)std::min<int64_t>(nsteps, std::min(kRing, s.batch_hint));
         launch_step_begin(s, next_base(s));
         for (int k = 0; k < m;) {

@@ -265,3 +265,25 @@ def test_rounds_launched_per_phase_after_a_step_of_many():
         sims.append(g)
     assert launched == {1: [0, 0, 0], 2: [48, 24, 24]}
     _same(*sims)
+
+
+def test_first_queued_steps_of_many_overlaps_cost_no_more_than_launched_ones():
+    """A fresh handle of 66,000 disks that overlap much in every step: the first twenty steps queued together take no
+    longer than launched one by one (which adapt after each step), with half as much again for the captures."""
+    import time
+
+    n = 66000
+    L = synth.box_side(n, 0.5)
+    xy = synth.rsa(n, L, 1.0, seed=8)
+    best = {}
+    for graph in (True, False) * 3:
+        g = binding.Sim(xy, np.ones(n), np.zeros(n, np.int32), None, np.array([[0.0]]), L=L, D=1.0, dt=2e-2, seed=2,
+                        kind="screened", A=1.0, lam=0.5, cutoff=2.5, skin=0.5)
+        g.set_graph_mode(graph)
+        g.state()
+        t = time.perf_counter()
+        g.step(20)
+        g.state()
+        best[graph] = min(best.get(graph, 1e9), time.perf_counter() - t)
+        g.close()
+    assert best[True] <= 1.5 * best[False], best
