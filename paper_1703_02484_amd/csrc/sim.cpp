@@ -596,6 +596,8 @@ int overlaps_budget(const Sim &s) {
     return nover;
 }
 
+constexpr int kTailMaxDisks = 16384;   // most disks of the one-workgroup form as the library's choice
+
 // How the overlap rounds after the first detection are launched (bd_set_tail_mode).
 int tail_mode_of(const Sim &s) {
     // Library choice: one workgroup for handles of at most 16,384 disks, measured per step with
@@ -606,7 +608,6 @@ int tail_mode_of(const Sim &s) {
     // measured 6-18 % faster than mode 1 on 32,768 disks, 0.96 vs 1.11 ms per step (mode 0) on
     // 65,536 and 0.64 vs 0.84 ms on 1M (all in one workgroup: 1.25 ms and 13.6 ms; the large
     // phases are latency chains over thousands of items that spread better over many CUs).
-    constexpr int kTailMaxDisks = 16384;
     if (s.tail_mode != -1) return s.tail_mode;
     return s.n <= kTailMaxDisks ? 1 : 2;
 }
@@ -1050,13 +1051,13 @@ int run_graph_steps(Sim &s, int64_t nsteps) {
         if (s.use_nl && s.need_rebuild) verlet_rebuild(s);
         Sim::StepGraph &g = step_graph(s);
         // steps queued after one that stops still cost their launches: queue about as many
-        // steps as recently ran between stops (neighbour-list rebuilds, budget growth).  Where rounds are launched on
-        // many workgroups (form 2) a handle starts with one step, which shows how many: until then the tail's one
+        // steps as recently ran between stops (neighbour-list rebuilds, budget growth).  A handle large enough for
+        // rounds launched on many workgroups starts with one step, which shows how many: until then the tail's one
         // workgroup runs them all.  A handle's first 20 steps, ms with all of them queued / so: 66,000 disks at area
         // fraction 0.5 with moves of 0.2 and 0.06 radii 36.4 / 14.7 and 9.2 / 6.8, 200,000 42.5 / 29.5 and 20.5 / 10.2;
         // 50,000 by the list method 2.66 / 1.50, 1,000,000 8.5 / 5.7; few overlaps, a graph more to capture: 17,000
         // disks of the all-pairs workload 3.95 / 4.41, 65,536 17.9 / 18.0
-        if (s.batch_hint == 0) s.batch_hint = tail_mode_of(s) == 2 ? 1 : kRing;
+        if (s.batch_hint == 0) s.batch_hint = s.n > kTailMaxDisks ? 1 : kRing;   // the same whatever form is set
         const int m = (int)std::min<int64_t>(nsteps, std::min(kRing, s.batch_hint));
         launch_step_begin(s, next_base(s));
         for (int k = 0; k < m;) {
