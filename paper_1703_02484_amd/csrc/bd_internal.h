@@ -407,7 +407,7 @@ void launch_flip_eval_list(Sim &s, int round, int slot);
 void launch_flip_eval_star(Sim &s, int k, int round, int slot);
 void launch_flip_apply(Sim &s, int round, int slot);
 void launch_flip_fix(Sim &s, int round, int slot);
-void launch_validate(Sim &s, int rep, int last = -1);   // last >= 0: also the repair check
+void launch_validate(Sim &s, int rep);
 void launch_snapshot(Sim &s);
 // overlap correction (k: overlap-round slot)
 // check: 0 none, 1 the overlap check of round k, 2 that and the final check

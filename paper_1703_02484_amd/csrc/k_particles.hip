@@ -712,7 +712,7 @@ int max_grid_p(bool fast) {
 
 }  // namespace
 
-// Tiles of 256 * per_lane particles; per_lane is 2 or 4.
+// Tiles of 256 * per_lane particles (per_lane 1, 2 or 4), or the symmetric form's chunk pairs.
 // src: positions in sorted order (null: those of the last cast).
 void launch_force(Sim &s, const void *src) {
     if (!src) src = s.pj_is_xy ? (const void *)s.xy : s.pj;

@@ -718,10 +718,6 @@ __global__ void k_flip_eval_list(TP t, int round, int slot) {
     cand_flush(t, slot, st);
 }
 
-// First evaluation of the repair after overlap round k: every edge of the triangles at the disks the round moved,
-// from the stars its gather recorded (the topology has not changed since).  Lane i of a star takes the edge to
-// its far vertex w_i and the edge w_i - w_(i+1) across from the disk.  No worklist: an edge of two moved disks is
-// evaluated by both.  65,536 disks: 17 us for the walk that queued the edges and 8 us for their evaluation before.
 // Evaluates the edges of the triangles at disk v (star s) and loads its positions.  False when an index was out of
 // range, or for a star above kStarMax (evaluated here by one lane): then the positions are not loaded.  The edge to
 // a far vertex and the one across from the disk go through one copy of the flip rule, in canonical order.
@@ -1019,8 +1015,6 @@ __device__ __forceinline__ void repair_check_body(int *ctl, int rep, int last) {
     }
 }
 
-// Validation of repair `rep`; with last >= 0 the last workgroup also runs the
-// repair's check (last: slot of its final round).
 // Adds a workgroup's count (in LDS) to a shared counter from thread 0; every
 // thread calls it.  Returns true in thread 0 when it added something.
 __device__ __forceinline__ bool add_block_count(int *counter, const int *block_count) {
@@ -1031,15 +1025,14 @@ __device__ __forceinline__ bool add_block_count(int *counter, const int *block_c
 }
 
 template <class TP>
-__global__ __launch_bounds__(kScanBlock) void k_validate(TP t, int rep, int last) {
+__global__ __launch_bounds__(kScanBlock) void k_validate(TP t, int rep) {
     __shared__ int inv;
     if (stopped(t.ctl)) return;   // nothing in this launch writes the stop flags: uniform
     if (threadIdx.x == 0) inv = 0;
     __syncthreads();
     for (int tri = xcd_block() * blockDim.x + threadIdx.x; tri < t.T; tri += gridDim.x * blockDim.x)
         validate_tri(t, tri, &inv);
-    const bool added = add_block_count(&t.ctl[K_INV + rep], &inv);
-    if (last >= 0 && last_workgroup(t.ctl, added) && threadIdx.x == 0) repair_check_body(t.ctl, rep, last);
+    add_block_count(&t.ctl[K_INV + rep], &inv);
 }
 
 // ---------------------------------------------------------------- overlaps
@@ -1645,11 +1638,15 @@ constexpr int kTailBlock = 1024;
 
 // In one workgroup, after a barrier: true when flip round `slot` has nothing
 // left to do, before its evaluation (empty worklist) or after it (no
-// candidate).  A round without a candidate queues no edge, so every later
-// round of the repair would find an empty worklist as well: leaving the loop
-// there gives the same result as running the remaining rounds.  The counters
-// were last written by atomics before the barrier and are not written again
-// before the decision, so every thread reads the same value.
+// candidate).  Leaving the loop there gives the same result as running the
+// remaining rounds: without a candidate a round queues only edges whose flip is
+// blocked (register_flip), and with positions and topology unchanged those stay
+// blocked in every later round.  They exist only beside an inverted triangle (on
+// an embedded triangulation the diagonal that a quad must flip to is no edge),
+// so the repair ends in HALT_INVALID and the host replays the move, whichever
+// round it left at.  The counters were last written by atomics before the
+// barrier and are not written again before the decision, so every thread reads
+// the same value.
 __device__ __forceinline__ bool rounds_done(const Topo &t, int slot, bool evaluated) {
     return ctl_read(t.ctl, (evaluated ? K_CAND : K_WL) + slot) == 0;
 }
@@ -1932,10 +1929,10 @@ void launch_flip_fix(Sim &s, int round, int slot) {
     hipLaunchKernelGGL(k_flip_fix, dim3(list_grid(s)), dim3(256), 0, s.stream, t, round, slot);
 }
 
-void launch_validate(Sim &s, int rep, int last) {
+void launch_validate(Sim &s, int rep) {
     const Topo t = topo_of(s);
     with_box(t, [&](auto tp) {
-        hipLaunchKernelGGL(k_validate<decltype(tp)>, dim3(grid_for((s.T + 3) / 4)), dim3(kScanBlock), 0, s.stream, tp, rep, last);
+        hipLaunchKernelGGL(k_validate<decltype(tp)>, dim3(grid_for((s.T + 3) / 4)), dim3(kScanBlock), 0, s.stream, tp, rep);
     });
 }
 

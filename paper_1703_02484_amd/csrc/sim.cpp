@@ -239,40 +239,40 @@ void update_ovl_phase(Sim &s, const int *h, const std::vector<int> &orounds, int
 inline int rev_mode(const Sim &s) { return s.p.max_dt_halvings > 0 ? 2 : 1; }
 
 // ------------------------------------------------------------------ budgeted sequence
-// Enqueues one repair of `rounds` flip rounds with no host read-back: a
-// topology snapshot, the rounds, the validation and the check that halts the
-// step when the budget was too small or a triangle stayed inverted.
 // The overlap detection that follows a repair, run in the same launch as the
 // repair's validation (same triangles or stars): round slot, stamp, check.
 struct FusedDetect {
     int k, stamp, check;
 };
 
-void enqueue_repair(Sim &s, Cursor &c, bool full, bool reversal, int rounds, std::vector<int> *first_slots,
-                    int oround = -1, const FusedDetect *fd = nullptr, int multi = 1 << 30) {
+// Enqueues one repair of `rounds` flip rounds with no host read-back: the
+// rounds, the validation, the check that halts the step when the budget was too
+// small or a triangle stayed inverted, and the detection fd.  oround < 0: the
+// repair after the move, which scans every edge, tests for reversed ones and
+// takes the topology snapshot; else the repair after overlap round oround.
+void enqueue_repair(Sim &s, Cursor &c, int rounds, std::vector<int> &first_slots, int oround, const FusedDetect &fd,
+                    int multi = 1 << 30) {
+    const bool full = oround < 0;
     // The repair after the move keeps the triangulation of the step's start
     // positions: a later repair of the same step that fails replays the
     // whole move from there (the Delaunay triangulation of the end positions
     // is unique), so the repairs after overlap rounds need no copy of their own.
     // The copy is taken by the first evaluation, which reads the whole topology.
     const int rep = c.take_rep();
-    if (first_slots) first_slots->push_back(c.slot);
+    first_slots.push_back(c.slot);
     int last = -1;
     if (full && rounds >= 1 && tail_fused(s)) {
         // the first evaluation scans every edge; the rest of the rounds run in one workgroup
         const int r0 = ++s.round_id;
         const int slot0 = c.take_slot();
-        launch_flip_eval_full(s, r0, slot0, reversal ? rev_mode(s) : 0, true);
+        launch_flip_eval_full(s, r0, slot0, rev_mode(s), true);
         last = slot0;
         for (int j = 1; j < rounds; ++j) {
             ++s.round_id;
             last = c.take_slot();
         }
         launch_repair_rounds(s, r0, slot0, rounds);
-        if (fd)
-            launch_ovl_detect(s, fd->stamp, fd->k, fd->check, rep, last);
-        else
-            launch_validate(s, rep, last);
+        launch_ovl_detect(s, fd.stamp, fd.k, fd.check, rep, last);
         return;
     }
     // the first `multi` rounds (the long worklists) on many workgroups, the rest in one workgroup
@@ -283,7 +283,7 @@ void enqueue_repair(Sim &s, Cursor &c, bool full, bool reversal, int rounds, std
         const int r = ++s.round_id;
         const int slot = c.take_slot();
         if (j == 0 && full)
-            launch_flip_eval_full(s, r, slot, reversal ? rev_mode(s) : 0, true);
+            launch_flip_eval_full(s, r, slot, rev_mode(s), true);
         else if (j == 0)
             launch_flip_eval_star(s, oround, r, slot);
         else
@@ -300,12 +300,10 @@ void enqueue_repair(Sim &s, Cursor &c, bool full, bool reversal, int rounds, std
         }
         launch_repair_rounds(s, r0, slot0, rounds - m, false);
     }
-    if (fd && oround >= 0)
-        launch_validate_detect_local(s, rep, oround, rfirst, last, fd->stamp, fd->k, fd->check);
-    else if (fd)
-        launch_ovl_detect(s, fd->stamp, fd->k, fd->check, rep, last);
+    if (full)
+        launch_ovl_detect(s, fd.stamp, fd.k, fd.check, rep, last);
     else
-        launch_validate(s, rep, last);
+        launch_validate_detect_local(s, rep, oround, rfirst, last, fd.stamp, fd.k, fd.check);
 }
 
 // ------------------------------------------------------------------ host-driven path
@@ -651,7 +649,7 @@ bool enqueue_rounds(Sim &s, Cursor &c, std::vector<int> &orounds, std::vector<in
         plan.r_used = s.round_id - s.rbase;
         plan.v_used = s.vround - s.vbase;
     };
-    if (mode != 1 || nover > MAXTAIL || nover == 0) {
+    if (mode != 1 || nover == 0) {
         // Each detection runs in the launch that validates the repair before it: the first one
         // scans every triangle (after the repair of the move), later ones the stars of the disks
         // the previous round moved and the diagonals flipped since; the launch's last workgroup
@@ -659,20 +657,18 @@ bool enqueue_rounds(Sim &s, Cursor &c, std::vector<int> &orounds, std::vector<in
         // Mode 2: each repair launches its first rounds on many workgroups and the rest in one, and
         // after the first ovl_phase overlap rounds the others run in one workgroup (k_tail).
         const bool hybrid = mode == 2;
-        const int per_phase =
-            hybrid ? std::min(nover, std::max({0, s.ovl_phase, nover - MAXTAIL})) : nover;   // the tail holds MAXTAIL
+        const int per_phase = hybrid ? std::min(nover, s.ovl_phase) : nover;
         int k = c.take_oround();
         orounds.push_back(k);
         FusedDetect fd{k, ++s.vround, nover == 0 ? 2 : 1};
-        enqueue_repair(s, c, true, true, s.budget.em, &rep_first, -1, &fd, hybrid ? s.multi_em : 1 << 30);
+        enqueue_repair(s, c, s.budget.em, rep_first, -1, fd, hybrid ? s.multi_em : 1 << 30);
         for (int j = 0; j < per_phase; ++j) {
             launch_ovl_gather(s, k);
             launch_ovl_apply(s, k);
             const int knext = c.take_oround();
             orounds.push_back(knext);
             FusedDetect fn{knext, ++s.vround, j + 1 == nover ? 2 : 1};
-            enqueue_repair(s, c, false, false, s.budget.ovl[j], &rep_first, k, &fn,
-                           hybrid ? s.multi_ovl : 1 << 30);
+            enqueue_repair(s, c, s.budget.ovl[j], rep_first, k, fn, hybrid ? s.multi_ovl : 1 << 30);
             k = knext;
         }
         if (per_phase < nover) {
@@ -719,7 +715,7 @@ bool enqueue_rounds(Sim &s, Cursor &c, std::vector<int> &orounds, std::vector<in
     int k = c.take_oround();
     orounds.push_back(k);
     const FusedDetect fd{k, ++s.vround, 1};
-    enqueue_repair(s, c, true, true, s.budget.em, &rep_first, -1, &fd);
+    enqueue_repair(s, c, s.budget.em, rep_first, -1, fd);
     // rounds after the first detection in one workgroup (same slots, stamps and round ids)
     TailPlan plan{};
     plan.nover = nover;

@@ -287,3 +287,29 @@ def test_first_queued_steps_of_many_overlaps_cost_no_more_than_launched_ones():
         best[graph] = min(best.get(graph, 1e9), time.perf_counter() - t)
         g.close()
     assert best[True] <= 1.5 * best[False], best
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_launch_forms_agree_where_overlap_rounds_fold_the_triangulation(graph):
+    """A compressed patch whose first overlap rounds throw disks across edges: repairs that end with inverted triangles
+    and edges whose flip is blocked, at different rounds in the three launch forms, and a move that the host replays."""
+    m = 64
+
+    def patch(d):
+        p = np.array([[i + 0.5 * (j & 1) - m / 2, 0.8660254 * (j - m / 2)] for i in range(m) for j in range(m)])
+        return 106.0 + d * p
+
+    n = m * m
+    xy = patch(1.95) + np.random.default_rng(4).uniform(0.0, 0.01, (n, 2))
+    sims = []
+    for mode in (0, 1, 2):
+        g = binding.Sim(patch(2.1), np.ones(n), np.zeros(n, np.int32), None, np.array([[0.0]]), L=212.0, D=0.0,
+                        dt=1e-6, seed=1)
+        g.set_tail_mode(mode)
+        g.set_graph_mode(graph)
+        g.set_positions(xy)
+        g.step(2)
+        sims.append(g)
+    assert sims[0].state()[3]["kinetic_repairs"] >= 2 and sims[0].state()[3]["inversion_flips"] > 0
+    _same(sims[0], sims[1])
+    _same(sims[0], sims[2])
