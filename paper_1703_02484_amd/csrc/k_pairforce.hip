@@ -398,7 +398,8 @@ __global__ __launch_bounds__(kPfBlock, sizeof(T) == 8 && LAW == PF_SCREENED && C
             if (threadIdx.x == 0) inside[turn] = 0;
         }
         for (int s = 0; s < S; ++s) {
-            const int k0 = __builtin_amdgcn_readfirstlane(st.seg[s]), k1 = __builtin_amdgcn_readfirstlane(st.seg[s + 1]);
+            const int k0 = __builtin_amdgcn_readfirstlane(st.seg[s]);
+            const int k1 = __builtin_amdgcn_readfirstlane(st.seg[s + 1]);
             T ax[P], ay[P];
 #pragma unroll
             for (int p = 0; p < P; ++p) ax[p] = ay[p] = (T)0;
@@ -1093,7 +1094,7 @@ PfPlan pf_plan(int n, int precision, const PfLaw &law) {
     if (p.cells) {
         PfCells<float> a32;
         PfCells<double> a64;
-        const size_t c = precision == BD_PREC_FP32 ? pf_cells_at(n, law, nullptr, a32) : pf_cells_at(n, law, nullptr, a64);
+        const size_t c = fp32 ? pf_cells_at(n, law, nullptr, a32) : pf_cells_at(n, law, nullptr, a64);
         const size_t most = kPfPartBytes - 256;
         p.J = std::min(p.J, (int)(most / row));
         p.bytes = std::max(256 + p.J * row, c);

@@ -1585,7 +1585,8 @@ __global__ __launch_bounds__(256) void k_ovl_gather(TP t, int k, double f, doubl
     if (stopped(t.ctl)) return;
     const int ntouched = t.ctl[K_TOUCH + k];
     const int *touched = touched_of(t, k);
-    for (int idx = (xcd_block() * blockDim.x + threadIdx.x) / kStarLanes; idx < ntouched; idx += gridDim.x * blockDim.x / kStarLanes) {
+    const int i0 = xcd_block() * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+    for (int idx = i0 / kStarLanes; idx < ntouched; idx += stride / kStarLanes) {
         double2 pv, np;
         gather_star(t, idx, touched[idx], f, cap_frac, keep, pv, np);
     }
@@ -1896,8 +1897,9 @@ void launch_flip_eval_full(Sim &s, int round, int slot, int reversal, bool snaps
     const Topo t = topo_of(s);
     const Snapshot snap = snapshot ? Snapshot{s.snap_v, s.snap_twin, s.snap_vh, s.nv + s.R} : Snapshot{};
     with_box(t, [&](auto tp) {
-        hipLaunchKernelGGL(k_flip_eval_full<decltype(tp)>, dim3(grid_for((long)(s.T + 3) / 4 * 1024 / kEvalBlock, kEvalGrid)), dim3(kEvalBlock), 0, s.stream, tp, round,
-                       slot, reversal, snap);
+        const int grid = grid_for((long)(s.T + 3) / 4 * 1024 / kEvalBlock, kEvalGrid);
+        hipLaunchKernelGGL(k_flip_eval_full<decltype(tp)>, dim3(grid), dim3(kEvalBlock), 0, s.stream, tp, round, slot,
+                           reversal, snap);
     });
 }
 
@@ -1913,7 +1915,8 @@ void launch_flip_eval_star(Sim &s, int k, int round, int slot) {
     round -= s.rbase;
     const Topo t = topo_of(s);
     with_box(t, [&](auto tp) {
-        hipLaunchKernelGGL(k_flip_eval_star<decltype(tp)>, dim3(star_grid(s)), dim3(256), 0, s.stream, tp, k, round, slot);
+        hipLaunchKernelGGL(k_flip_eval_star<decltype(tp)>, dim3(star_grid(s)), dim3(256), 0, s.stream, tp, k, round,
+                           slot);
     });
 }
 
@@ -1932,7 +1935,8 @@ void launch_flip_fix(Sim &s, int round, int slot) {
 void launch_validate(Sim &s, int rep) {
     const Topo t = topo_of(s);
     with_box(t, [&](auto tp) {
-        hipLaunchKernelGGL(k_validate<decltype(tp)>, dim3(grid_for((s.T + 3) / 4)), dim3(kScanBlock), 0, s.stream, tp, rep);
+        hipLaunchKernelGGL(k_validate<decltype(tp)>, dim3(grid_for((s.T + 3) / 4)), dim3(kScanBlock), 0, s.stream, tp,
+                           rep);
     });
 }
 
@@ -1940,8 +1944,8 @@ void launch_ovl_detect(Sim &s, int vstamp, int k, int check, int vrep, int vlast
     vstamp -= s.vbase;
     const Topo t = topo_of(s);
     with_box(t, [&](auto tp) {
-        hipLaunchKernelGGL(k_ovl_detect<decltype(tp)>, dim3(grid_for((s.T + 3) / 4)), dim3(kDetBlock), 0, s.stream, tp, vstamp,
-                       1.0 - s.p.contact_tol, k, check, vrep, vlast);
+        hipLaunchKernelGGL(k_ovl_detect<decltype(tp)>, dim3(grid_for((s.T + 3) / 4)), dim3(kDetBlock), 0, s.stream, tp,
+                           vstamp, 1.0 - s.p.contact_tol, k, check, vrep, vlast);
     });
 }
 
@@ -1950,16 +1954,16 @@ void launch_validate_detect_local(Sim &s, int rep, int k, int rfirst, int last, 
     rfirst -= s.rbase;
     const Topo t = topo_of(s);
     with_box(t, [&](auto tp) {
-        hipLaunchKernelGGL(k_validate_detect_local<decltype(tp)>, dim3(star_grid(s)), dim3(256), 0, s.stream, tp, rep, k, rfirst, last, vstamp,
-                       1.0 - s.p.contact_tol, knew, check);
+        hipLaunchKernelGGL(k_validate_detect_local<decltype(tp)>, dim3(star_grid(s)), dim3(256), 0, s.stream, tp, rep,
+                           k, rfirst, last, vstamp, 1.0 - s.p.contact_tol, knew, check);
     });
 }
 
 void launch_ovl_gather(Sim &s, int k) {
     const Topo t = topo_of(s);
     with_box(t, [&](auto tp) {
-        hipLaunchKernelGGL(k_ovl_gather<decltype(tp)>, dim3(star_grid(s)), dim3(256), 0, s.stream, tp, k, s.p.overlap_factor,
-                       s.p.cap_frac, 1.0 - s.p.contact_tol);
+        hipLaunchKernelGGL(k_ovl_gather<decltype(tp)>, dim3(star_grid(s)), dim3(256), 0, s.stream, tp, k,
+                           s.p.overlap_factor, s.p.cap_frac, 1.0 - s.p.contact_tol);
     });
 }
 
@@ -1978,8 +1982,8 @@ void launch_tail(Sim &s, const TailPlan &plan) {
 void launch_repair_rounds(Sim &s, int round0, int slot0, int rounds, bool first_evaluated) {
     const Topo t = topo_of(s);
     with_box(t, [&](auto tp) {
-        hipLaunchKernelGGL(k_repair_rounds<decltype(tp)>, dim3(1), dim3(kTailBlock), 0, s.stream, tp, round0 - s.rbase, slot0, rounds,
-                       first_evaluated ? 1 : 0);
+        hipLaunchKernelGGL(k_repair_rounds<decltype(tp)>, dim3(1), dim3(kTailBlock), 0, s.stream, tp, round0 - s.rbase,
+                           slot0, rounds, first_evaluated ? 1 : 0);
     });
 }
 

@@ -87,9 +87,9 @@ __global__ void k_cell_insert(int n, const double2 *__restrict__ xy, double inv_
 // to the place that the number of smaller ones gives.  cell_more becomes the start of the sorted ids.  The time is the
 // walk of the chain; room is taken with one atomic for all cells of a workgroup's turn (262,144 disks, 11 a cell, with
 // an atomic per cell here and in the insert 399 us a build, so 151).  Unit disks at area fraction 0.5, us a build with
-// every disk selecting a long cell's next id from its chain / sorted once (and as a counting sort of all cells): 262,144
-// with lists of radius 3 37 / 37 (52), 5.5 75 / 63 (90), 8.5 278 / 151 (190), 12.5 1158 / 271 (408); 40,009 with 12.5
-// 670 / 95 (224).
+// every disk selecting a long cell's next id from its chain / sorted once (and as a counting sort of all cells):
+// 262,144 with lists of radius 3 37 / 37 (52), 5.5 75 / 63 (90), 8.5 278 / 151 (190), 12.5 1158 / 271 (408); 40,009
+// with 12.5 670 / 95 (224).
 constexpr int kSortBlock = 256, kSortLanes = 8, kSortCells = kSortBlock / kSortLanes;
 
 __global__ __launch_bounds__(kSortBlock) void k_cells_sort(const int *__restrict__ rows, int *__restrict__ more,
@@ -255,7 +255,8 @@ __global__ void k_cells_clear(int n, const double2 *__restrict__ xy, double inv_
 // T is the precision of the law's arithmetic and of the sum (FP32 or FP64).  ONE_SPECIES: a single
 // species, so no neighbour's species is read.
 template <typename T, bool ONE_SPECIES, bool PER>
-__global__ __launch_bounds__(256) void k_force_nl(int n, const double2 *__restrict__ xy, const int *__restrict__ sp, const double *__restrict__ K, int S,
+__global__ __launch_bounds__(256) void k_force_nl(int n, const double2 *__restrict__ xy, const int *__restrict__ sp,
+                                                  const double *__restrict__ K, int S,
                                                   int kind, double q, double A, double lam, double rc,
                                                   const int *__restrict__ nl, const int *__restrict__ nl_cnt,
                                                   double2 *__restrict__ f, const StepBase *__restrict__ base,
