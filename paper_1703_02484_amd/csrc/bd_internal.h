@@ -332,6 +332,7 @@ struct Sim {
                                      // (1 + the leading later rounds that recently queued many disks)
     int touch_hi[MAXO] = {};         // most disks queued by overlap round j in the current window of steps
     int touch_prev[MAXO] = {};       // the same over the previous window
+    int touch_now[MAXO] = {};        // of the step being finished
     int touch_steps = 0;             // steps in the current window
     struct StepGraph {
         hipGraphExec_t one = nullptr, many = nullptr;   // one step; kGraphSteps steps (captured once in steady use)

@@ -1411,7 +1411,8 @@ __device__ __forceinline__ void ovl_check_body(int *ctl, int k, int stamp, const
         ctl[K_OVL_ROUNDS] = k + 1;
 }
 
-// After the last budgeted round: overlaps remain, the host continues.
+// After the last budgeted round, or where the tail's next one is for many workgroups: overlaps remain after k rounds,
+// the host continues.
 __device__ __forceinline__ void final_check_body(int *ctl, int k) {
     if (stopped(ctl)) return;
     ctl[K_REASON] = HALT_OVERLAP_BUDGET;
@@ -1635,6 +1636,19 @@ __global__ void k_ovl_apply(Topo t, int k) {
 // in the cache.  Small rounds took 13 us with 162 KiB of code (every phase
 // inlined for both box kinds), 10 us with 60 KiB; 1,024 disks 64 to 58 us a
 // step, 16,001 in the periodic box 272 to 247.
+//
+// A round of many disks is for many workgroups: the tail takes some 0.11 us a
+// disk and round, launches from the host some 120 us a round whatever it moves.
+// So a round that queues more than kTailMost disks goes to the host with the
+// rest of the step, and more than kTailLong where several rounds before it did
+// not bring the number down (kTailFirst).  A step
+// from positions where every disk of some patches overlaps, 116 to 137 rounds,
+// ms with the 48 rounds the tail holds / so: 2,304 disks 17.2 / 12.6, 5,184 31 /
+// 12.7, 14,400 76 / 14.7, 82,944 427 / 18.6, 230,400 1218 / 24; 16,000 disks with
+// moves of 0.2 radii 1.80 / 1.24 a step.  With kTailMost 2,048 and 1,024 instead
+// of 4,096: 5,000 such disks 1.03 and 1.03 a step for 0.67, 3,000 0.48 and 0.97
+// for 0.48.
+constexpr int kTailMost = 4096, kTailFirst = 7, kTailLong = 1400;
 constexpr int kTailBlock = 1024;
 
 // In one workgroup, after a barrier: true when flip round `slot` has nothing
@@ -1717,6 +1731,7 @@ template <class TP>
 __device__ __forceinline__ void tail_body(const TP &t, const TailPlan &p) {
     const int i0 = threadIdx.x, stride = blockDim.x;
     const int g0 = i0 / kStarLanes, gstep = kTailBlock / kStarLanes;
+    if (i0 == 0 && t.ctl[K_TOUCH + p.k[0]] > kTailMost) final_check_body(t.ctl, p.k[0]);
     if (tail_sync(t)) return;
     for (int j = 0; j < p.nover; ++j) {
         const int k = p.k[j], knew = p.k[j + 1];
@@ -1783,9 +1798,10 @@ __device__ __forceinline__ void tail_body(const TP &t, const TailPlan &p) {
         wave_sum_add(&t.ctl[K_OVL + knew], found);
         __syncthreads();
         if (i0 == 0) {
+            const int next = t.ctl[K_TOUCH + knew];
             repair_check_body(t.ctl, p.rep[j], last);
             ovl_check_body(t.ctl, knew, p.stamp[j + 1], t.base);
-            if (j + 1 == p.nover) final_check_body(t.ctl, knew);
+            if (j + 1 == p.nover || next > (j < kTailFirst ? kTailMost : kTailLong)) final_check_body(t.ctl, knew);
         }
         if (tail_sync(t)) return;
     }

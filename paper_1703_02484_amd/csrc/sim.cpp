@@ -232,7 +232,6 @@ inline int next_slot(int slot) { return slot + 1 == MAXR ? 0 : slot + 1; }
 
 bool tail_fused(const Sim &s);
 int tail_mode_of(const Sim &s);
-void update_ovl_phase(Sim &s, const int *h, const std::vector<int> &orounds, int rounds);
 
 // Evaluation mode of the first flip round after a move: count reversed edges, and with halving
 // enabled also flag the step so that its repair check halts it.
@@ -501,6 +500,7 @@ int host_overlap_loop(Sim &s, Cursor &c, int &rounds) {
             s.last_error = "overlap correction did not converge within max_overlap_rounds";
             return BD_ERR_NO_CONVERGENCE;
         }
+        if (rounds < MAXO) s.touch_now[rounds] = s.hctl[K_TOUCH + k];
         ++rounds;
         s.st.overlap_edges_total += nedges;
         launch_ovl_gather(s, k);
@@ -575,7 +575,8 @@ void write_base(Sim &s) {
 // slots hold.  Rounds launched per phase cost their launches whether or not the
 // step needs them: the adaptive budget in mode 0, those that recently queued many
 // disks in mode 2 (update_ovl_phase).  The one-workgroup tail leaves at the
-// first detection that finds nothing, so it gets all the rounds it holds: a step
+// first detection that finds nothing, or more than one workgroup should take, so
+// it gets all the rounds it holds: a step
 // the host has to continue costs some 100 us per round.  16,384 disks with the
 // contact factor 1/2 need up to 25 rounds a step and now and then 41; ten steps
 // with their reverse sweep, first pass of a handle 14.7 to 16.4 ms with a budget
@@ -618,10 +619,9 @@ int tail_mode_of(const Sim &s) {
 // graph of its own): one such step would cost the next 64 to 128 up to 24 empty rounds more.  Measured per step
 // with graph replay: 512 and 128 within 1 % of each other on 65,536 and 1M disks and on 16,384
 // disks with the contact factor; 2048 is 25-40 % slower on the first two.
-void update_ovl_phase(Sim &s, const int *h, const std::vector<int> &orounds, int rounds) {
+void update_ovl_phase(Sim &s) {
     constexpr int kTouchWindow = 64, kTailItems = 512;
-    for (int j = 0; j < rounds && j < (int)orounds.size() && j < MAXO; ++j)
-        s.touch_hi[j] = std::max(s.touch_hi[j], h[K_TOUCH + orounds[j]]);
+    for (int j = 0; j < MAXO; ++j) s.touch_hi[j] = std::max(s.touch_hi[j], s.touch_now[j]);
     if (++s.touch_steps >= kTouchWindow) {
         std::copy(s.touch_hi, s.touch_hi + MAXO, s.touch_prev);
         std::fill(s.touch_hi, s.touch_hi + MAXO, 0);
@@ -629,8 +629,7 @@ void update_ovl_phase(Sim &s, const int *h, const std::vector<int> &orounds, int
     }
     int phase = 0;
     while (phase < kMaxLaunchedRounds && std::max(s.touch_hi[phase], s.touch_prev[phase]) > kTailItems) ++phase;
-    const bool many = rounds > phase && rounds <= (int)orounds.size() && h[K_TOUCH + orounds[phase]] > kTailItems;
-    if (phase == kMaxLaunchedRounds && many) phase = MAXTAIL;
+    if (phase == kMaxLaunchedRounds && s.touch_now[phase] > kTailItems) phase = MAXTAIL;
     s.ovl_phase = phase;
 }
 
@@ -1049,10 +1048,10 @@ int run_graph_steps(Sim &s, int64_t nsteps) {
         // steps queued after one that stops still cost their launches: queue about as many
         // steps as recently ran between stops (neighbour-list rebuilds, budget growth).  A handle large enough for
         // rounds launched on many workgroups starts with one step, which shows how many: until then the tail's one
-        // workgroup runs them all.  A handle's first 20 steps, ms with all of them queued / so: 66,000 disks at area
-        // fraction 0.5 with moves of 0.2 and 0.06 radii 36.4 / 14.7 and 9.2 / 6.8, 200,000 42.5 / 29.5 and 20.5 / 10.2;
-        // 50,000 by the list method 2.66 / 1.50, 1,000,000 8.5 / 5.7; few overlaps, a graph more to capture: 17,000
-        // disks of the all-pairs workload 3.95 / 4.41, 65,536 17.9 / 18.0
+        // workgroup runs what it may take of them.  A handle's first 20 steps, ms with all of them queued / so: 20,000
+        // disks at area fraction 0.5 with moves of 0.2 radii 17.5 / 9.2, 66,000 14.3 / 13.5, 200,000 25.7 / 24.3; with
+        // moves of 0.06 radii 5.1 / 5.0, 9.1 / 6.7 and 10.8 / 9.9; 50,000 by the list method 2.6 / 1.4; few overlaps, a
+        // graph more to capture: 17,000 disks of the all-pairs workload 3.97 / 4.41, 65,536 17.9 / 18.0
         if (s.batch_hint == 0) s.batch_hint = s.n > kTailMaxDisks ? 1 : kRing;   // the same whatever form is set
         const int m = (int)std::min<int64_t>(nsteps, std::min(kRing, s.batch_hint));
         launch_step_begin(s, next_base(s));
@@ -1143,10 +1142,14 @@ int finish_step(Sim &s, const int *h_in, const StepPlan &plan) {
     // bookkeeping of the budgeted part: overlap rounds that moved disks
     int rounds = h[K_OVL_ROUNDS];
     if (h[K_HALT]) {
-        if (h[K_REASON] == HALT_OVERLAP_BUDGET) rounds = plan.overlaps;
+        if (h[K_REASON] == HALT_OVERLAP_BUDGET) rounds = h[K_STAGE];
         if (h[K_REASON] == HALT_REPAIR_BUDGET || h[K_REASON] == HALT_INVALID) rounds = h[K_STAGE];
     }
-    for (int j = 0; j < rounds; ++j) s.st.overlap_edges_total += h[K_OVL + orounds[j]];
+    std::fill(s.touch_now, s.touch_now + MAXO, 0);
+    for (int j = 0; j < rounds; ++j) {
+        s.st.overlap_edges_total += h[K_OVL + orounds[j]];
+        if (j < MAXO) s.touch_now[j] = h[K_TOUCH + orounds[j]];
+    }
     for (int j = 0; j < c.slot; ++j) s.st.flip_rounds_total += h[K_CAND + j] > 0 ? 1 : 0;
     int rc = BD_OK;
     if (h[K_HALT] || h[K_TOPO]) {
@@ -1238,7 +1241,7 @@ int finish_step(Sim &s, const int *h_in, const StepPlan &plan) {
         adapt(s.budget.ovl[j], used, s.slack_ovl[j]);
     }
     adapt(s.budget.overlaps, rounds, s.slack_over, kMaxLaunchedRounds);   // contact-factor runs need ~20 rounds
-    update_ovl_phase(s, h, plan.orounds, std::min(rounds, plan.overlaps));
+    update_ovl_phase(s);
     s.st.overlap_rounds_total += rounds;
     if (rounds > s.st.overlap_rounds_max) s.st.overlap_rounds_max = rounds;
     ++s.st.steps;

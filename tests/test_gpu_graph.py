@@ -313,3 +313,38 @@ def test_launch_forms_agree_where_overlap_rounds_fold_the_triangulation(graph):
     assert sims[0].state()[3]["kinetic_repairs"] >= 2 and sims[0].state()[3]["inversion_flips"] > 0
     _same(sims[0], sims[1])
     _same(sims[0], sims[2])
+
+
+@pytest.mark.parametrize("c", [6, 12])   # 5,184 disks (all rounds in one workgroup by default) and 20,736
+def test_a_step_of_many_large_rounds_is_not_left_to_one_workgroup(c):
+    """A step of more than a hundred rounds that each move most of the disks: the default launch form takes no longer
+    than launching its rounds (form 0, which hands them to the host after a few), with half as much again for the rounds
+    it takes before it sees that, and gives the same state and counters."""
+    import time
+
+    m = 12
+
+    def patches(d):
+        p = np.array([[i + 0.5 * (j & 1) - m / 2, 0.8660254 * (j - m / 2)] for i in range(m) for j in range(m)])
+        return np.concatenate([d * p + [20.0 + 32.0 * a, 20.0 + 32.0 * b] for a in range(c) for b in range(c)])
+
+    xy0 = patches(2.1)
+    n = len(xy0)
+    xy = patches(1.99) + np.random.default_rng(3).uniform(0, 0.001, (n, 2))
+    best, sims = {}, []
+    for mode in (0, -1):
+        for rep in range(3):
+            g = binding.Sim(xy0, np.ones(n), np.zeros(n, np.int32), None, np.array([[0.0]]), L=32.0 * c + 8, D=0.0,
+                            dt=1e-6, seed=1, kind="screened", A=1.0, lam=0.5, cutoff=2.5, skin=0.5, overlap_factor=0.5,
+                            contact_tol=1e-4)
+            g.set_tail_mode(mode)
+            g.step(2)
+            g.set_positions(xy)
+            t = time.perf_counter()
+            g.step(1)
+            best[mode] = min(best.get(mode, 1e9), time.perf_counter() - t)
+            g.step(3)
+        sims.append(g)
+    assert sims[0].state()[3]["overlap_rounds_max"] > 100
+    _same(*sims)
+    assert best[-1] <= 1.5 * best[0], best
