@@ -91,8 +91,8 @@ def measured_traffic(workload, n, fcfg):
 # rocprofv3 --pmc passes (FETCH_SIZE x 2, WRITE_SIZE x 1, calibrated on a plain copy), beside the algorithmic
 # bytes; valid for the kernel sources they were counted on (sha1 of the three kernel files, see
 # c3_source_sha1).  MB = 1e6 bytes.
-C3_TRAFFIC = {"sha1": "f015d36e923d35ba1c0684de4707c4140e9659b3", "kernels": {
-    "k_flip_eval_full": {"measured_MB": 186.5, "algorithmic_MB": 143.2},   # with the topology snapshot
+C3_TRAFFIC = {"sha1": "37967fe602369ce08e310c40e381562ba13451ae", "kernels": {
+    "k_flip_eval_full": {"measured_MB": 187.2, "algorithmic_MB": 143.2},   # with the topology snapshot
     "k_ovl_detect": {"measured_MB": 71.9, "algorithmic_MB": 67.4},
     "k_em": {"measured_MB": 101.0, "algorithmic_MB": 100.7},
     "k_force_nl": {"measured_MB": 61.9, "algorithmic_MB": 54.5},
