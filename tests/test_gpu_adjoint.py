@@ -295,3 +295,33 @@ def test_recorded_last_segment_equals_replayed(steps, every):
     g.adjoint_begin(steps + 1, every)
     got, ref = g.adjoint_backward(lam), fresh(2 * steps, steps + 1, every)
     assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
+
+
+def test_gradients_where_the_tail_hands_large_rounds_to_the_host():
+    """A recorded step whose overlap rounds are too large for one workgroup: stopped in the tail and finished by the
+    host while the tape runs.  Bitwise the gradients of the form that launches its rounds, from the record of the first
+    pass and from a replay."""
+    m, c = 12, 6
+
+    def patches(d):
+        p = np.array([[i + 0.5 * (j & 1) - m / 2, 0.8660254 * (j - m / 2)] for i in range(m) for j in range(m)])
+        return np.concatenate([d * p + [20.0 + 32.0 * a, 20.0 + 32.0 * b] for a in range(c) for b in range(c)])
+
+    xy0 = patches(2.1)
+    n = len(xy0)
+    xy = patches(1.99) + np.random.default_rng(3).uniform(0, 0.001, (n, 2))
+    lam = np.random.default_rng(0).normal(size=(n, 2))
+    out = []
+    for mode in (0, -1):
+        g = binding.Sim(xy0, np.ones(n), np.zeros(n, np.int32), None, np.array([[0.01]]), L=32.0 * c + 8, D=0.1,
+                        dt=1e-5, seed=1, overlap_factor=0.5, contact_tol=1e-4)
+        g.set_tail_mode(mode)
+        for every in (1, 2):
+            g.set_positions(xy)
+            g.adjoint_begin(2, every)
+            out.append((g.state()[0], *g.adjoint_backward(lam), *g.adjoint_backward(lam)))
+        assert g.state()[3]["overlap_rounds_max"] > 100
+    for a, b in zip(out[:2], out[2:]):
+        for u, v in zip(a, b):
+            assert np.array_equal(u, v)
+        assert np.array_equal(a[1], a[3]) and np.array_equal(a[2], a[4])
